@@ -215,7 +215,7 @@ struct dvl_volume {
     float lo[kMaxFields] = {}, hi[kMaxFields] = {};
     Executor* ex = nullptr;  // private executor of dvl_update
     dvl::Alloc alloc;        // every device buffer of the volume comes from here
-    unsigned int* scratch_range = nullptr;   // 4 words for dvl_set_field's range check
+    unsigned int* scratch_range = nullptr;   // dvl_set_field's range check (alloc_range_scratch)
     dvl_status sticky = DVL_OK;
     size_t bytes = 0;
 };
@@ -1065,12 +1065,79 @@ struct dvl_graph {
     }
 };
 
-// per-tile and per-step statistics of sorted field m
-static dvl_status tile_aggregates(dvl_volume* v, int m, hipStream_t s) {
-    const size_t ot = (size_t)m * v->n_tiles, os = ot * v->tile_steps;
-    return launch_tile_aggregates(v->n, v->dtype, v->fields_s[m], v->n_tiles, v->tile_steps, v->agg_sum + ot,
-                                  v->agg_min + ot, v->agg_max + ot, v->step_sum + os, v->step_min + os,
-                                  v->step_max + os, v->n_cu, s);
+// the statistics arrays of a volume as the placing pass writes them
+static PlaceStats place_stats(const dvl_volume* v, uint2* range) {
+    PlaceStats st{};
+    st.n_tiles = v->n_tiles;
+    st.tile_sum = v->agg_sum;
+    st.tile_min = v->agg_min;
+    st.tile_max = v->agg_max;
+    st.step_sum = v->step_sum;
+    st.step_min = v->step_min;
+    st.step_max = v->step_max;
+    st.range = range;
+    return st;
+}
+
+// Allocate the sorted levels, level codes, fields and statistics of a volume
+// and fill them in one pass from the given arrays (original order, or a
+// contiguous range of another volume's sorted arrays: perm NULL).  `ranges`
+// (device, 4 words per field) receives the data ranges; `range_part` is
+// device scratch of 8 bytes per field and tile.
+static dvl_status place_volume(dvl_volume* v, const uint32_t* perm, const uint8_t* level, const void* const* fields,
+                               uint2* range_part, unsigned int* ranges, hipStream_t s) {
+    const Alloc& A = v->alloc;
+    const int eb = elem_bytes_of(v->dtype);
+    const int64_t n_steps = v->n_pad / kStepCells;
+    PlaceArrays pa{};
+    pa.n_fields = v->M;
+    {
+        DevBuf lv(A), lc(A);
+        if (dvl_status st = lv.alloc((size_t)v->n_pad, "sorted levels")) return st;
+        v->level_s = (uint8_t*)lv.release();
+        v->bytes += (size_t)v->n_pad;
+        if (dvl_status st = lc.alloc((size_t)n_steps * 4, "level codes")) return st;
+        v->lcode_s = (uint32_t*)lc.release();
+        v->bytes += (size_t)n_steps * 4;
+    }
+    pa.level_src = level;
+    pa.level_dst = v->level_s;
+    pa.codes = v->lcode_s;
+    for (int m = 0; m < v->M; ++m) {
+        DevBuf fb(A);
+        if (dvl_status st = fb.alloc((size_t)v->n_pad * eb, "sorted field")) return st;
+        v->fields_s[m] = fb.release();
+        v->bytes += (size_t)v->n_pad * eb;
+        pa.src[m] = fields[m];
+        pa.dst[m] = v->fields_s[m];
+    }
+    DevBuf as(A), an(A), ax(A), ss(A), sn(A), sx(A);
+    const size_t mt = (size_t)v->M * v->n_tiles;
+    const size_t ms = mt * v->tile_steps;
+    if (dvl_status st = as.alloc(mt * 8, "tile sums")) return st;
+    if (dvl_status st = an.alloc(mt * 4, "tile minima")) return st;
+    if (dvl_status st = ax.alloc(mt * 4, "tile maxima")) return st;
+    if (dvl_status st = ss.alloc(ms * 8, "step sums")) return st;
+    if (dvl_status st = sn.alloc(ms * 4, "step minima")) return st;
+    if (dvl_status st = sx.alloc(ms * 4, "step maxima")) return st;
+    v->agg_sum = (double*)as.release();
+    v->agg_min = (float*)an.release();
+    v->agg_max = (float*)ax.release();
+    v->step_sum = (double*)ss.release();
+    v->step_min = (float*)sn.release();
+    v->step_max = (float*)sx.release();
+    v->bytes += (mt + ms) * 16;
+    return launch_place(v->n, v->dtype, v->tile_steps, perm, pa, place_stats(v, range_part), ranges, s);
+}
+
+// scratch of dvl_set_field's range check: the result (4 words), then the partial ranges
+static dvl_status alloc_range_scratch(dvl_volume* v) {
+    DevBuf sr(v->alloc);
+    const size_t bytes = 256 + range_scratch_bytes();
+    if (dvl_status st = sr.alloc(bytes, "range scratch")) return st;
+    v->scratch_range = (unsigned int*)sr.release();
+    v->bytes += bytes;
+    return DVL_OK;
 }
 
 extern "C" {
@@ -1117,8 +1184,6 @@ dvl_status dvl_build_order_ex(int64_t n, const int32_t* x, const int32_t* y, con
         run_waves = opt->run_waves;
     }
     hipStream_t s = (hipStream_t)stream;
-    const int eb = elem_bytes_of(dtype);
-
     dvl_volume* v = new (std::nothrow) dvl_volume();
     if (!v) return fail(DVL_E_NOMEM, "host allocation failed");
     struct Guard { dvl_volume* v; ~Guard() { if (v) dvl_destroy(v); } } guard{v};
@@ -1146,9 +1211,8 @@ dvl_status dvl_build_order_ex(int64_t n, const int32_t* x, const int32_t* y, con
 
     // extent, validity, grid bits
     DevBuf ext(A);
-    if (dvl_status st = ext.alloc(4 * sizeof(unsigned long long), "extent")) return st;
-    DVL_HIP(hipMemsetAsync(ext.p, 0, 4 * sizeof(unsigned long long), s));
-    if (dvl_status st = launch_extent(n, x, y, z, level, (unsigned long long*)ext.p, s)) return st;
+    if (dvl_status st = ext.alloc(256 + extent_scratch_bytes(), "extent")) return st;
+    if (dvl_status st = launch_extent(n, x, y, z, level, (unsigned long long*)ext.p, (char*)ext.p + 256, s)) return st;
     unsigned long long eh[4] = {};
     DVL_HIP(hipMemcpyAsync(eh, ext.p, sizeof eh, hipMemcpyDeviceToHost, s));
     DVL_HIP(hipStreamSynchronize(s));
@@ -1175,79 +1239,29 @@ dvl_status dvl_build_order_ex(int64_t n, const int32_t* x, const int32_t* y, con
                                    (uint32_t*)vb.p, (uint32_t*)counts.p, (uint32_t*)partial.p, s,
                                    &ksorted, &vsorted))
         return st;
-    DVL_HIP(hipMemsetAsync(ext.p, 0, 4 * sizeof(unsigned long long), s));
-    if (dvl_status st = launch_dup(n, ksorted, (unsigned long long*)ext.p, s)) return st;
-    DVL_HIP(hipMemcpyAsync(eh, ext.p, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    DVL_HIP(hipStreamSynchronize(s));
-    if (eh[0]) return fail(DVL_E_OVERLAP, "two cells share a Hilbert key (overlapping AMR cells)");
+    unsigned long long* dup = (unsigned long long*)ext.p + 3;   // zeroed with the extent
+    if (dvl_status st = launch_dup(n, ksorted, dup, s)) return st;
     // keep the sorted pair, free the other
     if (ksorted == ka.p) { v->keys_s = (uint64_t*)ka.release(); } else { v->keys_s = (uint64_t*)kb.release(); }
     if (vsorted == va.p) { v->perm = (uint32_t*)va.release(); } else { v->perm = (uint32_t*)vb.release(); }
     v->bytes += (size_t)n * 12;
 
-    // gather into sorted order (padded to whole tiles, padding zeroed)
-    DevBuf lv(A);
-    if (dvl_status st = lv.alloc((size_t)v->n_pad, "sorted levels")) return st;
-    DVL_HIP(hipMemsetAsync((char*)lv.p + n, 0, (size_t)(v->n_pad - n), s));
-    if (dvl_status st = launch_gather(n, v->perm, level, lv.p, 1, s)) return st;
-    v->level_s = (uint8_t*)lv.release();
-    v->bytes += (size_t)v->n_pad;
-    {
-        DevBuf lc(A);
-        const int64_t n_steps = v->n_pad / kStepCells;
-        if (dvl_status st = lc.alloc((size_t)n_steps * 4, "level codes")) return st;
-        if (dvl_status st = launch_level_codes(v->level_s, n_steps, (uint32_t*)lc.p, s)) return st;
-        v->lcode_s = (uint32_t*)lc.release();
-        v->bytes += (size_t)n_steps * 4;
-    }
-    DevBuf rng(A);
+    // sorted arrays (padded to whole tiles), statistics and data ranges
+    DevBuf rng(A), part(A);
     if (dvl_status st = rng.alloc((size_t)kMaxFields * 4 * sizeof(unsigned int), "ranges")) return st;
-    std::vector<unsigned int> rinit(kMaxFields * 4, 0u);
-    for (int m = 0; m < kMaxFields; ++m) rinit[m * 4] = 0xFFFFFFFFu;
-    DVL_HIP(hipMemcpyAsync(rng.p, rinit.data(), rinit.size() * 4, hipMemcpyHostToDevice, s));
-    for (int m = 0; m < M; ++m) {
-        DevBuf fb(A);
-        if (dvl_status st = fb.alloc((size_t)v->n_pad * eb, "sorted field")) return st;
-        DVL_HIP(hipMemsetAsync((char*)fb.p + (size_t)n * eb, 0, (size_t)(v->n_pad - n) * eb, s));
-        if (dvl_status st = launch_gather_range(n, v->perm, dtype, fields[m], fb.p, (unsigned int*)rng.p + 4 * m, s))
-            return st;
-        v->fields_s[m] = fb.release();
-        v->bytes += (size_t)v->n_pad * eb;
-    }
-    {
-        DevBuf as(A), an(A), ax(A), ss(A), sn(A), sx(A);
-        const size_t mt = (size_t)M * v->n_tiles;
-        const size_t ms = mt * v->tile_steps;
-        if (dvl_status st = as.alloc(mt * 8, "tile sums")) return st;
-        if (dvl_status st = an.alloc(mt * 4, "tile minima")) return st;
-        if (dvl_status st = ax.alloc(mt * 4, "tile maxima")) return st;
-        if (dvl_status st = ss.alloc(ms * 8, "step sums")) return st;
-        if (dvl_status st = sn.alloc(ms * 4, "step minima")) return st;
-        if (dvl_status st = sx.alloc(ms * 4, "step maxima")) return st;
-        v->agg_sum = (double*)as.release();
-        v->agg_min = (float*)an.release();
-        v->agg_max = (float*)ax.release();
-        v->step_sum = (double*)ss.release();
-        v->step_min = (float*)sn.release();
-        v->step_max = (float*)sx.release();
-        v->bytes += (mt + ms) * 16;
-        for (int m = 0; m < M; ++m)
-            if (dvl_status st = tile_aggregates(v, m, s)) return st;
-    }
-    DVL_HIP(hipMemcpyAsync(rinit.data(), rng.p, rinit.size() * 4, hipMemcpyDeviceToHost, s));
+    if (dvl_status st = part.alloc((size_t)M * v->n_tiles * sizeof(uint2), "partial ranges")) return st;
+    if (dvl_status st = place_volume(v, v->perm, level, fields, (uint2*)part.p, (unsigned int*)rng.p, s)) return st;
+    unsigned int rh[kMaxFields * 4] = {};
+    DVL_HIP(hipMemcpyAsync(eh, dup, sizeof eh[0], hipMemcpyDeviceToHost, s));
+    DVL_HIP(hipMemcpyAsync(rh, rng.p, (size_t)M * 4 * sizeof rh[0], hipMemcpyDeviceToHost, s));
     DVL_HIP(hipStreamSynchronize(s));
+    if (eh[0]) return fail(DVL_E_OVERLAP, "two cells share a Hilbert key (overlapping AMR cells)");
     for (int m = 0; m < M; ++m) {
-        if (rinit[m * 4 + 2]) return fail(DVL_E_RANGE, "field %d holds a NaN", m);
-        v->dmin[m] = unkey(rinit[m * 4]);
-        v->dmax[m] = unkey(rinit[m * 4 + 1]);
+        if (rh[m * 4 + 2]) return fail(DVL_E_RANGE, "field %d holds a NaN", m);
+        v->dmin[m] = unkey(rh[m * 4]);
+        v->dmax[m] = unkey(rh[m * 4 + 1]);
     }
-
-    {
-        DevBuf sr(A);
-        if (dvl_status st = sr.alloc(4 * sizeof(unsigned int), "range scratch")) return st;
-        v->scratch_range = (unsigned int*)sr.release();
-        v->bytes += 4 * sizeof(unsigned int);
-    }
+    if (dvl_status st = alloc_range_scratch(v)) return st;
     DVL_HIP(hipEventCreateWithFlags(&v->cache_ready, hipEventDisableTiming));
 
     // private executor of dvl_update, with the workspace of one request ready
@@ -1270,23 +1284,22 @@ dvl_status dvl_set_field(dvl_volume* v, int32_t m, const void* values, void* str
     if (m < 0 || m >= v->M) return fail(DVL_E_INVALID, "field index %d outside [0, %d)", m, v->M);
     if (!values) return fail(DVL_E_INVALID, "values is NULL");
     hipStream_t s = (hipStream_t)stream;
-    const int eb = elem_bytes_of(v->dtype);
     // The data range (and the NaN check) does not depend on the order, so it
     // is taken from the new values as given, before anything of the volume
     // changes: a rejected field leaves the volume as it was.
-    unsigned int r[4] = {0xFFFFFFFFu, 0u, 0u, 0u};
-    DVL_HIP(hipMemcpyAsync(v->scratch_range, r, sizeof r, hipMemcpyHostToDevice, s));
-    if (dvl_status st = launch_range(v->n, v->dtype, values, v->scratch_range, s)) return st;
+    unsigned int r[4] = {};
+    if (dvl_status st = launch_range(v->n, v->dtype, values, v->scratch_range, (char*)v->scratch_range + 256, s)) return st;
     DVL_HIP(hipMemcpyAsync(r, v->scratch_range, sizeof r, hipMemcpyDeviceToHost, s));
     DVL_HIP(hipStreamSynchronize(s));
     if (r[2]) return fail(DVL_E_RANGE, "field %d holds a NaN; the volume is unchanged", m);
     v->idx_valid = false;      // the cached entries describe the old values
     v->cand_set = false;
-    if (dvl_status st = launch_gather(v->n, v->perm, values, v->fields_s[m], eb, s)) {
-        v->sticky = st;
-        return st;
-    }
-    if (dvl_status st = tile_aggregates(v, m, s)) {
+    PlaceArrays pa{};
+    pa.n_fields = 1;
+    pa.first_field = m;
+    pa.src[0] = values;
+    pa.dst[0] = v->fields_s[m];
+    if (dvl_status st = launch_place(v->n, v->dtype, v->tile_steps, v->perm, pa, place_stats(v, nullptr), nullptr, s)) {
         v->sticky = st;
         return st;
     }
@@ -1625,67 +1638,20 @@ dvl_status dvl_zoom(const dvl_volume* v, uint32_t first, uint32_t last, const dv
         z->perm = (uint32_t*)pb.release();
         z->bytes += (size_t)n * 12;
     }
-    {
-        DevBuf lv(A);
-        if (dvl_status st = lv.alloc((size_t)z->n_pad, "sorted levels")) return st;
-        DVL_HIP(hipMemsetAsync((char*)lv.p + n, 0, (size_t)(z->n_pad - n), s));
-        DVL_HIP(hipMemcpyAsync(lv.p, v->level_s + first, (size_t)n, hipMemcpyDeviceToDevice, s));
-        z->level_s = (uint8_t*)lv.release();
-        z->bytes += (size_t)z->n_pad;
-        DevBuf lc(A);
-        const int64_t n_steps = z->n_pad / kStepCells;
-        if (dvl_status st = lc.alloc((size_t)n_steps * 4, "level codes")) return st;
-        if (dvl_status st = launch_level_codes(z->level_s, n_steps, (uint32_t*)lc.p, s)) return st;
-        z->lcode_s = (uint32_t*)lc.release();
-        z->bytes += (size_t)n_steps * 4;
-    }
-    DevBuf rng(A);
+    DevBuf rng(A), part(A);
     if (dvl_status st = rng.alloc((size_t)kMaxFields * 4 * sizeof(unsigned int), "ranges")) return st;
-    std::vector<unsigned int> rinit(kMaxFields * 4, 0u);
-    for (int m = 0; m < kMaxFields; ++m) rinit[m * 4] = 0xFFFFFFFFu;
-    DVL_HIP(hipMemcpyAsync(rng.p, rinit.data(), rinit.size() * 4, hipMemcpyHostToDevice, s));
-    for (int m = 0; m < z->M; ++m) {
-        DevBuf fb(A);
-        if (dvl_status st = fb.alloc((size_t)z->n_pad * eb, "sorted field")) return st;
-        DVL_HIP(hipMemsetAsync((char*)fb.p + (size_t)n * eb, 0, (size_t)(z->n_pad - n) * eb, s));
-        DVL_HIP(hipMemcpyAsync(fb.p, (const char*)v->fields_s[m] + (size_t)first * eb, (size_t)n * eb,
-                               hipMemcpyDeviceToDevice, s));
-        if (dvl_status st = launch_range(n, z->dtype, fb.p, (unsigned int*)rng.p + 4 * m, s)) return st;
-        z->fields_s[m] = fb.release();
-        z->bytes += (size_t)z->n_pad * eb;
-    }
-    {
-        DevBuf as(A), an(A), ax(A), ss(A), sn(A), sx(A);
-        const size_t mt = (size_t)z->M * z->n_tiles;
-        const size_t ms = mt * z->tile_steps;
-        if (dvl_status st = as.alloc(mt * 8, "tile sums")) return st;
-        if (dvl_status st = an.alloc(mt * 4, "tile minima")) return st;
-        if (dvl_status st = ax.alloc(mt * 4, "tile maxima")) return st;
-        if (dvl_status st = ss.alloc(ms * 8, "step sums")) return st;
-        if (dvl_status st = sn.alloc(ms * 4, "step minima")) return st;
-        if (dvl_status st = sx.alloc(ms * 4, "step maxima")) return st;
-        z->agg_sum = (double*)as.release();
-        z->agg_min = (float*)an.release();
-        z->agg_max = (float*)ax.release();
-        z->step_sum = (double*)ss.release();
-        z->step_min = (float*)sn.release();
-        z->step_max = (float*)sx.release();
-        z->bytes += (mt + ms) * 16;
-        for (int m = 0; m < z->M; ++m)
-            if (dvl_status st = tile_aggregates(z, m, s)) return st;
-    }
-    DVL_HIP(hipMemcpyAsync(rinit.data(), rng.p, rinit.size() * 4, hipMemcpyDeviceToHost, s));
+    if (dvl_status st = part.alloc((size_t)z->M * z->n_tiles * sizeof(uint2), "partial ranges")) return st;
+    const void* src[kMaxFields] = {};
+    for (int m = 0; m < z->M; ++m) src[m] = (const char*)v->fields_s[m] + (size_t)first * eb;
+    if (dvl_status st = place_volume(z, nullptr, v->level_s + first, src, (uint2*)part.p, (unsigned int*)rng.p, s)) return st;
+    unsigned int rh[kMaxFields * 4] = {};
+    DVL_HIP(hipMemcpyAsync(rh, rng.p, (size_t)z->M * 4 * sizeof rh[0], hipMemcpyDeviceToHost, s));
     DVL_HIP(hipStreamSynchronize(s));
     for (int m = 0; m < z->M; ++m) {
-        z->dmin[m] = unkey(rinit[m * 4]);
-        z->dmax[m] = unkey(rinit[m * 4 + 1]);
+        z->dmin[m] = unkey(rh[m * 4]);
+        z->dmax[m] = unkey(rh[m * 4 + 1]);
     }
-    {
-        DevBuf sr(A);
-        if (dvl_status st = sr.alloc(4 * sizeof(unsigned int), "range scratch")) return st;
-        z->scratch_range = (unsigned int*)sr.release();
-        z->bytes += 4 * sizeof(unsigned int);
-    }
+    if (dvl_status st = alloc_range_scratch(z)) return st;
     DVL_HIP(hipEventCreateWithFlags(&z->cache_ready, hipEventDisableTiming));
     if (dvl_status st = new_executor(A, &z->ex)) return st;
     if (dvl_status st = z->ex->ensure_ws(0, request_ws_bytes(z, 1))) return st;

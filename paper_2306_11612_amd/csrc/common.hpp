@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "dvl.h"
 
 namespace dvl {
@@ -145,6 +147,55 @@ __device__ __forceinline__ float wave_max_f(float v) {
         v = fmaxf(v, __int_as_float(__builtin_amdgcn_ds_bpermute((lane_id() ^ o) << 2, __float_as_int(v))));
     return v;
 }
+
+// Reductions of a whole wave through the lanes' data paths (DPP): rows of 16
+// by row shifts, then rows 0-1 and 2-3, then both halves by row broadcasts;
+// lane 63 holds the result, which every lane gets from a scalar register.
+// No LDS round trips: six dependent ds_bpermute of the butterflies above are
+// six LDS latencies.  All 64 lanes must be active.
+#define DVL_DPP_ROW_BCAST15 0x142
+#define DVL_DPP_ROW_BCAST31 0x143
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t old, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_d(double v) {
+    const uint64_t u = __double_as_longlong(v);
+    const uint32_t lo = dpp_move<CTRL, ROWS>(0u, (uint32_t)u), hi = dpp_move<CTRL, ROWS>(0u, (uint32_t)(u >> 32));
+    return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_total_d(double v) {
+    v = dpp_add_d<DVL_DPP_ROW_SHR(1), 0xF>(v);
+    v = dpp_add_d<DVL_DPP_ROW_SHR(2), 0xF>(v);
+    v = dpp_add_d<DVL_DPP_ROW_SHR(4), 0xF>(v);
+    v = dpp_add_d<DVL_DPP_ROW_SHR(8), 0xF>(v);
+    v = dpp_add_d<DVL_DPP_ROW_BCAST15, 0xA>(v);
+    v = dpp_add_d<DVL_DPP_ROW_BCAST31, 0xC>(v);
+    return readlane(v, kWave - 1);
+}
+// op: a commutative, associative and idempotent choice of two values (min, max)
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_choose(T v, Op op) {
+    static_assert(sizeof(T) == 4, "one 32-bit register per lane");
+    auto mv = [](auto ctrl, auto rows, T x) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, x);
+        return __builtin_bit_cast(T, dpp_move<decltype(ctrl)::value, decltype(rows)::value>(u, u));
+    };
+    using std::integral_constant;
+    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(1)>{}, integral_constant<int, 0xF>{}, v));
+    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(2)>{}, integral_constant<int, 0xF>{}, v));
+    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(4)>{}, integral_constant<int, 0xF>{}, v));
+    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(8)>{}, integral_constant<int, 0xF>{}, v));
+    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_BCAST15>{}, integral_constant<int, 0xA>{}, v));
+    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_BCAST31>{}, integral_constant<int, 0xC>{}, v));
+    return __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_readlane((int)__builtin_bit_cast(uint32_t, v), kWave - 1));
+}
+__device__ __forceinline__ float wave_lowest_f(float v) { return wave_choose(v, [](float a, float b) { return fminf(a, b); }); }
+__device__ __forceinline__ float wave_highest_f(float v) { return wave_choose(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ uint32_t wave_lowest_u(uint32_t v) { return wave_choose(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; }); }
+__device__ __forceinline__ uint32_t wave_highest_u(uint32_t v) { return wave_choose(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
 
 // ---------------------------------------------------------------- storage types
 

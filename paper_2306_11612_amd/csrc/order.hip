@@ -7,44 +7,105 @@
 // centroids, ordered along a Hilbert curve), GPU section (the order is
 // established once; only the spacing changes afterwards).
 #include "order.hpp"
+#include "update.hpp"
 
 #include <algorithm>
 
 namespace dvl {
 
 // ===================================================================
-// extent: max(corner + 2^level) over all cells and axes, plus range checks
+// extent: max(corner + 2^level) over all cells and axes, plus range checks.
+// Each workgroup writes its own maximum and flags; k_extent_fold takes them
+// together.  (Every wave's atomicMax on one word cost about 12 ns each
+// whatever the cell count, 32768 waves x 2 atomics: 771 us for 50 M cells;
+// 142 + 6 us like this.)
 // ===================================================================
-__global__ __launch_bounds__(256) void k_extent(int64_t n, const int32_t* __restrict__ x,
-                                                const int32_t* __restrict__ y,
-                                                const int32_t* __restrict__ z,
-                                                const uint8_t* __restrict__ level,
-                                                unsigned long long* __restrict__ out /* [0] max upper corner, [1] bad, [2] max level */) {
+constexpr int kReduceThreads = 256;
+constexpr int kReduceBlocks = 2048;   // at most; two words of partial result each
+
+struct ExtentPart {
+    unsigned long long upper;    // max(corner + 2^level)
+    uint32_t bad, level;         // a check failed; max level
+};
+
+__device__ __forceinline__ void extent_add(int32_t cx, int32_t cy, int32_t cz, uint32_t L, int64_t& mx,
+                                           uint32_t& bad, uint32_t& lmax) {
+    bad |= (cx < 0) | (cy < 0) | (cz < 0) | (L > 20u);
+    lmax = max(lmax, L);
+    const int64_t w = (int64_t)1 << (L & 31u);
+    mx = max(mx, max(max((int64_t)cx, (int64_t)cy), (int64_t)cz) + w);
+}
+
+// the workgroup's partial result (in thread 0); kWaves: waves of the workgroup
+template <int kWaves>
+__device__ __forceinline__ ExtentPart extent_block(int64_t mx, uint32_t bad, uint32_t lmax) {
+    __shared__ ExtentPart part[kWaves];
+    // mx < 2^33: the high word is 0 or 1, reduced first
+    const uint32_t hi = wave_highest_u((uint32_t)((uint64_t)mx >> 32));
+    const uint32_t lo = wave_highest_u((uint32_t)((uint64_t)mx >> 32) == hi ? (uint32_t)mx : 0u);
+    bad = __ballot(bad != 0u) != 0ull;
+    lmax = wave_highest_u(lmax);
+    if (lane_id() == 0) part[threadIdx.x / kWave] = ExtentPart{((unsigned long long)hi << 32) | lo, bad, lmax};
+    __syncthreads();
+    ExtentPart r = part[0];
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kWaves; ++k) {
+            r.upper = max(r.upper, part[k].upper);
+            r.bad |= part[k].bad;
+            r.level = max(r.level, part[k].level);
+        }
+    }
+    return r;
+}
+
+// Four consecutive cells per thread and iteration with vector loads when the
+// caller's arrays allow it (V4: x, y, z 16-byte and level 4-byte aligned,
+// checked by the launcher); the last n % 4 cells, or all, one by one.
+template <bool V4>
+__global__ __launch_bounds__(kReduceThreads) void k_extent(int64_t n, const int32_t* __restrict__ x,
+                                                           const int32_t* __restrict__ y,
+                                                           const int32_t* __restrict__ z,
+                                                           const uint8_t* __restrict__ level,
+                                                           ExtentPart* __restrict__ part) {
     int64_t mx = 0;
     uint32_t bad = 0, lmax = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const int32_t cx = x[i], cy = y[i], cz = z[i];
-        const uint32_t L = level[i];
-        bad |= (cx < 0) | (cy < 0) | (cz < 0) | (L > 20u);
-        lmax = max(lmax, L);
-        const int64_t w = (int64_t)1 << (L & 31u);
-        const int64_t m = max(max((int64_t)cx, (int64_t)cy), (int64_t)cz) + w;
-        mx = max(mx, m);
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t nq = V4 ? n >> 2 : 0;
+    if constexpr (V4) {
+        for (int64_t q = tid; q < nq; q += stride) {
+            const int4 cx = reinterpret_cast<const int4*>(x)[q];
+            const int4 cy = reinterpret_cast<const int4*>(y)[q];
+            const int4 cz = reinterpret_cast<const int4*>(z)[q];
+            const uint32_t lw = reinterpret_cast<const uint32_t*>(level)[q];
+            extent_add(cx.x, cy.x, cz.x, lw & 0xFFu, mx, bad, lmax);
+            extent_add(cx.y, cy.y, cz.y, (lw >> 8) & 0xFFu, mx, bad, lmax);
+            extent_add(cx.z, cy.z, cz.z, (lw >> 16) & 0xFFu, mx, bad, lmax);
+            extent_add(cx.w, cy.w, cz.w, lw >> 24, mx, bad, lmax);
+        }
     }
-    // wave reduce then one atomic per wave
-    for (int o = 32; o > 0; o >>= 1) {
-        const int l = lane_id() ^ o;
-        int lo = __builtin_amdgcn_ds_bpermute(l << 2, (int)(uint32_t)mx);
-        int hi = __builtin_amdgcn_ds_bpermute(l << 2, (int)(uint32_t)((uint64_t)mx >> 32));
-        mx = max(mx, (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
-        bad |= (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)bad);
-        lmax = max(lmax, (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)lmax));
+    for (int64_t i = 4 * nq + tid; i < n; i += stride) extent_add(x[i], y[i], z[i], level[i], mx, bad, lmax);
+    const ExtentPart r = extent_block<kReduceThreads / kWave>(mx, bad, lmax);
+    if (threadIdx.x == 0) part[blockIdx.x] = r;
+}
+
+// out: [0] max upper corner, [1] bad, [2] max level, [3] 0 (the duplicate flag of k_dup)
+__global__ __launch_bounds__(1024) void k_extent_fold(int n_part, const ExtentPart* __restrict__ part,
+                                                      unsigned long long* __restrict__ out) {
+    int64_t mx = 0;
+    uint32_t bad = 0, lmax = 0;
+    for (int i = threadIdx.x; i < n_part; i += blockDim.x) {
+        const ExtentPart p = part[i];
+        mx = max(mx, (int64_t)p.upper);
+        bad |= p.bad;
+        lmax = max(lmax, p.level);
     }
-    if (lane_id() == 0) {
-        atomicMax(&out[0], (unsigned long long)mx);
-        if (bad) atomicOr(&out[1], 1ull);
-        atomicMax(&out[2], (unsigned long long)lmax);
+    const ExtentPart r = extent_block<1024 / kWave>(mx, bad, lmax);
+    if (threadIdx.x == 0) {
+        out[0] = r.upper;
+        out[1] = r.bad;
+        out[2] = r.level;
+        out[3] = 0ull;
     }
 }
 
@@ -115,54 +176,10 @@ __global__ __launch_bounds__(256) void k_keys(int64_t n, const int32_t* __restri
     }
 }
 
-// The same two passes over four consecutive cells per thread and iteration
-// (x, y, z 16-byte aligned and level 4-byte aligned, checked by the
-// launchers): vector loads of the coordinates and levels, vector stores of
-// the keys and indices; the last n % 4 cells one by one.
-__device__ __forceinline__ void extent_add(int32_t cx, int32_t cy, int32_t cz, uint32_t L, int64_t& mx,
-                                           uint32_t& bad, uint32_t& lmax) {
-    bad |= (cx < 0) | (cy < 0) | (cz < 0) | (L > 20u);
-    lmax = max(lmax, L);
-    const int64_t w = (int64_t)1 << (L & 31u);
-    mx = max(mx, max(max((int64_t)cx, (int64_t)cy), (int64_t)cz) + w);
-}
-
-__global__ __launch_bounds__(256) void k_extent4(int64_t n, const int32_t* __restrict__ x,
-                                                 const int32_t* __restrict__ y,
-                                                 const int32_t* __restrict__ z,
-                                                 const uint8_t* __restrict__ level,
-                                                 unsigned long long* __restrict__ out) {
-    int64_t mx = 0;
-    uint32_t bad = 0, lmax = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nq = n >> 2;
-    for (int64_t q = tid; q < nq; q += stride) {
-        const int4 cx = reinterpret_cast<const int4*>(x)[q];
-        const int4 cy = reinterpret_cast<const int4*>(y)[q];
-        const int4 cz = reinterpret_cast<const int4*>(z)[q];
-        const uint32_t lw = reinterpret_cast<const uint32_t*>(level)[q];
-        extent_add(cx.x, cy.x, cz.x, lw & 0xFFu, mx, bad, lmax);
-        extent_add(cx.y, cy.y, cz.y, (lw >> 8) & 0xFFu, mx, bad, lmax);
-        extent_add(cx.z, cy.z, cz.z, (lw >> 16) & 0xFFu, mx, bad, lmax);
-        extent_add(cx.w, cy.w, cz.w, lw >> 24, mx, bad, lmax);
-    }
-    for (int64_t i = 4 * nq + tid; i < n; i += stride) extent_add(x[i], y[i], z[i], level[i], mx, bad, lmax);
-    for (int o = 32; o > 0; o >>= 1) {
-        const int l = lane_id() ^ o;
-        int lo = __builtin_amdgcn_ds_bpermute(l << 2, (int)(uint32_t)mx);
-        int hi = __builtin_amdgcn_ds_bpermute(l << 2, (int)(uint32_t)((uint64_t)mx >> 32));
-        mx = max(mx, (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
-        bad |= (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)bad);
-        lmax = max(lmax, (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)lmax));
-    }
-    if (lane_id() == 0) {
-        atomicMax(&out[0], (unsigned long long)mx);
-        if (bad) atomicOr(&out[1], 1ull);
-        atomicMax(&out[2], (unsigned long long)lmax);
-    }
-}
-
+// The same over four consecutive cells per thread and iteration (x, y, z
+// 16-byte aligned and level 4-byte aligned, checked by the launcher): vector
+// loads of the coordinates and levels, vector stores of the keys and indices;
+// the last n % 4 cells one by one.
 __global__ __launch_bounds__(256) void k_keys4(int64_t n, const int32_t* __restrict__ x,
                                                const int32_t* __restrict__ y,
                                                const int32_t* __restrict__ z,
@@ -511,119 +528,255 @@ int64_t sort_tile_count(int64_t n) {
 }
 
 // ===================================================================
-// gather into sorted order; data ranges
+// data ranges: order-preserving unsigned keys of floats, a NaN above them all
+// ===================================================================
+constexpr uint32_t kRangeNan = 0xFFFFFFFFu;   // above the key of +inf
+
+__device__ __forceinline__ void range_add(float f, uint32_t& lo, uint32_t& hi) {
+    uint32_t u = __float_as_uint(f);
+    u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    lo = min(lo, u);
+    hi = max(hi, f != f ? kRangeNan : u);
+}
+
+// a workgroup's range (in thread 0)
+__device__ __forceinline__ uint2 range_block(uint32_t lo, uint32_t hi, uint2* part) {
+    lo = wave_lowest_u(lo);
+    hi = wave_highest_u(hi);
+    if (lane_id() == 0) part[threadIdx.x / kWave] = make_uint2(lo, hi);
+    __syncthreads();
+    uint2 r = part[0];
+    if (threadIdx.x == 0)
+        for (int k = 1; k < (int)(blockDim.x / kWave); ++k) {
+            r.x = min(r.x, part[k].x);
+            r.y = max(r.y, part[k].y);
+        }
+    return r;
+}
+
+// Range of n values in any order: one partial range per workgroup (the
+// same-address atomics of every wave took 745 us whatever n, see k_extent;
+// 11.8 M fp32 values: 13 + 6 us).
+// V4: the values are aligned for vector loads of four, four of them in flight.
+template <typename S, bool V4>
+__global__ __launch_bounds__(kReduceThreads) void k_range(int64_t n, const typename S::raw* __restrict__ v,
+                                                          uint2* __restrict__ part) {
+    __shared__ uint2 sh[kReduceThreads / kWave];
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t nq = V4 ? n >> 2 : 0;
+    if constexpr (V4) {
+        int64_t q = tid;
+        for (; q + 3 * stride < nq; q += 4 * stride) {
+            Quad<S> d[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) d[g].load(v, q + g * stride);
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) range_add(d[g].get(k), lo, hi);
+        }
+        for (; q < nq; q += stride) {
+            Quad<S> d;
+            d.load(v, q);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) range_add(d.get(k), lo, hi);
+        }
+    }
+    for (int64_t i = 4 * nq + tid; i < n; i += stride) range_add(to_f32(S{}, v[i]), lo, hi);
+    const uint2 r = range_block(lo, hi, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = r;
+}
+
+// Workgroup m folds the n_part partial ranges part[m * n_part ..] of field m:
+// out[4 m] = min key, [4 m + 1] = max key, [4 m + 2] = NaN seen.
+__global__ __launch_bounds__(1024) void k_range_fold(int64_t n_part, const uint2* __restrict__ part,
+                                                     unsigned int* __restrict__ out) {
+    __shared__ uint2 sh[1024 / kWave];
+    const uint2* p = part + (int64_t)blockIdx.x * n_part;
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    for (int64_t i = threadIdx.x; i < n_part; i += blockDim.x) {
+        const uint2 r = p[i];
+        lo = min(lo, r.x);
+        hi = max(hi, r.y);
+    }
+    const uint2 r = range_block(lo, hi, sh);
+    if (threadIdx.x == 0) {
+        out[4 * blockIdx.x] = r.x;
+        out[4 * blockIdx.x + 1] = r.y;
+        out[4 * blockIdx.x + 2] = r.y == kRangeNan;
+    }
+}
+
+// ===================================================================
+// Sorted arrays of a volume, one pass: gather by the permutation (or a copy
+// of a contiguous range, perm NULL), zero padding, data range, per-tile and
+// per-step statistics, level codes.
+//
+// One workgroup per (tile, array): arrays 0 .. M - 1 are the fields, array M
+// (when present) the levels.  Its four waves take a quarter of the tile's
+// steps each, G steps' loads in flight (4 G scattered loads per lane).
+// Bound by the scattered reads.  The cells of a tile are neighbours on the
+// Hilbert curve, a compact block whose rows share the cache lines of the
+// original order, so a tile is read by one workgroup, and the tiles are dealt
+// to the 8 XCDs in contiguous eighths: lines shared by neighbouring tiles are
+// fetched into one L2, and a tile's permutation is read from HBM once for all
+// its arrays.  Statistics and ranges come from the registers that hold the
+// gathered values, instead of a second pass over the sorted arrays.
+// 50 M cells, 4 fp32 fields: 536 us (before, in separate passes: 4 gathers of
+// 769, 4 statistics passes of 73, levels 69, codes 38 us); 11.8 M cells, one
+// field of a data change: 33 us (gather 31 + statistics 30).
+// Tile sums: per lane, fp32 sums of 4 values accumulated in fp64 over the
+// wave's steps, then the wave, then the four waves in order; step sums: per
+// lane the fp64 sum of its 4 values, then the wave.
 // ===================================================================
 template <typename T>
 struct alignas(4 * sizeof(T)) Four {
     T v[4];
 };
 
-// dst[i] = src[perm[i]]; four consecutive i per thread and iteration (perm and
-// dst are the volume's own, 256-byte aligned): one 16-byte load of perm, four
-// scattered loads in flight together, one vector store
-template <typename T>
-__global__ __launch_bounds__(256) void k_gather(int64_t n, const uint32_t* __restrict__ perm,
-                                                const T* __restrict__ src, T* __restrict__ dst) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nq = n >> 2;
-    for (int64_t q = tid; q < nq; q += stride) {
-        const u32x4 p = *reinterpret_cast<const u32x4*>(perm + 4 * q);
-        const uint32_t pk[4] = {p.x, p.y, p.z, p.w};
-        Four<T> o;
+// the four original indices of the sorted cells c .. c + 3 (n for cells past the end)
+__device__ __forceinline__ Four<uint32_t> source_quad(const uint32_t* perm, int64_t c, int64_t n) {
+    Four<uint32_t> r;
+    if (perm && c + 3 < n) return *reinterpret_cast<const Four<uint32_t>*>(perm + c);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) o.v[k] = pk[k] < (uint64_t)n ? src[pk[k]] : T(0);
-        reinterpret_cast<Four<T>*>(dst)[q] = o;
-    }
-    for (int64_t i = 4 * nq + tid; i < n; i += stride) {
-        const uint32_t p = perm[i];
-        if (p < (uint64_t)n) dst[i] = src[p];
-    }
+    for (int k = 0; k < 4; ++k) r.v[k] = c + k < n ? (perm ? perm[c + k] : (uint32_t)(c + k)) : (uint32_t)n;
+    return r;
 }
 
-template <typename S>
-__global__ __launch_bounds__(256) void k_range(int64_t n, const typename S::raw* __restrict__ v,
-                                               unsigned int* __restrict__ out /* [0] min key, [1] max key, [2] nan */) {
-    // order-preserving map of floats to unsigned ints
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u, nan = 0u;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const float f = to_f32(S{}, v[i]);
-        if (f != f) { nan = 1u; continue; }
-        uint32_t u = __float_as_uint(f);
-        u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-        lo = min(lo, u);
-        hi = max(hi, u);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        const int l = lane_id() ^ o;
-        lo = min(lo, (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)lo));
-        hi = max(hi, (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)hi));
-        nan |= (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)nan);
-    }
-    if (lane_id() == 0) {
-        atomicMin(&out[0], lo);
-        atomicMax(&out[1], hi);
-        if (nan) atomicOr(&out[2], 1u);
-    }
-}
-
-// gather of one field into sorted order fused with its data range (the
-// order-preserving uint map of k_range; out[0] min, out[1] max, out[2] NaN)
-template <typename S>
-__device__ __forceinline__ void range_add(float f, uint32_t& lo, uint32_t& hi, uint32_t& nan) {
-    if (f != f) {
-        nan = 1u;
-        return;
-    }
-    uint32_t u = __float_as_uint(f);
-    u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    lo = min(lo, u);
-    hi = max(hi, u);
-}
-
-// Four consecutive sorted cells per thread and iteration: one 16-byte load of
-// their permutation entries, then the four (scattered) value loads in flight
-// together, one vector store; the last n % 4 cells one by one.
-template <typename S>
-__global__ __launch_bounds__(256) void k_gather_range(int64_t n, const uint32_t* __restrict__ perm,
-                                                      const typename S::raw* __restrict__ src,
-                                                      typename S::raw* __restrict__ dst,
-                                                      unsigned int* __restrict__ out) {
+template <typename S, int G>
+__device__ __forceinline__ void place_field(int64_t n, int64_t t, int tile_steps, const uint32_t* __restrict__ perm,
+                                            const typename S::raw* __restrict__ src, typename S::raw* __restrict__ dst,
+                                            int64_t stat, const PlaceStats& st) {
     using raw = typename S::raw;
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u, nan = 0u;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nq = n >> 2;
-    for (int64_t q = tid; q < nq; q += stride) {
-        const u32x4 p = *reinterpret_cast<const u32x4*>(perm + 4 * q);
-        const uint32_t pk[4] = {p.x, p.y, p.z, p.w};
-        raw r[4];
+    constexpr int kWaves = kReduceThreads / kWave;
+    __shared__ double wsum[kWaves];
+    __shared__ float wmin[kWaves], wmax[kWaves];
+    __shared__ uint2 wrange[kWaves];
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int per = tile_steps / kWaves;
+    const int64_t step0 = t * tile_steps + (int64_t)w * per;
+    double acc = 0.0;
+    float lo = INFINITY, hi = -INFINITY;
+    uint32_t rlo = 0xFFFFFFFFu, rhi = 0u;
+    for (int s = 0; s < per; s += G) {
+        Four<uint32_t> p[G];
+        Four<raw> r[G];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r[k] = pk[k] < (uint64_t)n ? src[pk[k]] : raw(0);
+        for (int g = 0; g < G; ++g) p[g] = source_quad(perm, (step0 + s + g) * kStepCells + 4 * lane, n);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            dst[4 * q + k] = r[k];
-            if (pk[k] < (uint64_t)n) range_add<S>(to_f32(S{}, r[k]), lo, hi, nan);
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[g].v[k] = p[g].v[k] < (uint64_t)n ? src[p[g].v[k]] : raw(0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int64_t c = (step0 + s + g) * kStepCells + 4 * lane;
+            *reinterpret_cast<Four<raw>*>(dst + c) = r[g];
+            float s4 = 0.0f, slo = INFINITY, shi = -INFINITY;
+            double d4 = 0.0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (c + k < n) {
+                    const float v = to_f32(S{}, r[g].v[k]);
+                    s4 += v;
+                    d4 += (double)v;
+                    slo = fminf(slo, v);
+                    shi = fmaxf(shi, v);
+                    range_add(v, rlo, rhi);
+                }
+            }
+            acc += (double)s4;
+            lo = fminf(lo, slo);
+            hi = fmaxf(hi, shi);
+            d4 = wave_total_d(d4);
+            slo = wave_lowest_f(slo);
+            shi = wave_highest_f(shi);
+            if (lane == 0) {
+                const int64_t o = stat * tile_steps * st.n_tiles + step0 + s + g;
+                st.step_sum[o] = d4;
+                st.step_min[o] = slo;
+                st.step_max[o] = shi;
+            }
         }
     }
-    for (int64_t i = 4 * nq + tid; i < n; i += stride) {
-        const uint32_t p = perm[i];
-        if (p >= (uint64_t)n) continue;
-        const raw r = src[p];
-        dst[i] = r;
-        range_add<S>(to_f32(S{}, r), lo, hi, nan);
+    acc = wave_total_d(acc);
+    lo = wave_lowest_f(lo);
+    hi = wave_highest_f(hi);
+    if (lane == 0) {
+        wsum[w] = acc;
+        wmin[w] = lo;
+        wmax[w] = hi;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        const int l = lane_id() ^ o;
-        lo = min(lo, (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)lo));
-        hi = max(hi, (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)hi));
-        nan |= (uint32_t)__builtin_amdgcn_ds_bpermute(l << 2, (int)nan);
+    const uint2 range = range_block(rlo, rhi, wrange);   // a barrier: the other waves' sums are there
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kWaves; ++k) {
+            acc += wsum[k];
+            lo = fminf(lo, wmin[k]);
+            hi = fmaxf(hi, wmax[k]);
+        }
+        const int64_t o = stat * st.n_tiles + t;
+        st.tile_sum[o] = acc;
+        st.tile_min[o] = lo;
+        st.tile_max[o] = hi;
+        if (st.range) st.range[o] = range;
     }
-    if (lane_id() == 0) {
-        atomicMin(&out[0], lo);
-        atomicMax(&out[1], hi);
-        if (nan) atomicOr(&out[2], 1u);
+}
+
+// Levels of one tile, with the 32-bit code of each 256-cell step: byte k
+// describes the cells [64 k, 64 k + 64) of the step (lanes 16 k .. 16 k + 15):
+// their common level, or 0xFF when they differ.
+template <int G>
+__device__ __forceinline__ void place_levels(int64_t n, int64_t t, int tile_steps, const uint32_t* __restrict__ perm,
+                                             const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
+                                             uint32_t* __restrict__ codes) {
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int per = tile_steps / (kReduceThreads / kWave);
+    const int64_t step0 = t * tile_steps + (int64_t)w * per;
+    for (int s = 0; s < per; s += G) {
+        Four<uint32_t> p[G];
+        Four<uint8_t> r[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) p[g] = source_quad(perm, (step0 + s + g) * kStepCells + 4 * lane, n);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[g].v[k] = p[g].v[k] < (uint64_t)n ? src[p[g].v[k]] : (uint8_t)0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            *reinterpret_cast<Four<uint8_t>*>(dst + (step0 + s + g) * kStepCells + 4 * lane) = r[g];
+            const uint32_t word = __builtin_bit_cast(uint32_t, r[g]);
+            const uint32_t b0 = word & 0xFFu;
+            uint32_t code = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t first = readlane(b0, 16 * k);
+                const uint64_t same = __ballot(word == first * 0x01010101u) >> (16 * k);
+                code |= ((same & 0xFFFFull) == 0xFFFFull ? first : 0xFFu) << (8 * k);
+            }
+            if (lane == 0) codes[step0 + s + g] = code;
+        }
+    }
+}
+
+template <typename S, int G>
+__global__ __launch_bounds__(kReduceThreads) void k_place(int64_t n, int tile_steps, const uint32_t* __restrict__ perm,
+                                                          PlaceArrays a, PlaceStats st) {
+    const int n_arrays = a.n_fields + (a.level_src ? 1 : 0);
+    const int64_t units = st.n_tiles * n_arrays, bid = blockIdx.x;
+    // one round unless there are more units than a launch may have workgroups
+    for (int64_t u0 = 0; u0 + bid < units; u0 += gridDim.x) {
+        const int64_t nb = min((int64_t)gridDim.x, units - u0);
+        const int64_t xcd = bid % kXcds, per = nb / kXcds, rem = nb % kXcds;
+        const int64_t u = u0 + xcd * per + min(xcd, rem) + bid / kXcds;
+        const int64_t t = u / n_arrays;
+        const int m = (int)(u - t * n_arrays);
+        if (m < a.n_fields)
+            place_field<S, G>(n, t, tile_steps, perm, reinterpret_cast<const typename S::raw*>(a.src[m]),
+                              reinterpret_cast<typename S::raw*>(a.dst[m]), a.first_field + m, st);
+        else
+            place_levels<G>(n, t, tile_steps, perm, a.level_src, a.level_dst, a.codes);
+        __syncthreads();
     }
 }
 
@@ -648,12 +801,17 @@ static bool vec4_inputs(const int32_t* x, const int32_t* y, const int32_t* z, co
            (reinterpret_cast<uintptr_t>(level) & 3u) == 0;
 }
 
+size_t extent_scratch_bytes() { return (size_t)kReduceBlocks * sizeof(ExtentPart); }
+
 dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
-                         const uint8_t* level, unsigned long long* out, hipStream_t s) {
+                         const uint8_t* level, unsigned long long* out, void* scratch, hipStream_t s) {
+    ExtentPart* part = reinterpret_cast<ExtentPart*>(scratch);
+    const unsigned grid = grid_for((n + 3) / 4, kReduceThreads, kReduceBlocks);
     if (vec4_inputs(x, y, z, level))
-        hipLaunchKernelGGL(k_extent4, dim3(grid_for((n + 3) / 4)), dim3(256), 0, s, n, x, y, z, level, out);
+        hipLaunchKernelGGL(k_extent<true>, dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
     else
-        hipLaunchKernelGGL(k_extent, dim3(grid_for(n)), dim3(256), 0, s, n, x, y, z, level, out);
+        hipLaunchKernelGGL(k_extent<false>, dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
+    hipLaunchKernelGGL(k_extent_fold, dim3(1), dim3(1024), 0, s, (int)grid, part, out);
     DVL_HIP(hipGetLastError());
     return DVL_OK;
 }
@@ -674,21 +832,6 @@ dvl_status launch_dup(int64_t n, const uint64_t* keys, unsigned long long* flag,
     return DVL_OK;
 }
 
-dvl_status launch_gather(int64_t n, const uint32_t* perm, const void* src, void* dst, int elem_bytes,
-                         hipStream_t s) {
-    if (elem_bytes == 4)
-        hipLaunchKernelGGL(k_gather<uint32_t>, dim3(grid_for(n)), dim3(256), 0, s, n, perm,
-                           (const uint32_t*)src, (uint32_t*)dst);
-    else if (elem_bytes == 2)
-        hipLaunchKernelGGL(k_gather<uint16_t>, dim3(grid_for(n)), dim3(256), 0, s, n, perm,
-                           (const uint16_t*)src, (uint16_t*)dst);
-    else
-        hipLaunchKernelGGL(k_gather<uint8_t>, dim3(grid_for(n)), dim3(256), 0, s, n, perm,
-                           (const uint8_t*)src, (uint8_t*)dst);
-    DVL_HIP(hipGetLastError());
-    return DVL_OK;
-}
-
 dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sorted, void* orig,
                                int elem_bytes, hipStream_t s) {
     if (elem_bytes == 8)
@@ -700,29 +843,56 @@ dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sort
     return DVL_OK;
 }
 
-dvl_status launch_gather_range(int64_t n, const uint32_t* perm, int dtype, const void* src, void* dst,
-                               unsigned int* out, hipStream_t s) {
-    if (dtype == DVL_F32)
-        hipLaunchKernelGGL(k_gather_range<F32>, dim3(grid_for(n)), dim3(256), 0, s, n, perm, (const float*)src,
-                           (float*)dst, out);
-    else if (dtype == DVL_F16)
-        hipLaunchKernelGGL(k_gather_range<F16>, dim3(grid_for(n)), dim3(256), 0, s, n, perm, (const uint16_t*)src,
-                           (uint16_t*)dst, out);
+size_t range_scratch_bytes() { return (size_t)kReduceBlocks * sizeof(uint2); }
+
+template <typename S>
+static void range_of(int64_t n, const void* v, uint2* part, unsigned grid, hipStream_t s) {
+    const auto* p = reinterpret_cast<const typename S::raw*>(v);
+    if ((reinterpret_cast<uintptr_t>(v) & (Quad<S>::kBytes - 1)) == 0)
+        hipLaunchKernelGGL((k_range<S, true>), dim3(grid), dim3(kReduceThreads), 0, s, n, p, part);
     else
-        hipLaunchKernelGGL(k_gather_range<BF16>, dim3(grid_for(n)), dim3(256), 0, s, n, perm, (const uint16_t*)src,
-                           (uint16_t*)dst, out);
+        hipLaunchKernelGGL((k_range<S, false>), dim3(grid), dim3(kReduceThreads), 0, s, n, p, part);
+}
+
+dvl_status launch_range(int64_t n, int dtype, const void* v, unsigned int* out, void* scratch, hipStream_t s) {
+    uint2* part = reinterpret_cast<uint2*>(scratch);
+    const unsigned grid = grid_for((n + 3) / 4, kReduceThreads, kReduceBlocks);
+    if (dtype == DVL_F32)
+        range_of<F32>(n, v, part, grid, s);
+    else if (dtype == DVL_F16)
+        range_of<F16>(n, v, part, grid, s);
+    else
+        range_of<BF16>(n, v, part, grid, s);
+    hipLaunchKernelGGL(k_range_fold, dim3(1), dim3(1024), 0, s, (int64_t)grid, part, out);
     DVL_HIP(hipGetLastError());
     return DVL_OK;
 }
 
-dvl_status launch_range(int64_t n, int dtype, const void* v, unsigned int* out, hipStream_t s) {
-    if (dtype == DVL_F32)
-        hipLaunchKernelGGL(k_range<F32>, dim3(grid_for(n)), dim3(256), 0, s, n, (const float*)v, out);
-    else if (dtype == DVL_F16)
-        hipLaunchKernelGGL(k_range<F16>, dim3(grid_for(n)), dim3(256), 0, s, n, (const uint16_t*)v, out);
+template <typename S>
+static void place_typed(int64_t n, int tile_steps, const uint32_t* perm, const PlaceArrays& a, const PlaceStats& st,
+                        unsigned grid, hipStream_t s) {
+    // tiles of 8 steps: two steps per wave; 16 and 32: four at a time
+    if (tile_steps < 16)
+        hipLaunchKernelGGL((k_place<S, 2>), dim3(grid), dim3(kReduceThreads), 0, s, n, tile_steps, perm, a, st);
     else
-        hipLaunchKernelGGL(k_range<BF16>, dim3(grid_for(n)), dim3(256), 0, s, n, (const uint16_t*)v, out);
+        hipLaunchKernelGGL((k_place<S, 4>), dim3(grid), dim3(kReduceThreads), 0, s, n, tile_steps, perm, a, st);
+}
+
+dvl_status launch_place(int64_t n, int dtype, int tile_steps, const uint32_t* perm, const PlaceArrays& a,
+                        const PlaceStats& st, unsigned int* ranges, hipStream_t s) {
+    const int64_t units = st.n_tiles * (a.n_fields + (a.level_src ? 1 : 0));
+    const unsigned grid = (unsigned)std::min<int64_t>(units, (int64_t)1 << 23);   // below 2^32 work-items
+    if (dtype == DVL_F32)
+        place_typed<F32>(n, tile_steps, perm, a, st, grid, s);
+    else if (dtype == DVL_F16)
+        place_typed<F16>(n, tile_steps, perm, a, st, grid, s);
+    else
+        place_typed<BF16>(n, tile_steps, perm, a, st, grid, s);
     DVL_HIP(hipGetLastError());
+    if (ranges) {
+        hipLaunchKernelGGL(k_range_fold, dim3(a.n_fields), dim3(1024), 0, s, st.n_tiles, st.range, ranges);
+        DVL_HIP(hipGetLastError());
+    }
     return DVL_OK;
 }
 

@@ -5,8 +5,11 @@
 
 namespace dvl {
 
+// out: [0] max(corner + 2^level), [1] a cell fails the checks, [2] max level, [3] zeroed;
+// scratch: extent_scratch_bytes() of device memory
+size_t extent_scratch_bytes();
 dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
-                         const uint8_t* level, unsigned long long* out, hipStream_t s);
+                         const uint8_t* level, unsigned long long* out, void* scratch, hipStream_t s);
 dvl_status launch_keys(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
                        const uint8_t* level, int bits, uint64_t* keys, uint32_t* idx, hipStream_t s);
 // stable LSD sort of (keys, vals) on the low key_bits bits; ping-pongs between the
@@ -17,14 +20,38 @@ dvl_status radix_sort(int64_t n, int key_bits, uint64_t* keys, uint32_t* vals, u
 int64_t sort_tile_count(int64_t n);        // sort tiles rounded up to a group of 16; counts needs 256 * that
 int64_t scan_partial_count(int64_t n);     // partial sums the count scan needs for n entries
 dvl_status launch_dup(int64_t n, const uint64_t* keys, unsigned long long* flag, hipStream_t s);
-dvl_status launch_gather(int64_t n, const uint32_t* perm, const void* src, void* dst, int elem_bytes,
-                         hipStream_t s);
 dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sorted, void* orig,
                                int elem_bytes, hipStream_t s);
-// out[0] = min, out[1] = max as order-preserving uint keys, out[2] = NaN seen
-dvl_status launch_range(int64_t n, int dtype, const void* v, unsigned int* out, hipStream_t s);
-// dst[i] = src[perm[i]] for a field of storage `dtype`, with the range of the values as launch_range
-dvl_status launch_gather_range(int64_t n, const uint32_t* perm, int dtype, const void* src, void* dst,
-                               unsigned int* out, hipStream_t s);
+// out[0] = min, out[1] = max as order-preserving uint keys, out[2] = NaN seen;
+// scratch: range_scratch_bytes() of device memory
+size_t range_scratch_bytes();
+dvl_status launch_range(int64_t n, int dtype, const void* v, unsigned int* out, void* scratch, hipStream_t s);
+
+// The sorted arrays of a volume: fields src -> dst (statistics rows
+// first_field ..) and, when level_src is not NULL, the levels and their codes.
+// dst arrays hold whole tiles; cells past n are zeroed.
+struct PlaceArrays {
+    const void* src[kMaxFields];
+    void* dst[kMaxFields];
+    int n_fields;
+    int first_field;
+    const uint8_t* level_src;
+    uint8_t* level_dst;
+    uint32_t* codes;         // one 32-bit level code per 256-cell step
+};
+struct PlaceStats {
+    int64_t n_tiles;
+    double* tile_sum;        // [M][n_tiles]
+    float* tile_min;
+    float* tile_max;
+    double* step_sum;        // [M][n_tiles * tile_steps]
+    float* step_min;
+    float* step_max;
+    uint2* range;            // [n_fields][n_tiles] range keys per tile, or NULL
+};
+// sorted cell i from original cell perm[i], or from src[i] when perm is NULL;
+// ranges (optional, needs st.range and first_field 0): per field as launch_range
+dvl_status launch_place(int64_t n, int dtype, int tile_steps, const uint32_t* perm, const PlaceArrays& a,
+                        const PlaceStats& st, unsigned int* ranges, hipStream_t s);
 
 }  // namespace dvl

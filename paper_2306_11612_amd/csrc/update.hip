@@ -35,7 +35,7 @@
 // K0, K1, K3b and K4 depend on the field storage type and the field count;
 // they live in update_kernels.hpp and are instantiated once per (type,
 // count) in translation units the build generates.  This file holds K2, K3a,
-// the per-tile statistics, the TF entry cache builder and the launcher.
+// the TF entry cache builder and the launcher.
 #include "update_kernels.hpp"
 
 namespace dvl {
@@ -332,129 +332,6 @@ __global__ __launch_bounds__(kClassifyThreads) void k_carry_classify(BatchDev bd
         for (int k = 0; k < w; ++k) base += wcount[path][k];
         gstore<uint64_t>(bd.rescan_queue, path * bd.k3_units + base + mine_before[path], (uint64_t)u);
     }
-}
-
-// ------------------------------------------------------------------ per-tile statistics
-
-// sum / min / max of one sorted field over every tile and over every 256-cell
-// step; one wave per tile (computed once per volume and per data change, not
-// per update).  Tile sums: per lane, fp32 sums of 4 values accumulated in fp64
-// over the steps, then the wave; step sums: per lane the fp64 sum of its 4
-// values, then the wave.
-template <typename S>
-__global__ __launch_bounds__(kUpdThreads) void k_tile_aggregates(int64_t n, const void* __restrict__ field,
-                                                                 int64_t n_tiles, int tile_steps,
-                                                                 double* __restrict__ sum,
-                                                                 float* __restrict__ mn, float* __restrict__ mx,
-                                                                 double* __restrict__ ssum,
-                                                                 float* __restrict__ smn, float* __restrict__ smx) {
-    const int lane = lane_id();
-    const int64_t wave = (int64_t)block_x() * (kUpdThreads / kWave) + thread_x() / kWave;
-    const int64_t nwaves = (int64_t)grid_dim_x() * (kUpdThreads / kWave);
-    for (int64_t t = wave; t < n_tiles; t += nwaves) {
-        const int64_t tbase = t * tile_steps * (int64_t)kStepCells;
-        double acc = 0.0;
-        float lo = INFINITY, hi = -INFINITY;
-        // four steps' loads in flight together (tile_steps is a multiple of 4);
-        // the arithmetic runs step after step as in a plain loop
-        for (int st0 = 0; st0 < tile_steps; st0 += 4) {
-            const int64_t quad0 = ((tbase + (int64_t)st0 * kStepCells) >> 2) + lane;
-            Quad<S> qs[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) qs[g].load(field, quad0 + (int64_t)g * kWave);
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int st = st0 + g;
-                const int64_t quad = quad0 + (int64_t)g * kWave;
-                const Quad<S>& q = qs[g];
-                float s4 = 0.0f;
-                double d4 = 0.0;
-                float slo = INFINITY, shi = -INFINITY;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if ((quad << 2) + k < n) {
-                        const float v = q.get(k);
-                        s4 += v;
-                        d4 += (double)v;
-                        slo = fminf(slo, v);
-                        shi = fmaxf(shi, v);
-                    }
-                }
-                acc += (double)s4;
-                lo = fminf(lo, slo);
-                hi = fmaxf(hi, shi);
-                d4 = wave_sum_d(d4);
-                slo = wave_min_f(slo);
-                shi = wave_max_f(shi);
-                if (lane == 0) {
-                    const int64_t gs = t * tile_steps + st;
-                    ssum[gs] = d4;
-                    smn[gs] = slo;
-                    smx[gs] = shi;
-                }
-            }
-        }
-        acc = wave_sum_d(acc);
-        lo = wave_min_f(lo);
-        hi = wave_max_f(hi);
-        if (lane == 0) {
-            sum[t] = acc;
-            mn[t] = lo;
-            mx[t] = hi;
-        }
-    }
-}
-
-dvl_status launch_tile_aggregates(int64_t n, int dtype, const void* field, int64_t n_tiles, int tile_steps,
-                                  double* sum, float* mn, float* mx, double* ssum, float* smn, float* smx,
-                                  int n_cu, hipStream_t s) {
-    const int64_t wg_needed = (n_tiles + (kUpdThreads / kWave) - 1) / (kUpdThreads / kWave);
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(wg_needed, (int64_t)n_cu * 8));
-    if (dtype == DVL_F16)
-        hipLaunchKernelGGL(k_tile_aggregates<F16>, dim3(grid), dim3(kUpdThreads), 0, s, n, field, n_tiles,
-                           tile_steps, sum, mn, mx, ssum, smn, smx);
-    else if (dtype == DVL_BF16)
-        hipLaunchKernelGGL(k_tile_aggregates<BF16>, dim3(grid), dim3(kUpdThreads), 0, s, n, field, n_tiles,
-                           tile_steps, sum, mn, mx, ssum, smn, smx);
-    else
-        hipLaunchKernelGGL(k_tile_aggregates<F32>, dim3(grid), dim3(kUpdThreads), 0, s, n, field, n_tiles,
-                           tile_steps, sum, mn, mx, ssum, smn, smx);
-    DVL_HIP(hipGetLastError());
-    return DVL_OK;
-}
-
-// ------------------------------------------------------------------ level codes
-
-// One 32-bit code per 256-cell step of the sorted levels: byte k describes
-// the cells [64 k, 64 k + 64) of the step (the 16 lanes 16 k .. 16 k + 15 of
-// a wave reading the step): their common level, or 0xFF when they differ.
-// One wave per step.
-__global__ __launch_bounds__(256) void k_level_codes(const uint32_t* __restrict__ lev4, int64_t n_steps,
-                                                     uint32_t* __restrict__ codes) {
-    const int64_t st = ((int64_t)block_x() * block_dim_x() + thread_x()) / kWave;
-    if (st >= n_steps) return;   // the whole wave
-    const int lane = lane_id();
-    const uint32_t w = lev4[st * kWave + lane];
-    const uint32_t b0 = w & 0xFFu;
-    const uint32_t c = w == b0 * 0x01010101u ? b0 : 0xFFu;
-    uint32_t lo = c, hi = c;
-    for (int o = 1; o < 16; o <<= 1) {
-        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
-        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
-    }
-    const uint32_t seg = lo == hi ? lo : 0xFFu;
-    const uint32_t s0 = (uint32_t)__shfl((int)seg, 0), s1 = (uint32_t)__shfl((int)seg, 16);
-    const uint32_t s2 = (uint32_t)__shfl((int)seg, 32), s3 = (uint32_t)__shfl((int)seg, 48);
-    if (lane == 0) codes[st] = s0 | (s1 << 8) | (s2 << 16) | (s3 << 24);
-}
-
-dvl_status launch_level_codes(const uint8_t* level, int64_t n_steps, uint32_t* codes, hipStream_t s) {
-    const int64_t threads = n_steps * kWave;
-    const unsigned grid = (unsigned)std::max<int64_t>(1, (threads + 255) / 256);
-    hipLaunchKernelGGL(k_level_codes, dim3(grid), dim3(256), 0, s, reinterpret_cast<const uint32_t*>(level),
-                       n_steps, codes);
-    DVL_HIP(hipGetLastError());
-    return DVL_OK;
 }
 
 // ------------------------------------------------------------------ TF entry cache
