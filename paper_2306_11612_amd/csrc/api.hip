@@ -730,8 +730,17 @@ static dvl_status cache_mark_readers(const Plan& P, hipStream_t s) {
 // carry itself (dvl_set_carry_wait)
 static std::atomic<int> g_carry_wait_polls{kCarryWaitPolls};
 
-// `paths`: importance-pass variants to launch (a captured graph takes both,
-// since its jobs choose at every launch)
+// The kernel variants this plan's jobs and requests use (workspaces carved,
+// caches decided): launches of variants without work are left out.
+static int plan_paths(const Plan& P) {
+    int paths = 0;
+    for (const JobDev& j : P.jobs) paths |= j.idx[0] ? kPathEntries : kPathValues;
+    for (const ReqDev& d : P.rdev)
+        paths |= d.ws.fstore ? kPathBinStoredF : (P.jobs[d.job].idx[0] ? kPathBinEntries : kPathBinValues);
+    return paths;
+}
+
+// `paths`: the variants to launch (plan_paths)
 static BatchDev batch_dev(const Plan& P, char* d, int paths) {
     BatchDev b{};
     b.paths = paths;
@@ -956,11 +965,7 @@ struct Executor {
         if (dvl_status st = upload(P, s)) return st;
         hipEvent_t* ev = nullptr;
         if (dvl_status st = timing_events(&ev)) return st;
-        int paths = 0;
-        for (const JobDev& j : P.jobs) paths |= j.idx[0] ? kPathEntries : kPathValues;
-        for (const ReqDev& d : P.rdev)
-            if (d.ws.fstore) paths |= kPathStoredF;
-        if (dvl_status st = launch_batch(batch_dev(P, blk, paths), P.dtype, P.max_m, P.max_req, n_cu, s, kDescriptorLayout, ev))
+        if (dvl_status st = launch_batch(batch_dev(P, blk, plan_paths(P)), P.dtype, P.max_m, P.max_req, n_cu, s, kDescriptorLayout, ev))
             return st;
         cache_add_readers(P, s);
         hipEvent_t done = nullptr;
@@ -1432,9 +1437,7 @@ dvl_status dvl_update_noalloc(dvl_volume* v, const dvl_params* p, const dvl_bins
         v->sticky = st;
         return st;
     }
-    int paths = 0;
-    for (const JobDev& j : P.jobs) paths |= j.idx[0] ? kPathEntries : kPathValues;
-    if (dvl_status st = launch_batch(batch_dev(P, base, paths), P.dtype, P.max_m, P.max_req, v->n_cu, s, kDescriptorLayout, nullptr)) {
+    if (dvl_status st = launch_batch(batch_dev(P, base, plan_paths(P)), P.dtype, P.max_m, P.max_req, v->n_cu, s, kDescriptorLayout, nullptr)) {
         if (st == DVL_E_HIP) v->sticky = st;
         return st;
     }
@@ -1918,10 +1921,7 @@ dvl_status dvl_graph_launch(dvl_graph* g, void* stream) {
     if (dvl_status st = decide_cache(g->plan, builds)) return st;
     if (dvl_status st = run_cache_builds(builds, s)) return st;
     if (dvl_status st = cache_wait(g->plan, s)) return st;
-    int paths = 0;
-    for (const JobDev& j : g->plan.jobs) paths |= j.idx[0] ? kPathEntries : kPathValues;
-    for (const ReqDev& d : g->plan.rdev)
-        if (d.ws.fstore) paths |= kPathStoredF;
+    const int paths = plan_paths(g->plan);
     const int slot = g->launches % dvl_graph::kSlots;
     hipGraphExec_t exec = nullptr;
     if (dvl_status st = graph_exec_for(g, paths, slot, &exec)) return st;

@@ -18,7 +18,9 @@ constexpr int kMaxReqPerJob = 8;
 constexpr int kPhases = 5;                       // exact vmax, tile sums, carry + classification, rescan, bin statistics
 constexpr int kPathValues = 1;                   // jobs that read the field values
 constexpr int kPathEntries = 2;                  // jobs that read cached TF entries
-constexpr int kPathStoredF = 4;                  // requests whose projection reads stored f
+constexpr int kPathBinStoredF = 4;               // requests whose projection reads stored f,
+constexpr int kPathBinEntries = 8;               // cached entries,
+constexpr int kPathBinValues = 16;               // or values
 constexpr int kIdxTable = 256;                   // LDS floats per table on the cached-entry path
 
 // Workspace of one request on a volume of T tiles and M fields.
@@ -117,7 +119,7 @@ struct BatchDev {
     int64_t k3_units;
     int64_t k4_units;
     int any_exact;
-    int paths;                // kPathValues | kPathEntries: which importance-pass variants to launch
+    int paths;                // kPath*: which variants of the importance pass and the projection to launch
     int max_req_tf;           // largest request table block (floats): LDS of the projection
     int max_job_tf;           // largest job table block (floats): LDS of the importance pass
     int max_req_job;          // most requests in one job

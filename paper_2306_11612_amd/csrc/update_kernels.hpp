@@ -695,12 +695,6 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
         v = max(v, (uint32_t)__builtin_amdgcn_ds_bpermute((lane_id() ^ o) << 2, (int)v));
     return v;
 }
-__device__ __forceinline__ int wave_min_i32(int v) {
-    for (int o = 32; o > 0; o >>= 1)
-        v = min(v, __builtin_amdgcn_ds_bpermute((lane_id() ^ o) << 2, v));
-    return v;
-}
-
 // Sum of the importance of all tiles before tile t (t = T gives F_tot): the
 // run's base plus the tile's prefix inside its run, never above the next
 // run's base.  One definition serves both neighbours of every tile boundary,
@@ -713,22 +707,6 @@ __device__ __forceinline__ double tile_offset(const JobDev& j, const UpdWorkspac
     const int64_t r = t / j.tiles_per_run;
     const double lo = gload<double>(ws.run_base, r), hi = gload<double>(ws.run_base, r + 1);
     return fmin(fmax(lo + gload<double>(ws.local_prefix, t), lo), hi);
-}
-
-// Cell range [first, last] of bin `key` found in tile t: a bin that starts
-// and ends inside the tile (dest 0) is stored as the request's output; the
-// tile's first bin (dest 1) and last bin (dest 2) go to the tile's head and
-// tail records, merged across tiles by K4.  Called by the whole wave.
-__device__ __forceinline__ void close_bin(const ReqDev& q, int64_t T, int dest, int64_t t, int key,
-                                          uint32_t first, uint32_t last) {
-    if (lane_id() != 0) return;
-    if (dest == 0) {
-        gstore<uint32_t>(q.first_cell, key, first);
-        gstore<uint32_t>(q.last_cell, key, last);
-    } else {
-        gstore<uint32_t>(q.ws.rec_first, (dest - 1) * T + t, first);
-        gstore<uint32_t>(q.ws.rec_last, (dest - 1) * T + t, last);
-    }
 }
 
 // ------------------------------------------------------------------ K3
@@ -911,13 +889,39 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, const JobDev& j, i
     }
 }
 
-// Phase 2, by one wave: the cells' pixel intervals and bins from the staged
-// prefixes, step after step (the running base of a step is the fp32 sum of
-// the earlier steps' totals, in order).  Each bin's cell range is closed as
-// soon as it is known: bins inside the tile are written as outputs, the
-// tile's first and last bin as its head and tail records.
-__device__ __forceinline__ void rescan_walk(const ReqDev& q, const JobDev& j, int64_t t, const Stage stage) {
+// Phase 2, by every wave: the cells' pixel intervals and bins from the staged
+// prefixes.  Along the sorted order the first and the last bin of a cell
+// never decrease, every bin has a cell, and the next cell starts in the bin
+// where this one ends or in the one after.  So each cell settles alone, from
+// its own bins [blo, bhi], the last bin `prev_hi` of the cell before it and
+// the first bin `next_lo` of the cell after it, which bins start with it,
+// (prev_hi, bhi], and which end with it, [blo, next_lo): no walk from bin to
+// bin.  (One wave walking the open bin through the steps, three wave
+// reductions per bin, took 36 us for the 64 tiles of a 64^3 grid plotted 1024
+// wide, 60 us for 50 M cells from values and 34 us for the 1900 tiles of
+// 501 M cells at W = 1920; this takes 16, 45 and 33 us, most of it the loads
+// before.)  Bins inside the tile are written as outputs; the tile's first bin
+// (Bh) and last bin (O) go to its head and tail records,
+// merged across tiles by K4.
+struct TileBins {
+    int Bh, O;              // bins of the tile's first and last cell
+    bool one;               // the whole tile in one bin
+};
+
+__device__ __forceinline__ void bin_starts(const ReqDev& q, int64_t T, int64_t t, const TileBins& tb, int from, int to,
+                                           uint32_t cell) {
+    for (int b = from; b <= to; ++b)
+        gstore<uint32_t>(b == tb.O ? q.ws.rec_first : q.first_cell, b == tb.O ? T + t : (int64_t)b, cell);
+}
+__device__ __forceinline__ void bin_ends(const ReqDev& q, int64_t t, const TileBins& tb, int from, int before,
+                                         uint32_t cell) {
+    for (int b = from; b < before; ++b)
+        gstore<uint32_t>(b == tb.Bh ? q.ws.rec_last : q.last_cell, b == tb.Bh ? t : (int64_t)b, cell);
+}
+
+__device__ __forceinline__ void rescan_bins(const ReqDev& q, const JobDev& j, int64_t t, const Stage stage) {
     const int lane = lane_id();
+    const int w = uni((int)(thread_x() / kWave));
     const int64_t T = uni(j.n_tiles);
     const int64_t n = uni(j.n);
     const TileSpan sp = tile_span(q, j, t);
@@ -930,153 +934,105 @@ __device__ __forceinline__ void rescan_walk(const ReqDev& q, const JobDev& j, in
     const uint32_t last_valid = (uint32_t)(tend - 1);
     const int nsteps = (int)((tend - tbase + kStepCells - 1) / kStepCells);
 
-    // The per-step quantities of the sequential walk, for every step at once
-    // (lane s: step s): the running base (the fp32 sum of the earlier steps'
-    // totals, added in step order as the walk would), the bins of the step's
-    // first and last cell, and whether it lies inside one bin.  Lanes past
-    // the last step repeat it.
+    // Every step at once (lane s: step s; lanes past the last step repeat
+    // it): its running base (the fp32 sum of the earlier steps' totals, in
+    // step order), the first bin of its first cell and the last bin of its
+    // last cell.
+    const int ls = min(lane, nsteps - 1);
     float run_v = 0.0f;
-    int key0_v, key_end_v, fast_v = 0;
+    for (int k = 0; k < nsteps; ++k) {
+        const float st_k = stage.ex_p[k * kWave].x;   // step k's total (lane 0's Bex slot)
+        if (k < ls) run_v = run_v + st_k;
+    }
+    int key0_v, key_end_v;
     {
-        const int ls = min(lane, nsteps - 1);
-        for (int k = 0; k < nsteps; ++k) {
-            const float st_k = stage.ex_p[k * kWave].x;   // step k's total (lane 0's Bex slot)
-            if (k < ls) run_v = run_v + st_k;
-        }
         const int64_t c0 = tbase + (int64_t)ls * kStepCells;
-        const float B63 = stage.ex_p[ls * kWave].x;       // the step total: B of lane 63
+        const float total = stage.ex_p[ls * kWave].x;     // the step total: B of lane 63
         const float B0 = stage.ex_p[ls * kWave + 1].x;    // B of lane 0: Bex of lane 1
-        const f32x4 e63 = stage.ex_p[ls * kWave + kWave - 1];
         const float x_first = fminf(fmaf(run_v + fminf(0.0f, B0), scale_f, X0), X1);
         key0_v = max(0, min((int)floorf(x_first), W1));
-        key_end_v = INT_MAX;
-        if (c0 + kStepCells <= n) {
-            const float x3 = fminf(fmaf(run_v + fminf(e63.x + e63.w, B63), scale_f, X0), X1);
-            const float x4 = (uint32_t)(c0 + kStepCells - 1) == last_valid ? X1
-                                                                          : fminf(fmaf(run_v + B63, scale_f, X0), X1);
-            const int lo3 = max(0, min((int)floorf(x3), W1));
-            key_end_v = max(lo3, min((int)ceilf(x4) - 1, W1));
-            fast_v = key0_v == key_end_v;
+        // the step's last valid cell: cell kl of lane ll
+        const int r = (int)(min(c0 + kStepCells, n) - 1 - c0), ll = r >> 2, kl = r & 3;
+        const f32x4 e = stage.ex_p[ls * kWave + ll];
+        const float Bex = ll == 0 ? 0.0f : e.x;
+        const float B = ll == kWave - 1 ? total : stage.ex_p[ls * kWave + ll + 1].x;
+        const float p = kl == 0 ? 0.0f : (kl == 1 ? e.y : (kl == 2 ? e.z : e.w));
+        const float x3 = fminf(fmaf(run_v + fminf(Bex + p, B), scale_f, X0), X1);
+        const float x4 = (uint32_t)(c0 + r) == last_valid ? X1 : fminf(fmaf(run_v + B, scale_f, X0), X1);
+        const int lo3 = max(0, min((int)floorf(x3), W1));
+        key_end_v = max(lo3, min((int)ceilf(x4) - 1, W1));
+    }
+    TileBins tb;
+    tb.Bh = readlane(key0_v, 0);
+    tb.O = readlane(key_end_v, nsteps - 1);
+    tb.one = tb.Bh == tb.O;
+    // last bin of the cell before the step, first bin of the cell after it
+    // (the tile's own first and last bin stand in at its ends: those bins are
+    // its records)
+    const int before_v = shfl_i(key_end_v, max(lane - 1, 0)), after_v = shfl_i(key0_v, min(lane + 1, kWave - 1));
+    const int prev_v = lane == 0 ? tb.Bh : before_v, next_v = lane >= nsteps - 1 ? tb.O : after_v;
+
+    if (w == 0) {
+        if (lane == 0) {
+            gstore<int32_t>(q.ws.head_bin, t, tb.Bh);
+            gstore<int32_t>(q.ws.tail_bin, t, tb.O);
+            gstore<uint32_t>(q.ws.rec_first, t, (uint32_t)tbase);
+            gstore<uint32_t>(q.ws.rec_last, (tb.one ? 0 : T) + t, last_valid);
+        }
+        // steps inside one bin, a lane each
+        if (!tb.one && lane < nsteps && key0_v == key_end_v) {
+            const int64_t c0 = tbase + (int64_t)lane * kStepCells;
+            bin_starts(q, T, t, tb, prev_v + 1, key_end_v, (uint32_t)c0);
+            bin_ends(q, t, tb, key0_v, next_v, (uint32_t)(min(c0 + kStepCells, n) - 1));
         }
     }
+    if (tb.one) return;
 
-    bool o_valid = false;
-    int O = -1, Bh = -1;
-    uint32_t O_first = 0;
-
-    for (int s = 0; s < nsteps; ++s) {
+    // steps holding a bin edge, a wave each
+    for (int s = w; s < nsteps; s += kBinWaves) {
+        const int key0 = readlane(key0_v, s), key_end = readlane(key_end_v, s);
+        if (key0 == key_end) continue;
         const int64_t c0 = tbase + (int64_t)s * kStepCells;
-        const int key0 = readlane(key0_v, s);
-        if (s == 0) Bh = key0;
-        if (readlane(fast_v, s) && (!o_valid || key0 == O)) {
-            // the whole step lies in the open bin
-            if (!o_valid) {
-                o_valid = true;
-                O = key0;
-                O_first = (uint32_t)c0;
-            }
-            continue;
-        }
-        const int key_end = readlane(key_end_v, s);
         const float run = readlane(run_v, s);
+        // read in uniform control flow: under a lane's own branch the compiler
+        // may compute the source register for that lane alone
+        const int step_prev = readlane(prev_v, s), step_next = readlane(next_v, s);
         const int64_t quad = (c0 >> 2) + lane;
         const StepPrefix pr = stage.get(s);
         const float Bex = pr.ex_p.x, p1 = pr.ex_p.y, p2 = pr.ex_p.z, p3 = pr.ex_p.w, B = pr.B;
-        const bool full = c0 + kStepCells <= n;
-
-        uint32_t g[4];
-        bool valid[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            g[k] = (uint32_t)((quad << 2) + k);
-            valid[k] = (int64_t)g[k] < n;
-        }
         float xs[5];
         xs[0] = fminf(fmaf(run + fminf(Bex, B), scale_f, X0), X1);
         xs[1] = fminf(fmaf(run + fminf(Bex + p1, B), scale_f, X0), X1);
         xs[2] = fminf(fmaf(run + fminf(Bex + p2, B), scale_f, X0), X1);
         xs[3] = fminf(fmaf(run + fminf(Bex + p3, B), scale_f, X0), X1);
         xs[4] = fminf(fmaf(run + B, scale_f, X0), X1);
-
         // pixel bins of each cell: [floor(x1), ceil(x2) - 1], clamped
         int blo[4], bhi[4];
+        bool last[4];                     // the tile's last cell
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const float en = (g[k] == last_valid) ? X1 : xs[k + 1];
+            last[k] = (uint32_t)((quad << 2) + k) == last_valid;
+            const float en = last[k] ? X1 : xs[k + 1];
             blo[k] = max(0, min((int)floorf(xs[k]), W1));
             bhi[k] = max(blo[k], min((int)ceilf(en) - 1, W1));
         }
-
-        // ---- bin boundary inside the step ----
-        const int last_lane = full ? kWave - 1 : (int)((n - 1 - c0) >> 2);
-        const int kl = (int)((n - 1 - c0) & 3);
-        const int bhi_last = kl == 0 ? bhi[0] : (kl == 1 ? bhi[1] : (kl == 2 ? bhi[2] : bhi[3]));
-        const int key_last = full ? key_end : readlane(bhi_last, last_lane);
-        // (1) the open bin ended with the previous step
-        if (o_valid && key0 != O) {
-            close_bin(q, T, O == Bh ? 1 : 0, t, O, O_first, (uint32_t)(c0 - 1));
-            o_valid = false;
-        }
-        // (2) bins strictly inside a wide cell hold that cell alone
+        int prev_hi = shfl_i(bhi[3], max(lane - 1, 0)), next_lo = shfl_i(blo[0], min(lane + 1, kWave - 1));
+        prev_hi = lane == 0 ? step_prev : prev_hi;
+        next_lo = lane == kWave - 1 ? step_next : next_lo;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (valid[k] && bhi[k] > blo[k] + 1)
-                for (int bb = blo[k] + 1; bb < bhi[k]; ++bb) {
-                    gstore<uint32_t>(q.first_cell, bb, g[k]);
-                    gstore<uint32_t>(q.last_cell, bb, g[k]);
-                }
-        // (3) every bin that is the first or last bin of some cell of this
-        //     step, in increasing order; all but the step's last one close
-        int b = key0;
-        while (true) {
-            uint32_t gmin = 0xFFFFFFFFu, gmax = 0u;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (valid[k] && (blo[k] == b || bhi[k] == b)) {
-                    gmin = min(gmin, g[k]);
-                    gmax = max(gmax, g[k]);
-                }
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t g = (uint32_t)((quad << 2) + k);
+            if (g <= last_valid) {
+                bin_starts(q, T, t, tb, (k == 0 ? prev_hi : bhi[k - 1]) + 1, bhi[k], g);
+                bin_ends(q, t, tb, blo[k], last[k] ? tb.O : (k == 3 ? next_lo : blo[k + 1]), g);
             }
-            const uint32_t bfirst = (o_valid && b == O) ? O_first : wave_min_u32(gmin);
-            if (b == key_last) {
-                // stays open into the next step
-                O = b;
-                O_first = bfirst;
-                o_valid = true;
-                break;
-            }
-            close_bin(q, T, b == Bh ? 1 : 0, t, b, bfirst, wave_max_u32(gmax));
-            o_valid = false;
-            int nk = INT_MAX;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (valid[k]) {
-                    if (blo[k] > b) nk = min(nk, blo[k]);
-                    if (bhi[k] > b) nk = min(nk, bhi[k]);
-                }
-            }
-            b = wave_min_i32(nk);
-            if (b == INT_MAX) break;   // cannot happen: key_last is above
-        }
-    }
-
-    // tile end: the open bin is the tile's last bin
-    if (o_valid) {
-        close_bin(q, T, O == Bh ? 1 : 2, t, O, O_first, last_valid);
-        if (lane == 0) {
-            gstore<int32_t>(q.ws.head_bin, t, Bh);
-            gstore<int32_t>(q.ws.tail_bin, t, O);
         }
     }
 }
 
 // K3b: the queued tiles, one workgroup each.  Its waves stage the prefixes
-// of the tile's steps in LDS together (phase 1; the loads of three waves in
-// flight instead of one), then the first wave walks the bins (phase 2).
-// Three waves, not four: at 62 VGPRs a compute unit holds seven waves per
-// SIMD, so seven workgroups of four waves (1792 on the chip) would leave some
-// of the ~1900 tiles of W = 1920 to a second round, while eight workgroups of
-// three fit (LDS: 20 KB each); measured 36 instead of 41 us.
+// of the tile's steps in LDS together (phase 1; the loads of all waves in
+// flight), then settle the bins of the steps that hold a bin edge (phase 2).
 // IDX: this instance serves the requests whose projection reads values (0),
 // cached entries (1) or the f the importance pass stored (2); each skips the
 // others' tiles.  LDS: the request's tables, then the staged prefixes.
@@ -1109,7 +1065,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
         else
             rescan_stage<MT, S, StepData<MT, S>>(q, j, t, tf_lds, stage);
         __syncthreads();
-        if (thread_x() < kWave) rescan_walk(q, j, t, stage);
+        rescan_bins(q, j, t, stage);
         __syncthreads();
     }
 }
@@ -1397,15 +1353,15 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
     if (dvl_status st = mark(3)) return st;
     const size_t lds3 = (size_t)((b.max_req_tf + 3) & ~3) * sizeof(float) + (size_t)b.max_tile_steps * kStageBytesPerStep;
     const unsigned g3 = (unsigned)std::max<int64_t>(1, std::min<int64_t>(b.k3_units, (int64_t)n_cu * 16));
-    if (b.paths & kPathValues) {
+    if (b.paths & kPathBinValues) {
         hipLaunchKernelGGL((k_bin<MT, S, 0>), dim3(g3), dim3(kBinThreads), lds3, s, b);
         DVL_HIP(hipGetLastError());
     }
-    if (b.paths & kPathEntries) {
+    if (b.paths & kPathBinEntries) {
         hipLaunchKernelGGL((k_bin<MT, S, 1>), dim3(g3), dim3(kBinThreads), lds3, s, b);
         DVL_HIP(hipGetLastError());
     }
-    if (b.paths & kPathStoredF) {
+    if (b.paths & kPathBinStoredF) {
         hipLaunchKernelGGL((k_bin<MT, S, 2>), dim3(g3), dim3(kBinThreads), lds3, s, b);
         DVL_HIP(hipGetLastError());
     }
