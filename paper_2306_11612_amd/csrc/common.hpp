@@ -236,26 +236,31 @@ __device__ __forceinline__ T gload_at(const char* base, uint32_t byte_off) {
     return *(const DVL_GLOBAL T*)(g + byte_off);
 }
 
-// The constant address space (the dispatch packet is read through it).
+// The constant address space (kernel arguments are read through it).
 #define DVL_CONST __attribute__((address_space(4)))
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
-// Work-item and work-group indices from the hardware and the dispatch packet.
-// The kernels of the update run in non-IEEE float mode, which keeps the
-// device library's functions from being inlined into them; an out-of-line
-// call waits for every memory operation in flight on entry, so the hot
-// kernels use these instead of threadIdx / blockIdx / blockDim / gridDim.
+// Work-item and work-group indices from the hardware, work-group size and
+// count from the implicit kernel arguments (code object version 5 and later:
+// the block count at byte 0, the group size at byte 12), which lie beside the
+// explicit ones.  The kernels of the update run in non-IEEE float mode, which
+// keeps the device library's functions from being inlined into them; an
+// out-of-line call waits for every memory operation in flight on entry, so
+// the hot kernels use these instead of threadIdx / blockIdx / blockDim /
+// gridDim.  (The dispatch packet holds the same numbers, but in the queue's
+// ring in host memory: each workgroup of the importance pass waited 8 to 21
+// thousand cycles for that read over PCIe before it could stage its tables,
+// and the rescan's 9 to 22 thousand before its first tile.)
 __device__ __forceinline__ int thread_x() { return (int)__builtin_amdgcn_workitem_id_x(); }
 __device__ __forceinline__ int block_x() { return (int)__builtin_amdgcn_workgroup_id_x(); }
 __device__ __forceinline__ int block_dim_x() {
-    const DVL_CONST uint16_t* pk = (const DVL_CONST uint16_t*)__builtin_amdgcn_dispatch_ptr();
-    return (int)pk[2];                        // workgroup_size_x
+    const DVL_CONST uint16_t* ia = (const DVL_CONST uint16_t*)__builtin_amdgcn_implicitarg_ptr();
+    return (int)ia[6];                        // group size x
 }
 __device__ __forceinline__ int grid_dim_x() {
-    const DVL_CONST uint32_t* pk = (const DVL_CONST uint32_t*)__builtin_amdgcn_dispatch_ptr();
-    const uint32_t wg = (uint32_t)block_dim_x();
-    return (int)((pk[3] + wg - 1) / wg);      // grid_size_x in work-items
+    const DVL_CONST uint32_t* ia = (const DVL_CONST uint32_t*)__builtin_amdgcn_implicitarg_ptr();
+    return (int)ia[0];                        // block count x
 }
 
 // Values that are the same in every lane (descriptor fields) moved to scalar
