@@ -115,6 +115,10 @@ static float unkey(unsigned int u) {
     return f;
 }
 
+// Bins of up to this size are read back through one kernel and a pinned
+// buffer of this size per volume (1920 bins of 16 fields: 0.5 MB); larger
+// ones array by array, where the copies' own rate counts.
+constexpr size_t kReadStageBytes = (size_t)1 << 20;
 constexpr int kRing = 4;                 // descriptor uploads that may be in flight
 constexpr int kJobTfFloats = 32768;      // LDS budget of one job's tables (128 KB)
 
@@ -216,6 +220,8 @@ struct dvl_volume {
     Executor* ex = nullptr;  // private executor of dvl_update
     dvl::Alloc alloc;        // every device buffer of the volume comes from here
     unsigned int* scratch_range = nullptr;   // dvl_set_field's range check (alloc_range_scratch)
+    // pinned staging of dvl_read_bins (kReadStageBytes, made on first use)
+    mutable uint32_t* read_stage = nullptr;
     dvl_status sticky = DVL_OK;
     size_t bytes = 0;
 };
@@ -1468,23 +1474,70 @@ dvl_status dvl_read_bins(const dvl_volume* v, const dvl_bins* b, int32_t W, void
     if (!b) return fail(DVL_E_INVALID, "bins is NULL");
     if (W < 1 || W > (1 << 20)) return fail(DVL_E_INVALID, "n_bins=%d outside [1, 2^20]", W);
     hipStream_t s = (hipStream_t)stream;
-    DVL_HIP(hipStreamSynchronize(s));
-    const size_t mw = (size_t)v->M * W;
+    const size_t w4 = (size_t)W * 4, mw4 = (size_t)v->M * w4;
+    // count needs both cell ranges, wanted by the caller or not
+    struct Item {
+        void* host;
+        const void* dev;
+        size_t bytes;
+        bool want;
+    } items[8] = {{first, b->first_cell, w4, first || count}, {last, b->last_cell, w4, last || count},
+                  {mean, b->mean, mw4, mean != nullptr},      {vmin, b->vmin, mw4, vmin != nullptr},
+                  {vmax, b->vmax, mw4, vmax != nullptr},      {y, b->y, mw4, y != nullptr},
+                  {f_total, b->f_total, 8, f_total != nullptr}, {vmax_used, b->vmax_used, 4, vmax_used != nullptr}};
+    PackList l{};
+    size_t words = 0;
+    for (const Item& it : items) {
+        if (!it.want) continue;
+        if (!it.dev) return fail(DVL_E_INVALID, "a bins pointer is NULL");
+        l.src[l.n] = (const uint32_t*)it.dev;
+        l.words[l.n] = (uint32_t)(it.bytes / 4);
+        l.at[l.n] = (uint32_t)words;
+        words += (it.bytes / 4 + 15) & ~(size_t)15;
+        ++l.n;
+    }
+    if (l.n == 0) {
+        DVL_HIP(hipStreamSynchronize(s));
+        return DVL_OK;
+    }
+    const uint32_t *fh = first, *lh = last;
     std::vector<uint32_t> f_tmp, l_tmp;
-    uint32_t* fh = first;
-    uint32_t* lh = last;
-    if (count && !fh) { f_tmp.resize(W); fh = f_tmp.data(); }
-    if (count && !lh) { l_tmp.resize(W); lh = l_tmp.data(); }
-    if (fh) DVL_HIP(hipMemcpy(fh, b->first_cell, (size_t)W * 4, hipMemcpyDeviceToHost));
-    if (lh) DVL_HIP(hipMemcpy(lh, b->last_cell, (size_t)W * 4, hipMemcpyDeviceToHost));
+    int dev = -1;
+    DVL_HIP(hipGetDevice(&dev));
+    if (words * 4 <= kReadStageBytes && dev == v->device) {
+        // one kernel writes every array into the volume's pinned staging buffer
+        if (!v->read_stage &&
+            hipHostMalloc((void**)&v->read_stage, kReadStageBytes, hipHostMallocDefault) != hipSuccess) {
+            v->read_stage = nullptr;
+            (void)hipGetLastError();
+            return fail(DVL_E_NOMEM, "pinned host allocation failed");
+        }
+        if (dvl_status st = launch_pack(l, v->read_stage, s)) return st;
+        DVL_HIP(hipStreamSynchronize(s));
+        int a = 0;
+        for (int k = 0; k < 8; ++k) {
+            if (!items[k].want) continue;
+            const uint32_t* src = v->read_stage + l.at[a++];
+            if (k == 0) fh = src;
+            if (k == 1) lh = src;
+            if (items[k].host) memcpy(items[k].host, src, items[k].bytes);
+        }
+    } else {
+        DVL_HIP(hipStreamSynchronize(s));
+        for (int k = 0; k < 8; ++k) {
+            if (!items[k].want) continue;
+            void* to = items[k].host;
+            if (!to) {
+                std::vector<uint32_t>& tmp = k == 0 ? f_tmp : l_tmp;
+                tmp.resize(W);
+                to = tmp.data();
+                (k == 0 ? fh : lh) = tmp.data();
+            }
+            DVL_HIP(hipMemcpy(to, items[k].dev, items[k].bytes, hipMemcpyDeviceToHost));
+        }
+    }
     if (count)
         for (int i = 0; i < W; ++i) count[i] = (fh[i] == 0xFFFFFFFFu) ? 0u : lh[i] - fh[i] + 1u;
-    if (mean) DVL_HIP(hipMemcpy(mean, b->mean, mw * 4, hipMemcpyDeviceToHost));
-    if (vmin) DVL_HIP(hipMemcpy(vmin, b->vmin, mw * 4, hipMemcpyDeviceToHost));
-    if (vmax) DVL_HIP(hipMemcpy(vmax, b->vmax, mw * 4, hipMemcpyDeviceToHost));
-    if (y) DVL_HIP(hipMemcpy(y, b->y, mw * 4, hipMemcpyDeviceToHost));
-    if (f_total) DVL_HIP(hipMemcpy(f_total, b->f_total, 8, hipMemcpyDeviceToHost));
-    if (vmax_used) DVL_HIP(hipMemcpy(vmax_used, b->vmax_used, 4, hipMemcpyDeviceToHost));
     return DVL_OK;
 }
 
@@ -1747,6 +1800,7 @@ void dvl_destroy(dvl_volume* v) {
     A.put(v->scratch_range, nullptr);
     for (int m = 0; m < kMaxFields; ++m) A.put(v->idx_s[m], nullptr);
     if (v->cache_ready) (void)hipEventDestroy(v->cache_ready);
+    if (v->read_stage) (void)hipHostFree(v->read_stage);
     delete v;
 }
 

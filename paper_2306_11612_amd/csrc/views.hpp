@@ -25,4 +25,14 @@ dvl_status launch_select_mask(int64_t n, const uint64_t* keys_sorted, const uint
 // out[i] = i
 dvl_status launch_iota(int64_t n, uint32_t* out, hipStream_t st);
 
+// n arrays of 32-bit words, array a copied to out + at[a] (out: host memory
+// the device can write, complete once the stream is synchronised)
+struct PackList {
+    int n;
+    const uint32_t* src[8];
+    uint32_t words[8];
+    uint32_t at[8];
+};
+dvl_status launch_pack(const PackList& l, uint32_t* out, hipStream_t st);
+
 }  // namespace dvl
