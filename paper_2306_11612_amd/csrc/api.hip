@@ -1235,26 +1235,24 @@ dvl_status dvl_build_order_ex(int64_t n, const int32_t* x, const int32_t* y, con
     v->max_level = (int)eh[2];
 
     // keys + sort
-    DevBuf ka(A), kb(A), va(A), vb(A), counts(A), partial(A);
+    const SortPlan sp = sort_plan(n, 3 * bits);
+    DevBuf ka(A), kb(A), va(A), vb(A), counts(A);
     if (dvl_status st = ka.alloc((size_t)n * 8, "keys")) return st;
     if (dvl_status st = kb.alloc((size_t)n * 8, "keys (sort buffer)")) return st;
     if (dvl_status st = va.alloc((size_t)n * 4, "permutation")) return st;
-    if (dvl_status st = vb.alloc((size_t)n * 4, "permutation (sort buffer)")) return st;
-    const int64_t n_counts = 256 * sort_tile_count(n);
-    if (dvl_status st = counts.alloc((size_t)n_counts * 4, "sort counts")) return st;
-    if (dvl_status st = partial.alloc((size_t)scan_partial_count(n_counts) * 4 + 16, "scan partials")) return st;
-    if (dvl_status st = launch_keys(n, x, y, z, level, bits, (uint64_t*)ka.p, (uint32_t*)va.p, s)) return st;
-    uint64_t* ksorted = nullptr;
-    uint32_t* vsorted = nullptr;
-    if (dvl_status st = radix_sort(n, 3 * bits, (uint64_t*)ka.p, (uint32_t*)va.p, (uint64_t*)kb.p,
-                                   (uint32_t*)vb.p, (uint32_t*)counts.p, (uint32_t*)partial.p, s,
-                                   &ksorted, &vsorted))
+    if (!sp.packed)
+        if (dvl_status st = vb.alloc((size_t)n * 4, "permutation (sort buffer)")) return st;
+    if (dvl_status st = counts.alloc(sp.scratch_bytes, "sort counts")) return st;
+    bool in_second = false;
+    if (dvl_status st = launch_order(sp, n, x, y, z, level, bits, (uint64_t*)ka.p, (uint64_t*)kb.p, (uint32_t*)va.p,
+                                     (uint32_t*)vb.p, (uint32_t*)counts.p, s, &in_second))
         return st;
+    uint64_t* ksorted = (uint64_t*)(in_second ? kb.p : ka.p);
     unsigned long long* dup = (unsigned long long*)ext.p + 3;   // zeroed with the extent
     if (dvl_status st = launch_dup(n, ksorted, dup, s)) return st;
     // keep the sorted pair, free the other
-    if (ksorted == ka.p) { v->keys_s = (uint64_t*)ka.release(); } else { v->keys_s = (uint64_t*)kb.release(); }
-    if (vsorted == va.p) { v->perm = (uint32_t*)va.release(); } else { v->perm = (uint32_t*)vb.release(); }
+    v->keys_s = (uint64_t*)(in_second ? kb.release() : ka.release());
+    v->perm = (uint32_t*)(in_second && !sp.packed ? vb.release() : va.release());
     v->bytes += (size_t)n * 12;
 
     // sorted arrays (padded to whole tiles), statistics and data ranges

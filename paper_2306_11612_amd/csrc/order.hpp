@@ -10,15 +10,24 @@ namespace dvl {
 size_t extent_scratch_bytes();
 dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
                          const uint8_t* level, unsigned long long* out, void* scratch, hipStream_t s);
-dvl_status launch_keys(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
-                       const uint8_t* level, int bits, uint64_t* keys, uint32_t* idx, hipStream_t s);
-// stable LSD sort of (keys, vals) on the low key_bits bits; ping-pongs between the
-// two buffer pairs and reports which holds the result
-dvl_status radix_sort(int64_t n, int key_bits, uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp,
-                      uint32_t* vals_tmp, uint32_t* counts, uint32_t* partial, hipStream_t s,
-                      uint64_t** keys_out, uint32_t** vals_out);
-int64_t sort_tile_count(int64_t n);        // sort tiles rounded up to a group of 16; counts needs 256 * that
-int64_t scan_partial_count(int64_t n);     // partial sums the count scan needs for n entries
+// The ordering of n cells with keys of key_bits bits: sort layout and scratch.
+struct SortPlan {
+    int64_t n_tiles, n_chunks;
+    int chunk;               // tiles per counting workgroup
+    int idx_bits;            // bits of a cell index
+    bool packed;             // key and index in one 64-bit word
+    int digit_bits, passes;
+    size_t rows_words;
+    size_t scratch_bytes;    // device scratch of launch_order
+};
+SortPlan sort_plan(int64_t n, int key_bits);
+// Hilbert keys of the cells (bits per axis) and a stable sort of (key, index):
+// the sorted keys end in kb when *in_second, else in ka, the permutation
+// likewise in vb or va; with p.packed vb is not used (may be NULL) and the
+// permutation is in va.  ka, kb: 8 bytes per cell; va, vb: 4.
+dvl_status launch_order(const SortPlan& p, int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
+                        const uint8_t* level, int bits, uint64_t* ka, uint64_t* kb, uint32_t* va, uint32_t* vb,
+                        uint32_t* scratch, hipStream_t s, bool* in_second);
 dvl_status launch_dup(int64_t n, const uint64_t* keys, unsigned long long* flag, hipStream_t s);
 dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sorted, void* orig,
                                int elem_bytes, hipStream_t s);

@@ -1,0 +1,73 @@
+"""The ordering's radix sort at the edges of its layout: digits of 8 and 9
+bits, key and index in one word or apart, tiles and counting chunks with
+remainders, aligned and unaligned inputs; bit-exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_cases import check_order, dvl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dvl()
+
+
+def _cells(n, bits, seed):
+    """n distinct finest-level cells of a 2^bits cube, its far corner among them, in random order."""
+    import synth
+    g = np.random.default_rng(seed)
+    side = 1 << bits
+    if bits <= 7:
+        flat = g.permutation(side ** 3)[:n].astype(np.int64)
+        flat[0] = side ** 3 - 1 if side ** 3 - 1 not in flat else flat[0]
+    else:
+        flat = np.unique(g.integers(0, side ** 3, n + n // 8 + 16))
+        flat = g.permutation(flat)[:n]
+        flat[0] = side ** 3 - 1
+        assert np.unique(flat).size == n
+    c = [torch.from_numpy(((flat >> (bits * k)) & (side - 1)).astype(np.int32)) for k in range(3)]
+    f = torch.from_numpy(g.random(n).astype(np.float32))
+    return synth.Volume(c[0], c[1], c[2], torch.zeros(n, dtype=torch.uint8), [f], ["f"], side, 1, [])
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("n,bits", [(1, 1), (8, 1), (60, 2), (4095, 4), (4096, 5), (4097, 6), (70000, 7), (131072, 9),
+                                    (300001, 11), (4097, 12), (65537, 14), (20000, 16), (20000, 17), (9000, 18),
+                                    (70001, 19), (4096, 20), (300001, 21), (5, 21), (2, 21)])
+def test_order_bit_exact(n, bits, offset):
+    D = dvl()
+    vol = _cells(n, bits, seed=n + bits)
+
+    def put(t):
+        buf = torch.zeros(t.numel() + offset, dtype=t.dtype, device="cuda")
+        buf[offset:] = t.to("cuda")
+        return buf[offset:]
+
+    V = D.build_order(put(vol.x), put(vol.y), put(vol.z), put(vol.level), [put(vol.fields[0])])
+    try:
+        check_order(V, vol)
+    finally:
+        V.close()
+
+
+def test_order_of_a_large_volume_is_a_sorted_permutation():
+    """More tiles than one counting chunk per column wave: 24 M cells of a
+    regular grid in reversed order; keys increase along the permutation and
+    the permutation holds every cell once."""
+    D = dvl()
+    s = 288
+    i = torch.arange(s ** 3, device="cuda", dtype=torch.int64).flip(0)
+    x, y, z = (i % s).int(), ((i // s) % s).int(), (i // (s * s)).int()
+    V = D.build_order(x, y, z, torch.zeros_like(x, dtype=torch.uint8), [i.float()])
+    try:
+        keys, perm = V.export_order()
+        k = keys[perm.long()]
+        assert bool((k[1:] > k[:-1]).all())
+        assert bool((torch.bincount(perm.long(), minlength=s ** 3) == 1).all())
+    finally:
+        V.close()
