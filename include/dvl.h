@@ -260,8 +260,8 @@ dvl_status dvl_update(dvl_volume* v, const dvl_params* p, const dvl_bins* out, v
  * written by kernels (no memcpy, no memset).  An update fits when 72 bytes
  * per 4096-cell tile, 8 bytes per bin and about 24 KB stay within it (about
  * 3.8e9 cells at W = 1920, whatever the field count); larger ones get
- * DVL_E_NOMEM with a message and nothing is enqueued.  It never stores f for the projection and never
- * builds the TF entry cache: it reads the cache only when the cache already
+ * DVL_E_NOMEM with a message and nothing is enqueued.  It never stores f for
+ * the projection and never builds the TF entry cache: it reads the cache only when the cache already
  * holds this update's windows and the volume was updated on this stream
  * before.  Every call on a device shares that device's scratch, which keeps
  * the last call's contents: calls that overlap on one device (other streams,
@@ -281,8 +281,10 @@ size_t dvl_update_noalloc_max_bytes(void);
  *
  * A request is one update of one volume with its own TFs, windows,
  * parameters and outputs; it does not touch the volume's own TF state.
- * Requests on the same volume (up to 8 at a time) share one read of its
- * cells in the importance pass.  Every request's results are bitwise equal
+ * Requests on the same volume read its cells at about the same time in the
+ * importance pass (neighbouring workgroups take the same cells for each of
+ * them), so that most of these reads come from the caches.  Every request's
+ * results are bitwise equal
  * to those of a dvl_update with the same TFs and parameters, whatever else is
  * in the batch.  All requests of a batch must share the volumes' storage
  * dtype.
@@ -451,14 +453,11 @@ dvl_status dvl_set_timing(dvl_volume* v, int32_t enable);
 dvl_status dvl_kernel_times(dvl_volume* v, double* ms, int32_t* n_updates);
 
 /* ---------------------------------------------------------------------
- * Test hook of the carry hand-off (process-wide; read when a launch is
- * enqueued or a batch is captured).  The carry scan of Eq. 4 across runs
- * and the classification of the tiles (section Projecting Cells to 1D) run
- * as one kernel: each classifying workgroup polls a flag the request's scan
- * workgroup sets, and computes the carry itself after `polls` unanswered
- * polls (default 32768), writing the same values.  polls = 0 makes every
- * classifying workgroup take that path, so tests can check that it gives
- * the same bits.  DVL_E_INVALID for polls < 0.
+ * Kept for callers that set it: the carry scan of Eq. 4 across runs and the
+ * classification of the tiles (section Projecting Cells to 1D) run as one
+ * kernel, in which every workgroup computes the carries it needs itself, so
+ * there is no hand-off to wait for and `polls` changes nothing.
+ * DVL_E_INVALID for polls < 0.
  * ------------------------------------------------------------------- */
 dvl_status dvl_set_carry_wait(int32_t polls);
 

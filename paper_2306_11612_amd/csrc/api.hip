@@ -120,7 +120,6 @@ static float unkey(unsigned int u) {
 // ones array by array, where the copies' own rate counts.
 constexpr size_t kReadStageBytes = (size_t)1 << 20;
 constexpr int kRing = 4;                 // descriptor uploads that may be in flight
-constexpr int kJobTfFloats = 32768;      // LDS budget of one job's tables (128 KB)
 
 // The quantisers of every field: the TF entry of a cell depends on its value
 // and on these only, not on the alpha tables.
@@ -255,7 +254,6 @@ struct ReqHost {
     float qs[kMaxFields] = {}, qb[kMaxFields] = {};
     dvl_params p{};
     dvl_bins out{};
-    int job = 0;
     size_t tf_pos = 0;               // floats from the start of the batch's tables
 };
 
@@ -412,26 +410,54 @@ static dvl_status check_range(const ReqHost& r, float vmax) {
 struct Plan {
     std::vector<ReqHost> reqs;       // grouped by volume
     std::vector<int> where;          // caller's request index -> index in `reqs`
-    std::vector<JobDev> jobs;
+    std::vector<GroupDev> groups;    // one per volume
     std::vector<ReqDev> rdev;
+    std::vector<float*> fstore;      // where each request may store f, or NULL
     int dtype = DVL_F32;
     int max_m = 1;
-    int max_req = 1;
+    int max_fields = 1;
     int max_req_tf = 0;
-    int max_job_tf = 0;
+    int max_tile_steps = 8;
+    int max_tiles = 1;
+    int max_w = 1;
+    int max_bin_units = 1;
     int any_exact = 0;
-    int64_t k1_units = 0, k3_units = 0, k4_units = 0;
+    int64_t k1_units = 0;
     size_t tf_floats = 0;
     // descriptor block, uploaded before every launch:
-    //   [header: 3 rescan counters][JobDev x jobs][ReqDev x reqs][max V x reqs][tables]
-    // followed on the device (not uploaded) by the rescan queues [3][k3_units]
-    size_t off_jobs = 0, off_reqs = 0, off_vmax = 0, off_tf = 0, block_bytes = 0;
-    size_t off_queue = 0, device_bytes = 0;
+    //   [GroupDev x groups][ReqDev x reqs][max V x reqs][tables]
+    size_t off_reqs = 0, off_vmax = 0, off_tf = 0, block_bytes = 0;
 };
 
-// Group the requests into jobs (one volume; at most kMaxReqPerJob requests
-// whose tables fit the importance pass's LDS) and lay out the work units of
-// every phase and the descriptor block.
+// Volumes of at most this many one-tile runs have each tile shared by a
+// workgroup's four waves in the importance pass: up to 4 such workgroups fit
+// a compute unit, so a wave per tile would leave most of the chip idle.
+constexpr int kSplitTiles = 1024;
+
+static VolDev vol_dev(const dvl_volume* v) {
+    VolDev d{};
+    d.n = v->n;
+    d.n_tiles = (int)v->n_tiles;
+    d.tiles_per_run = (int)v->tiles_per_run;
+    d.n_runs = (int)v->n_runs;
+    d.M = v->M;
+    d.tile_steps = v->tile_steps;
+    // a wave's quarter of a tile must start on a group of four level codes
+    d.split = v->tiles_per_run == 1 && v->n_tiles <= kSplitTiles && v->tile_steps >= 16;
+    d.level = v->level_s;
+    d.lcode = v->lcode_s;
+    for (int m = 0; m < v->M; ++m) d.fields[m] = v->fields_s[m];
+    d.agg_sum = v->agg_sum;
+    d.agg_min = v->agg_min;
+    d.agg_max = v->agg_max;
+    d.step_sum = v->step_sum;
+    d.step_min = v->step_min;
+    d.step_max = v->step_max;
+    return d;
+}
+
+// Group the requests by volume and lay out the work units of every phase and
+// the descriptor block.
 static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
     P = Plan();
     if (reqs.empty()) return fail(DVL_E_INVALID, "empty batch");
@@ -442,75 +468,39 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
     P.where.assign(reqs.size(), 0);
     for (size_t i = 0; i < reqs.size(); ++i) {
         if (taken[i]) continue;
+        GroupDev g{};
+        g.unit0 = P.k1_units;
+        g.req0 = (int)P.reqs.size();
+        dvl_volume* v = reqs[i].v;
         for (size_t k = i; k < reqs.size(); ++k)
-            if (!taken[k] && reqs[k].v == reqs[i].v) {
+            if (!taken[k] && reqs[k].v == v) {
                 P.where[k] = (int)P.reqs.size();
                 P.reqs.push_back(std::move(reqs[k]));
                 taken[k] = true;
             }
-    }
-    size_t tf_pos = 0;
-    for (size_t i = 0; i < P.reqs.size();) {
-        dvl_volume* v = P.reqs[i].v;
-        JobDev j{};
-        j.n = v->n;
-        j.n_tiles = v->n_tiles;
-        j.tiles_per_run = v->tiles_per_run;
-        j.n_runs = v->n_runs;
-        j.k1_unit0 = P.k1_units;
-        j.M = v->M;
-        j.req0 = (int)i;
-        j.tile_steps = v->tile_steps;
-        j.level = v->level_s;
-        j.lcode = v->lcode_s;
-        for (int m = 0; m < v->M; ++m) j.fields[m] = v->fields_s[m];
-        j.agg_sum = v->agg_sum;
-        j.agg_min = v->agg_min;
-        j.agg_max = v->agg_max;
-        j.step_sum = v->step_sum;
-        j.step_min = v->step_min;
-        j.step_max = v->step_max;
-        int tf_job = 0;
-        size_t k = i;
-        while (k < P.reqs.size() && P.reqs[k].v == v && (int)(k - i) < kMaxReqPerJob &&
-               (k == i || tf_job + P.reqs[k].total <= kJobTfFloats)) {
-            ReqHost& r = P.reqs[k];
-            r.job = (int)P.jobs.size();
-            r.tf_pos = tf_pos;
-            tf_pos += r.total;
-            tf_job += r.total;
-            P.max_req_tf = std::max(P.max_req_tf, r.total);
-            if (r.p.vmax_mode == DVL_VMAX_EXACT) P.any_exact = 1;
-            ++k;
-        }
-        j.n_req = (int)(k - i);
-        j.tf_total_all = tf_job;
-        P.max_job_tf = std::max(P.max_job_tf, tf_job);
-        P.max_m = std::max(P.max_m, v->M);
-        P.max_req = std::max(P.max_req, j.n_req);
-        // one importance-pass unit is one workgroup: a run per wave
-        P.k1_units += (j.n_runs + (kUpdThreads / kWave) - 1) / (kUpdThreads / kWave);
-        P.jobs.push_back(j);
-        i = k;
+        g.n_req = (int)P.reqs.size() - g.req0;
+        // one importance-pass unit is one workgroup: a run per wave, or a tile
+        const VolDev d = vol_dev(v);
+        P.k1_units += (int64_t)g.n_req * (d.split ? d.n_runs : (d.n_runs + kUpdWaves - 1) / kUpdWaves);
+        P.groups.push_back(g);
     }
     // The kernels are specialised on the field count: batches whose volumes
-    // all have M <= 8 fields run the M-field variant; batches that mix field
-    // counts (or have more than 8) run the general one, which reads M per job.
-    for (const JobDev& j : P.jobs)
-        if (j.M != P.jobs[0].M) P.max_m = kMaxFields;
-    if (P.max_m > 8) P.max_m = kMaxFields;
-    P.tf_floats = tf_pos;
+    // all have 1, 2, 4 or 8 fields run that variant; others the general one,
+    // which reads M per volume.
+    P.max_m = P.reqs[0].v->M;
     P.rdev.resize(P.reqs.size());
+    P.fstore.assign(P.reqs.size(), nullptr);
     for (size_t q = 0; q < P.reqs.size(); ++q) {
-        const ReqHost& r = P.reqs[q];
-        const JobDev& j = P.jobs[r.job];
+        ReqHost& r = P.reqs[q];
         ReqDev& d = P.rdev[q];
         d = ReqDev{};
+        d.v = vol_dev(r.v);
+        r.tf_pos = P.tf_floats;
+        P.tf_floats += r.total;
         for (int m = 0; m < r.v->M; ++m) {
             d.nmax[m] = (float)(r.n_tf[m] - 1);
             d.tf_off[m] = r.off[m];
         }
-        d.tf_job_off = (int)(r.tf_pos - P.reqs[j.req0].tf_pos);
         d.tf_total = r.total;
         d.W = r.p.n_bins;
         d.exponent = r.p.exponent;
@@ -520,11 +510,9 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         d.level_shift = r.p.level_scale;
         d.scan_mode = r.p.scan_mode;
         d.vmax_exact = r.p.vmax_mode == DVL_VMAX_EXACT;
-        d.job = r.job;
-        d.k3_unit0 = P.k3_units;
-        d.k4_unit0 = P.k4_units;
-        P.k3_units += j.n_tiles;
-        P.k4_units += r.p.n_bins;
+        // a workgroup of k_bin per tile when there are no more tiles than
+        // bins, else per bin edge
+        d.by_tile = d.v.n_tiles <= d.W;
         d.first_cell = r.out.first_cell;
         d.last_cell = r.out.last_cell;
         d.mean = r.out.mean;
@@ -533,14 +521,20 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         d.y = r.out.y;
         d.f_total = r.out.f_total;
         d.vmax_used = r.out.vmax_used;
+        if (r.v->M != P.max_m) P.max_m = kMaxFields;
+        P.max_fields = std::max(P.max_fields, r.v->M);
+        P.max_req_tf = std::max(P.max_req_tf, r.total);
+        P.max_tile_steps = std::max(P.max_tile_steps, d.v.tile_steps);
+        P.max_tiles = std::max(P.max_tiles, d.v.n_tiles);
+        P.max_w = std::max(P.max_w, d.W);
+        P.max_bin_units = std::max(P.max_bin_units, d.by_tile ? d.v.n_tiles : d.W - 1);
+        P.any_exact |= d.vmax_exact;
     }
-    P.off_jobs = 256 + al256(P.rdev.size() * sizeof(uint32_t));   // counters, then carry flags
-    P.off_reqs = P.off_jobs + al256(P.jobs.size() * sizeof(JobDev));
-    P.off_vmax = P.off_reqs + al256(P.rdev.size() * sizeof(ReqDev));
-    P.off_tf = P.off_vmax + al256(P.rdev.size() * sizeof(float));
-    P.block_bytes = P.off_tf + al256(P.tf_floats * sizeof(float));
-    P.off_queue = P.block_bytes;
-    P.device_bytes = P.off_queue + al256((size_t)3 * P.k3_units * sizeof(uint64_t));
+    if (P.max_m > 8) P.max_m = kMaxFields;
+    P.off_reqs = (P.groups.size() * sizeof(GroupDev) + 63) & ~(size_t)63;
+    P.off_vmax = P.off_reqs + P.rdev.size() * sizeof(ReqDev);
+    P.off_tf = (P.off_vmax + P.rdev.size() * sizeof(float) + 63) & ~(size_t)63;
+    P.block_bytes = al256(P.off_tf + P.tf_floats * sizeof(float));
     return DVL_OK;
 }
 
@@ -563,9 +557,7 @@ static dvl_status fill_block(Plan& P, char* h, char* d) {
         P.rdev[q].tf = (const float*)(d + P.off_tf) + r.tf_pos;
         P.rdev[q].vmax_dev = (float*)(d + P.off_vmax) + q;
     }
-    for (auto& j : P.jobs) j.tf_all = (const float*)(d + P.off_tf) + P.reqs[j.req0].tf_pos;
-    memset(h, 0, P.off_jobs);   // rescan counters and carry flags start at 0
-    memcpy(h + P.off_jobs, P.jobs.data(), P.jobs.size() * sizeof(JobDev));
+    memcpy(h, P.groups.data(), P.groups.size() * sizeof(GroupDev));
     memcpy(h + P.off_reqs, P.rdev.data(), P.rdev.size() * sizeof(ReqDev));
     return DVL_OK;
 }
@@ -590,29 +582,36 @@ struct CacheBuild {
     CacheKey key;
 };
 
-// Choose, per job, between reading the field values and reading the
+// the requests of group g read their volume's entry cache
+static void use_cache(Plan& P, const GroupDev& g) {
+    const dvl_volume* v = P.reqs[g.req0].v;
+    for (int k = 0; k < g.n_req; ++k) {
+        ReqDev& d = P.rdev[g.req0 + k];
+        d.entries = 1;
+        for (int m = 0; m < v->M; ++m) d.v.idx[m] = v->idx_s[m];
+    }
+}
+
+// Choose, per request, between reading the field values and reading the
 // volume's TF entry cache; schedule the cache (re)builds this launch needs.
-// A job reads the cache if all its requests share one key and the cache holds
-// it (or is built for it now).  One volume's cache serves one key per launch.
+// The requests on one volume read the cache if they share one key and the
+// cache holds it (or is built for it now): one volume's cache serves one key
+// per launch.
 static dvl_status decide_cache(Plan& P, std::vector<CacheBuild>& builds) {
     builds.clear();
-    std::vector<std::pair<dvl_volume*, CacheKey>> serving;   // cache contents per volume in this launch
-    for (JobDev& j : P.jobs) {
-        for (int m = 0; m < kMaxFields; ++m) j.idx[m] = nullptr;
-        dvl_volume* v = P.reqs[j.req0].v;
+    for (const GroupDev& g : P.groups) {
+        for (int k = 0; k < g.n_req; ++k) P.rdev[g.req0 + k].entries = 0;
+        dvl_volume* v = P.reqs[g.req0].v;
         if (v->idx_policy == DVL_ENTRY_CACHE_NEVER) continue;
         CacheKey key;
-        bool agree = key_of(P.reqs[j.req0], key);
-        for (int k = 1; agree && k < j.n_req; ++k) {
+        bool agree = key_of(P.reqs[g.req0], key);
+        for (int k = 1; agree && k < g.n_req; ++k) {
             CacheKey k2;
-            agree = key_of(P.reqs[j.req0 + k], k2) && k2 == key;
+            agree = key_of(P.reqs[g.req0 + k], k2) && k2 == key;
         }
         if (!agree) continue;
-        auto it = std::find_if(serving.begin(), serving.end(), [&](const auto& e) { return e.first == v; });
         bool use = false;
-        if (it != serving.end()) {
-            use = it->second == key;            // another key already serves this launch: values
-        } else if (v->idx_valid && v->idx_key == key) {
+        if (v->idx_valid && v->idx_key == key) {
             use = true;
         } else if (v->idx_policy == DVL_ENTRY_CACHE_ALWAYS || (v->cand_set && v->cand_key == key)) {
             for (int m = 0; m < v->M; ++m) {
@@ -628,10 +627,7 @@ static dvl_status decide_cache(Plan& P, std::vector<CacheBuild>& builds) {
             v->cand_key = key;
             v->cand_set = true;
         }
-        if (use) {
-            if (it == serving.end()) serving.push_back({v, key});
-            for (int m = 0; m < v->M; ++m) j.idx[m] = v->idx_s[m];
-        }
+        if (use) use_cache(P, g);
     }
     return DVL_OK;
 }
@@ -696,13 +692,13 @@ static dvl_status run_cache_builds(const std::vector<CacheBuild>& builds, hipStr
     return DVL_OK;
 }
 
-// Before a launch on stream s that reads the caches of the jobs in `P`: wait
+// Before a launch on stream s that reads the caches of the volumes in `P`: wait
 // for their latest rebuild when it ran on another stream (on s itself the
 // stream order already follows it).
 static dvl_status cache_wait(const Plan& P, hipStream_t s) {
-    for (const JobDev& j : P.jobs) {
-        if (!j.idx[0]) continue;
-        dvl_volume* v = P.reqs[j.req0].v;
+    for (const GroupDev& g : P.groups) {
+        if (!P.rdev[g.req0].entries) continue;
+        dvl_volume* v = P.reqs[g.req0].v;
         if (v->cache_ready_recorded && v->cache_ready_stream != s)
             DVL_HIP(hipStreamWaitEvent(s, v->cache_ready, 0));
     }
@@ -710,12 +706,12 @@ static dvl_status cache_wait(const Plan& P, hipStream_t s) {
 }
 
 // After such a launch: s is a reader stream of those volumes (returns
-// whether any job read a cache).  The caller records s's reader event.
+// whether any request read a cache).  The caller records s's reader event.
 static bool cache_add_readers(const Plan& P, hipStream_t s) {
     bool any = false;
-    for (const JobDev& j : P.jobs) {
-        if (!j.idx[0]) continue;
-        dvl_volume* v = P.reqs[j.req0].v;
+    for (const GroupDev& g : P.groups) {
+        if (!P.rdev[g.req0].entries) continue;
+        dvl_volume* v = P.reqs[g.req0].v;
         if (std::find(v->cache_readers.begin(), v->cache_readers.end(), s) == v->cache_readers.end())
             v->cache_readers.push_back(s);
         any = true;
@@ -732,41 +728,42 @@ static dvl_status cache_mark_readers(const Plan& P, hipStream_t s) {
     return DVL_OK;
 }
 
-// polls of a request's carry flag before a classifying workgroup computes the
-// carry itself (dvl_set_carry_wait)
-static std::atomic<int> g_carry_wait_polls{kCarryWaitPolls};
-
-// The kernel variants this plan's jobs and requests use (workspaces carved,
-// caches decided): launches of variants without work are left out.
-static int plan_paths(const Plan& P) {
+// What each request's projection reads (caches decided), and the kernel
+// variants that have work.  A request whose bins number a quarter of its tiles
+// or more rescans most of the volume; it stores f in the importance pass (4
+// bytes per cell written and read again) unless reading the cached entries
+// again (M bytes) costs no more and f is cheap to compute again (no pow):
+// stored, 20 M cells of 4 fields with three such requests of four spent 480
+// of 820 MB of the importance pass on f.
+static int plan_paths(Plan& P) {
     int paths = 0;
-    for (const JobDev& j : P.jobs) paths |= j.idx[0] ? kPathEntries : kPathValues;
-    for (const ReqDev& d : P.rdev)
-        paths |= d.ws.fstore ? kPathBinStoredF : (P.jobs[d.job].idx[0] ? kPathBinEntries : kPathBinValues);
+    for (size_t q = 0; q < P.rdev.size(); ++q) {
+        ReqDev& d = P.rdev[q];
+        const bool again = d.entries && d.v.M <= 8 && d.exp_is_one;
+        d.ws.fstore = again ? nullptr : P.fstore[q];
+        d.bin_path = d.ws.fstore ? 2 : (d.entries ? 1 : 0);
+        paths |= d.entries ? kPathEntries : kPathValues;
+        paths |= d.bin_path == 2 ? kPathBinStoredF : (d.bin_path == 1 ? kPathBinEntries : kPathBinValues);
+    }
     return paths;
 }
 
 // `paths`: the variants to launch (plan_paths)
 static BatchDev batch_dev(const Plan& P, char* d, int paths) {
     BatchDev b{};
-    b.paths = paths;
-    b.jobs = (const JobDev*)(d + P.off_jobs);
+    b.groups = (const GroupDev*)d;
     b.reqs = (const ReqDev*)(d + P.off_reqs);
-    b.rescan_count = (uint32_t*)d;
-    b.carry_ready = (uint32_t*)(d + 256);
-    b.rescan_queue = (uint64_t*)(d + P.off_queue);
-    b.n_jobs = (int)P.jobs.size();
+    b.n_groups = (int)P.groups.size();
     b.n_reqs = (int)P.rdev.size();
     b.k1_units = P.k1_units;
-    b.k3_units = P.k3_units;
-    b.k4_units = P.k4_units;
     b.any_exact = P.any_exact;
+    b.paths = paths;
     b.max_req_tf = P.max_req_tf;
-    b.max_job_tf = P.max_job_tf;
-    b.max_req_job = P.max_req;
-    b.max_tile_steps = 8;
-    b.carry_wait_polls = g_carry_wait_polls.load(std::memory_order_relaxed);
-    for (const JobDev& j : P.jobs) b.max_tile_steps = std::max(b.max_tile_steps, j.tile_steps);
+    b.max_fields = P.max_fields;
+    b.max_tile_steps = P.max_tile_steps;
+    b.max_tiles = P.max_tiles;
+    b.max_w = P.max_w;
+    b.max_bin_units = P.max_bin_units;
     return b;
 }
 
@@ -775,6 +772,12 @@ static int64_t fstore_cells(const dvl_volume* v, int n_bins) {
 }
 static size_t request_ws_bytes(const dvl_volume* v, int n_bins) {
     return workspace_bytes(v->n_tiles, v->M, n_bins, fstore_cells(v, n_bins));
+}
+// request q's workspace at `base`; fcells: see workspace_bytes
+static void carve_request(Plan& P, size_t q, void* base, int64_t fcells) {
+    const ReqHost& r = P.reqs[q];
+    workspace_carve(base, r.v->n_tiles, r.v->M, r.p.n_bins, fcells, &P.rdev[q].ws);
+    P.fstore[q] = P.rdev[q].ws.fstore;
 }
 
 // ================================================================== executor
@@ -954,13 +957,13 @@ struct Executor {
         for (size_t q = 0; q < P.reqs.size(); ++q) {
             const ReqHost& r = P.reqs[q];
             if (dvl_status st = ensure_ws(q, request_ws_bytes(r.v, r.p.n_bins))) return st;
-            workspace_carve(ws[q].first, r.v->n_tiles, r.v->M, r.p.n_bins, fstore_cells(r.v, r.p.n_bins), &P.rdev[q].ws);
+            carve_request(P, q, ws[q].first, fstore_cells(r.v, r.p.n_bins));
         }
         std::vector<CacheBuild> builds;
         if (dvl_status st = decide_cache(P, builds)) return st;
         if (dvl_status st = run_cache_builds(builds, s)) return st;
         if (dvl_status st = cache_wait(P, s)) return st;
-        if (dvl_status st = ensure_block(P.device_bytes)) return st;
+        if (dvl_status st = ensure_block(P.block_bytes)) return st;
         // a launch on another stream than the previous one first waits for it
         // (it may still read the block and the workspaces)
         if (launched && s != last_stream) {
@@ -968,10 +971,11 @@ struct Executor {
             if (dvl_status st = last_event(&prev)) return st;
             if (prev) DVL_HIP(hipStreamWaitEvent(s, prev, 0));
         }
+        const int paths = plan_paths(P);
         if (dvl_status st = upload(P, s)) return st;
         hipEvent_t* ev = nullptr;
         if (dvl_status st = timing_events(&ev)) return st;
-        if (dvl_status st = launch_batch(batch_dev(P, blk, plan_paths(P)), P.dtype, P.max_m, P.max_req, n_cu, s, kDescriptorLayout, ev))
+        if (dvl_status st = launch_batch(batch_dev(P, blk, paths), P.dtype, P.max_m, n_cu, s, kDescriptorLayout, ev))
             return st;
         cache_add_readers(P, s);
         hipEvent_t done = nullptr;
@@ -1395,20 +1399,30 @@ static dvl_status scratch_address(int dev, char** out) {
 // Upload of a host image into device memory through kernel arguments (the
 // runtime copies them at launch): no staging buffer, no memcpy node.
 
-// A job reads the volume's entry cache here only when the cache already holds
-// its key (it is never built here) and this stream is already one of the
+// A request reads the volume's entry cache here only when the cache already
+// holds its key (it is never built here) and this stream is already one of the
 // volume's reader streams (its reader event exists and is re-recorded below,
 // creating nothing), so a later rebuild elsewhere still waits for this launch.
 static void use_existing_cache(Plan& P, hipStream_t s) {
-    for (JobDev& j : P.jobs) {
-        for (int m = 0; m < kMaxFields; ++m) j.idx[m] = nullptr;
-        dvl_volume* v = P.reqs[j.req0].v;
+    for (const GroupDev& g : P.groups) {
+        P.rdev[g.req0].entries = 0;      // one request per plan here
+        dvl_volume* v = P.reqs[g.req0].v;
         if (v->idx_policy == DVL_ENTRY_CACHE_NEVER || !v->idx_valid) continue;
         CacheKey key;
-        if (!key_of(P.reqs[j.req0], key) || !(key == v->idx_key)) continue;
+        if (!key_of(P.reqs[g.req0], key) || !(key == v->idx_key)) continue;
         if (std::find(v->cache_readers.begin(), v->cache_readers.end(), s) == v->cache_readers.end()) continue;
-        for (int m = 0; m < v->M; ++m) j.idx[m] = v->idx_s[m];
+        use_cache(P, g);
     }
+}
+
+// Scratch an update is charged in dvl_update_noalloc: the limit that the
+// header documents (72 bytes per tile of workspace and queues, 8 per bin, the
+// tables and descriptors), kept where the layout itself has become smaller,
+// so that the same updates are refused.
+static size_t noalloc_charge(const Plan& P) {
+    const size_t T = (size_t)P.rdev[0].v.n_tiles, W = (size_t)P.rdev[0].W;
+    const size_t block = 1792 + al256(P.tf_floats * sizeof(float)) + al256(24 * T);
+    return block + 4 * al256(8 * T) + al256(8 * (T + 1)) + 2 * al256(4 * T) + 2 * al256(4 * W) + 256;
 }
 
 }  // namespace dvl
@@ -1425,33 +1439,32 @@ dvl_status dvl_update_noalloc(dvl_volume* v, const dvl_params* p, const dvl_bins
     hipStream_t s = (hipStream_t)stream;
     Plan P;
     if (dvl_status st = plan_batch(std::move(reqs), P)) return st;
-    const size_t block = al256(P.device_bytes);
-    const size_t need = block + workspace_bytes(v->n_tiles, v->M, p->n_bins, 0);
+    const size_t block = al256(P.block_bytes);
+    const size_t need = std::max(noalloc_charge(P), block + workspace_bytes(v->n_tiles, v->M, p->n_bins, 0));
     if (need > kScratchBytes)
         return fail(DVL_E_NOMEM, "this update needs %zu bytes of scratch; dvl_update_noalloc has %zu "
                     "(use dvl_update)", need, kScratchBytes);
     char* base = nullptr;
     if (dvl_status st = scratch_address(dev, &base)) return st;
-    workspace_carve(base + block, v->n_tiles, v->M, p->n_bins, 0, &P.rdev[0].ws);
+    carve_request(P, 0, base + block, 0);
     use_existing_cache(P, s);
     if (dvl_status st = cache_wait(P, s)) return st;
+    const int paths = plan_paths(P);
     std::vector<char> img(P.block_bytes);
     if (dvl_status st = fill_block(P, img.data(), base)) return st;
     if (dvl_status st = poke(base, img.data(), P.block_bytes, s)) {
         v->sticky = st;
         return st;
     }
-    if (dvl_status st = launch_batch(batch_dev(P, base, plan_paths(P)), P.dtype, P.max_m, P.max_req, v->n_cu, s, kDescriptorLayout, nullptr)) {
+    if (dvl_status st = launch_batch(batch_dev(P, base, paths), P.dtype, P.max_m, v->n_cu, s, kDescriptorLayout, nullptr)) {
         if (st == DVL_E_HIP) v->sticky = st;
         return st;
     }
-    for (const JobDev& j : P.jobs)
-        if (j.idx[0]) {
-            hipEvent_t ev = nullptr;   // exists: s is a reader stream of the volume
-            if (dvl_status st = reader_event(s, false, &ev)) return st;
-            if (ev) DVL_HIP(hipEventRecord(ev, s));
-            break;
-        }
+    if (P.rdev[0].entries) {
+        hipEvent_t ev = nullptr;   // exists: s is a reader stream of the volume
+        if (dvl_status st = reader_event(s, false, &ev)) return st;
+        if (ev) DVL_HIP(hipEventRecord(ev, s));
+    }
     return DVL_OK;
 }
 
@@ -1460,8 +1473,7 @@ size_t dvl_update_noalloc_max_bytes(void) { return kScratchBytes; }
 dvl_status dvl_set_carry_wait(int32_t polls) {
     g_err.clear();
     if (polls < 0) return fail(DVL_E_INVALID, "polls %d < 0", (int)polls);
-    g_carry_wait_polls.store(polls, std::memory_order_relaxed);
-    return DVL_OK;
+    return DVL_OK;   // every classifying workgroup computes its carry itself
 }
 
 dvl_status dvl_read_bins(const dvl_volume* v, const dvl_bins* b, int32_t W, void* stream, uint32_t* count,
@@ -1869,11 +1881,11 @@ dvl_status dvl_graph_create(const dvl_request* reqs, int32_t n_reqs, dvl_graph**
         const ReqHost& r = P.reqs[q];
         if (dvl_status st = w.alloc(request_ws_bytes(r.v, r.p.n_bins), "request workspace")) return st;
         g->ws.push_back(w.release());
-        workspace_carve(g->ws.back(), r.v->n_tiles, r.v->M, r.p.n_bins, fstore_cells(r.v, r.p.n_bins), &P.rdev[q].ws);
+        carve_request(P, q, g->ws.back(), fstore_cells(r.v, r.p.n_bins));
     }
     for (int k = 0; k < dvl_graph::kSlots; ++k) {
         DevBuf d(g->alloc);
-        if (dvl_status st = d.alloc(P.device_bytes, "graph descriptors")) return st;
+        if (dvl_status st = d.alloc(P.block_bytes, "graph descriptors")) return st;
         g->dev[k] = (char*)d.release();
     }
     {
@@ -1911,7 +1923,7 @@ static dvl_status graph_exec_for(dvl_graph* g, int paths, int slot, hipGraphExec
         return hip_fail(e, "hipStreamBeginCapture");
     }
     const dvl_status cst =
-        launch_batch(batch_dev(P, g->dev[slot], paths), P.dtype, P.max_m, P.max_req, g->n_cu, cs, kDescriptorLayout, nullptr);
+        launch_batch(batch_dev(P, g->dev[slot], paths), P.dtype, P.max_m, g->n_cu, cs, kDescriptorLayout, nullptr);
     hipGraph_t graph = nullptr;
     const hipError_t ee = hipStreamEndCapture(cs, &graph);
     (void)hipStreamDestroy(cs);

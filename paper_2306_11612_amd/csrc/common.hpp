@@ -254,6 +254,7 @@ typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 // and the rescan's 9 to 22 thousand before its first tile.)
 __device__ __forceinline__ int thread_x() { return (int)__builtin_amdgcn_workitem_id_x(); }
 __device__ __forceinline__ int block_x() { return (int)__builtin_amdgcn_workgroup_id_x(); }
+__device__ __forceinline__ int block_y() { return (int)__builtin_amdgcn_workgroup_id_y(); }
 __device__ __forceinline__ int block_dim_x() {
     const DVL_CONST uint16_t* ia = (const DVL_CONST uint16_t*)__builtin_amdgcn_implicitarg_ptr();
     return (int)ia[6];                        // group size x

@@ -1,23 +1,22 @@
 // Per-update kernels of dynamic volume lines (Eqs. 1-4 and section
 // "Projecting Cells to 1D" of Zellmann et al., arXiv 2306.11612), over a
-// batch of jobs (a job = one volume and up to 8 TF requests).
+// batch of requests (a request = one volume, its TFs and parameters).
 //
 //   K0 k_vmax_exact   (DVL_VMAX_EXACT requests only) max over cells of V_h
 //   K1 k_tile_sums    TF lookup, V_h (Eq. 1) and importance f (Eq. 3) of every
-//                     cell for every request of its job (one read of the
-//                     cells); fp64 sum of f per tile; each wave owns a run of
+//                     cell; fp64 sum of f per tile; each wave owns a run of
 //                     consecutive tiles and records their prefix inside it
 //   K2 + K3a k_carry_classify (one kernel)
-//                     K2, per request: exclusive scan of the run totals (Eq. 4
-//                     across runs; fp64 or compensated fp32), made monotone;
-//                     K3a, per (request, tile), one lane each, once the
-//                     request's carry is published: if the tile's pixel
+//                     K2: exclusive scan of the run totals (Eq. 4 across runs;
+//                     fp64 or compensated fp32), made monotone; K3a, per
+//                     tile, one lane each: its pixel position; if its pixel
 //                     interval lies inside one bin, the whole tile is that
-//                     bin's part; otherwise the tile is queued
-//   K3b k_bin         per queued tile: recompute f, monotone in-tile prefix,
-//                     pixel interval of every cell; the cell range of every
-//                     bin that starts and ends inside the tile, and of the
-//                     tile's first and last bin (per-tile records)
+//                     bin's part
+//   K3b k_bin         per tile holding a bin edge: recompute f, monotone
+//                     in-tile prefix, pixel interval of every cell; the cell
+//                     range of every bin that starts and ends inside the
+//                     tile, and of the tile's first and last bin (per-tile
+//                     records)
 //   K4 k_bin_stats    per (request, bin): the bin's cell range (merged from
 //                     the records of the tiles it touches), then its mean,
 //                     min and max per field from the values of its partial
@@ -48,7 +47,7 @@ size_t workspace_bytes(int64_t T, int M, int W, int64_t fcells) {
     size_t b = 0;
     b += al256((size_t)T * 8);             // local_prefix
     b += al256((size_t)T * 8);             // run_total
-    b += al256((size_t)(T + 1) * 8);       // run_base
+    b += al256((size_t)(T + 1) * 4);       // tile positions
     b += 2 * al256((size_t)T * 4);         // head/tail bin
     b += 2 * al256((size_t)2 * T * 4);     // rec first/last
     b += 2 * al256((size_t)W * 4);         // per-bin tile bounds
@@ -62,13 +61,13 @@ void workspace_carve(void* base, int64_t T, int M, int W, int64_t fcells, UpdWor
     auto take = [&](size_t bytes) { char* q = p; p += al256(bytes); return (void*)q; };
     w->local_prefix = (double*)take((size_t)T * 8);
     w->run_total = (double*)take((size_t)T * 8);
-    w->run_base = (double*)take((size_t)(T + 1) * 8);
+    w->x0 = (float*)take((size_t)(T + 1) * 4);
     w->head_bin = (int32_t*)take((size_t)T * 4);
     w->tail_bin = (int32_t*)take((size_t)T * 4);
     w->rec_first = (uint32_t*)take((size_t)2 * T * 4);
     w->rec_last = (uint32_t*)take((size_t)2 * T * 4);
     w->bin_t1 = (int32_t*)take((size_t)W * 4);
-    w->bin_ta = (int32_t*)take((size_t)W * 4);
+    w->bin_ta = (uint32_t*)take((size_t)W * 4);
     w->scal = (double*)take(8 * 8);
     w->fstore = fcells ? (float*)take((size_t)fcells * 4) : nullptr;
 }
@@ -126,30 +125,34 @@ constexpr int kCarryItems = 8;                              // run totals per th
 constexpr int kCarryRound = kCarryThreads * kCarryItems;
 constexpr int kCarryWaves = kCarryThreads / kWave;
 
-// One workgroup per request.  run_base[r] = sum of the run totals before r,
-// run_base[R] = F_tot: a sequential prefix over each thread's 8 totals, a
-// wave scan of the thread totals made monotone by a running maximum, and
-// sequential wave and round bases; every base is clamped to the next thread's
-// base, so the bases never decrease.
+// Bases of the runs a classifying workgroup needs (its 1024 tiles touch at
+// most 1025 runs and the base after them).
+constexpr int kClassifyTiles = kCarryThreads;
+constexpr int kRunBases = kClassifyTiles + 2;
+
+// The exclusive scan of request q's R run totals, by the whole workgroup:
+// base[r] = sum of the run totals before r for the runs r_lo .. r_hi + 1 (into
+// LDS), and F_tot, the base after the last run.  A sequential prefix over each
+// thread's 8 totals, a wave scan of the thread totals made monotone by a
+// running maximum, and sequential wave and round bases; every base is clamped
+// to the next thread's base, so the bases never decrease.
 template <typename Acc>
-__device__ void carry_scan(const ReqDev& q, int64_t T, int64_t n_cells) {
+__device__ double carry_scan(const double* run_total, int R, int r_lo, int r_hi, double* base) {
     __shared__ double wave_base[kCarryWaves + 1];
     __shared__ Acc wave_acc[kCarryWaves];
     __shared__ Acc round_acc;
     __shared__ double round_end;
     const int tid = thread_x(), lane = lane_id(), w = tid / kWave;
-    const double* ts = q.ws.run_total;
-    double* base_out = q.ws.run_base;
     if (tid == 0) {
         round_acc = Acc::zero();
         round_end = 0.0;
     }
     __syncthreads();
-    for (int64_t r0 = 0; r0 < T; r0 += kCarryRound) {
-        const int64_t b0 = r0 + (int64_t)tid * kCarryItems;
+    for (int r0 = 0; r0 < R; r0 += kCarryRound) {
+        const int b0 = r0 + tid * kCarryItems;
         double v[kCarryItems];
 #pragma unroll
-        for (int k = 0; k < kCarryItems; ++k) v[k] = (b0 + k < T) ? gload<double>(ts, b0 + k) : 0.0;
+        for (int k = 0; k < kCarryItems; ++k) v[k] = (b0 + k < R) ? gload<double>(run_total, b0 + k) : 0.0;
         Acc pre[kCarryItems];
         Acc run = Acc::zero();
 #pragma unroll
@@ -165,17 +168,21 @@ __device__ void carry_scan(const ReqDev& q, int64_t T, int64_t n_cells) {
         if (lane == kWave - 1) wave_acc[w] = inc;
         __syncthreads();
         if (tid == 0) {
-            Acc base = round_acc;
+            Acc acc[kCarryWaves];
+#pragma unroll
+            for (int k = 0; k < kCarryWaves; ++k) acc[k] = wave_acc[k];
+            Acc sum = round_acc;
             double prev = round_end;
+#pragma unroll
             for (int k = 0; k < kCarryWaves; ++k) {
-                prev = fmax(prev, base.value());
+                prev = fmax(prev, sum.value());
                 wave_base[k] = prev;
-                base = Acc::combine(base, wave_acc[k]);
+                sum = Acc::combine(sum, acc[k]);
             }
-            prev = fmax(prev, base.value());
+            prev = fmax(prev, sum.value());
             wave_base[kCarryWaves] = prev;
             round_end = prev;
-            round_acc = base;
+            round_acc = sum;
         }
         __syncthreads();
         const double wb = wave_base[w], wn = wave_base[w + 1];
@@ -195,36 +202,28 @@ __device__ void carry_scan(const ReqDev& q, int64_t T, int64_t n_cells) {
 #pragma unroll
         for (int k = 0; k < kCarryItems; ++k) {
             c = fmax(c, fmin(tb + pre[k].value(), nb));
-            if (b0 + k < T) gstore<double>(base_out, b0 + k, c);
+            const int r = b0 + k;
+            if (r < R && r >= r_lo && r <= r_hi + 1) base[r - r_lo] = c;
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        gstore<double>(base_out, T, round_end);
-        // a zero total means every f was zero: fall back to f = 1 (linear map;
-        // the projection then derives the tile offsets from the cell counts)
-        const bool degenerate = !(round_end > 0.0);
-        gstore<double>(q.ws.scal, 0, degenerate ? (double)n_cells : round_end);
-        gstore<double>(q.ws.scal, 1, degenerate ? 1.0 : 0.0);
-    }
+    const double total = round_end;
+    if (tid == 0 && r_hi + 1 >= R) base[R - r_lo] = total;
+    __syncthreads();
+    return total;
 }
 
-// The carry of request q, in the request's scan arithmetic (the whole
-// workgroup; writes run_base and the scalars).
-__device__ void scan_request(const BatchDev& b, int q_index) {
-    const ReqDev& q = b.reqs[q_index];
-    const JobDev& j = b.jobs[q.job];
-    if (q.scan_mode == DVL_SCAN_KAHAN_FP32)
-        carry_scan<AccKahan32>(q, j.n_runs, j.n);
-    else if (q.scan_mode == DVL_SCAN_NAIVE_FP32)
-        carry_scan<AccF32>(q, j.n_runs, j.n);
-    else
-        carry_scan<AccF64>(q, j.n_runs, j.n);
-}
-
-// K3a.  A tile whose pixel interval lies inside one bin puts every cell in
-// that bin: its head record is the whole tile and no cell is read (the
-// projection is hierarchical over tiles).  Other tiles are queued for K3b.
+// Grid: x chunks of 1024 tiles, y requests.  Every workgroup scans its
+// request's run totals itself (at most 8192 in the default layout: 64 KB from
+// L2, the same code on the same inputs, so the same bits) and keeps the bases
+// of its own runs in LDS: one kernel with no hand-off.  (One scanning
+// workgroup per request that published its carry through a flag, polled by
+// the others, took 8.5 us for 64 tiles, 11.4 for 2880 and 20 for 122363; this
+// takes 6.3, 6.7 and 9.6.)
+//
+// K3a, a tile per thread.  A tile whose pixel interval lies inside one bin
+// puts every cell in that bin: its head record is the whole tile and no cell
+// is read (the projection is hierarchical over tiles).  The others are K3b's.
 // Every tile also writes, for the bins its interval reaches, where K4 finds
 // their tiles: with b0(t) = bin of X0(t) (the bin of the tile's first cell)
 // and b1(t) = bin of X1(t) = b0(t + 1), the last tile touching bin b is the
@@ -232,105 +231,69 @@ __device__ void scan_request(const BatchDev& b, int q_index) {
 // is the t with b1(t - 1) < b <= b1(t) (bin_ta, the first tile: b <= b1),
 // or the next tile when tile t's last cell ends exactly at bin b's left edge
 // (K4 checks it with the tile's tail bin).  These ranges partition the bins.
-// Each thread classifies one tile; the workgroup appends its queued tiles
-// with one atomic per projection path (a single counter contended by every
-// wave was the cost of this pass).
-//
-// K2 and K3a run as one kernel: workgroup q < n_reqs scans request q's run
-// totals and then publishes it (agent-scope release of carry_ready[q]);
-// the other workgroups classify 1024 tiles each once the carries of their
-// requests are published (agent-scope acquire), which saves a launch and
-// its queue drain between the two.  The wait is bounded: a workgroup that
-// has not seen the flag after b.carry_wait_polls polls scans the request
-// itself (the same code on the same inputs writes the same bits), so the
-// kernel finishes whatever the order in which its workgroups run.
-constexpr int kClassifyThreads = kCarryThreads;
-
-__device__ __forceinline__ void await_carry(const BatchDev& b, int q) {
-    __shared__ int ready;
-    if (thread_x() == 0) {
-        // polls are relaxed (an acquiring load invalidates the L2 each time,
-        // which slowed the scan it waits for); one acquire fence follows
-        uint32_t* flag = b.carry_ready + q;
-        int spins = 0;
-        while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u && spins < b.carry_wait_polls) {
-            __builtin_amdgcn_s_sleep(4);
-            ++spins;
-        }
-        ready = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+// bin_ta of a tile's first inner edge carries kFirstEdge: K3b's worklist.
+__global__ __launch_bounds__(kCarryThreads) void k_carry_classify(BatchDev bd) {
+    __shared__ double base[kRunBases];
+    const ReqDev& q = bd.reqs[block_y()];
+    const VolDev& v = q.v;
+    const int T = uni(v.n_tiles), tpr = uni(v.tiles_per_run), R = uni(v.n_runs);
+    const int t0 = block_x() * kClassifyTiles;
+    if (t0 >= T) return;
+    const int64_t n = uni(v.n);
+    const int t = t0 + thread_x();
+    const int t_last = min(t0 + kClassifyTiles, T) - 1;
+    const int r_lo = t0 / tpr, r_hi = min((t_last + 1) / tpr, R - 1);
+    // in-run prefixes of this tile and the next, on their way during the scan
+    const double lp = t < T ? gload<double>(q.ws.local_prefix, t) : 0.0;
+    const double lp_next = t + 1 < T ? gload<double>(q.ws.local_prefix, t + 1) : 0.0;
+    const int mode = uni(q.scan_mode);
+    const double* run_total = uni(q.ws.run_total);
+    double total;
+    if (mode == DVL_SCAN_KAHAN_FP32)
+        total = carry_scan<AccKahan32>(run_total, R, r_lo, r_hi, base);
+    else if (mode == DVL_SCAN_NAIVE_FP32)
+        total = carry_scan<AccF32>(run_total, R, r_lo, r_hi, base);
+    else
+        total = carry_scan<AccF64>(run_total, R, r_lo, r_hi, base);
+    // a zero total means every f was zero: fall back to f = 1 (linear map; the
+    // tile offsets then follow from the cell counts)
+    const bool degenerate = !(total > 0.0);
+    const double f_tot = degenerate ? (double)n : total;
+    const int W = uni(q.W);
+    const double scale = (double)W / f_tot;
+    if (t0 == 0 && thread_x() == 0) {
+        gstore<double>(q.ws.scal, 0, f_tot);
+        gstore<double>(q.ws.scal, 1, degenerate ? 1.0 : 0.0);
+        gstore<double>(q.ws.scal, 2, scale);
     }
-    __syncthreads();
-    if (!ready) scan_request(b, q);
-    __syncthreads();
-}
-
-__global__ __launch_bounds__(kClassifyThreads) void k_carry_classify(BatchDev bd) {
-    if (block_x() < bd.n_reqs) {
-        scan_request(bd, block_x());
-        __syncthreads();
-        if (thread_x() == 0) {
-            __threadfence();
-            __hip_atomic_store(bd.carry_ready + block_x(), 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        return;
-    }
-    __shared__ uint32_t wcount[3][kClassifyThreads / kWave];
-    __shared__ uint32_t wbase[3];
-    const int lane = lane_id(), w = thread_x() / kWave;
-    const int64_t u0 = (int64_t)(block_x() - bd.n_reqs) * kClassifyThreads;
-    // the requests of this workgroup's tiles: their carries first
-    {
-        const int qa = find_req_k3(bd, u0);
-        const int qb = find_req_k3(bd, min(u0 + kClassifyThreads, bd.k3_units) - 1);
-        for (int q = qa; q <= qb; ++q) await_carry(bd, q);
-    }
-    const int64_t u = u0 + thread_x();
-    bool need = false;
-    int path = 0;
-    if (u < bd.k3_units) {
-        const ReqDev& q = bd.reqs[find_req_k3(bd, u)];
-        const JobDev& j = bd.jobs[q.job];
-        path = q.ws.fstore ? 2 : (j.idx[0] ? 1 : 0);
-        const int64_t t = u - q.k3_unit0;
-        const TileSpan sp = tile_span(q, j, t);
-        const bool last_tile = t == j.n_tiles - 1;
-        const int W1 = q.W - 1;
-        for (int b = sp.b0, e = last_tile ? W1 : sp.b1 - 1; b <= e; ++b)
-            gstore<int32_t>(q.ws.bin_t1, b, (int32_t)t);
-        for (int b = t == 0 ? 0 : sp.b0 + 1, e = last_tile ? W1 : sp.b1; b <= e; ++b)
-            gstore<int32_t>(q.ws.bin_ta, b, (int32_t)t);
-        if (sp.b0 == sp.b1) {
-            const int64_t tile_cells = (int64_t)j.tile_steps * kStepCells;
-            const int64_t tbase = t * tile_cells;
-            gstore<uint32_t>(q.ws.rec_first, t, (uint32_t)tbase);
-            gstore<uint32_t>(q.ws.rec_last, t, (uint32_t)(min(tbase + tile_cells, j.n) - 1));
-            gstore<int32_t>(q.ws.head_bin, t, sp.b0);
-            gstore<int32_t>(q.ws.tail_bin, t, sp.b0);
-        } else {
-            need = true;
-        }
-    }
-    // per path: the wave's queued tiles, then one atomic for the workgroup
-    uint32_t mine_before[3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        const uint64_t mask = __ballot(need && path == p);
-        mine_before[p] = (uint32_t)__popcll(mask & lanemask_lt());
-        if (lane == 0) wcount[p][w] = (uint32_t)__popcll(mask);
-    }
-    __syncthreads();
-    if (thread_x() < 3) {
-        const int p = thread_x();
-        uint32_t tot = 0;
-        for (int k = 0; k < kClassifyThreads / kWave; ++k) tot += wcount[p][k];
-        wbase[p] = tot ? atomicAdd(bd.rescan_count + p, tot) : 0u;
-    }
-    __syncthreads();
-    if (need) {
-        uint32_t base = wbase[path];
-        for (int k = 0; k < w; ++k) base += wcount[path][k];
-        gstore<uint64_t>(bd.rescan_queue, path * bd.k3_units + base + mine_before[path], (uint64_t)u);
+    if (t >= T) return;
+    const int64_t tile_cells = (int64_t)uni(v.tile_steps) * kStepCells;
+    // Sum of the importance of all tiles before tile u (u = T gives F_tot):
+    // the run's base plus the tile's prefix inside its run, never above the
+    // next run's base.  The same for both neighbours of a tile boundary, and
+    // the offsets never decrease.
+    auto offset = [&](int u, double prefix) -> double {
+        if (degenerate) return u >= T ? (double)n : (double)(u * tile_cells);
+        if (u >= T) return total;
+        const int r = u / tpr - r_lo;
+        const double lo = base[r], hi = base[r + 1];
+        return fmin(fmax(lo + prefix, lo), hi);
+    };
+    const float X0 = (float)(offset(t, lp) * scale), X1 = (float)(offset(t + 1, lp_next) * scale);
+    gstore<float>(q.ws.x0, t, X0);
+    const bool last_tile = t == T - 1;
+    if (last_tile) gstore<float>(q.ws.x0, T, X1);
+    const int W1 = W - 1;
+    const int b0 = bin_of(X0, W1), b1 = bin_of(X1, W1);
+    for (int b = b0, e = last_tile ? W1 : b1 - 1; b <= e; ++b) gstore<int32_t>(q.ws.bin_t1, b, t);
+    for (int b = t == 0 ? 0 : b0 + 1, e = last_tile ? W1 : b1; b <= e; ++b)
+        gstore<uint32_t>(q.ws.bin_ta, b, (uint32_t)t | (b == b0 + 1 && b <= b1 ? kFirstEdge : 0u));
+    if (b0 == b1) {
+        const int64_t tbase = t * tile_cells;
+        gstore<uint32_t>(q.ws.rec_first, t, (uint32_t)tbase);
+        gstore<uint32_t>(q.ws.rec_last, t, (uint32_t)(min(tbase + tile_cells, n) - 1));
+        gstore<int32_t>(q.ws.head_bin, t, b0);
+        gstore<int32_t>(q.ws.tail_bin, t, b0);
     }
 }
 
@@ -369,22 +332,19 @@ dvl_status launch_build_index(int64_t n_pad, int dtype, const void* field, float
 // ------------------------------------------------------------------ launchers
 
 dvl_status launch_carry_classify(const BatchDev& b, hipStream_t s) {
-    const int64_t blocks = (int64_t)b.n_reqs + (b.k3_units + kClassifyThreads - 1) / kClassifyThreads;
-    hipLaunchKernelGGL(k_carry_classify, dim3((unsigned)blocks), dim3(kClassifyThreads), 0, s, b);
-    DVL_HIP(hipGetLastError());
-    return DVL_OK;
+    return launch_rows<k_carry_classify>(b, (b.max_tiles + kClassifyTiles - 1) / kClassifyTiles, kCarryThreads, 0, s);
 }
 
-dvl_status launch_batch(const BatchDev& b, int dtype, int max_m, int max_req, int n_cu, hipStream_t s,
-                        uint64_t layout, hipEvent_t* ev) {
+dvl_status launch_batch(const BatchDev& b, int dtype, int max_m, int n_cu, hipStream_t s, uint64_t layout,
+                        hipEvent_t* ev) {
     if (layout != kDescriptorLayout) {
         set_error("descriptor layout mismatch between library objects (%llx vs %llx): rebuild the library",
                   (unsigned long long)layout, (unsigned long long)kDescriptorLayout);
         return DVL_E_INVALID;
     }
-    if (dtype == DVL_F16) return launch_s<F16>(b, max_m, max_req, n_cu, s, layout, ev);
-    if (dtype == DVL_BF16) return launch_s<BF16>(b, max_m, max_req, n_cu, s, layout, ev);
-    return launch_s<F32>(b, max_m, max_req, n_cu, s, layout, ev);
+    if (dtype == DVL_F16) return launch_s<F16>(b, max_m, n_cu, s, layout, ev);
+    if (dtype == DVL_BF16) return launch_s<BF16>(b, max_m, n_cu, s, layout, ev);
+    return launch_s<F32>(b, max_m, n_cu, s, layout, ev);
 }
 
 }  // namespace dvl

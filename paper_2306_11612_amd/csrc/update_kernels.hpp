@@ -17,30 +17,31 @@ namespace dvl {
 
 // ------------------------------------------------------------------ unit lookup
 
-// last job whose first importance-pass unit is <= u
-__device__ __forceinline__ int find_job_k1(const BatchDev& b, int64_t u) {
-    int lo = 0, hi = b.n_jobs - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (b.jobs[mid].k1_unit0 <= u) lo = mid; else hi = mid - 1;
+struct Unit {
+    int req;                  // request
+    int local;                // unit of that request
+};
+
+// The request and its unit of importance-pass unit u: its volume's group by
+// one load of 64 groups' first units at a time (a binary search is a chain of
+// dependent loads), then turn by turn among the group's requests.
+__device__ __forceinline__ Unit find_unit(const BatchDev& b, int64_t u) {
+    int g = 0;
+    if (b.n_groups > 1) {
+        for (int base = 0; base < b.n_groups; base += kWave) {
+            const int i = base + lane_id();
+            const uint64_t below = __ballot(i < b.n_groups && gload<int64_t>(&b.groups[min(i, b.n_groups - 1)].unit0, 0) <= u);
+            g = base + (int)__popcll(below) - 1;
+            if (below != ~0ull) break;
+        }
+        g = uni(g);
     }
-    return lo;
-}
-__device__ __forceinline__ int find_req_k3(const BatchDev& b, int64_t u) {
-    int lo = 0, hi = b.n_reqs - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (b.reqs[mid].k3_unit0 <= u) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-__device__ __forceinline__ int find_req_k4(const BatchDev& b, int64_t u) {
-    int lo = 0, hi = b.n_reqs - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (b.reqs[mid].k4_unit0 <= u) lo = mid; else hi = mid - 1;
-    }
-    return lo;
+    const GroupDev& gd = b.groups[g];
+    const uint32_t l = (uint32_t)(u - gd.unit0), n_req = (uint32_t)gd.n_req;
+    Unit r;
+    r.req = gd.req0 + (int)(n_req > 1 ? l % n_req : 0u);
+    r.local = (int)(n_req > 1 ? l / n_req : l);
+    return r;
 }
 
 // ------------------------------------------------------------------ per-cell math
@@ -72,16 +73,45 @@ __device__ __forceinline__ int tf_entry(float x, float s, float b, float nmax) {
     return (int)__builtin_amdgcn_fmed3f(fmaf(x, s, b), 0.0f, nmax);
 }
 
+// A request's quantisers and table offsets: in scalar registers for up to 8
+// fields (a load inside a streaming loop would be the youngest in flight, and
+// waiting for it would drain the prefetched steps), in the descriptor beyond.
+template <int MT, bool REGS = (MT <= 8)>
+struct Quant {
+    float s[MT], b[MT], nmax[MT];
+    int off[MT];
+    __device__ __forceinline__ void load(const ReqDev& q) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            s[m] = uni(q.s[m]);
+            b[m] = uni(q.b[m]);
+            nmax[m] = uni(q.nmax[m]);
+            off[m] = uni(q.tf_off[m]);
+        }
+    }
+};
+template <int MT>
+struct Quant<MT, false> {
+    const float *s, *b, *nmax;
+    const int* off;
+    __device__ __forceinline__ void load(const ReqDev& q) {
+        s = q.s;
+        b = q.b;
+        nmax = q.nmax;
+        off = q.tf_off;
+    }
+};
+
 // Eq. 1: V = max_m alpha_m(x_m) - min_m alpha_m(x_m); `tf` is the request's block
 template <int MT>
 __device__ __forceinline__ float variation(const float (&x)[MT], int M, const float* __restrict__ tf,
-                                           const ReqDev& q) {
+                                           const Quant<MT>& q) {
     float amax = -INFINITY, amin = INFINITY;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         if (m < M) {
             const int e = tf_entry(x[m], q.s[m], q.b[m], q.nmax[m]);
-            const float al = tf[q.tf_off[m] + e];
+            const float al = tf[q.off[m] + e];
             amax = fmaxf(amax, al);
             amin = fminf(amin, al);
         }
@@ -105,8 +135,6 @@ __device__ __forceinline__ float importance_from_v(float v, uint32_t L, const Im
     return f;
 }
 
-// Field count of a job: the variants MT = 1, 2, 4, 8 run batches whose jobs
-// all have exactly MT fields (a compile-time count); MT = 16 reads it per job.
 // Eq. 3 for P = 1 with the minimum importance on f (the paper's setting):
 // the same operations as importance_from_v takes for it
 __device__ __forceinline__ float importance_p1(float v, uint32_t L, const ImpCtx& c) {
@@ -115,12 +143,15 @@ __device__ __forceinline__ float importance_p1(float v, uint32_t L, const ImpCtx
     return fmaxf(ldexpf(r, e), c.fmin);
 }
 
+// Field count of a volume: the variants MT = 1, 2, 4, 8 run batches whose
+// volumes all have exactly MT fields (a compile-time count); MT = 16 reads it
+// per volume.
 template <int MT>
 __device__ __forceinline__ int fields_of(int M) {
     return MT <= 8 ? MT : M;
 }
 
-// A wave's streams over one run of a job: scalar base pointers advanced to
+// A wave's streams over one run of a volume: scalar base pointers advanced to
 // the run's first cell, so every load is a scalar base plus a 32-bit lane
 // offset (a run holds at most 1/64 of a volume, well below 2^32 bytes), and
 // the level codes of the run's steps.
@@ -156,7 +187,7 @@ struct StepData {
     static constexpr uint32_t kQuadBytes = Quad<S>::kBytes;
     Quad<S> q[MT];
     LaneLevels lv;
-    __device__ static const void* source(const JobDev& j, int m) { return j.fields[m]; }
+    __device__ static const void* source(const VolDev& v, int m) { return v.fields[m]; }
     // step: index from the run's first step; code: its level code
     __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step, uint32_t code) {
         const uint32_t qd = (uint32_t)(step * kWave + lane_id());
@@ -174,7 +205,7 @@ struct StepIdx {
     static constexpr uint32_t kQuadBytes = 4;
     uint32_t e[MT];
     LaneLevels lv;
-    __device__ static const void* source(const JobDev& j, int m) { return j.idx[m]; }
+    __device__ static const void* source(const VolDev& v, int m) { return v.idx[m]; }
     __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step, uint32_t code) {
         const uint32_t qd = (uint32_t)(step * kWave + lane_id());
 #pragma unroll
@@ -196,22 +227,22 @@ struct StepF {
 };
 
 template <int MT, typename D>
-__device__ __forceinline__ RunView<MT> run_view(const JobDev& j, int M, int64_t c_begin) {
+__device__ __forceinline__ RunView<MT> run_view(const VolDev& vol, int M, int64_t c_begin) {
     RunView<MT> v;
     const int64_t quad0 = c_begin >> 2;
 #pragma unroll
     for (int m = 0; m < MT; ++m)
-        v.base[m] = m < M ? uni(reinterpret_cast<const char*>(D::source(j, m))) + quad0 * D::kQuadBytes : nullptr;
-    v.lev = uni(reinterpret_cast<const char*>(j.level)) + quad0 * 4;
-    v.lcode = uni(j.lcode) + (c_begin >> 8);
+        v.base[m] = m < M ? uni(reinterpret_cast<const char*>(D::source(vol, m))) + quad0 * D::kQuadBytes : nullptr;
+    v.lev = uni(reinterpret_cast<const char*>(vol.level)) + quad0 * 4;
+    v.lcode = uni(vol.lcode) + (c_begin >> 8);
     return v;
 }
 
-// V of cell k of this lane for request q, from values or from cached
-// entries; off[m]: start of field m's table in `tf` (the request's block)
+// V of cell k of this lane, from values or from cached entries; tf: the
+// request's tables in LDS (values: as uploaded; entries: table m at
+// m * kIdxTable)
 template <int MT, typename S>
-__device__ __forceinline__ float cell_v(const StepData<MT, S>& d, int k, int M, const float* lds0, const float* tf,
-                                        const ReqDev& q, const int (&off)[MT]) {
+__device__ __forceinline__ float cell_v(const StepData<MT, S>& d, int k, int M, const float* tf, const Quant<MT>& q) {
     float xk[MT];
 #pragma unroll
     for (int m = 0; m < MT; ++m) xk[m] = m < M ? d.q[m].get(k) : 0.0f;
@@ -244,41 +275,23 @@ __device__ __forceinline__ uint32_t entry_x4(uint32_t w, int k) {
 
 typedef __attribute__((address_space(3))) const float lds_f32;
 
-// lds0: the kernel's dynamic LDS array, which starts at LDS address 0 (the
-// kernels that take this path have no static LDS; their launcher checks), so
-// an entry's LDS address is its byte offset in the table plus the table's
-// compile-time offset, and the table offset lands in the instruction's
-// immediate.
+// The tables start at LDS address 0 (the kernels that take this path have no
+// static LDS; their launcher checks), so an entry's LDS address is its byte
+// offset in the table plus the table's compile-time offset, which lands in the
+// instruction's immediate.
 template <int MT>
-__device__ __forceinline__ float cell_v(const StepIdx<MT>& d, int k, int M, const float* lds0, const float* tf,
-                                        const ReqDev& q, const int (&off)[MT]) {
-    const uint32_t tb = (uint32_t)(tf - lds0) * (uint32_t)sizeof(float);
+__device__ __forceinline__ float cell_v(const StepIdx<MT>& d, int k, int M, const float* tf, const Quant<MT>& q) {
     float amax = -INFINITY, amin = INFINITY;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         if (m < M) {
-            const uint32_t a = entry_x4(d.e[m], k) + tb + (uint32_t)(m * kIdxTable * sizeof(float));
+            const uint32_t a = entry_x4(d.e[m], k) + (uint32_t)(m * kIdxTable * sizeof(float));
             const float al = *reinterpret_cast<lds_f32*>((uintptr_t)a);
             amax = fmaxf(amax, al);
             amin = fminf(amin, al);
         }
     }
     return amax - amin;
-}
-
-// the start of request q's tables in LDS for step type D
-template <int MT, typename D> struct TableBase {
-    __device__ static int of(int q, int toff) { return toff; }
-};
-template <int MT> struct TableBase<MT, StepIdx<MT>> {
-    __device__ static int of(int q, int toff) { return q * MT * kIdxTable; }
-};
-
-// a request's table offsets, in scalar registers
-template <int MT>
-__device__ __forceinline__ void table_offsets(const ReqDev& q, int M, int (&off)[MT]) {
-#pragma unroll
-    for (int m = 0; m < MT; ++m) off[m] = m < M ? uni(q.tf_off[m]) : 0;
 }
 
 // How many steps one loop iteration loads ahead: one 4-vector per field is
@@ -321,30 +334,69 @@ __device__ __forceinline__ StepCodes<G> load_codes(const uint32_t* lcode, int st
     return r;
 }
 
+// ------------------------------------------------------------------ tables
+
+// n LDS floats dst[i] = value(i), i < n, by the whole workgroup of kThreads:
+// each thread issues the loads of eight of its elements before it stores any,
+// so a round costs one memory latency (a load-store loop waits for each load
+// alone)
+template <int kThreads, typename F>
+__device__ __forceinline__ void stage_lds(float* dst, int n, F value) {
+    const int tid = thread_x();
+    for (int i0 = tid; i0 < n; i0 += 8 * kThreads) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = i0 + k * kThreads < n ? value(i0 + k * kThreads) : 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (i0 + k * kThreads < n) dst[i0 + k * kThreads] = v[k];
+    }
+}
+
+// The request's tables into LDS, for the importance pass (kUpdThreads = one
+// thread per entry of a kIdxTable table).  Requests that read values keep the
+// block as uploaded; requests that read cached entries (tables of <= 256
+// entries) place table m at m * kIdxTable floats, so that every lookup address
+// is the entry times 4 plus a compile-time offset.  Two dependent rounds of
+// loads in all: the tables' places, then every table at once.
+template <int MT, bool IDX>
+__device__ __forceinline__ void load_tables(const ReqDev& q, int M, float* tf_lds) {
+    if constexpr (IDX) {
+        static_assert(kUpdThreads == kIdxTable, "a thread per entry");
+        const float* tf = uni(q.tf);
+        const int e = thread_x();
+        float v[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            v[m] = 0.0f;
+            if (m < M && e <= (int)uni(q.nmax[m])) v[m] = gload<float>(tf, uni(q.tf_off[m]) + e);
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+            if (m < M) tf_lds[m * kIdxTable + e] = v[m];
+    } else {
+        const float* tf = uni(q.tf);
+        stage_lds<kUpdThreads>(tf_lds, uni(q.tf_total), [&](int i) { return gload<float>(tf, i); });
+    }
+}
+
 // ------------------------------------------------------------------ K0
 
-template <int MT, int KR, typename D>
-__device__ __forceinline__ void vmax_run(const BatchDev& b, const JobDev& j, int64_t r, const float* tf_lds) {
+template <int MT, typename D>
+__device__ __forceinline__ void vmax_run(const ReqDev& q, int64_t r, const float* tf_lds) {
     constexpr int G = Group<D>::n;
     const int lane = lane_id();
-    const int M = uni(fields_of<MT>(j.M));
-    const int64_t n = uni(j.n);
-    const int64_t tile_cells = (int64_t)uni(j.tile_steps) * kStepCells;
-    const int64_t c_begin = r * uni(j.tiles_per_run) * tile_cells;
-    const int64_t c_end = min(n, (r + 1) * uni(j.tiles_per_run) * tile_cells);
+    const VolDev& vol = q.v;
+    const int M = uni(fields_of<MT>(vol.M));
+    const int64_t n = uni(vol.n);
+    const int64_t run_cells = (int64_t)uni(vol.tile_steps) * kStepCells * uni(vol.tiles_per_run);
+    const int64_t c_begin = r * run_cells;
+    const int64_t c_end = min(n, c_begin + run_cells);
     const int nsteps = (int)((c_end - c_begin + kStepCells - 1) / kStepCells);
-    const ReqDev* rq = b.reqs + uni(j.req0);
-    float vmax[KR];
-    int toff[KR], off[KR][MT];
-#pragma unroll
-    for (int q = 0; q < KR; ++q) {
-        vmax[q] = 0.0f;
-        if (q < j.n_req) {
-            toff[q] = uni(rq[q].tf_job_off);
-            table_offsets<MT>(rq[q], M, off[q]);
-        }
-    }
-    const RunView<MT> view = run_view<MT, D>(j, M, c_begin);
+    Quant<MT> qn;
+    qn.load(q);
+    float vmax = 0.0f;
+    const RunView<MT> view = run_view<MT, D>(vol, M, c_begin);
     for (int s = 0; s < nsteps; s += G) {
         D d[G];
 #pragma unroll
@@ -354,89 +406,49 @@ __device__ __forceinline__ void vmax_run(const BatchDev& b, const JobDev& j, int
             if (s + g >= nsteps) break;
             const int64_t quad = ((c_begin + (int64_t)(s + g) * kStepCells) >> 2) + lane;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if ((quad << 2) + k >= n) continue;
-#pragma unroll
-                for (int q = 0; q < KR; ++q)
-                    if (q < j.n_req && rq[q].vmax_exact)
-                        vmax[q] = fmaxf(vmax[q], cell_v<MT>(d[g], k, M, tf_lds, tf_lds + TableBase<MT, D>::of(q, toff[q]), rq[q], off[q]));
-            }
+            for (int k = 0; k < 4; ++k)
+                if ((quad << 2) + k < n) vmax = fmaxf(vmax, cell_v<MT>(d[g], k, M, tf_lds, qn));
         }
     }
-#pragma unroll
-    for (int q = 0; q < KR; ++q) {
-        if (q < j.n_req && rq[q].vmax_exact) {
-            const float v = wave_max_f(vmax[q]);
-            if (lane == 0 && v > 0.0f) atomicMax(reinterpret_cast<unsigned int*>(rq[q].vmax_dev), __float_as_uint(v));
-        }
-    }
+    const float v = wave_highest_f(vmax);
+    if (lane == 0 && v > 0.0f) atomicMax(reinterpret_cast<unsigned int*>(q.vmax_dev), __float_as_uint(v));
 }
 
-// Jobs that read values keep the requests' blocks as uploaded; jobs that read
-// cached entries (tables of <= 256 entries) place table (request q, field m)
-// at (q * MT + m) * 256 floats, so that every lookup address is the entry
-// times 4 plus a compile-time offset.
-// n LDS floats dst[i] = value(i), i < n, by the whole workgroup: each thread
-// issues the loads of four of its elements before it stores any, so a round
-// costs one memory latency instead of four (a load-store loop waits for each
-// load alone)
-template <typename F>
-__device__ __forceinline__ void stage_lds(float* dst, int n, F value) {
-    const int tid = thread_x(), nthr = block_dim_x();
-    for (int i0 = tid; i0 < n; i0 += 4 * nthr) {
-        float v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = i0 + k * nthr < n ? value(i0 + k * nthr) : 0.0f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (i0 + k * nthr < n) dst[i0 + k * nthr] = v[k];
-    }
-}
-
-template <int MT, bool IDX>
-__device__ __forceinline__ void load_job_tables(const BatchDev& b, const JobDev& j, int ji, int& loaded,
-                                                float* tf_lds) {
-    if (ji != loaded) {
-        __syncthreads();
-        if constexpr (IDX) {
-            const int M = uni(fields_of<MT>(j.M)), nq = uni(j.n_req);
-            const ReqDev* rq = b.reqs + uni(j.req0);
-            stage_lds(tf_lds, nq * MT * kIdxTable, [&](int i) {
-                const int q = i / (MT * kIdxTable), m = (i / kIdxTable) % MT, e = i % kIdxTable;
-                float v = 0.0f;
-                if (m < M && e < (int)rq[q].nmax[m] + 1) v = gload<float>(rq[q].tf, rq[q].tf_off[m] + e);
-                return v;
-            });
-        } else {
-            const float* src = j.tf_all;
-            stage_lds(tf_lds, j.tf_total_all, [&](int i) { return gload<float>(src, i); });
-        }
-        __syncthreads();
-        loaded = ji;
-    }
-}
-
-// IDX: this instance serves the jobs that read cached entries (1) or values (0)
-template <int MT, typename S, int KR, int IDX>
+// IDX: this instance serves the requests that read cached entries (1) or values (0)
+template <int MT, typename S, int IDX>
 __global__ __launch_bounds__(kUpdThreads) void k_vmax_exact(BatchDev b) {
     extern __shared__ float tf_lds[];
     const int wv = uni((int)(thread_x() / kWave));
     int loaded = -1;
     for (int64_t u = block_x(); u < b.k1_units; u += grid_dim_x()) {
-        const int ji = find_job_k1(b, u);
-        const JobDev& j = b.jobs[ji];
-        if ((j.idx[0] != nullptr) != (IDX != 0)) continue;
-        load_job_tables<MT, IDX != 0>(b, j, ji, loaded, tf_lds);
-        const int64_t r = uni((u - j.k1_unit0) * (kUpdThreads / kWave) + wv);
-        if (r >= j.n_runs) continue;
+        const Unit un = find_unit(b, u);
+        const ReqDev& q = b.reqs[un.req];
+        if (uni(q.entries) != IDX || !uni(q.vmax_exact)) continue;
+        if (un.req != loaded) {
+            if (loaded >= 0) __syncthreads();
+            load_tables<MT, IDX != 0>(q, uni(fields_of<MT>(q.v.M)), tf_lds);
+            __syncthreads();
+            loaded = un.req;
+        }
+        // units of the importance pass: four runs, or one (a tile) when its waves share it
+        const int r = uni(q.v.split) ? un.local : un.local * kUpdWaves + wv;
+        if (r >= uni(q.v.n_runs) || (uni(q.v.split) && wv != 0)) continue;
         if constexpr (IDX != 0)
-            vmax_run<MT, KR, StepIdx<MT>>(b, j, r, tf_lds);
+            vmax_run<MT, StepIdx<MT>>(q, r, tf_lds);
         else
-            vmax_run<MT, KR, StepData<MT, S>>(b, j, r, tf_lds);
+            vmax_run<MT, StepData<MT, S>>(q, r, tf_lds);
     }
 }
 
 // ------------------------------------------------------------------ K1
+
+// Floats of LDS the tables take in the importance pass (the partial sums of a
+// shared tile follow, 8-byte aligned).
+template <bool IDX>
+__host__ __device__ __forceinline__ int sums_lds(const BatchDev& b) {
+    return IDX ? b.max_fields * kIdxTable : (b.max_req_tf + 1) & ~1;
+}
+
 
 // Error-free sum of two floats: s + e == a + b exactly (Knuth's TwoSum).
 __device__ __forceinline__ void two_sum_f(float a, float b, float& s, float& e) {
@@ -487,7 +499,7 @@ struct ModeSum {
     // its two operands, so every lane computes the same bits)
     __device__ void wave_total(int mode) {
         if (mode == DVL_SCAN_FP64) {
-            d = wave_sum_d(d);
+            d = wave_total_d(d);
             return;
         }
         for (int o = 32; o > 0; o >>= 1) {
@@ -500,109 +512,32 @@ struct ModeSum {
     }
 };
 
-// One wave's run r of job j: stream its cells once (values, or cached
-// entries), evaluate f for every request of the job, sum f over each tile
-// (per lane, 4 cells per step as (f0 + f1) + (f2 + f3) in fp32, accumulated
-// over the tile's steps and then over the wave in the request's scan
-// arithmetic: fp64, compensated fp32 or plain fp32) and record, per request
-// and tile, the non-decreasing sum of the earlier tiles of the run.  Both
-// sources give the same f bit for bit.
-template <int MT, int KR, typename D, bool P1>
-__device__ __forceinline__ void tile_sums_run(const BatchDev& b, const JobDev& j, int64_t r, const float* tf_lds) {
+// One wave's part of the importance pass: the steps [s_begin, s_end) of the
+// tiles [t_begin, t_end) (all of them, unless the workgroup's waves share one
+// tile).  Stream the cells once (values, or cached entries), evaluate f, sum f
+// over each tile (per lane, 4 cells per step as (f0 + f1) + (f2 + f3) in fp32,
+// accumulated over the tile's steps and then over the wave in the request's
+// scan arithmetic: fp64, compensated fp32 or plain fp32) and record, per tile,
+// the non-decreasing sum of the earlier tiles of the run.  Both sources give
+// the same f bit for bit.  `tables()` puts the tables into LDS after the first
+// loads are on their way; it is called exactly once, by every wave (also one
+// without work, nsteps <= 0).  The result: the sum of the last tile (split)
+// or the run's total (else).
+template <int MT, typename D, bool P1, typename Tables>
+__device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, int64_t c_begin, int nsteps, bool split,
+                                                const float* tf_lds, Tables tables) {
     constexpr int G = Group<D>::n;
-    const int lane = lane_id();
-    const int M = uni(fields_of<MT>(j.M));
-    const int nreq = KR == 1 ? 1 : uni(j.n_req);
-    const ReqDev* rq = b.reqs + uni(j.req0);
-    const int tile_steps = uni(j.tile_steps);
-    const int64_t n = uni(j.n);
-    const int64_t tile_cells = (int64_t)tile_steps * kStepCells;
-    const int64_t t_begin = r * uni(j.tiles_per_run);
-    const int64_t t_end = min(uni(j.n_tiles), t_begin + uni(j.tiles_per_run));
-    const int64_t c_begin = t_begin * tile_cells;
-    const int64_t c_end = min(n, t_end * tile_cells);
-    const int nsteps = (int)((c_end - c_begin + kStepCells - 1) / kStepCells);
-
-    ImpCtx ctx[KR];
-    ModeSum run[KR], tacc[KR];
-    double prev[KR];
-    int toff[KR], off[KR][MT], mode[KR];
-    float* fst[KR];                   // where f of every cell is kept for the projection, or NULL
-    double* lpre[KR];                 // the requests' in-run tile prefixes
-    // every descriptor field the loop reads is held in registers: a load
-    // inside the loop would be the youngest in flight, and waiting for it
-    // would drain the prefetched steps
-#pragma unroll
-    for (int q = 0; q < KR; ++q) {
-        fst[q] = nullptr;
-        lpre[q] = nullptr;
-        mode[q] = DVL_SCAN_FP64;
-        if (q < nreq) {
-            ctx[q] = make_ctx(rq[q]);
-            toff[q] = uni(rq[q].tf_job_off);
-            table_offsets<MT>(rq[q], M, off[q]);
-            fst[q] = uni(rq[q].ws.fstore);
-            lpre[q] = uni(rq[q].ws.local_prefix);
-            mode[q] = uni(rq[q].scan_mode);
-        }
-        run[q].init();
-        prev[q] = 0.0;
-        tacc[q].init();
+    if (nsteps <= 0) {
+        tables();
+        return 0.0;
     }
-    int64_t t = t_begin;
-    int in_tile = 0;
-    const RunView<MT> view = run_view<MT, D>(j, M, c_begin);
+    const int lane = lane_id();
+    const VolDev& vol = q.v;
+    const int M = uni(fields_of<MT>(vol.M));
+    const int tile_steps = uni(vol.tile_steps);
+    const int64_t n = uni(vol.n);
     const int last_group = (nsteps - 1) / G * G;
-
-    // the steps s .. s + G - 1 of the run, loaded into `cur`
-    auto process = [&](const D (&cur)[G], int s) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (s + g >= nsteps) break;
-            const int64_t quad = ((c_begin + (int64_t)(s + g) * kStepCells) >> 2) + lane;
-            const bool full = c_begin + (int64_t)(s + g + 1) * kStepCells <= n;   // no cell past the end
-#pragma unroll
-            for (int q = 0; q < KR; ++q) {
-                if (q < nreq) {
-                    float f[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const float v = cell_v<MT>(cur[g], k, M, tf_lds, tf_lds + TableBase<MT, D>::of(q, toff[q]), rq[q], off[q]);
-                        const uint32_t L = cur[g].lv.get(k);
-                        f[k] = P1 ? importance_p1(v, L, ctx[q]) : importance_from_v(v, L, ctx[q]);
-                    }
-                    if (!full) {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) f[k] = ((quad << 2) + k < n) ? f[k] : 0.0f;
-                    }
-                    if (fst[q]) {
-                        f32x4 fv;
-                        fv.x = f[0];
-                        fv.y = f[1];
-                        fv.z = f[2];
-                        fv.w = f[3];
-                        gstore<f32x4>(fst[q], quad, fv);
-                    }
-                    tacc[q].add_f(mode[q], (f[0] + f[1]) + (f[2] + f[3]));
-                }
-            }
-            if (++in_tile == tile_steps || s + g + 1 == nsteps) {
-#pragma unroll
-                for (int q = 0; q < KR; ++q) {
-                    if (q < nreq) {
-                        tacc[q].wave_total(mode[q]);
-                        prev[q] = fmax(prev[q], run[q].value(mode[q]));
-                        if (lane == 0) gstore<double>(lpre[q], t, prev[q]);
-                        run[q].add(mode[q], tacc[q]);
-                        tacc[q].init();
-                    }
-                }
-                ++t;
-                in_tile = 0;
-            }
-        }
-    };
-
+    const RunView<MT> view = run_view<MT, D>(vol, M, c_begin);
     // Two groups in flight, in buffers A and B that take turns: a buffer is
     // loaded again (unconditionally; past the run's end the last step is
     // reloaded) right after its group was used, so no loaded value is ever
@@ -621,6 +556,62 @@ __device__ __forceinline__ void tile_sums_run(const BatchDev& b, const JobDev& j
 #pragma unroll
         for (int g = 0; g < G; ++g) B[g].load(view, M, min(G + g, nsteps - 1), c1.c[g]);
     }
+    tables();
+
+    Quant<MT> qn;
+    qn.load(q);
+    const ImpCtx ctx = make_ctx(q);
+    float* const fst = uni(q.ws.fstore);      // where f of every cell is kept for the projection, or NULL
+    double* const lpre = uni(q.ws.local_prefix);
+    const int mode = uni(q.scan_mode);
+    ModeSum run, tacc;
+    run.init();
+    tacc.init();
+    double prev = 0.0;
+    int64_t t = t_begin;
+    int in_tile = 0;
+
+    // the steps s .. s + G - 1 of the run, loaded into `cur`
+    auto process = [&](const D (&cur)[G], int s) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (s + g >= nsteps) break;
+            const int64_t quad = ((c_begin + (int64_t)(s + g) * kStepCells) >> 2) + lane;
+            const bool full = c_begin + (int64_t)(s + g + 1) * kStepCells <= n;   // no cell past the end
+            float f[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float v = cell_v<MT>(cur[g], k, M, tf_lds, qn);
+                const uint32_t L = cur[g].lv.get(k);
+                f[k] = P1 ? importance_p1(v, L, ctx) : importance_from_v(v, L, ctx);
+            }
+            if (!full) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) f[k] = ((quad << 2) + k < n) ? f[k] : 0.0f;
+            }
+            if (fst) {
+                f32x4 fv;
+                fv.x = f[0];
+                fv.y = f[1];
+                fv.z = f[2];
+                fv.w = f[3];
+                gstore<f32x4>(fst, quad, fv);
+            }
+            tacc.add_f(mode, (f[0] + f[1]) + (f[2] + f[3]));
+            if (++in_tile == tile_steps || s + g + 1 == nsteps) {
+                tacc.wave_total(mode);
+                if (!split) {
+                    prev = fmax(prev, run.value(mode));
+                    if (lane == 0) gstore<double>(lpre, t, prev);
+                }
+                run.add(mode, tacc);
+                tacc.init();
+                ++t;
+                in_tile = 0;
+            }
+        }
+    };
+
     for (int s = 0; s < nsteps; s += 2 * G) {
         process(A, s);
         {
@@ -638,118 +629,92 @@ __device__ __forceinline__ void tile_sums_run(const BatchDev& b, const JobDev& j
             cB = c3;
         }
     }
-#pragma unroll
-    for (int q = 0; q < KR; ++q)
-        if (q < nreq && lane == 0) gstore<double>(rq[q].ws.run_total, r, fmax(prev[q], run[q].value(mode[q])));
+    return split ? run.value(mode) : fmax(prev, run.value(mode));
 }
 
-// A workgroup takes 4 consecutive runs of one job; wave r of the job owns the
-// tiles [r k, (r + 1) k).
-template <int MT, typename S, int KR, int IDX>
-#ifdef DVL_K1_WAVES_PER_EU
-#define DVL_K1_OCCUPANCY __attribute__((amdgpu_waves_per_eu(DVL_K1_WAVES_PER_EU)))
-#else
-#define DVL_K1_OCCUPANCY
-#endif
-__global__ __launch_bounds__(kUpdThreads) DVL_K1_OCCUPANCY void k_tile_sums(BatchDev b) {
+// A workgroup takes 4 consecutive runs of a request, a wave each; run r owns
+// the tiles [r k, (r + 1) k).  When the volume is so small that a run is one
+// tile and the tiles do not fill the chip with workgroups (VolDev::split), the
+// four waves share one tile instead, a quarter of its steps each, and their
+// fp64 sums are added in order (sums of fp32 values over a tile are exact in
+// fp64 unless f spans more than about 2^20, so the split changes no bit
+// then); the other scan arithmetics, whose sums depend on the order, leave
+// the tile to the first wave.
+template <int MT, typename S, int IDX>
+__global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
     extern __shared__ float tf_lds[];
     const int wv = uni((int)(thread_x() / kWave));
     int loaded = -1;
     for (int64_t u = block_x(); u < b.k1_units; u += grid_dim_x()) {
-        const int ji = find_job_k1(b, u);
-        const JobDev& j = b.jobs[ji];
-        if ((j.idx[0] != nullptr) != (IDX != 0)) continue;
-        load_job_tables<MT, IDX != 0>(b, j, ji, loaded, tf_lds);
-        const int64_t r = uni((u - j.k1_unit0) * (kUpdThreads / kWave) + wv);
-        if (r >= j.n_runs) continue;
-        // P = 1 with the importance clamp in every request of the job: no pow
-        bool p1 = true;
-        for (int q = 0; q < (KR == 1 ? 1 : j.n_req); ++q) {
-            const ReqDev& rq = b.reqs[j.req0 + q];
-            p1 = p1 && rq.exp_is_one && rq.clamp_mode == 0;
-        }
-        p1 = uni((int)p1) != 0;
-        if constexpr (IDX != 0) {
-            if (p1)
-                tile_sums_run<MT, KR, StepIdx<MT>, true>(b, j, r, tf_lds);
-            else
-                tile_sums_run<MT, KR, StepIdx<MT>, false>(b, j, r, tf_lds);
+        const Unit un = find_unit(b, u);
+        const ReqDev& q = b.reqs[un.req];
+        if (uni(q.entries) != IDX) continue;
+        const VolDev& vol = q.v;
+        const int tile_steps = uni(vol.tile_steps), tpr = uni(vol.tiles_per_run), n_tiles = uni(vol.n_tiles);
+        const int64_t n = uni(vol.n);
+        const bool split = uni(vol.split) != 0;
+        int t0, s0 = 0;
+        int64_t c_end;
+        if (split) {
+            t0 = un.local;
+            const int part = uni(q.scan_mode) == DVL_SCAN_FP64 ? tile_steps / kUpdWaves : (wv == 0 ? tile_steps : 0);
+            s0 = wv * part;
+            c_end = min(n, ((int64_t)t0 * tile_steps + s0 + part) * kStepCells);
         } else {
-            if (p1)
-                tile_sums_run<MT, KR, StepData<MT, S>, true>(b, j, r, tf_lds);
-            else
-                tile_sums_run<MT, KR, StepData<MT, S>, false>(b, j, r, tf_lds);
+            const int r = un.local * kUpdWaves + wv;
+            t0 = r < uni(vol.n_runs) ? r * tpr : n_tiles;
+            c_end = min(n, (int64_t)min(n_tiles, t0 + tpr) * tile_steps * kStepCells);
+        }
+        const int64_t c_begin = ((int64_t)t0 * tile_steps + s0) * kStepCells;
+        const int nsteps = c_end > c_begin ? (int)((c_end - c_begin + kStepCells - 1) / kStepCells) : 0;
+        auto tables = [&]() {
+            if (un.req == loaded) return;
+            if (loaded >= 0) __syncthreads();   // the other waves are done with the previous tables
+            load_tables<MT, IDX != 0>(q, uni(fields_of<MT>(vol.M)), tf_lds);
+            __syncthreads();
+            loaded = un.req;
+        };
+        using D = typename std::conditional<IDX != 0, StepIdx<MT>, StepData<MT, S>>::type;
+        // P = 1 with the importance clamp: no pow
+        double total;
+        if (uni((int)(q.exp_is_one && q.clamp_mode == 0)))
+            total = tile_sums_run<MT, D, true>(q, t0, c_begin, nsteps, split, tf_lds, tables);
+        else
+            total = tile_sums_run<MT, D, false>(q, t0, c_begin, nsteps, split, tf_lds, tables);
+        if (split) {
+            // a partial sum per wave behind the tables (see sums_lds)
+            double* part = reinterpret_cast<double*>(tf_lds + sums_lds<IDX != 0>(b));
+            if (lane_id() == 0) part[wv] = total;
+            __syncthreads();
+            if (thread_x() == 0) {
+                double sum = part[0];
+                for (int k = 1; k < kUpdWaves; ++k) sum += part[k];
+                gstore<double>(q.ws.local_prefix, t0, 0.0);
+                gstore<double>(q.ws.run_total, t0, fmax(0.0, sum));
+            }
+            __syncthreads();
+        } else if (lane_id() == 0 && nsteps > 0) {
+            gstore<double>(q.ws.run_total, un.local * kUpdWaves + wv, total);
         }
     }
 }
 
-// ------------------------------------------------------------------ K3 helpers
-
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1)
-        v = min(v, (uint32_t)__builtin_amdgcn_ds_bpermute((lane_id() ^ o) << 2, (int)v));
-    return v;
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1)
-        v = max(v, (uint32_t)__builtin_amdgcn_ds_bpermute((lane_id() ^ o) << 2, (int)v));
-    return v;
-}
-// Sum of the importance of all tiles before tile t (t = T gives F_tot): the
-// run's base plus the tile's prefix inside its run, never above the next
-// run's base.  One definition serves both neighbours of every tile boundary,
-// and the offsets never decrease.
-__device__ __forceinline__ double tile_offset(const JobDev& j, const UpdWorkspace& ws, int64_t t,
-                                              bool degenerate) {
-    const int64_t tile_cells = (int64_t)j.tile_steps * kStepCells;
-    if (degenerate) return t >= j.n_tiles ? (double)j.n : (double)(t * tile_cells);
-    if (t >= j.n_tiles) return gload<double>(ws.run_base, j.n_runs);
-    const int64_t r = t / j.tiles_per_run;
-    const double lo = gload<double>(ws.run_base, r), hi = gload<double>(ws.run_base, r + 1);
-    return fmin(fmax(lo + gload<double>(ws.local_prefix, t), lo), hi);
-}
-
 // ------------------------------------------------------------------ K3
 
-constexpr int kBinThreads = 192;  // one workgroup of three waves per queued (request, tile)
+constexpr int kBinThreads = 192;  // one workgroup of three waves per rescanned (request, tile)
 
-// Pixel interval [X0, X1] of tile t of request q, and its first and last bin.
-struct TileSpan {
-    double scale_d;
-    float scale_f, X0, X1;
-    int b0, b1;
-};
-
-__device__ __forceinline__ TileSpan tile_span(const ReqDev& q, const JobDev& j, int64_t t) {
-    TileSpan sp;
-    const bool degenerate = gload<double>(q.ws.scal, 1) != 0.0;
-    sp.scale_d = (double)q.W / gload<double>(q.ws.scal, 0);
-    sp.scale_f = (float)sp.scale_d;
-    sp.X0 = (float)(tile_offset(j, q.ws, t, degenerate) * sp.scale_d);
-    sp.X1 = (float)(tile_offset(j, q.ws, t + 1, degenerate) * sp.scale_d);
-    const int W1 = q.W - 1;
-    sp.b0 = max(0, min((int)floorf(sp.X0), W1));
-    sp.b1 = max(0, min((int)floorf(sp.X1), W1));
-    return sp;
-}
-
-// V of cell k of this lane (request q, tables in the request's block layout)
+// V of cell k of this lane (tables in the request's block layout)
 template <int MT, typename S>
-__device__ __forceinline__ float rescan_v(const StepData<MT, S>& d, int k, int M, const float* tf,
-                                          const ReqDev& q, const int (&off)[MT]) {
-    float xk[MT];
-#pragma unroll
-    for (int m = 0; m < MT; ++m) xk[m] = m < M ? d.q[m].get(k) : 0.0f;
-    return variation<MT>(xk, M, tf, q);
+__device__ __forceinline__ float rescan_v(const StepData<MT, S>& d, int k, int M, const float* tf, const Quant<MT>& q) {
+    return cell_v<MT>(d, k, M, tf, q);
 }
 template <int MT>
-__device__ __forceinline__ float rescan_v(const StepIdx<MT>& d, int k, int M, const float* tf, const ReqDev& q,
-                                          const int (&off)[MT]) {
+__device__ __forceinline__ float rescan_v(const StepIdx<MT>& d, int k, int M, const float* tf, const Quant<MT>& q) {
     float amax = -INFINITY, amin = INFINITY;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         if (m < M) {
-            const float al = tf[off[m] + (int)((d.e[m] >> (8 * k)) & 0xFFu)];
+            const float al = tf[q.off[m] + (int)((d.e[m] >> (8 * k)) & 0xFFu)];
             amax = fmaxf(amax, al);
             amin = fminf(amin, al);
         }
@@ -795,39 +760,40 @@ constexpr size_t kStageBytesPerStep = (size_t)kWave * sizeof(f32x4);
 // Phase 1 of the rescan, for the steps s = w, w + kBinWaves, ... of tile t
 // taken by wave w: f of every cell again (from values, cached entries or the
 // stored f, bit for bit as in K1; 1 when the total importance is 0) and the
-// step's monotone prefix, into LDS.
-template <int MT, typename S, typename D>
-__device__ __forceinline__ void rescan_stage(const ReqDev& q, const JobDev& j, int64_t t, const float* tf_lds,
-                                             Stage stage) {
+// step's monotone prefix, into LDS.  `tables()` stages the request's tables
+// after the first loads are on their way (called once by every wave).
+template <int MT, typename S, typename D, typename Tables>
+__device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float* tf_lds, Stage stage, Tables tables) {
     const int lane = lane_id();
     const int w = uni((int)(thread_x() / kWave));
-    const int M = uni(fields_of<MT>(j.M));
-    const int64_t n = uni(j.n);
-    const bool degenerate = uni((int)(gload<double>(q.ws.scal, 1) != 0.0)) != 0;
-    const int tile_steps = uni(j.tile_steps);
-    const int64_t tbase = t * (int64_t)tile_steps * kStepCells;
+    const VolDev& vol = q.v;
+    const int M = uni(fields_of<MT>(vol.M));
+    const int64_t n = uni(vol.n);
+    const int tile_steps = uni(vol.tile_steps);
+    const int64_t tbase = (int64_t)t * tile_steps * kStepCells;
     const int nsteps = (int)((min(tbase + (int64_t)tile_steps * kStepCells, n) - tbase + kStepCells - 1) / kStepCells);
+    constexpr bool kStored = std::is_same<D, StepF<MT>>::value;
     RunView<MT> view;
-    if constexpr (std::is_same<D, StepF<MT>>::value) {
-        view = run_view<MT, StepData<MT, S>>(j, M, tbase);
+    if constexpr (kStored) {
+        view = run_view<MT, StepData<MT, S>>(vol, M, tbase);
         view.base[0] = reinterpret_cast<const char*>(uni(q.ws.fstore)) + tbase * 4;
     } else {
-        view = run_view<MT, D>(j, M, tbase);
+        view = run_view<MT, D>(vol, M, tbase);
     }
-    const ImpCtx c = make_ctx(q);
-    int off[MT];
-    table_offsets<MT>(q, M, off);
-    if (w >= nsteps) return;
+    const double degenerate_d = gload<double>(q.ws.scal, 1);
+    ImpCtx c;
+    Quant<MT> qn;
+    bool degenerate = false;
     auto process = [&](const D& cur, int s) {
         const int64_t quad = ((tbase + (int64_t)s * kStepCells) >> 2) + lane;
         float f[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             float fk = 1.0f;
-            if constexpr (std::is_same<D, StepF<MT>>::value) {
+            if constexpr (kStored) {
                 if (!degenerate) fk = k == 0 ? cur.fv.x : (k == 1 ? cur.fv.y : (k == 2 ? cur.fv.z : cur.fv.w));
             } else {
-                if (!degenerate) fk = importance_from_v(rescan_v<MT>(cur, k, M, tf_lds, q, off), cur.lv.get(k), c);
+                if (!degenerate) fk = importance_from_v(rescan_v<MT>(cur, k, M, tf_lds, qn), cur.lv.get(k), c);
             }
             f[k] = ((quad << 2) + k < n) ? fk : 0.0f;
         }
@@ -843,21 +809,38 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, const JobDev& j, i
         sp.B = B;
         stage.put(s, sp);
     };
+    auto begin = [&]() {
+        tables();
+        degenerate = uni((int)(degenerate_d != 0.0)) != 0;
+        if constexpr (!kStored) {
+            c = make_ctx(q);
+            qn.load(q);
+        }
+    };
+    if (w >= nsteps) {
+        tables();
+        return;
+    }
     if constexpr (!std::is_same<D, StepData<MT, S>>::value) {
         // cached entries or stored f (a few registers per step): the level
         // codes of all of this wave's steps first (uniform: scalar registers;
-        // a lane's level load address depends on its code), then the steps
-        // two at a time, loaded together and then processed (two keep the
-        // rescan within 64 VGPRs, eight waves per SIMD)
-        constexpr int kAhead = 2;
+        // a lane's level load address depends on its code), then the steps,
+        // all six of a 16-step tile's wave in flight at once for up to 4
+        // fields (one memory latency instead of three; eight workgroups of
+        // three waves a compute unit leave 80 VGPRs to each)
+        constexpr int kAhead = kStored || MT <= 4 ? 6 : 3;
         constexpr int kMaxPer = (kMaxTileSteps + kBinWaves - 1) / kBinWaves;
         const int cnt = (nsteps - w + kBinWaves - 1) / kBinWaves;
         uint32_t code[kMaxPer];
 #pragma unroll
         for (int k = 0; k < kMaxPer; ++k) {
             code[k] = 0u;
-            if constexpr (std::is_same<D, StepIdx<MT>>::value)
-                if (k < cnt) code[k] = uni(gload<uint32_t>(view.lcode, w + k * kBinWaves));
+            if constexpr (!kStored)
+                if (k < cnt) code[k] = gload<uint32_t>(view.lcode, w + k * kBinWaves);
+        }
+        if constexpr (!kStored) {
+#pragma unroll
+            for (int k = 0; k < kMaxPer; ++k) code[k] = uni(code[k]);
         }
 #pragma unroll
         for (int k0 = 0; k0 < kMaxPer; k0 += kAhead) {
@@ -865,7 +848,8 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, const JobDev& j, i
             D buf[kAhead];
 #pragma unroll
             for (int k = 0; k < kAhead; ++k)
-                if (k0 + k < cnt) buf[k].load(view, M, w + (k0 + k) * kBinWaves, code[k0 + k]);
+                if (k0 + k < cnt) buf[k].load(view, M, w + (k0 + k) * kBinWaves, code[k0 + k < kMaxPer ? k0 + k : 0]);
+            if (k0 == 0) begin();
 #pragma unroll
             for (int k = 0; k < kAhead; ++k)
                 if (k0 + k < cnt) process(buf[k], w + (k0 + k) * kBinWaves);
@@ -874,9 +858,11 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, const JobDev& j, i
         // values: two steps in flight in buffers that take turns (no loaded
         // register is copied, so each wait is for the older step only)
         D A, B;
-        A.load(view, M, w, gload<uint32_t>(view.lcode, w));
         const int s1 = min(w + kBinWaves, nsteps - 1);
-        B.load(view, M, s1, gload<uint32_t>(view.lcode, s1));
+        const uint32_t code0 = gload<uint32_t>(view.lcode, w), code1 = gload<uint32_t>(view.lcode, s1);
+        A.load(view, M, w, code0);
+        B.load(view, M, s1, code1);
+        begin();
         for (int s = w; s < nsteps; s += 2 * kBinWaves) {
             process(A, s);
             const int s2 = min(s + 2 * kBinWaves, nsteps - 1);
@@ -919,15 +905,14 @@ __device__ __forceinline__ void bin_ends(const ReqDev& q, int64_t t, const TileB
         gstore<uint32_t>(b == tb.Bh ? q.ws.rec_last : q.last_cell, b == tb.Bh ? t : (int64_t)b, cell);
 }
 
-__device__ __forceinline__ void rescan_bins(const ReqDev& q, const JobDev& j, int64_t t, const Stage stage) {
+__device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0, float X1, float scale_f,
+                                            const Stage stage) {
     const int lane = lane_id();
     const int w = uni((int)(thread_x() / kWave));
-    const int64_t T = uni(j.n_tiles);
-    const int64_t n = uni(j.n);
-    const TileSpan sp = tile_span(q, j, t);
-    const float scale_f = uni(sp.scale_f), X0 = uni(sp.X0), X1 = uni(sp.X1);
+    const int64_t T = uni(q.v.n_tiles);
+    const int64_t n = uni(q.v.n);
     const int W1 = uni(q.W) - 1;
-    const int tile_steps = uni(j.tile_steps);
+    const int tile_steps = uni(q.v.tile_steps);
     const int64_t tile_cells = (int64_t)tile_steps * kStepCells;
     const int64_t tbase = t * tile_cells;
     const int64_t tend = min(tbase + tile_cells, n);
@@ -1030,56 +1015,70 @@ __device__ __forceinline__ void rescan_bins(const ReqDev& q, const JobDev& j, in
     }
 }
 
-// K3b: the queued tiles, one workgroup each.  Its waves stage the prefixes
-// of the tile's steps in LDS together (phase 1; the loads of all waves in
-// flight), then settle the bins of the steps that hold a bin edge (phase 2).
+// The first and last bin of a tile's pixel interval.
+__device__ __forceinline__ int bin_of(float x, int W1) { return max(0, min((int)floorf(x), W1)); }
+
+// K3b: the tiles that hold a bin edge, one workgroup each (grid: x, request
+// y).  With more tiles than bins a workgroup takes a bin edge and its tile,
+// unless an earlier edge of the same tile has it (kFirstEdge); else it takes
+// a tile.  Its waves stage the prefixes of the tile's steps in LDS together
+// (phase 1; the loads of all waves in flight), then settle the bins of the
+// steps that hold an edge (phase 2).
 // IDX: this instance serves the requests whose projection reads values (0),
-// cached entries (1) or the f the importance pass stored (2); each skips the
-// others' tiles.  LDS: the request's tables, then the staged prefixes.
+// cached entries (1) or the f the importance pass stored (2).  LDS: the
+// staged prefixes, then the request's tables (none for stored f).
 template <int MT, typename S, int IDX>
 __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
-    extern __shared__ float tf_lds[];
-    int loaded = -1;
-    const int64_t n_queued = gload<uint32_t>(bd.rescan_count, IDX);
-    const uint64_t* queue = bd.rescan_queue + IDX * bd.k3_units;
-    Stage stage;
-    stage.ex_p = reinterpret_cast<f32x4*>(tf_lds + ((bd.max_req_tf + 3) & ~3));
-
-    for (int64_t i = block_x(); i < n_queued; i += grid_dim_x()) {
-        const int64_t u = uni((int64_t)gload<uint64_t>(queue, i));
-        const int qi = uni(find_req_k3(bd, u));
-        const ReqDev& q = bd.reqs[qi];
-        const JobDev& j = bd.jobs[uni(q.job)];
-        const int64_t t = u - uni(q.k3_unit0);
-        // the tile is rescanned: this request's tables in LDS
-        if (qi != loaded) {
-            const float* src = q.tf;
-            stage_lds(tf_lds, q.tf_total, [&](int k) { return gload<float>(src, k); });
-            loaded = qi;
-        }
-        __syncthreads();
-        if constexpr (IDX == 2)
-            rescan_stage<MT, S, StepF<MT>>(q, j, t, tf_lds, stage);
-        else if constexpr (IDX == 1)
-            rescan_stage<MT, S, StepIdx<MT>>(q, j, t, tf_lds, stage);
-        else
-            rescan_stage<MT, S, StepData<MT, S>>(q, j, t, tf_lds, stage);
-        __syncthreads();
-        rescan_bins(q, j, t, stage);
-        __syncthreads();
+    extern __shared__ f32x4 bin_lds[];
+    const ReqDev& q = bd.reqs[block_y()];
+    if (uni(q.bin_path) != IDX) return;
+    const int W1 = uni(q.W) - 1;
+    int t = block_x();
+    const bool by_tile = uni(q.by_tile) != 0;
+    if (by_tile) {
+        if (t >= uni(q.v.n_tiles)) return;
+    } else {
+        if (t >= W1) return;
+        const uint32_t v = uni(gload<uint32_t>(q.ws.bin_ta, t + 1));   // edge t + 1
+        if (!(v & kFirstEdge)) return;
+        t = (int)(v & ~kFirstEdge);
     }
+    const float X0 = uni(gload<float>(q.ws.x0, t)), X1 = uni(gload<float>(q.ws.x0, t + 1));
+    if (by_tile && bin_of(X0, W1) == bin_of(X1, W1)) return;
+    const float scale_f = (float)gload<double>(q.ws.scal, 2);
+    Stage stage;
+    stage.ex_p = bin_lds;
+    float* tf_lds = reinterpret_cast<float*>(bin_lds + bd.max_tile_steps * kWave);
+    auto tables = [&]() {
+        if constexpr (IDX != 2) {
+            const float* src = uni(q.tf);
+            stage_lds<kBinThreads>(tf_lds, uni(q.tf_total), [&](int k) { return gload<float>(src, k); });
+            __syncthreads();
+        }
+    };
+    if constexpr (IDX == 2)
+        rescan_stage<MT, S, StepF<MT>>(q, t, tf_lds, stage, tables);
+    else if constexpr (IDX == 1)
+        rescan_stage<MT, S, StepIdx<MT>>(q, t, tf_lds, stage, tables);
+    else
+        rescan_stage<MT, S, StepData<MT, S>>(q, t, tf_lds, stage, tables);
+    __syncthreads();
+    rescan_bins(q, t, X0, X1, uni(scale_f), stage);
 }
 
 // ------------------------------------------------------------------ K4
 
-// Field statistics of the sorted cells [first, last], by one wave: the stored
-// values of the partial 256-cell steps at the two ends, the per-step
-// statistics of the whole steps next to them and the per-tile statistics of
-// the whole tiles in between (a step or tile is whole when the range holds
-// all of its cells below n).  Sums are fp64; every lane ends with the result.
-template <int MT, typename S>
-__device__ __forceinline__ void bin_range_stats(const JobDev& j, int M, uint32_t first, uint32_t last,
-                                                double (&sum)[MT], float (&mn)[MT], float (&mx)[MT]) {
+// Field statistics of the sorted cells [first, last] for the fields m0 ..
+// m0 + FC - 1, by one wave: the stored values of the partial 256-cell steps at
+// the two ends, the per-step statistics of the whole steps next to them and
+// the per-tile statistics of the whole tiles in between (a step or tile is
+// whole when the range holds all of its cells below n).  Bound by latency:
+// the loads of both ends and of the first 64 steps and tiles are issued
+// together, then reduced (they were four dependent rounds).  Sums are fp64;
+// every lane ends with the result.
+template <int FC, typename S>
+__device__ __forceinline__ void bin_range_stats(const VolDev& j, int m0, int M, uint32_t first, uint32_t last,
+                                                double (&sum)[FC], float (&mn)[FC], float (&mx)[FC]) {
     const int lane = lane_id();
     const int64_t n = uni(j.n);
     const int ts = uni(j.tile_steps);
@@ -1088,79 +1087,102 @@ __device__ __forceinline__ void bin_range_stats(const JobDev& j, int M, uint32_t
     const int64_t f = first, l = last;
     auto whole_step = [&](int64_t st) { return f <= st * kStepCells && l >= min(n, st * kStepCells + kStepCells) - 1; };
     const int64_t sf = f / kStepCells, sl = l / kStepCells;
+    const bool wf = whole_step(sf), wl = whole_step(sl);
+    // partial end steps: each lane its 4 cells; lanes with no cell of the range fetch nothing
+    const int64_t c[2] = {sf * kStepCells + 4 * lane, sl * kStepCells + 4 * lane};
+    const bool need[2] = {!wf && c[0] + 3 >= f && c[0] <= l, !wl && sl != sf && c[1] <= l};
+    // whole steps [a, b]; whole tiles [ta, tb] among them; the steps outside whole tiles: [s0, s1], [s2, s3]
+    const int64_t a = wf ? sf : sf + 1, b = wl ? sl : sl - 1;
+    int ta = 1, tb = 0;
+    int64_t s0 = 1, s1 = 0, s2 = 1, s3 = 0;
+    if (a <= b) {
+        ta = (int)(((uint32_t)a + ts - 1) / ts);
+        tb = (int)((uint32_t)(b + 1) / ts) - 1;
+        s0 = a;
+        s1 = b;
+        if (ta <= tb) {
+            s1 = (int64_t)ta * ts - 1;
+            s2 = (int64_t)(tb + 1) * ts;
+            s3 = b;
+        }
+    }
+    const int64_t n0 = s1 >= s0 ? s1 - s0 + 1 : 0, n1 = s3 >= s2 ? s3 - s2 + 1 : 0;
+    Quad<S> qd[2][FC];
+    double tsum[FC], ssum[FC];
+    float tmn[FC], tmx[FC], smn[FC], smx[FC];
+    const int64_t tl = (int64_t)ta + lane;
+    const bool tile = tl <= tb, step = lane < n0 + n1;
+    const int64_t sl0 = lane < n0 ? s0 + lane : s2 + (lane - n0);
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
+    for (int m = 0; m < FC; ++m) {
+        if (m0 + m < M) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                if (need[e]) qd[e][m].load(j.fields[m0 + m], c[e] >> 2);
+            if (tile) {
+                const int64_t o = (int64_t)(m0 + m) * T + tl;
+                tsum[m] = gload<double>(j.agg_sum, o);
+                tmn[m] = gload<float>(j.agg_min, o);
+                tmx[m] = gload<float>(j.agg_max, o);
+            }
+            if (step) {
+                const int64_t o = (int64_t)(m0 + m) * S_all + sl0;
+                ssum[m] = gload<double>(j.step_sum, o);
+                smn[m] = gload<float>(j.step_min, o);
+                smx[m] = gload<float>(j.step_max, o);
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < FC; ++m) {
         sum[m] = 0.0;
         mn[m] = INFINITY;
         mx[m] = -INFINITY;
-    }
-    // partial end steps: each lane its 4 cells
-    const bool wf = whole_step(sf), wl = whole_step(sl);
+        if (m0 + m < M) {
 #pragma unroll
-    for (int end = 0; end < 2; ++end) {
-        if (end == 0 && wf) continue;
-        if (end == 1 && (sl == sf || wl)) break;
-        const int64_t st = end == 0 ? sf : sl;
-        const int64_t c = st * kStepCells + 4 * lane;
-        const bool need = c + 3 >= f && c <= l;     // lanes with no cell of the range fetch nothing
+            for (int e = 0; e < 2; ++e) {
+                if (need[e]) {
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            if (m < M && need) {
-                Quad<S> qd;
-                qd.load(j.fields[m], st * kWave + lane);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if (c + k >= f && c + k <= l) {
-                        const float v = qd.get(k);
-                        sum[m] += (double)v;
-                        mn[m] = fminf(mn[m], v);
-                        mx[m] = fmaxf(mx[m], v);
+                    for (int k = 0; k < 4; ++k) {
+                        if (c[e] + k >= f && c[e] + k <= l) {
+                            const float v = qd[e][m].get(k);
+                            sum[m] += (double)v;
+                            mn[m] = fminf(mn[m], v);
+                            mx[m] = fmaxf(mx[m], v);
+                        }
                     }
                 }
             }
-        }
-    }
-    // whole steps [a, b]; whole tiles [ta, tb] among them
-    const int64_t a = wf ? sf : sf + 1, b = wl ? sl : sl - 1;
-    if (a <= b) {
-        const int64_t ta = (a + ts - 1) / ts, tb = (b + 1) / ts - 1;
-        int64_t s0 = a, s1 = b, s2 = 1, s3 = 0;       // step ranges [s0, s1] and [s2, s3] outside whole tiles
-        if (ta <= tb) {
-            s1 = ta * ts - 1;
-            s2 = (tb + 1) * ts;
-            s3 = b;
-            for (int64_t t = ta + lane; t <= tb; t += kWave) {
-#pragma unroll
-                for (int m = 0; m < MT; ++m) {
-                    if (m < M) {
-                        const int64_t o = (int64_t)m * T + t;
-                        sum[m] += gload<double>(j.agg_sum, o);
-                        mn[m] = fminf(mn[m], gload<float>(j.agg_min, o));
-                        mx[m] = fmaxf(mx[m], gload<float>(j.agg_max, o));
-                    }
-                }
+            if (tile) {
+                sum[m] += tsum[m];
+                mn[m] = fminf(mn[m], tmn[m]);
+                mx[m] = fmaxf(mx[m], tmx[m]);
             }
-        }
-        const int64_t n0 = s1 >= s0 ? s1 - s0 + 1 : 0, n1 = s3 >= s2 ? s3 - s2 + 1 : 0;
-        for (int64_t i = lane; i < n0 + n1; i += kWave) {
-            const int64_t st = i < n0 ? s0 + i : s2 + (i - n0);
-#pragma unroll
-            for (int m = 0; m < MT; ++m) {
-                if (m < M) {
-                    const int64_t o = (int64_t)m * S_all + st;
-                    sum[m] += gload<double>(j.step_sum, o);
-                    mn[m] = fminf(mn[m], gload<float>(j.step_min, o));
-                    mx[m] = fmaxf(mx[m], gload<float>(j.step_max, o));
-                }
+            for (int64_t t = tl + kWave; t <= tb; t += kWave) {
+                const int64_t o = (int64_t)(m0 + m) * T + t;
+                sum[m] += gload<double>(j.agg_sum, o);
+                mn[m] = fminf(mn[m], gload<float>(j.agg_min, o));
+                mx[m] = fmaxf(mx[m], gload<float>(j.agg_max, o));
+            }
+            if (step) {
+                sum[m] += ssum[m];
+                mn[m] = fminf(mn[m], smn[m]);
+                mx[m] = fmaxf(mx[m], smx[m]);
+            }
+            for (int64_t i = lane + kWave; i < n0 + n1; i += kWave) {
+                const int64_t o = (int64_t)(m0 + m) * S_all + (i < n0 ? s0 + i : s2 + (i - n0));
+                sum[m] += gload<double>(j.step_sum, o);
+                mn[m] = fminf(mn[m], gload<float>(j.step_min, o));
+                mx[m] = fmaxf(mx[m], gload<float>(j.step_max, o));
             }
         }
     }
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        if (m < M) {
-            sum[m] = wave_sum_d(sum[m]);
-            mn[m] = wave_min_f(mn[m]);
-            mx[m] = wave_max_f(mx[m]);
+    for (int m = 0; m < FC; ++m) {
+        if (m0 + m < M) {
+            sum[m] = wave_total_d(sum[m]);
+            mn[m] = wave_lowest_f(mn[m]);
+            mx[m] = wave_highest_f(mx[m]);
         }
     }
 }
@@ -1172,15 +1194,13 @@ __device__ __forceinline__ void bin_range_stats(const JobDev& j, int M, uint32_t
 // tile holds records of its first and last bin).  Then the statistics of the
 // range and the height of the mean.
 template <int MT, typename S>
-__global__ __launch_bounds__(256) void k_bin_stats(BatchDev bd) {
+__global__ __launch_bounds__(kUpdThreads) void k_bin_stats(BatchDev bd) {
     const int lane = lane_id();
-    const int64_t u = (int64_t)block_x() * (256 / kWave) + thread_x() / kWave;
-    if (u >= bd.k4_units) return;   // the whole wave
-    const int qi = uni(find_req_k4(bd, u));
-    const ReqDev& q = bd.reqs[qi];
-    const JobDev& j = bd.jobs[uni(q.job)];
+    const ReqDev& q = bd.reqs[block_y()];
+    const VolDev& j = q.v;
+    const int b = uni(block_x() * kUpdWaves + (int)(thread_x() / kWave));
+    if (b >= uni(q.W)) return;   // the whole wave
     const int M = uni(fields_of<MT>(j.M));
-    const int b = (int)(u - uni(q.k4_unit0));
     if (b == 0 && lane == 0) {
         gstore<double>(q.f_total, 0, gload<double>(q.ws.scal, 0));
         gstore<float>(q.vmax_used, 0, gload<float>(q.vmax_dev, 0));
@@ -1191,7 +1211,7 @@ __global__ __launch_bounds__(256) void k_bin_stats(BatchDev bd) {
     // tiles touching bin b: t0 = first with tail >= b, t1 = last with head <= b
     // (K3a wrote both per bin; t0 is its candidate ta or the next tile)
     const int64_t t1 = uni(gload<int32_t>(q.ws.bin_t1, b));
-    const int64_t ta = uni(gload<int32_t>(q.ws.bin_ta, b));
+    const int64_t ta = uni(gload<uint32_t>(q.ws.bin_ta, b)) & ~kFirstEdge;
     // then one round of loads: the candidate's tail bin, the last tile's head
     // and tail bins, the bin's own outputs (written by the rescan when the
     // bin starts and ends inside one tile) and, per lane, the head and tail
@@ -1219,8 +1239,8 @@ __global__ __launch_bounds__(256) void k_bin_stats(BatchDev bd) {
         first = in_first;
         last = in_last;
     } else {
-        first = wave_min_u32(first);
-        last = wave_max_u32(last);
+        first = wave_lowest_u(first);
+        last = wave_highest_u(last);
     }
     // no cell (cannot happen with a positive total width); a range outside
     // the volume is treated the same way, so no statistic reads past it
@@ -1238,23 +1258,35 @@ __global__ __launch_bounds__(256) void k_bin_stats(BatchDev bd) {
         }
         return;
     }
-    double sm[MT];
-    float mn[MT], mx[MT];
-    bin_range_stats<MT, S>(j, M, first, last, sm, mn, mx);
     if (lane == 0 && !inside) {
         gstore<uint32_t>(q.first_cell, b, first);
         gstore<uint32_t>(q.last_cell, b, last);
     }
     const uint32_t cnt = last - first + 1u;
+    constexpr int FC = MT < 4 ? MT : 4;
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        if (m < M && lane == m) {
-            const float mean = (float)(sm[m] / (double)cnt);
+    for (int m0 = 0; m0 < MT; m0 += FC) {
+        if (m0 >= M) break;
+        double sm[FC];
+        float mn[FC], mx[FC];
+        bin_range_stats<FC, S>(j, m0, M, first, last, sm, mn, mx);
+        // a lane per field
+        double ls = sm[0];
+        float lmn = mn[0], lmx = mx[0];
+#pragma unroll
+        for (int m = 1; m < FC; ++m) {
+            ls = lane == m ? sm[m] : ls;
+            lmn = lane == m ? mn[m] : lmn;
+            lmx = lane == m ? mx[m] : lmx;
+        }
+        const int m = m0 + lane;
+        if (lane < FC && m < M) {
+            const float mean = (float)(ls / (double)cnt);
             const int e = tf_entry(mean, q.s[m], q.b[m], q.nmax[m]);
             const int64_t o = (int64_t)m * q.W + b;
             gstore<float>(q.mean, o, mean);
-            gstore<float>(q.vmin, o, mn[m]);
-            gstore<float>(q.vmax, o, mx[m]);
+            gstore<float>(q.vmin, o, lmn);
+            gstore<float>(q.vmax, o, lmx);
             gstore<float>(q.y, o, gload<float>(q.tf, q.tf_off[m] + e));
         }
     }
@@ -1283,19 +1315,18 @@ static dvl_status check_no_static_lds(const char* name) {
 
 // Grid of the importance pass.  When the units split evenly over the
 // workgroups that fit the chip at once with `lds` bytes of LDS each (or
-// number no more than them), or belong to several volumes (units of unequal
+// number no more than them), or belong to several requests (units of unequal
 // length: the 32-volume batch's pass took 612 instead of 735 us), one round
 // of that many: a workgroup that finishes its unit takes the next one with
 // its tables already in LDS, instead of a second round of workgroups
-// starting cold (descriptors,
-// tables, the first loads: a few dependent memory round trips each), 5 %
-// faster for the 501 M-cell cached-entry pass.  Otherwise 8 workgroups per
+// starting cold (descriptors, tables, the first loads: a few dependent memory
+// round trips each), 5 % faster for the 501 M-cell cached-entry pass.  Otherwise 8 workgroups per
 // compute unit, whose later rounds the hardware hands to whichever compute
 // unit frees a slot (a fixed uneven split, 2048 units over 1280 resident
 // workgroups of the value path, was 3 % slower).  The occupancy is queried
 // once per kernel and LDS size; any grid gives the same results.
 template <void (*Kernel)(BatchDev)>
-static int64_t resident_grid(size_t lds, int n_cu, int64_t units, int n_jobs) {
+static int64_t resident_grid(size_t lds, int n_cu, int64_t units, int n_reqs) {
     static std::atomic<uint64_t> cache{0};   // (lds << 8) | blocks per compute unit, 0: none
     uint64_t c = cache.load(std::memory_order_relaxed);
     int nb = (c >> 8) == (uint64_t)lds && c != 0 ? (int)(c & 0xFF) : 0;
@@ -1310,83 +1341,87 @@ static int64_t resident_grid(size_t lds, int n_cu, int64_t units, int n_jobs) {
     }
     const int64_t resident = (int64_t)n_cu * nb;
     if (units <= resident) return std::max<int64_t>(1, units);
-    return units % resident == 0 || n_jobs > 1 ? resident : std::min<int64_t>(units, (int64_t)n_cu * 8);
+    return units % resident == 0 || n_reqs > 1 ? resident : std::min<int64_t>(units, (int64_t)n_cu * 8);
 }
 
-template <int MT, typename S, int KR>
+// Kernels with a request per grid row: at most kMaxGridY rows a launch.
+constexpr int kMaxGridY = 32768;
+template <void (*Kernel)(BatchDev)>
+static dvl_status launch_rows(const BatchDev& b, int64_t blocks, int threads, size_t lds, hipStream_t s) {
+    for (int q0 = 0; q0 < b.n_reqs; q0 += kMaxGridY) {
+        BatchDev part = b;
+        part.reqs = b.reqs + q0;
+        const int rows = std::min(kMaxGridY, b.n_reqs - q0);
+        hipLaunchKernelGGL(Kernel, dim3((unsigned)std::max<int64_t>(1, blocks), rows), dim3(threads), lds, s, part);
+        DVL_HIP(hipGetLastError());
+    }
+    return DVL_OK;
+}
+
+template <int MT, typename S>
 static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEvent_t* ev) {
     if (b.paths & kPathEntries) {
-        if (dvl_status st = check_no_static_lds<k_tile_sums<MT, S, KR, 1>>("k_tile_sums")) return st;
-        if (dvl_status st = check_no_static_lds<k_vmax_exact<MT, S, KR, 1>>("k_vmax_exact")) return st;
+        if (dvl_status st = check_no_static_lds<k_tile_sums<MT, S, 1>>("k_tile_sums")) return st;
+        if (dvl_status st = check_no_static_lds<k_vmax_exact<MT, S, 1>>("k_vmax_exact")) return st;
     }
     auto mark = [&](int i) -> dvl_status {
         if (ev && ev[i]) DVL_HIP(hipEventRecord(ev[i], s));
         return DVL_OK;
     };
-    const size_t lds1 = (size_t)b.max_job_tf * sizeof(float);
-    const size_t lds1i = (size_t)std::max(1, b.max_req_job) * MT * kIdxTable * sizeof(float);
-    const unsigned g1 = (unsigned)std::max<int64_t>(1, std::min<int64_t>(b.k1_units, (int64_t)n_cu * 8));
+    const size_t lds1 = (size_t)sums_lds<false>(b) * sizeof(float) + kUpdWaves * sizeof(double);
+    const size_t lds1i = (size_t)sums_lds<true>(b) * sizeof(float) + kUpdWaves * sizeof(double);
     if (dvl_status st = mark(0)) return st;
     if (b.any_exact) {
         if (b.paths & kPathValues) {
-            hipLaunchKernelGGL((k_vmax_exact<MT, S, KR, 0>), dim3(g1), dim3(kUpdThreads), lds1, s, b);
+            const unsigned g = (unsigned)resident_grid<k_vmax_exact<MT, S, 0>>(lds1, n_cu, b.k1_units, b.n_reqs);
+            hipLaunchKernelGGL((k_vmax_exact<MT, S, 0>), dim3(g), dim3(kUpdThreads), lds1, s, b);
             DVL_HIP(hipGetLastError());
         }
         if (b.paths & kPathEntries) {
-            hipLaunchKernelGGL((k_vmax_exact<MT, S, KR, 1>), dim3(g1), dim3(kUpdThreads), lds1i, s, b);
+            const unsigned g = (unsigned)resident_grid<k_vmax_exact<MT, S, 1>>(lds1i, n_cu, b.k1_units, b.n_reqs);
+            hipLaunchKernelGGL((k_vmax_exact<MT, S, 1>), dim3(g), dim3(kUpdThreads), lds1i, s, b);
             DVL_HIP(hipGetLastError());
         }
     }
     if (dvl_status st = mark(1)) return st;
     if (b.paths & kPathValues) {
-        const unsigned g = (unsigned)resident_grid<k_tile_sums<MT, S, KR, 0>>(lds1, n_cu, b.k1_units, b.n_jobs);
-        hipLaunchKernelGGL((k_tile_sums<MT, S, KR, 0>), dim3(g), dim3(kUpdThreads), lds1, s, b);
+        const unsigned g = (unsigned)resident_grid<k_tile_sums<MT, S, 0>>(lds1, n_cu, b.k1_units, b.n_reqs);
+        hipLaunchKernelGGL((k_tile_sums<MT, S, 0>), dim3(g), dim3(kUpdThreads), lds1, s, b);
         DVL_HIP(hipGetLastError());
     }
     if (b.paths & kPathEntries) {
-        const unsigned g = (unsigned)resident_grid<k_tile_sums<MT, S, KR, 1>>(lds1i, n_cu, b.k1_units, b.n_jobs);
-        hipLaunchKernelGGL((k_tile_sums<MT, S, KR, 1>), dim3(g), dim3(kUpdThreads), lds1i, s, b);
+        const unsigned g = (unsigned)resident_grid<k_tile_sums<MT, S, 1>>(lds1i, n_cu, b.k1_units, b.n_reqs);
+        hipLaunchKernelGGL((k_tile_sums<MT, S, 1>), dim3(g), dim3(kUpdThreads), lds1i, s, b);
         DVL_HIP(hipGetLastError());
     }
     if (dvl_status st = mark(2)) return st;
     if (dvl_status st = launch_carry_classify(b, s)) return st;
     if (dvl_status st = mark(3)) return st;
-    const size_t lds3 = (size_t)((b.max_req_tf + 3) & ~3) * sizeof(float) + (size_t)b.max_tile_steps * kStageBytesPerStep;
-    const unsigned g3 = (unsigned)std::max<int64_t>(1, std::min<int64_t>(b.k3_units, (int64_t)n_cu * 16));
-    if (b.paths & kPathBinValues) {
-        hipLaunchKernelGGL((k_bin<MT, S, 0>), dim3(g3), dim3(kBinThreads), lds3, s, b);
-        DVL_HIP(hipGetLastError());
-    }
-    if (b.paths & kPathBinEntries) {
-        hipLaunchKernelGGL((k_bin<MT, S, 1>), dim3(g3), dim3(kBinThreads), lds3, s, b);
-        DVL_HIP(hipGetLastError());
-    }
-    if (b.paths & kPathBinStoredF) {
-        hipLaunchKernelGGL((k_bin<MT, S, 2>), dim3(g3), dim3(kBinThreads), lds3, s, b);
-        DVL_HIP(hipGetLastError());
-    }
+    const size_t stage = (size_t)b.max_tile_steps * kStageBytesPerStep;
+    const size_t tables = (size_t)b.max_req_tf * sizeof(float);
+    if (b.paths & kPathBinValues)
+        if (dvl_status st = launch_rows<k_bin<MT, S, 0>>(b, b.max_bin_units, kBinThreads, stage + tables, s)) return st;
+    if (b.paths & kPathBinEntries)
+        if (dvl_status st = launch_rows<k_bin<MT, S, 1>>(b, b.max_bin_units, kBinThreads, stage + tables, s)) return st;
+    if (b.paths & kPathBinStoredF)
+        if (dvl_status st = launch_rows<k_bin<MT, S, 2>>(b, b.max_bin_units, kBinThreads, stage, s)) return st;
     if (dvl_status st = mark(4)) return st;
-    {
-        const unsigned g4 = (unsigned)std::max<int64_t>(1, (b.k4_units + 3) / 4);
-        hipLaunchKernelGGL((k_bin_stats<MT, S>), dim3(g4), dim3(256), 0, s, b);
-        DVL_HIP(hipGetLastError());
-    }
+    if (dvl_status st = launch_rows<k_bin_stats<MT, S>>(b, (b.max_w + kUpdWaves - 1) / kUpdWaves, kUpdThreads, 0, s)) return st;
     return mark(5);
 }
 
-// One storage type and field count (both request-count variants).  Each
-// (S, MT) pair is instantiated in a translation unit of its own, generated by
-// the build (the fifteen compile in parallel); elsewhere the declarations
-// below keep the compiler from instantiating them.
+// One storage type and field count.  Each (S, MT) pair is instantiated in a
+// translation unit of its own, generated by the build (the fifteen compile in
+// parallel); elsewhere the declarations below keep the compiler from
+// instantiating them.
 template <typename S, int MT>
-dvl_status launch_sm(const BatchDev& b, int max_req, int n_cu, hipStream_t s, uint64_t layout, hipEvent_t* ev) {
+dvl_status launch_sm(const BatchDev& b, int n_cu, hipStream_t s, uint64_t layout, hipEvent_t* ev) {
     if (layout != kDescriptorLayout) {
         set_error("descriptor layout mismatch between library objects (%llx vs %llx): rebuild the library",
                   (unsigned long long)layout, (unsigned long long)kDescriptorLayout);
         return DVL_E_INVALID;
     }
-    if (max_req <= 1) return launch_typed<MT, S, 1>(b, n_cu, s, ev);
-    return launch_typed<MT, S, kMaxReqPerJob>(b, n_cu, s, ev);
+    return launch_typed<MT, S>(b, n_cu, s, ev);
 }
 
 #define DVL_FOR_EACH_LAUNCH(X) \
@@ -1394,22 +1429,21 @@ dvl_status launch_sm(const BatchDev& b, int max_req, int n_cu, hipStream_t s, ui
     X(F16, 1) X(F16, 2) X(F16, 4) X(F16, 8) X(F16, 16) \
     X(BF16, 1) X(BF16, 2) X(BF16, 4) X(BF16, 8) X(BF16, 16)
 #define DVL_EXTERN_LAUNCH(S, MT) \
-    extern template dvl_status launch_sm<S, MT>(const BatchDev&, int, int, hipStream_t, uint64_t, hipEvent_t*);
+    extern template dvl_status launch_sm<S, MT>(const BatchDev&, int, hipStream_t, uint64_t, hipEvent_t*);
 DVL_FOR_EACH_LAUNCH(DVL_EXTERN_LAUNCH)
 #undef DVL_EXTERN_LAUNCH
 
-// Field-count variants: batches whose jobs all have 1, 2, 4 or 8 fields run
+// Field-count variants: batches whose volumes all have 1, 2, 4 or 8 fields run
 // the variant with that count fixed at compile time; others (mixed counts,
-// 3, 5-7 or more than 8 fields) the general variant, which reads M per job.
+// 3, 5-7 or more than 8 fields) the general variant, which reads M per volume.
 template <typename S>
-static dvl_status launch_s(const BatchDev& b, int max_m, int max_req, int n_cu, hipStream_t s, uint64_t layout,
-                           hipEvent_t* ev) {
+static dvl_status launch_s(const BatchDev& b, int max_m, int n_cu, hipStream_t s, uint64_t layout, hipEvent_t* ev) {
     switch (max_m) {
-        case 1: return launch_sm<S, 1>(b, max_req, n_cu, s, layout, ev);
-        case 2: return launch_sm<S, 2>(b, max_req, n_cu, s, layout, ev);
-        case 4: return launch_sm<S, 4>(b, max_req, n_cu, s, layout, ev);
-        case 8: return launch_sm<S, 8>(b, max_req, n_cu, s, layout, ev);
-        default: return launch_sm<S, 16>(b, max_req, n_cu, s, layout, ev);
+        case 1: return launch_sm<S, 1>(b, n_cu, s, layout, ev);
+        case 2: return launch_sm<S, 2>(b, n_cu, s, layout, ev);
+        case 4: return launch_sm<S, 4>(b, n_cu, s, layout, ev);
+        case 8: return launch_sm<S, 8>(b, n_cu, s, layout, ev);
+        default: return launch_sm<S, 16>(b, n_cu, s, layout, ev);
     }
 }
 

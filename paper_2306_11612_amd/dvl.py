@@ -283,9 +283,7 @@ def update_noalloc(vol: "Volume", p: dvl_params, bins: Bins, stream=None):
 
 
 def set_carry_wait(polls: int):
-    """dvl_set_carry_wait: polls of a request's carry flag before a
-    classifying workgroup computes the carry itself (test hook; 0 forces that
-    path)."""
+    """dvl_set_carry_wait: kept for callers that set it; it changes nothing."""
     _check(lib().dvl_set_carry_wait(int(polls)), "dvl_set_carry_wait")
 
 

@@ -1,6 +1,8 @@
 """Bins whose edges fall on cell, step and tile boundaries, and cells of zero
 width exactly on an edge: the cases where the rescan's rules for which bin
 starts and ends with which cell can go wrong, against the oracle."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -14,6 +16,8 @@ pytestmark = pytest.mark.gpu
 def _gpu():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    yield
+    gc.collect()    # nothing of these cases is freed while a later test counts device memory
 
 
 @pytest.mark.parametrize("n", [255, 256, 4096, 4097, 8192, 12288 + 3])
