@@ -187,14 +187,9 @@ struct dvl_volume {
     uint32_t* perm = nullptr;
     float dmin[kMaxFields] = {};
     float dmax[kMaxFields] = {};
-    // per-tile statistics of the sorted fields: sum [M][T], min [M][T], max [M][T],
-    // and per 256-cell step: [M][S], S = T * tile_steps
-    double* agg_sum = nullptr;
-    float* agg_min = nullptr;
-    float* agg_max = nullptr;
-    double* step_sum = nullptr;
-    float* step_min = nullptr;
-    float* step_max = nullptr;
+    // statistics of the sorted fields per tile and per 64-cell segment
+    FieldStat* tile_stat = nullptr;   // [T][M]
+    FieldStat* seg_stat = nullptr;    // [T * tile_steps * kSegsPerStep][M]
     // TF entry cache: one byte per sorted cell and field for one CacheKey
     // (policy DVL_ENTRY_CACHE_*); `cand` is the key of the last update that
     // could have used a cache, so a key seen twice in a row gets one
@@ -430,9 +425,10 @@ struct Plan {
 };
 
 // Volumes of at most this many one-tile runs have each tile shared by a
-// workgroup's four waves in the importance pass: up to 4 such workgroups fit
-// a compute unit, so a wave per tile would leave most of the chip idle.
-constexpr int kSplitTiles = 1024;
+// workgroup's four waves in the importance pass: a wave per tile would leave
+// half the chip's wave slots or more idle (1264 tiles with P = 2: 52 us against
+// 35; 2880 tiles: 17.7 against 23.5, three cold rounds of short units).
+constexpr int kSplitTiles = 2048;
 
 static VolDev vol_dev(const dvl_volume* v) {
     VolDev d{};
@@ -447,12 +443,8 @@ static VolDev vol_dev(const dvl_volume* v) {
     d.level = v->level_s;
     d.lcode = v->lcode_s;
     for (int m = 0; m < v->M; ++m) d.fields[m] = v->fields_s[m];
-    d.agg_sum = v->agg_sum;
-    d.agg_min = v->agg_min;
-    d.agg_max = v->agg_max;
-    d.step_sum = v->step_sum;
-    d.step_min = v->step_min;
-    d.step_max = v->step_max;
+    d.tile_stat = v->tile_stat;
+    d.seg_stat = v->seg_stat;
     return d;
 }
 
@@ -1084,12 +1076,9 @@ struct dvl_graph {
 static PlaceStats place_stats(const dvl_volume* v, uint2* range) {
     PlaceStats st{};
     st.n_tiles = v->n_tiles;
-    st.tile_sum = v->agg_sum;
-    st.tile_min = v->agg_min;
-    st.tile_max = v->agg_max;
-    st.step_sum = v->step_sum;
-    st.step_min = v->step_min;
-    st.step_max = v->step_max;
+    st.M = v->M;
+    st.tile = v->tile_stat;
+    st.seg = v->seg_stat;
     st.range = range;
     return st;
 }
@@ -1126,22 +1115,14 @@ static dvl_status place_volume(dvl_volume* v, const uint32_t* perm, const uint8_
         pa.src[m] = fields[m];
         pa.dst[m] = v->fields_s[m];
     }
-    DevBuf as(A), an(A), ax(A), ss(A), sn(A), sx(A);
-    const size_t mt = (size_t)v->M * v->n_tiles;
-    const size_t ms = mt * v->tile_steps;
-    if (dvl_status st = as.alloc(mt * 8, "tile sums")) return st;
-    if (dvl_status st = an.alloc(mt * 4, "tile minima")) return st;
-    if (dvl_status st = ax.alloc(mt * 4, "tile maxima")) return st;
-    if (dvl_status st = ss.alloc(ms * 8, "step sums")) return st;
-    if (dvl_status st = sn.alloc(ms * 4, "step minima")) return st;
-    if (dvl_status st = sx.alloc(ms * 4, "step maxima")) return st;
-    v->agg_sum = (double*)as.release();
-    v->agg_min = (float*)an.release();
-    v->agg_max = (float*)ax.release();
-    v->step_sum = (double*)ss.release();
-    v->step_min = (float*)sn.release();
-    v->step_max = (float*)sx.release();
-    v->bytes += (mt + ms) * 16;
+    DevBuf ts(A), ss(A);
+    const size_t tile_bytes = (size_t)v->M * v->n_tiles * sizeof(FieldStat);
+    const size_t seg_bytes = tile_bytes * v->tile_steps * kSegsPerStep;
+    if (dvl_status st = ts.alloc(tile_bytes, "tile statistics")) return st;
+    if (dvl_status st = ss.alloc(seg_bytes, "segment statistics")) return st;
+    v->tile_stat = (FieldStat*)ts.release();
+    v->seg_stat = (FieldStat*)ss.release();
+    v->bytes += tile_bytes + seg_bytes;
     return launch_place(v->n, v->dtype, v->tile_steps, perm, pa, place_stats(v, range_part), ranges, s);
 }
 
@@ -1801,12 +1782,8 @@ void dvl_destroy(dvl_volume* v) {
     for (int m = 0; m < kMaxFields; ++m) A.put(v->fields_s[m], nullptr);
     A.put(v->keys_s, nullptr);
     A.put(v->perm, nullptr);
-    A.put(v->agg_sum, nullptr);
-    A.put(v->agg_min, nullptr);
-    A.put(v->agg_max, nullptr);
-    A.put(v->step_sum, nullptr);
-    A.put(v->step_min, nullptr);
-    A.put(v->step_max, nullptr);
+    A.put(v->tile_stat, nullptr);
+    A.put(v->seg_stat, nullptr);
     A.put(v->scratch_range, nullptr);
     for (int m = 0; m < kMaxFields; ++m) A.put(v->idx_s[m], nullptr);
     if (v->cache_ready) (void)hipEventDestroy(v->cache_ready);

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
 
 #include "dvl.h"
 
@@ -166,6 +165,13 @@ __device__ __forceinline__ double dpp_add_d(double v) {
     const uint32_t lo = dpp_move<CTRL, ROWS>(0u, (uint32_t)u), hi = dpp_move<CTRL, ROWS>(0u, (uint32_t)(u >> 32));
     return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
 }
+// within each row of 16 lanes: lane 15 of the row holds the result
+__device__ __forceinline__ double row_total_d(double v) {
+    v = dpp_add_d<DVL_DPP_ROW_SHR(1), 0xF>(v);
+    v = dpp_add_d<DVL_DPP_ROW_SHR(2), 0xF>(v);
+    v = dpp_add_d<DVL_DPP_ROW_SHR(4), 0xF>(v);
+    return dpp_add_d<DVL_DPP_ROW_SHR(8), 0xF>(v);
+}
 __device__ __forceinline__ double wave_total_d(double v) {
     v = dpp_add_d<DVL_DPP_ROW_SHR(1), 0xF>(v);
     v = dpp_add_d<DVL_DPP_ROW_SHR(2), 0xF>(v);
@@ -176,22 +182,29 @@ __device__ __forceinline__ double wave_total_d(double v) {
     return readlane(v, kWave - 1);
 }
 // op: a commutative, associative and idempotent choice of two values (min, max)
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_choice(T v) {
+    static_assert(sizeof(T) == 4, "one 32-bit register per lane");
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    return __builtin_bit_cast(T, dpp_move<CTRL, ROWS>(u, u));
+}
+// lane 15 of every row: the row's choice
+template <typename T, typename Op>
+__device__ __forceinline__ T row_choose(T v, Op op) {
+    v = op(v, dpp_choice<DVL_DPP_ROW_SHR(1), 0xF>(v));
+    v = op(v, dpp_choice<DVL_DPP_ROW_SHR(2), 0xF>(v));
+    v = op(v, dpp_choice<DVL_DPP_ROW_SHR(4), 0xF>(v));
+    return op(v, dpp_choice<DVL_DPP_ROW_SHR(8), 0xF>(v));
+}
 template <typename T, typename Op>
 __device__ __forceinline__ T wave_choose(T v, Op op) {
-    static_assert(sizeof(T) == 4, "one 32-bit register per lane");
-    auto mv = [](auto ctrl, auto rows, T x) {
-        const uint32_t u = __builtin_bit_cast(uint32_t, x);
-        return __builtin_bit_cast(T, dpp_move<decltype(ctrl)::value, decltype(rows)::value>(u, u));
-    };
-    using std::integral_constant;
-    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(1)>{}, integral_constant<int, 0xF>{}, v));
-    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(2)>{}, integral_constant<int, 0xF>{}, v));
-    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(4)>{}, integral_constant<int, 0xF>{}, v));
-    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_SHR(8)>{}, integral_constant<int, 0xF>{}, v));
-    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_BCAST15>{}, integral_constant<int, 0xA>{}, v));
-    v = op(v, mv(integral_constant<int, DVL_DPP_ROW_BCAST31>{}, integral_constant<int, 0xC>{}, v));
+    v = row_choose(v, op);
+    v = op(v, dpp_choice<DVL_DPP_ROW_BCAST15, 0xA>(v));
+    v = op(v, dpp_choice<DVL_DPP_ROW_BCAST31, 0xC>(v));
     return __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_readlane((int)__builtin_bit_cast(uint32_t, v), kWave - 1));
 }
+__device__ __forceinline__ float row_lowest_f(float v) { return row_choose(v, [](float a, float b) { return fminf(a, b); }); }
+__device__ __forceinline__ float row_highest_f(float v) { return row_choose(v, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float wave_lowest_f(float v) { return wave_choose(v, [](float a, float b) { return fminf(a, b); }); }
 __device__ __forceinline__ float wave_highest_f(float v) { return wave_choose(v, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ uint32_t wave_lowest_u(uint32_t v) { return wave_choose(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; }); }
@@ -312,6 +325,19 @@ template <>
 struct Quad<F16> : Quad16<F16> {};
 template <>
 struct Quad<BF16> : Quad16<BF16> {};
+
+// ---------------------------------------------------------------- statistics
+
+// Sum, minimum and maximum of one field over a stretch of sorted cells: a tile
+// or a segment of kSegCells cells.  The statistics of a stretch lie together,
+// field after field ([tiles or segments][M]): a bin reads a few neighbouring
+// stretches of all fields, one or two pages instead of 24.
+struct alignas(16) FieldStat {
+    double sum;
+    float mn, mx;
+};
+constexpr int kSegCells = 64;      // 16 lanes of a wave's step
+constexpr int kSegsPerStep = 4;
 
 // ---------------------------------------------------------------- host side
 

@@ -707,7 +707,7 @@ __global__ __launch_bounds__(1024) void k_range_fold(int64_t n_part, const uint2
 // ===================================================================
 // Sorted arrays of a volume, one pass: gather by the permutation (or a copy
 // of a contiguous range, perm NULL), zero padding, data range, per-tile and
-// per-step statistics, level codes.
+// per-segment statistics, level codes.
 //
 // One workgroup per (tile, array): arrays 0 .. M - 1 are the fields, array M
 // (when present) the levels.  Its four waves take a quarter of the tile's
@@ -723,8 +723,8 @@ __global__ __launch_bounds__(1024) void k_range_fold(int64_t n_part, const uint2
 // 769, 4 statistics passes of 73, levels 69, codes 38 us); 11.8 M cells, one
 // field of a data change: 33 us (gather 31 + statistics 30).
 // Tile sums: per lane, fp32 sums of 4 values accumulated in fp64 over the
-// wave's steps, then the wave, then the four waves in order; step sums: per
-// lane the fp64 sum of its 4 values, then the wave.
+// wave's steps, then the wave, then the four waves in order; segment sums: per
+// lane the fp64 sum of its 4 values, then the row of 16 lanes.
 // ===================================================================
 template <typename T>
 struct alignas(4 * sizeof(T)) Four {
@@ -784,15 +784,11 @@ __device__ __forceinline__ void place_field(int64_t n, int64_t t, int tile_steps
             acc += (double)s4;
             lo = fminf(lo, slo);
             hi = fmaxf(hi, shi);
-            d4 = wave_total_d(d4);
-            slo = wave_lowest_f(slo);
-            shi = wave_highest_f(shi);
-            if (lane == 0) {
-                const int64_t o = stat * tile_steps * st.n_tiles + step0 + s + g;
-                st.step_sum[o] = d4;
-                st.step_min[o] = slo;
-                st.step_max[o] = shi;
-            }
+            // a row of 16 lanes holds one segment
+            d4 = row_total_d(d4);
+            slo = row_lowest_f(slo);
+            shi = row_highest_f(shi);
+            if ((lane & 15) == 15) st.seg[((step0 + s + g) * kSegsPerStep + (lane >> 4)) * st.M + stat] = FieldStat{d4, slo, shi};
         }
     }
     acc = wave_total_d(acc);
@@ -810,11 +806,8 @@ __device__ __forceinline__ void place_field(int64_t n, int64_t t, int tile_steps
             lo = fminf(lo, wmin[k]);
             hi = fmaxf(hi, wmax[k]);
         }
-        const int64_t o = stat * st.n_tiles + t;
-        st.tile_sum[o] = acc;
-        st.tile_min[o] = lo;
-        st.tile_max[o] = hi;
-        if (st.range) st.range[o] = range;
+        st.tile[t * st.M + stat] = FieldStat{acc, lo, hi};
+        if (st.range) st.range[stat * st.n_tiles + t] = range;
     }
 }
 

@@ -50,12 +50,9 @@ struct PlaceArrays {
 };
 struct PlaceStats {
     int64_t n_tiles;
-    double* tile_sum;        // [M][n_tiles]
-    float* tile_min;
-    float* tile_max;
-    double* step_sum;        // [M][n_tiles * tile_steps]
-    float* step_min;
-    float* step_max;
+    int M;                   // fields of the volume
+    FieldStat* tile;         // [n_tiles][M]
+    FieldStat* seg;          // [n_tiles * tile_steps * kSegsPerStep][M]
     uint2* range;            // [n_fields][n_tiles] range keys per tile, or NULL
 };
 // sorted cell i from original cell perm[i], or from src[i] when perm is NULL;

@@ -20,8 +20,8 @@
 //   K4 k_bin_stats    per (request, bin): the bin's cell range (merged from
 //                     the records of the tiles it touches), then its mean,
 //                     min and max per field from the values of its partial
-//                     end steps and the per-step and per-tile statistics of
-//                     the steps and tiles it covers whole; the height
+//                     end segments and the statistics of the segments and
+//                     tiles it covers whole; the height
 //
 // The paper's GPU version runs the projection once per field with global
 // atomics on the W bins (its Table 1 bottleneck).  Here the projection is
@@ -51,6 +51,7 @@ size_t workspace_bytes(int64_t T, int M, int W, int64_t fcells) {
     b += 2 * al256((size_t)T * 4);         // head/tail bin
     b += 2 * al256((size_t)2 * T * 4);     // rec first/last
     b += 2 * al256((size_t)W * 4);         // per-bin tile bounds
+    b += al256((size_t)W * sizeof(EdgeRec));
     b += al256(8 * 8);                     // scalars
     b += al256((size_t)fcells * 4);        // stored importance
     return b;
@@ -67,7 +68,8 @@ void workspace_carve(void* base, int64_t T, int M, int W, int64_t fcells, UpdWor
     w->rec_first = (uint32_t*)take((size_t)2 * T * 4);
     w->rec_last = (uint32_t*)take((size_t)2 * T * 4);
     w->bin_t1 = (int32_t*)take((size_t)W * 4);
-    w->bin_ta = (uint32_t*)take((size_t)W * 4);
+    w->bin_ta = (int32_t*)take((size_t)W * 4);
+    w->edge = (EdgeRec*)take((size_t)W * sizeof(EdgeRec));
     w->scal = (double*)take(8 * 8);
     w->fstore = fcells ? (float*)take((size_t)fcells * 4) : nullptr;
 }
@@ -231,7 +233,7 @@ __device__ double carry_scan(const double* run_total, int R, int r_lo, int r_hi,
 // is the t with b1(t - 1) < b <= b1(t) (bin_ta, the first tile: b <= b1),
 // or the next tile when tile t's last cell ends exactly at bin b's left edge
 // (K4 checks it with the tile's tail bin).  These ranges partition the bins.
-// bin_ta of a tile's first inner edge carries kFirstEdge: K3b's worklist.
+// A tile's first inner edge also gets the tile's record: K3b's worklist.
 __global__ __launch_bounds__(kCarryThreads) void k_carry_classify(BatchDev bd) {
     __shared__ double base[kRunBases];
     const ReqDev& q = bd.reqs[block_y()];
@@ -285,9 +287,25 @@ __global__ __launch_bounds__(kCarryThreads) void k_carry_classify(BatchDev bd) {
     if (last_tile) gstore<float>(q.ws.x0, T, X1);
     const int W1 = W - 1;
     const int b0 = bin_of(X0, W1), b1 = bin_of(X1, W1);
-    for (int b = b0, e = last_tile ? W1 : b1 - 1; b <= e; ++b) gstore<int32_t>(q.ws.bin_t1, b, t);
-    for (int b = t == 0 ? 0 : b0 + 1, e = last_tile ? W1 : b1; b <= e; ++b)
-        gstore<uint32_t>(q.ws.bin_ta, b, (uint32_t)t | (b == b0 + 1 && b <= b1 ? kFirstEdge : 0u));
+    const bool edges = !uni(q.by_tile);
+    int32_t* const t1 = uni(q.ws.bin_t1);
+    int32_t* const ta = uni(q.ws.bin_ta);
+    EdgeRec* const edge = uni(q.ws.edge);
+    auto upto = [&](int b, int tile) {        // tile t ends in bin >= b
+        gstore<int32_t>(ta, b, t);
+        if (edges) gstore<u32x4>(edge, b, u32x4{(uint32_t)tile, __float_as_uint(X0), __float_as_uint(X1), 0u});
+    };
+    for (int b = b0; b < b1; ++b) {
+        gstore<int32_t>(t1, b, t);
+        upto(b + 1, b == b0 ? t : -1);
+    }
+    if (t == 0)
+        for (int b = 0; b <= b0; ++b) upto(b, -1);
+    if (last_tile)
+        for (int b = b1; b <= W1; ++b) {
+            gstore<int32_t>(t1, b, t);
+            if (b > b1) upto(b, -1);
+        }
     if (b0 == b1) {
         const int64_t tbase = t * tile_cells;
         gstore<uint32_t>(q.ws.rec_first, t, (uint32_t)tbase);

@@ -21,6 +21,14 @@ constexpr int kPathBinEntries = 8;               // cached entries,
 constexpr int kPathBinValues = 16;               // or values
 constexpr int kIdxTable = 256;                   // LDS floats per table on the cached-entry path
 
+// A bin edge's tile and its pixel interval, when the edge is the tile's first
+// inner edge; else tile < 0 (another edge has the tile, or no tile holds it).
+struct alignas(16) EdgeRec {
+    int32_t tile;
+    float X0, X1;
+    int32_t pad_;
+};
+
 // Workspace of one request on a volume of T tiles and M fields.
 struct UpdWorkspace {
     double* local_prefix; // [T]  sum of the importance of earlier tiles of the same run
@@ -31,13 +39,12 @@ struct UpdWorkspace {
     uint32_t* rec_first;  // [2][T]  cell range of the tile's head bin, then of its tail bin
     uint32_t* rec_last;   // [2][T]
     int32_t* bin_t1;      // [W]  last tile whose first cell's bin is <= b (the last tile touching bin b)
-    uint32_t* bin_ta;     // [W]  first tile whose pixel interval ends in bin >= b (bin b's first
-                          //      tile, or the one before it when that tile's last cell ends exactly at b);
-                          //      kFirstEdge set when b is the first bin edge inside that tile
+    int32_t* bin_ta;      // [W]  first tile whose pixel interval ends in bin >= b (bin b's first
+                          //      tile, or the one before it when that tile's last cell ends exactly at b)
+    EdgeRec* edge;        // [W]  the tile that holds bin edge b (left edge of bin b)
     double* scal;         // [0] F_tot, [1] degenerate (0/1), [2] pixels per importance
     float* fstore;        // [n_pad] importance of every cell, or NULL (see wants_fstore)
 };
-constexpr uint32_t kFirstEdge = 0x80000000u;     // tiles number fewer than 2^31
 
 // n_bins: the request's W; fcells: cells of the stored importance (0: none)
 size_t workspace_bytes(int64_t n_tiles, int M, int n_bins, int64_t fcells = 0);
@@ -59,12 +66,8 @@ struct VolDev {
     int split;                // a workgroup's waves share one tile (see k_tile_sums)
     const uint8_t* level;
     const uint32_t* lcode;    // per-step level codes (launch_place)
-    const double* agg_sum;    // per-tile field statistics [M][T]
-    const float* agg_min;
-    const float* agg_max;
-    const double* step_sum;   // per-step (256 cells) field statistics [M][T * tile_steps]
-    const float* step_min;
-    const float* step_max;
+    const FieldStat* tile_stat;   // [T][M]
+    const FieldStat* seg_stat;    // [T * tile_steps * kSegsPerStep][M]
     const void* fields[kMaxFields];
     const uint8_t* idx[kMaxFields];   // cached TF entries per field (entries path)
 };

@@ -217,13 +217,49 @@ struct StepIdx {
     }
 };
 
+// The rescan's forms of both: levels loaded as they are (a quarter more bytes
+// of few tiles, one dependent load less than through the level codes).
+struct PlainLevels {
+    uint32_t lv;
+    __device__ __forceinline__ uint32_t get(int k) const { return (lv >> (8 * k)) & 0xFFu; }
+};
+template <int MT, typename S>
+struct BinData {
+    static constexpr uint32_t kQuadBytes = Quad<S>::kBytes;
+    Quad<S> q[MT];
+    PlainLevels lv;
+    __device__ static const void* source(const VolDev& v, int m) { return v.fields[m]; }
+    __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step) {
+        const uint32_t qd = (uint32_t)(step * kWave + lane_id());
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+            if (m < M) q[m].load_at(v.base[m], qd * kQuadBytes);
+        lv.lv = gload_at<uint32_t>(v.lev, qd * 4u);
+    }
+};
+template <int MT>
+struct BinIdx {
+    static constexpr uint32_t kQuadBytes = 4;
+    uint32_t e[MT];
+    PlainLevels lv;
+    __device__ static const void* source(const VolDev& v, int m) { return v.idx[m]; }
+    __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step) {
+        const uint32_t qd = (uint32_t)(step * kWave + lane_id());
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+            if (m < M) e[m] = gload_at<uint32_t>(v.base[m], qd * 4u);
+        lv.lv = gload_at<uint32_t>(v.lev, qd * 4u);
+    }
+};
+
 // the importance of the 4 cells of this lane, as the importance pass stored
 // it (view.base[0]: the request's stored f)
 template <int MT>
 struct StepF {
     static constexpr uint32_t kQuadBytes = 16;
     f32x4 fv;
-    __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step, uint32_t code) {
+    __device__ static const void* source(const VolDev&, int) { return nullptr; }
+    __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step) {
         fv = gload_at<f32x4>(v.base[0], (uint32_t)(step * kWave + lane_id()) * kQuadBytes);
     }
 };
@@ -244,11 +280,19 @@ __device__ __forceinline__ RunView<MT> run_view(const VolDev& vol, int M, int64_
 // request's tables in LDS (values: as uploaded; entries: table m at
 // m * kIdxTable)
 template <int MT, typename S>
-__device__ __forceinline__ float cell_v(const StepData<MT, S>& d, int k, int M, const float* tf, const Quant<MT>& q) {
+__device__ __forceinline__ float values_v(const Quad<S> (&v)[MT], int k, int M, const float* tf, const Quant<MT>& q) {
     float xk[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) xk[m] = m < M ? d.q[m].get(k) : 0.0f;
+    for (int m = 0; m < MT; ++m) xk[m] = m < M ? v[m].get(k) : 0.0f;
     return variation<MT>(xk, M, tf, q);
+}
+template <int MT, typename S>
+__device__ __forceinline__ float cell_v(const StepData<MT, S>& d, int k, int M, const float* tf, const Quant<MT>& q) {
+    return values_v<MT, S>(d.q, k, M, tf, q);
+}
+template <int MT, typename S>
+__device__ __forceinline__ float cell_v(const BinData<MT, S>& d, int k, int M, const float* tf, const Quant<MT>& q) {
+    return values_v<MT, S>(d.q, k, M, tf, q);
 }
 // 4 x byte k of w (the byte offset of an entry in its table), one
 // instruction through the byte operand select of the SDWA encoding
@@ -282,18 +326,26 @@ typedef __attribute__((address_space(3))) const float lds_f32;
 // offset in the table plus the table's compile-time offset, which lands in the
 // instruction's immediate.
 template <int MT>
-__device__ __forceinline__ float cell_v(const StepIdx<MT>& d, int k, int M, const float* tf, const Quant<MT>& q) {
+__device__ __forceinline__ float entries_v(const uint32_t (&e)[MT], int k, int M) {
     float amax = -INFINITY, amin = INFINITY;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         if (m < M) {
-            const uint32_t a = entry_x4(d.e[m], k) + (uint32_t)(m * kIdxTable * sizeof(float));
+            const uint32_t a = entry_x4(e[m], k) + (uint32_t)(m * kIdxTable * sizeof(float));
             const float al = *reinterpret_cast<lds_f32*>((uintptr_t)a);
             amax = fmaxf(amax, al);
             amin = fminf(amin, al);
         }
     }
     return amax - amin;
+}
+template <int MT>
+__device__ __forceinline__ float cell_v(const StepIdx<MT>& d, int k, int M, const float* tf, const Quant<MT>& q) {
+    return entries_v<MT>(d.e, k, M);
+}
+template <int MT>
+__device__ __forceinline__ float cell_v(const BinIdx<MT>& d, int k, int M, const float* tf, const Quant<MT>& q) {
+    return entries_v<MT>(d.e, k, M);
 }
 
 // How many steps one loop iteration loads ahead: one 4-vector per field is
@@ -382,19 +434,25 @@ __device__ __forceinline__ void load_tables(const ReqDev& q, int M, float* tf_ld
     }
 }
 
+// Floats of LDS the tables take in the importance pass and K0 (the
+// partial results of the waves follow, 8-byte aligned).
+template <bool IDX>
+__host__ __device__ __forceinline__ int sums_lds(const BatchDev& b) {
+    return IDX ? b.max_fields * kIdxTable : (b.max_req_tf + 1) & ~1;
+}
+
+
 // ------------------------------------------------------------------ K0
 
+// max V over nsteps steps from cell c_begin, by one wave (per lane); eight
+// steps of cached entries (two of values) in flight
 template <int MT, typename D>
-__device__ __forceinline__ void vmax_run(const ReqDev& q, int64_t r, const float* tf_lds) {
-    constexpr int G = Group<D>::n;
+__device__ __forceinline__ float vmax_run(const ReqDev& q, int64_t c_begin, int nsteps, const float* tf_lds) {
+    constexpr int G = 2 * Group<D>::n;
     const int lane = lane_id();
     const VolDev& vol = q.v;
     const int M = uni(fields_of<MT>(vol.M));
     const int64_t n = uni(vol.n);
-    const int64_t run_cells = (int64_t)uni(vol.tile_steps) * kStepCells * uni(vol.tiles_per_run);
-    const int64_t c_begin = r * run_cells;
-    const int64_t c_end = min(n, c_begin + run_cells);
-    const int nsteps = (int)((c_end - c_begin + kStepCells - 1) / kStepCells);
     Quant<MT> qn;
     qn.load(q);
     float vmax = 0.0f;
@@ -402,7 +460,7 @@ __device__ __forceinline__ void vmax_run(const ReqDev& q, int64_t r, const float
     for (int s = 0; s < nsteps; s += G) {
         D d[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) d[g].load(view, M, s + g, 0u);   // levels unused
+        for (int g = 0; g < G; ++g) d[g].load(view, M, min(s + g, nsteps - 1), 0u);   // levels unused
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (s + g >= nsteps) break;
@@ -412,45 +470,80 @@ __device__ __forceinline__ void vmax_run(const ReqDev& q, int64_t r, const float
                 if ((quad << 2) + k < n) vmax = fmaxf(vmax, cell_v<MT>(d[g], k, M, tf_lds, qn));
         }
     }
-    const float v = wave_highest_f(vmax);
-    if (lane == 0 && v > 0.0f) atomicMax(reinterpret_cast<unsigned int*>(q.vmax_dev), __float_as_uint(v));
+    return vmax;
 }
 
+// The steps of wave wv in unit `local` of a request: four runs a workgroup, a
+// wave each, or (VolDev::split) one tile, `part` steps a wave.
+struct WaveSteps {
+    int t0;                   // first tile
+    int64_t c_begin;
+    int nsteps;
+};
+__device__ __forceinline__ WaveSteps wave_steps(const VolDev& vol, int local, int wv, bool split, int part) {
+    const int tile_steps = uni(vol.tile_steps), tpr = uni(vol.tiles_per_run), n_tiles = uni(vol.n_tiles);
+    const int64_t n = uni(vol.n);
+    WaveSteps w;
+    int s0 = 0;
+    int64_t c_end;
+    if (split) {
+        w.t0 = local;
+        s0 = wv * part;
+        c_end = min(n, ((int64_t)w.t0 * tile_steps + s0 + part) * kStepCells);
+    } else {
+        const int r = local * kUpdWaves + wv;
+        w.t0 = r < uni(vol.n_runs) ? r * tpr : n_tiles;
+        c_end = min(n, (int64_t)min(n_tiles, w.t0 + tpr) * tile_steps * kStepCells);
+    }
+    w.c_begin = ((int64_t)w.t0 * tile_steps + s0) * kStepCells;
+    w.nsteps = c_end > w.c_begin ? (int)((c_end - w.c_begin + kStepCells - 1) / kStepCells) : 0;
+    return w;
+}
+
+// A workgroup keeps the maximum of its units and publishes it with one atomic
+// per request (an atomic per wave on the one word cost 12 ns each: 15 of 24 us
+// for 5.2 M cells).
 // IDX: this instance serves the requests that read cached entries (1) or values (0)
 template <int MT, typename S, int IDX>
 __global__ __launch_bounds__(kUpdThreads) void k_vmax_exact(BatchDev b) {
     extern __shared__ float tf_lds[];
+    float* part = tf_lds + sums_lds<IDX != 0>(b);   // a maximum per wave behind the tables
     const int wv = uni((int)(thread_x() / kWave));
     int loaded = -1;
+    float vmax = 0.0f;
+    auto publish = [&]() {
+        const float v = wave_highest_f(vmax);
+        if (lane_id() == 0) part[wv] = v;
+        __syncthreads();
+        if (thread_x() == 0) {
+            float m = part[0];
+            for (int k = 1; k < kUpdWaves; ++k) m = fmaxf(m, part[k]);
+            if (m > 0.0f) atomicMax(reinterpret_cast<unsigned int*>(b.reqs[loaded].vmax_dev), __float_as_uint(m));
+        }
+        __syncthreads();
+        vmax = 0.0f;
+    };
     for (int64_t u = block_x(); u < b.k1_units; u += grid_dim_x()) {
         const Unit un = find_unit(b, u);
         const ReqDev& q = b.reqs[un.req];
         if (uni(q.entries) != IDX || !uni(q.vmax_exact)) continue;
         if (un.req != loaded) {
-            if (loaded >= 0) __syncthreads();
+            if (loaded >= 0) publish();             // also: every wave is done with the tables
             load_tables<MT, IDX != 0>(q, uni(fields_of<MT>(q.v.M)), tf_lds);
             __syncthreads();
             loaded = un.req;
         }
-        // units of the importance pass: four runs, or one (a tile) when its waves share it
-        const int r = uni(q.v.split) ? un.local : un.local * kUpdWaves + wv;
-        if (r >= uni(q.v.n_runs) || (uni(q.v.split) && wv != 0)) continue;
+        const WaveSteps ws = wave_steps(q.v, un.local, wv, uni(q.v.split) != 0, uni(q.v.tile_steps) / kUpdWaves);
+        if (ws.nsteps <= 0) continue;
         if constexpr (IDX != 0)
-            vmax_run<MT, StepIdx<MT>>(q, r, tf_lds);
+            vmax = fmaxf(vmax, vmax_run<MT, StepIdx<MT>>(q, ws.c_begin, ws.nsteps, tf_lds));
         else
-            vmax_run<MT, StepData<MT, S>>(q, r, tf_lds);
+            vmax = fmaxf(vmax, vmax_run<MT, StepData<MT, S>>(q, ws.c_begin, ws.nsteps, tf_lds));
     }
+    if (loaded >= 0) publish();
 }
 
 // ------------------------------------------------------------------ K1
-
-// Floats of LDS the tables take in the importance pass (the partial sums of a
-// shared tile follow, 8-byte aligned).
-template <bool IDX>
-__host__ __device__ __forceinline__ int sums_lds(const BatchDev& b) {
-    return IDX ? b.max_fields * kIdxTable : (b.max_req_tf + 1) & ~1;
-}
-
 
 // Error-free sum of two floats: s + e == a + b exactly (Knuth's TwoSum).
 __device__ __forceinline__ void two_sum_f(float a, float b, float& s, float& e) {
@@ -697,23 +790,13 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
         const ReqDev& q = b.reqs[un.req];
         if (uni(q.entries) != IDX) continue;
         const VolDev& vol = q.v;
-        const int tile_steps = uni(vol.tile_steps), tpr = uni(vol.tiles_per_run), n_tiles = uni(vol.n_tiles);
+        const int tile_steps = uni(vol.tile_steps);
         const int64_t n = uni(vol.n);
         const bool split = uni(vol.split) != 0;
-        int t0, s0 = 0;
-        int64_t c_end;
-        if (split) {
-            t0 = un.local;
-            const int part = uni(q.scan_mode) == DVL_SCAN_FP64 ? tile_steps / kUpdWaves : (wv == 0 ? tile_steps : 0);
-            s0 = wv * part;
-            c_end = min(n, ((int64_t)t0 * tile_steps + s0 + part) * kStepCells);
-        } else {
-            const int r = un.local * kUpdWaves + wv;
-            t0 = r < uni(vol.n_runs) ? r * tpr : n_tiles;
-            c_end = min(n, (int64_t)min(n_tiles, t0 + tpr) * tile_steps * kStepCells);
-        }
-        const int64_t c_begin = ((int64_t)t0 * tile_steps + s0) * kStepCells;
-        const int nsteps = c_end > c_begin ? (int)((c_end - c_begin + kStepCells - 1) / kStepCells) : 0;
+        const int part = uni(q.scan_mode) == DVL_SCAN_FP64 ? tile_steps / kUpdWaves : (wv == 0 ? tile_steps : 0);
+        const WaveSteps ws = wave_steps(vol, un.local, wv, split, part);
+        const int t0 = ws.t0, nsteps = ws.nsteps;
+        const int64_t c_begin = ws.c_begin;
         auto tables = [&]() {
             if (un.req == loaded) return;
             if (loaded >= 0) __syncthreads();   // the other waves are done with the previous tables
@@ -754,26 +837,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
 
 // ------------------------------------------------------------------ K3
 
-constexpr int kBinThreads = 192;  // one workgroup of three waves per rescanned (request, tile)
-
-// V of cell k of this lane (tables in the request's block layout)
-template <int MT, typename S>
-__device__ __forceinline__ float rescan_v(const StepData<MT, S>& d, int k, int M, const float* tf, const Quant<MT>& q) {
-    return cell_v<MT>(d, k, M, tf, q);
-}
-template <int MT>
-__device__ __forceinline__ float rescan_v(const StepIdx<MT>& d, int k, int M, const float* tf, const Quant<MT>& q) {
-    float amax = -INFINITY, amin = INFINITY;
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        if (m < M) {
-            const float al = tf[q.off[m] + (int)((d.e[m] >> (8 * k)) & 0xFFu)];
-            amax = fmaxf(amax, al);
-            amin = fminf(amin, al);
-        }
-    }
-    return amax - amin;
-}
+constexpr int kBinThreads = 256;  // one workgroup of four waves per rescanned (request, tile)
 
 // The in-step prefix of one 256-cell step, per lane (4 cells): the wave's
 // exclusive prefix before the lane (Bex), the lane's own partial sums p1..p3
@@ -813,9 +877,14 @@ constexpr size_t kStageBytesPerStep = (size_t)kWave * sizeof(f32x4);
 // Phase 1 of the rescan, for the steps s = w, w + kBinWaves, ... of tile t
 // taken by wave w: f of every cell again (from values, cached entries or the
 // stored f, bit for bit as in K1; 1 when the total importance is 0) and the
-// step's monotone prefix, into LDS.  `tables()` stages the request's tables
-// after the first loads are on their way (called once by every wave).
-template <int MT, typename S, typename D, typename Tables>
+// step's monotone prefix, into LDS.  A wave's loads go out in groups of kAhead
+// steps, all four of a 16-step tile's wave at once (values of four or more
+// 4-byte fields: two, which keeps six waves a SIMD); `tables()` waits for the request's tables, whose loads
+// went out before them.
+// POW: the importance needs powf or the other clamp; its steps go one after
+// another in a rolled loop (six copies of four powf were 20 KB of code, run
+// cold by every workgroup).
+template <int MT, typename D, bool POW, typename Tables>
 __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float* tf_lds, Stage stage, Tables tables) {
     const int lane = lane_id();
     const int w = uni((int)(thread_x() / kWave));
@@ -826,13 +895,8 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float
     const int64_t tbase = (int64_t)t * tile_steps * kStepCells;
     const int nsteps = (int)((min(tbase + (int64_t)tile_steps * kStepCells, n) - tbase + kStepCells - 1) / kStepCells);
     constexpr bool kStored = std::is_same<D, StepF<MT>>::value;
-    RunView<MT> view;
-    if constexpr (kStored) {
-        view = run_view<MT, StepData<MT, S>>(vol, M, tbase);
-        view.base[0] = reinterpret_cast<const char*>(uni(q.ws.fstore)) + tbase * 4;
-    } else {
-        view = run_view<MT, D>(vol, M, tbase);
-    }
+    RunView<MT> view = run_view<MT, D>(vol, kStored ? 0 : M, tbase);
+    if constexpr (kStored) view.base[0] = reinterpret_cast<const char*>(uni(q.ws.fstore)) + tbase * 4;
     const double degenerate_d = gload<double>(q.ws.scal, 1);
     ImpCtx c;
     Quant<MT> qn;
@@ -846,7 +910,10 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float
             if constexpr (kStored) {
                 if (!degenerate) fk = k == 0 ? cur.fv.x : (k == 1 ? cur.fv.y : (k == 2 ? cur.fv.z : cur.fv.w));
             } else {
-                if (!degenerate) fk = importance_from_v(rescan_v<MT>(cur, k, M, tf_lds, qn), cur.lv.get(k), c);
+                if (!degenerate) {
+                    const float v = cell_v<MT>(cur, k, M, tf_lds, qn);
+                    fk = POW ? importance_from_v(v, cur.lv.get(k), c) : importance_p1(v, cur.lv.get(k), c);
+                }
             }
             f[k] = ((quad << 2) + k < n) ? fk : 0.0f;
         }
@@ -862,69 +929,27 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float
         sp.B = B;
         stage.put(s, sp);
     };
-    auto begin = [&]() {
-        tables();
-        degenerate = uni((int)(degenerate_d != 0.0)) != 0;
-        if constexpr (!kStored) {
-            c = make_ctx(q);
-            qn.load(q);
-        }
-    };
-    if (w >= nsteps) {
-        tables();
-        return;
-    }
-    if constexpr (!std::is_same<D, StepData<MT, S>>::value) {
-        // cached entries or stored f (a few registers per step): the level
-        // codes of all of this wave's steps first (uniform: scalar registers;
-        // a lane's level load address depends on its code), then the steps,
-        // all six of a 16-step tile's wave in flight at once for up to 4
-        // fields (one memory latency instead of three; eight workgroups of
-        // three waves a compute unit leave 80 VGPRs to each)
-        constexpr int kAhead = kStored || MT <= 4 ? 6 : 3;
-        constexpr int kMaxPer = (kMaxTileSteps + kBinWaves - 1) / kBinWaves;
-        const int cnt = (nsteps - w + kBinWaves - 1) / kBinWaves;
-        uint32_t code[kMaxPer];
+    constexpr int kAhead = POW ? 1 : (MT * D::kQuadBytes >= 64 ? 2 : 4);
+    const int cnt = nsteps > w ? (nsteps - w + kBinWaves - 1) / kBinWaves : 0;
+    bool first = true;
+#pragma unroll 1
+    for (int k0 = 0; k0 < cnt || first; k0 += kAhead) {
+        D buf[kAhead];
 #pragma unroll
-        for (int k = 0; k < kMaxPer; ++k) {
-            code[k] = 0u;
-            if constexpr (!kStored)
-                if (k < cnt) code[k] = gload<uint32_t>(view.lcode, w + k * kBinWaves);
-        }
-        if constexpr (!kStored) {
-#pragma unroll
-            for (int k = 0; k < kMaxPer; ++k) code[k] = uni(code[k]);
+        for (int k = 0; k < kAhead; ++k)
+            if (k0 + k < cnt) buf[k].load(view, M, w + (k0 + k) * kBinWaves);
+        if (first) {
+            tables();
+            degenerate = uni((int)(degenerate_d != 0.0)) != 0;
+            if constexpr (!kStored) {
+                c = make_ctx(q);
+                qn.load(q);
+            }
+            first = false;
         }
 #pragma unroll
-        for (int k0 = 0; k0 < kMaxPer; k0 += kAhead) {
-            if (k0 >= cnt) break;
-            D buf[kAhead];
-#pragma unroll
-            for (int k = 0; k < kAhead; ++k)
-                if (k0 + k < cnt) buf[k].load(view, M, w + (k0 + k) * kBinWaves, code[k0 + k < kMaxPer ? k0 + k : 0]);
-            if (k0 == 0) begin();
-#pragma unroll
-            for (int k = 0; k < kAhead; ++k)
-                if (k0 + k < cnt) process(buf[k], w + (k0 + k) * kBinWaves);
-        }
-    } else {
-        // values: two steps in flight in buffers that take turns (no loaded
-        // register is copied, so each wait is for the older step only)
-        D A, B;
-        const int s1 = min(w + kBinWaves, nsteps - 1);
-        const uint32_t code0 = gload<uint32_t>(view.lcode, w), code1 = gload<uint32_t>(view.lcode, s1);
-        A.load(view, M, w, code0);
-        B.load(view, M, s1, code1);
-        begin();
-        for (int s = w; s < nsteps; s += 2 * kBinWaves) {
-            process(A, s);
-            const int s2 = min(s + 2 * kBinWaves, nsteps - 1);
-            A.load(view, M, s2, gload<uint32_t>(view.lcode, s2));
-            if (s + kBinWaves >= nsteps) break;
-            process(B, s + kBinWaves);
-            const int s3 = min(s + 3 * kBinWaves, nsteps - 1);
-            B.load(view, M, s3, gload<uint32_t>(view.lcode, s3));
-        }
+        for (int k = 0; k < kAhead; ++k)
+            if (k0 + k < cnt) process(buf[k], w + (k0 + k) * kBinWaves);
     }
 }
 
@@ -945,17 +970,16 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float
 struct TileBins {
     int Bh, O;              // bins of the tile's first and last cell
     bool one;               // the whole tile in one bin
+    // the outputs, and this tile's tail first and head last (descriptor fields
+    // in registers: behind a store they would be loaded again)
+    uint32_t *first_cell, *last_cell, *tail_first, *head_last;
 };
 
-__device__ __forceinline__ void bin_starts(const ReqDev& q, int64_t T, int64_t t, const TileBins& tb, int from, int to,
-                                           uint32_t cell) {
-    for (int b = from; b <= to; ++b)
-        gstore<uint32_t>(b == tb.O ? q.ws.rec_first : q.first_cell, b == tb.O ? T + t : (int64_t)b, cell);
+__device__ __forceinline__ void bin_starts(const TileBins& tb, int from, int to, uint32_t cell) {
+    for (int b = from; b <= to; ++b) gstore<uint32_t>(b == tb.O ? tb.tail_first : tb.first_cell + b, 0, cell);
 }
-__device__ __forceinline__ void bin_ends(const ReqDev& q, int64_t t, const TileBins& tb, int from, int before,
-                                         uint32_t cell) {
-    for (int b = from; b < before; ++b)
-        gstore<uint32_t>(b == tb.Bh ? q.ws.rec_last : q.last_cell, b == tb.Bh ? t : (int64_t)b, cell);
+__device__ __forceinline__ void bin_ends(const TileBins& tb, int from, int before, uint32_t cell) {
+    for (int b = from; b < before; ++b) gstore<uint32_t>(b == tb.Bh ? tb.head_last : tb.last_cell + b, 0, cell);
 }
 
 __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0, float X1, float scale_f,
@@ -966,6 +990,15 @@ __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0
     const int64_t n = uni(q.v.n);
     const int W1 = uni(q.W) - 1;
     const int tile_steps = uni(q.v.tile_steps);
+    TileBins tb;
+    tb.first_cell = uni(q.first_cell);
+    tb.last_cell = uni(q.last_cell);
+    uint32_t* const rec_first = uni(q.ws.rec_first) + t;
+    uint32_t* const rec_last = uni(q.ws.rec_last) + t;
+    tb.tail_first = rec_first + T;
+    tb.head_last = rec_last;
+    int32_t* const head_bin = uni(q.ws.head_bin) + t;
+    int32_t* const tail_bin = uni(q.ws.tail_bin) + t;
     const int64_t tile_cells = (int64_t)tile_steps * kStepCells;
     const int64_t tbase = t * tile_cells;
     const int64_t tend = min(tbase + tile_cells, n);
@@ -1000,7 +1033,6 @@ __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0
         const int lo3 = max(0, min((int)floorf(x3), W1));
         key_end_v = max(lo3, min((int)ceilf(x4) - 1, W1));
     }
-    TileBins tb;
     tb.Bh = readlane(key0_v, 0);
     tb.O = readlane(key_end_v, nsteps - 1);
     tb.one = tb.Bh == tb.O;
@@ -1012,16 +1044,16 @@ __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0
 
     if (w == 0) {
         if (lane == 0) {
-            gstore<int32_t>(q.ws.head_bin, t, tb.Bh);
-            gstore<int32_t>(q.ws.tail_bin, t, tb.O);
-            gstore<uint32_t>(q.ws.rec_first, t, (uint32_t)tbase);
-            gstore<uint32_t>(q.ws.rec_last, (tb.one ? 0 : T) + t, last_valid);
+            gstore<int32_t>(head_bin, 0, tb.Bh);
+            gstore<int32_t>(tail_bin, 0, tb.O);
+            gstore<uint32_t>(rec_first, 0, (uint32_t)tbase);
+            gstore<uint32_t>(rec_last, tb.one ? 0 : T, last_valid);
         }
         // steps inside one bin, a lane each
         if (!tb.one && lane < nsteps && key0_v == key_end_v) {
             const int64_t c0 = tbase + (int64_t)lane * kStepCells;
-            bin_starts(q, T, t, tb, prev_v + 1, key_end_v, (uint32_t)c0);
-            bin_ends(q, t, tb, key0_v, next_v, (uint32_t)(min(c0 + kStepCells, n) - 1));
+            bin_starts(tb, prev_v + 1, key_end_v, (uint32_t)c0);
+            bin_ends(tb, key0_v, next_v, (uint32_t)(min(c0 + kStepCells, n) - 1));
         }
     }
     if (tb.one) return;
@@ -1061,8 +1093,8 @@ __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0
         for (int k = 0; k < 4; ++k) {
             const uint32_t g = (uint32_t)((quad << 2) + k);
             if (g <= last_valid) {
-                bin_starts(q, T, t, tb, (k == 0 ? prev_hi : bhi[k - 1]) + 1, bhi[k], g);
-                bin_ends(q, t, tb, blo[k], last[k] ? tb.O : (k == 3 ? next_lo : blo[k + 1]), g);
+                bin_starts(tb, (k == 0 ? prev_hi : bhi[k - 1]) + 1, bhi[k], g);
+                bin_ends(tb, blo[k], last[k] ? tb.O : (k == 3 ? next_lo : blo[k + 1]), g);
             }
         }
     }
@@ -1073,13 +1105,20 @@ __device__ __forceinline__ int bin_of(float x, int W1) { return max(0, min((int)
 
 // K3b: the tiles that hold a bin edge, one workgroup each (grid: x, request
 // y).  With more tiles than bins a workgroup takes a bin edge and its tile,
-// unless an earlier edge of the same tile has it (kFirstEdge); else it takes
-// a tile.  Its waves stage the prefixes of the tile's steps in LDS together
-// (phase 1; the loads of all waves in flight), then settle the bins of the
-// steps that hold an edge (phase 2).
+// unless an earlier edge of the same tile has it (EdgeRec::tile < 0); else it
+// takes a tile.  Its waves stage the prefixes of the tile's steps in LDS
+// together (phase 1; the loads of all waves in flight), then settle the bins
+// of the steps that hold an edge (phase 2).  Bound by latency on a large
+// volume (a chain of kernel arguments, descriptor, edge and cells), by the
+// arithmetic of phase 1 when most tiles are rescanned.  From cached entries:
+// 64^3 cells W 1024 13.6 -> 9.8 us, 11.8 M cells 21 -> 18.9, eight requests on
+// two 20 M-cell volumes 102 -> 89 us against three waves a tile that found
+// their tile through the per-bin bounds, read levels through their codes and
+// looked entries up in the request's own table layout.
 // IDX: this instance serves the requests whose projection reads values (0),
 // cached entries (1) or the f the importance pass stored (2).  LDS: the
-// staged prefixes, then the request's tables (none for stored f).
+// request's tables (as in the importance pass; none for stored f), then the
+// staged prefixes.
 template <int MT, typename S, int IDX>
 __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
     extern __shared__ f32x4 bin_lds[];
@@ -1087,34 +1126,37 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
     if (uni(q.bin_path) != IDX) return;
     const int W1 = uni(q.W) - 1;
     int t = block_x();
-    const bool by_tile = uni(q.by_tile) != 0;
-    if (by_tile) {
+    float X0, X1;
+    if (uni(q.by_tile)) {
         if (t >= uni(q.v.n_tiles)) return;
+        X0 = uni(gload<float>(q.ws.x0, t));
+        X1 = uni(gload<float>(q.ws.x0, t + 1));
+        if (bin_of(X0, W1) == bin_of(X1, W1)) return;
     } else {
         if (t >= W1) return;
-        const uint32_t v = uni(gload<uint32_t>(q.ws.bin_ta, t + 1));   // edge t + 1
-        if (!(v & kFirstEdge)) return;
-        t = (int)(v & ~kFirstEdge);
+        const u32x4 e = gload<u32x4>(q.ws.edge, t + 1);   // edge t + 1
+        t = uni((int)e.x);
+        if (t < 0) return;
+        X0 = uni(__uint_as_float(e.y));
+        X1 = uni(__uint_as_float(e.z));
     }
-    const float X0 = uni(gload<float>(q.ws.x0, t)), X1 = uni(gload<float>(q.ws.x0, t + 1));
-    if (by_tile && bin_of(X0, W1) == bin_of(X1, W1)) return;
     const float scale_f = (float)gload<double>(q.ws.scal, 2);
+    float* tf_lds = reinterpret_cast<float*>(bin_lds);
     Stage stage;
-    stage.ex_p = bin_lds;
-    float* tf_lds = reinterpret_cast<float*>(bin_lds + bd.max_tile_steps * kWave);
+    stage.ex_p = IDX == 2 ? bin_lds : bin_lds + ((IDX == 1 ? bd.max_fields * kIdxTable : bd.max_req_tf) + 3) / 4;
+    static_assert(kBinThreads == kUpdThreads, "load_tables");
+    if constexpr (IDX != 2) load_tables<MT, IDX == 1>(q, uni(fields_of<MT>(q.v.M)), tf_lds);
     auto tables = [&]() {
-        if constexpr (IDX != 2) {
-            const float* src = uni(q.tf);
-            stage_lds<kBinThreads>(tf_lds, uni(q.tf_total), [&](int k) { return gload<float>(src, k); });
-            __syncthreads();
-        }
+        if constexpr (IDX != 2) __syncthreads();
     };
+    const bool pow = uni((int)!(q.exp_is_one && q.clamp_mode == 0)) != 0;
+    using D = typename std::conditional<IDX == 1, BinIdx<MT>, BinData<MT, S>>::type;
     if constexpr (IDX == 2)
-        rescan_stage<MT, S, StepF<MT>>(q, t, tf_lds, stage, tables);
-    else if constexpr (IDX == 1)
-        rescan_stage<MT, S, StepIdx<MT>>(q, t, tf_lds, stage, tables);
+        rescan_stage<MT, StepF<MT>, false>(q, t, tf_lds, stage, tables);
+    else if (pow)
+        rescan_stage<MT, D, true>(q, t, tf_lds, stage, tables);
     else
-        rescan_stage<MT, S, StepData<MT, S>>(q, t, tf_lds, stage, tables);
+        rescan_stage<MT, D, false>(q, t, tf_lds, stage, tables);
     __syncthreads();
     rescan_bins(q, t, X0, X1, uni(scale_f), stage);
 }
@@ -1122,69 +1164,68 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
 // ------------------------------------------------------------------ K4
 
 // Field statistics of the sorted cells [first, last] for the fields m0 ..
-// m0 + FC - 1, by one wave: the stored values of the partial 256-cell steps at
-// the two ends, the per-step statistics of the whole steps next to them and
-// the per-tile statistics of the whole tiles in between (a step or tile is
-// whole when the range holds all of its cells below n).  Bound by latency:
-// the loads of both ends and of the first 64 steps and tiles are issued
-// together, then reduced (they were four dependent rounds).  Sums are fp64;
-// every lane ends with the result.
+// m0 + FC - 1, by one wave: the stored values of the partial 64-cell segments
+// at the two ends (16 lanes each), the statistics of the whole segments next
+// to them and of the whole tiles in between (a segment or tile is whole when
+// the range holds all of its cells below n).  Bound by the latency of cold
+// loads, above all their address translation: with the values of 256-cell
+// end steps and six statistics arrays per field a wave issued 32 loads from
+// as many pages, 4 us of the kernel's 8 at 11.8 M cells; now about 16 loads
+// from 10 pages, and on dense bins a third of the bytes: eight volumes of 8
+// fields, W 2048, 60 -> 40 us; 501 M cells, W 1920, 16.1 -> 12.7 us.  All are issued
+// before the first is used.  Sums are fp64; every lane ends with the result.
 template <int FC, typename S>
 __device__ __forceinline__ void bin_range_stats(const VolDev& j, int m0, int M, uint32_t first, uint32_t last,
                                                 double (&sum)[FC], float (&mn)[FC], float (&mx)[FC]) {
     const int lane = lane_id();
     const int64_t n = uni(j.n);
-    const int ts = uni(j.tile_steps);
-    const int64_t T = uni(j.n_tiles);
-    const int64_t S_all = T * ts;
+    const int shift = __builtin_ctz((unsigned)uni(j.tile_steps)) + 2;     // segments per tile: a power of two
     const int64_t f = first, l = last;
-    auto whole_step = [&](int64_t st) { return f <= st * kStepCells && l >= min(n, st * kStepCells + kStepCells) - 1; };
-    const int64_t sf = f / kStepCells, sl = l / kStepCells;
-    const bool wf = whole_step(sf), wl = whole_step(sl);
-    // partial end steps: each lane its 4 cells; lanes with no cell of the range fetch nothing
-    const int64_t c[2] = {sf * kStepCells + 4 * lane, sl * kStepCells + 4 * lane};
-    const bool need[2] = {!wf && c[0] + 3 >= f && c[0] <= l, !wl && sl != sf && c[1] <= l};
-    // whole steps [a, b]; whole tiles [ta, tb] among them; the steps outside whole tiles: [s0, s1], [s2, s3]
+    auto whole = [&](int64_t sg) { return f <= sg * kSegCells && l >= min(n, sg * kSegCells + kSegCells) - 1; };
+    const int64_t sf = f / kSegCells, sl = l / kSegCells;
+    const bool wf = whole(sf), wl = whole(sl);
+    // partial end segments: lanes 0-15 the first, 16-31 the last, 4 cells each;
+    // lanes with no cell of the range fetch nothing
+    const int64_t c = (lane < 16 ? sf : sl) * kSegCells + 4 * (lane & 15);
+    const bool need = (lane < 16 ? !wf : lane < 32 && !wl && sl != sf) && c + 3 >= f && c <= l;
+    // whole segments [a, b]; whole tiles [ta, tb] among them; the segments
+    // outside whole tiles: [s0, s0 + n0) and [s2, s2 + n1)
     const int64_t a = wf ? sf : sf + 1, b = wl ? sl : sl - 1;
-    int ta = 1, tb = 0;
-    int64_t s0 = 1, s1 = 0, s2 = 1, s3 = 0;
+    int64_t ta = 1, tb = 0, s2 = 0;
+    int n0 = 0, n1 = 0;
     if (a <= b) {
-        ta = (int)(((uint32_t)a + ts - 1) / ts);
-        tb = (int)((uint32_t)(b + 1) / ts) - 1;
-        s0 = a;
-        s1 = b;
+        ta = (a + (1 << shift) - 1) >> shift;
+        tb = ((b + 1) >> shift) - 1;
         if (ta <= tb) {
-            s1 = (int64_t)ta * ts - 1;
-            s2 = (int64_t)(tb + 1) * ts;
-            s3 = b;
+            n0 = (int)((ta << shift) - a);
+            s2 = (tb + 1) << shift;
+            n1 = (int)(b + 1 - s2);
+        } else {
+            n0 = (int)(b + 1 - a);      // less than two tiles
         }
     }
-    const int64_t n0 = s1 >= s0 ? s1 - s0 + 1 : 0, n1 = s3 >= s2 ? s3 - s2 + 1 : 0;
-    Quad<S> qd[2][FC];
-    double tsum[FC], ssum[FC];
-    float tmn[FC], tmx[FC], smn[FC], smx[FC];
-    const int64_t tl = (int64_t)ta + lane;
-    const bool tile = tl <= tb, step = lane < n0 + n1;
-    const int64_t sl0 = lane < n0 ? s0 + lane : s2 + (lane - n0);
+    auto segment = [&](int i) { return i < n0 ? a + i : s2 + (i - n0); };
+    constexpr int kAhead = 2;           // segments per lane loaded at once (all of 16-step tiles)
+    const bool tile = ta + lane <= tb;
+    Quad<S> qd[FC];
+    FieldStat ts[FC], ss[kAhead][FC];
+    const FieldStat* const tile_stat = uni(j.tile_stat) + m0;
+    const FieldStat* const seg_stat = uni(j.seg_stat) + m0;
+    auto stat = [](const FieldStat* p, int64_t i) {
+        return __builtin_bit_cast(FieldStat, gload<u32x4>(p + i, 0));
+    };
 #pragma unroll
-    for (int m = 0; m < FC; ++m) {
-        if (m0 + m < M) {
+    for (int m = 0; m < FC; ++m)
+        if (m0 + m < M && need) qd[m].load(j.fields[m0 + m], c >> 2);
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
-                if (need[e]) qd[e][m].load(j.fields[m0 + m], c[e] >> 2);
-            if (tile) {
-                const int64_t o = (int64_t)(m0 + m) * T + tl;
-                tsum[m] = gload<double>(j.agg_sum, o);
-                tmn[m] = gload<float>(j.agg_min, o);
-                tmx[m] = gload<float>(j.agg_max, o);
-            }
-            if (step) {
-                const int64_t o = (int64_t)(m0 + m) * S_all + sl0;
-                ssum[m] = gload<double>(j.step_sum, o);
-                smn[m] = gload<float>(j.step_min, o);
-                smx[m] = gload<float>(j.step_max, o);
-            }
-        }
+    for (int m = 0; m < FC; ++m)
+        if (m0 + m < M && tile) ts[m] = stat(tile_stat, (ta + lane) * M + m);
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+        const int i = lane + k * kWave;
+#pragma unroll
+        for (int m = 0; m < FC; ++m)
+            if (m0 + m < M && i < n0 + n1) ss[k][m] = stat(seg_stat, segment(i) * M + m);
     }
 #pragma unroll
     for (int m = 0; m < FC; ++m) {
@@ -1192,42 +1233,26 @@ __device__ __forceinline__ void bin_range_stats(const VolDev& j, int m0, int M, 
         mn[m] = INFINITY;
         mx[m] = -INFINITY;
         if (m0 + m < M) {
+            auto add = [&](const FieldStat& x) {
+                sum[m] += x.sum;
+                mn[m] = fminf(mn[m], x.mn);
+                mx[m] = fmaxf(mx[m], x.mx);
+            };
+            if (need) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                if (need[e]) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        if (c[e] + k >= f && c[e] + k <= l) {
-                            const float v = qd[e][m].get(k);
-                            sum[m] += (double)v;
-                            mn[m] = fminf(mn[m], v);
-                            mx[m] = fmaxf(mx[m], v);
-                        }
+                for (int k = 0; k < 4; ++k) {
+                    if (c + k >= f && c + k <= l) {
+                        const float v = qd[m].get(k);
+                        add(FieldStat{(double)v, v, v});
                     }
                 }
             }
-            if (tile) {
-                sum[m] += tsum[m];
-                mn[m] = fminf(mn[m], tmn[m]);
-                mx[m] = fmaxf(mx[m], tmx[m]);
-            }
-            for (int64_t t = tl + kWave; t <= tb; t += kWave) {
-                const int64_t o = (int64_t)(m0 + m) * T + t;
-                sum[m] += gload<double>(j.agg_sum, o);
-                mn[m] = fminf(mn[m], gload<float>(j.agg_min, o));
-                mx[m] = fmaxf(mx[m], gload<float>(j.agg_max, o));
-            }
-            if (step) {
-                sum[m] += ssum[m];
-                mn[m] = fminf(mn[m], smn[m]);
-                mx[m] = fmaxf(mx[m], smx[m]);
-            }
-            for (int64_t i = lane + kWave; i < n0 + n1; i += kWave) {
-                const int64_t o = (int64_t)(m0 + m) * S_all + (i < n0 ? s0 + i : s2 + (i - n0));
-                sum[m] += gload<double>(j.step_sum, o);
-                mn[m] = fminf(mn[m], gload<float>(j.step_min, o));
-                mx[m] = fmaxf(mx[m], gload<float>(j.step_max, o));
-            }
+            if (tile) add(ts[m]);
+            for (int64_t t = ta + lane + kWave; t <= tb; t += kWave) add(stat(tile_stat, t * M + m));
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k)
+                if (lane + k * kWave < n0 + n1) add(ss[k][m]);
+            for (int i = lane + kAhead * kWave; i < n0 + n1; i += kWave) add(stat(seg_stat, segment(i) * M + m));
         }
     }
 #pragma unroll
@@ -1264,7 +1289,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_bin_stats(BatchDev bd) {
     // tiles touching bin b: t0 = first with tail >= b, t1 = last with head <= b
     // (K3a wrote both per bin; t0 is its candidate ta or the next tile)
     const int64_t t1 = uni(gload<int32_t>(q.ws.bin_t1, b));
-    const int64_t ta = uni(gload<uint32_t>(q.ws.bin_ta, b)) & ~kFirstEdge;
+    const int64_t ta = uni(gload<int32_t>(q.ws.bin_ta, b));
     // then one round of loads: the candidate's tail bin, the last tile's head
     // and tail bins, the bin's own outputs (written by the rescan when the
     // bin starts and ends inside one tile) and, per lane, the head and tail
@@ -1416,6 +1441,7 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
     if (b.paths & kPathEntries) {
         if (dvl_status st = check_no_static_lds<k_tile_sums<MT, S, 1>>("k_tile_sums")) return st;
         if (dvl_status st = check_no_static_lds<k_vmax_exact<MT, S, 1>>("k_vmax_exact")) return st;
+        if (dvl_status st = check_no_static_lds<k_bin<MT, S, 1>>("k_bin")) return st;
     }
     auto mark = [&](int i) -> dvl_status {
         if (ev && ev[i]) DVL_HIP(hipEventRecord(ev[i], s));
@@ -1425,13 +1451,13 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
     const size_t lds1i = (size_t)sums_lds<true>(b) * sizeof(float) + kUpdWaves * sizeof(double);
     if (dvl_status st = mark(0)) return st;
     if (b.any_exact) {
+        // few enough workgroups that their atomics on one word stay a few us
+        const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(b.k1_units, (int64_t)n_cu * 4));
         if (b.paths & kPathValues) {
-            const unsigned g = (unsigned)resident_grid<k_vmax_exact<MT, S, 0>>(lds1, n_cu, b.k1_units, b.n_reqs);
             hipLaunchKernelGGL((k_vmax_exact<MT, S, 0>), dim3(g), dim3(kUpdThreads), lds1, s, b);
             DVL_HIP(hipGetLastError());
         }
         if (b.paths & kPathEntries) {
-            const unsigned g = (unsigned)resident_grid<k_vmax_exact<MT, S, 1>>(lds1i, n_cu, b.k1_units, b.n_reqs);
             hipLaunchKernelGGL((k_vmax_exact<MT, S, 1>), dim3(g), dim3(kUpdThreads), lds1i, s, b);
             DVL_HIP(hipGetLastError());
         }
@@ -1451,11 +1477,12 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
     if (dvl_status st = launch_carry_classify(b, s)) return st;
     if (dvl_status st = mark(3)) return st;
     const size_t stage = (size_t)b.max_tile_steps * kStageBytesPerStep;
-    const size_t tables = (size_t)b.max_req_tf * sizeof(float);
+    const size_t tables = ((size_t)b.max_req_tf * sizeof(float) + 15) & ~(size_t)15;
+    const size_t tables_i = (size_t)b.max_fields * kIdxTable * sizeof(float);
     if (b.paths & kPathBinValues)
         if (dvl_status st = launch_rows<k_bin<MT, S, 0>>(b, b.max_bin_units, kBinThreads, stage + tables, s)) return st;
     if (b.paths & kPathBinEntries)
-        if (dvl_status st = launch_rows<k_bin<MT, S, 1>>(b, b.max_bin_units, kBinThreads, stage + tables, s)) return st;
+        if (dvl_status st = launch_rows<k_bin<MT, S, 1>>(b, b.max_bin_units, kBinThreads, stage + tables_i, s)) return st;
     if (b.paths & kPathBinStoredF)
         if (dvl_status st = launch_rows<k_bin<MT, S, 2>>(b, b.max_bin_units, kBinThreads, stage, s)) return st;
     if (dvl_status st = mark(4)) return st;
