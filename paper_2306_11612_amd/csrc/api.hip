@@ -86,6 +86,7 @@ static dvl_status make_alloc(const dvl_allocator* a, Alloc& out) {
 struct DevBuf {
     const Alloc* A;
     void* p = nullptr;
+    bool idle = false;      // the stream of every kernel that used it was synchronised
     explicit DevBuf(const Alloc& a) : A(&a) {}
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
@@ -93,7 +94,7 @@ struct DevBuf {
     // call: kernels enqueued on it may still run, so wait before handing it back
     ~DevBuf() {
         if (p) {
-            (void)hipDeviceSynchronize();
+            if (!idle) (void)hipDeviceSynchronize();
             A->put(p, nullptr);
         }
     }
@@ -106,6 +107,57 @@ struct DevBuf {
 };
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// A page of pinned host memory for a call that waits for a few results: a
+// kernel writes them here directly, and the host reads them after it has
+// synchronised the stream (a copy of a few bytes into pageable memory costs
+// 10 to 15 us more).  Pages come from a process-wide list of at most
+// kHostPagesKept free ones (16 KB each; allocating one takes longer than most
+// calls that need it); a page is used by one call at a time and goes back when
+// the call ends, after the device is idle unless the call says it has
+// synchronised.
+constexpr size_t kHostPageBytes = 16384;
+constexpr size_t kHostPagesKept = 8;
+static std::mutex g_pages_mu;
+static std::vector<void*> g_pages;
+
+struct HostPage {
+    void* p = nullptr;
+    bool idle = false;
+    HostPage() = default;
+    HostPage(const HostPage&) = delete;
+    HostPage& operator=(const HostPage&) = delete;
+    dvl_status take() {
+        {
+            std::lock_guard<std::mutex> lk(g_pages_mu);
+            if (!g_pages.empty()) {
+                p = g_pages.back();
+                g_pages.pop_back();
+                return DVL_OK;
+            }
+        }
+        if (hipHostMalloc(&p, kHostPageBytes, hipHostMallocPortable) != hipSuccess) {
+            p = nullptr;
+            (void)hipGetLastError();
+            return fail(DVL_E_NOMEM, "pinned host allocation of %zu bytes failed", kHostPageBytes);
+        }
+        return DVL_OK;
+    }
+    ~HostPage() {
+        if (!p) return;
+        if (!idle) (void)hipDeviceSynchronize();
+        {
+            std::lock_guard<std::mutex> lk(g_pages_mu);
+            if (g_pages.size() < kHostPagesKept) {
+                if (g_pages.capacity() == 0) g_pages.reserve(kHostPagesKept);
+                g_pages.push_back(p);
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+};
+static_assert((size_t)kRangeParts * sizeof(uint2) <= kHostPageBytes, "the partial ranges fit a page");
 
 // order-preserving uint key (as produced by the range kernel) back to float
 static float unkey(unsigned int u) {
@@ -199,6 +251,7 @@ struct dvl_volume {
     CacheKey idx_key;
     bool cand_set = false;
     CacheKey cand_key;
+    // (the cache of every field is one allocation, idx_s[0])
     // Ordering of cache rebuilds against the launches that read the cache,
     // by events instead of device synchronisation: a rebuild on stream s
     // first waits for the last reading launch on every stream; a launch that
@@ -213,7 +266,8 @@ struct dvl_volume {
     float lo[kMaxFields] = {}, hi[kMaxFields] = {};
     Executor* ex = nullptr;  // private executor of dvl_update
     dvl::Alloc alloc;        // every device buffer of the volume comes from here
-    unsigned int* scratch_range = nullptr;   // dvl_set_field's range check (alloc_range_scratch)
+    char* slab = nullptr;    // the arrays above in one hipMalloc, when the caller gave no allocator
+    size_t slab_size = 0, slab_used = 0;
     // pinned staging of dvl_read_bins (kReadStageBytes, made on first use)
     mutable uint32_t* read_stage = nullptr;
     dvl_status sticky = DVL_OK;
@@ -606,12 +660,12 @@ static dvl_status decide_cache(Plan& P, std::vector<CacheBuild>& builds) {
         if (v->idx_valid && v->idx_key == key) {
             use = true;
         } else if (v->idx_policy == DVL_ENTRY_CACHE_ALWAYS || (v->cand_set && v->cand_key == key)) {
-            for (int m = 0; m < v->M; ++m) {
-                if (v->idx_s[m]) continue;
+            if (!v->idx_s[0]) {
                 DevBuf b(v->alloc);
-                if (dvl_status st = b.alloc((size_t)v->n_pad, "TF entry cache")) return st;
-                v->idx_s[m] = (uint8_t*)b.release();
-                v->bytes += (size_t)v->n_pad;
+                if (dvl_status st = b.alloc((size_t)v->n_pad * v->M, "TF entry cache")) return st;
+                uint8_t* base = (uint8_t*)b.release();
+                for (int m = 0; m < v->M; ++m) v->idx_s[m] = base + (size_t)m * v->n_pad;
+                v->bytes += (size_t)v->n_pad * v->M;
             }
             builds.push_back({v, key});
             use = true;
@@ -1083,57 +1137,80 @@ static PlaceStats place_stats(const dvl_volume* v, uint2* range) {
     return st;
 }
 
-// Allocate the sorted levels, level codes, fields and statistics of a volume
-// and fill them in one pass from the given arrays (original order, or a
-// contiguous range of another volume's sorted arrays: perm NULL).  `ranges`
-// (device, 4 words per field) receives the data ranges; `range_part` is
-// device scratch of 8 bytes per field and tile.
+// Device memory a build works in before the volume's arrays are filled.
+struct BuildScratch {
+    char* small = nullptr;      // the extent, then the partial ranges per tile
+    char* spare = nullptr;      // the arrays that are filled last, free until then
+    size_t spare_bytes = 0;
+};
+static size_t build_small_bytes(const dvl_volume* v) {
+    return al256(256 + extent_scratch_bytes()) + al256((size_t)v->M * v->n_tiles * sizeof(uint2));
+}
+
+// The volume's own arrays.  Through the caller's allocator each is an
+// allocation; without one they are parts of one hipMalloc, with the build's
+// small scratch, and the sort may use the space of the arrays that are filled
+// after it.  (hipMalloc and hipFree of more than 4 MB take 50 to 300 us each:
+// loading 1.1 M cells spent 0.9 ms in twenty of them, 0.2 ms in its kernels.)
+static dvl_status alloc_arrays(dvl_volume* v, BuildScratch* scratch) {
+    const size_t eb = elem_bytes_of(v->dtype);
+    const size_t tile_bytes = (size_t)v->M * v->n_tiles * sizeof(FieldStat);
+    struct Array {
+        void** to;
+        size_t bytes;
+        const char* what;
+    } arrays[7 + kMaxFields] = {{(void**)&v->keys_s, (size_t)v->n * 8, "keys"},
+                                {(void**)&v->perm, (size_t)v->n * 4, "permutation"},
+                                {(void**)&scratch->small, build_small_bytes(v), "build scratch"},
+                                {(void**)&v->level_s, (size_t)v->n_pad, "sorted levels"},
+                                {(void**)&v->lcode_s, (size_t)v->n_pad / kStepCells * 4, "level codes"},
+                                {(void**)&v->tile_stat, tile_bytes, "tile statistics"},
+                                {(void**)&v->seg_stat, tile_bytes * v->tile_steps * kSegsPerStep, "segment statistics"}};
+    constexpr int kFilledLast = 3;     // the first array that nothing reads before it is filled
+    int n_arrays = 7;
+    for (int m = 0; m < v->M; ++m) arrays[n_arrays++] = {&v->fields_s[m], (size_t)v->n_pad * eb, "sorted field"};
+    if (!v->alloc.custom) {
+        for (int k = 0; k < n_arrays; ++k) v->slab_size += al256(arrays[k].bytes);
+        if (hipMalloc((void**)&v->slab, v->slab_size) != hipSuccess) {
+            v->slab = nullptr;
+            (void)hipGetLastError();
+            return fail(DVL_E_NOMEM, "device allocation of %zu bytes for the volume failed", v->slab_size);
+        }
+    }
+    for (int k = 0; k < n_arrays; ++k) {
+        if (v->slab) {
+            *arrays[k].to = v->slab + v->slab_used;
+            if (k == kFilledLast) scratch->spare = v->slab + v->slab_used;
+            v->slab_used += al256(arrays[k].bytes);
+            v->bytes += al256(arrays[k].bytes);
+        } else if (arrays[k].to != (void**)&scratch->small) {
+            DevBuf b(v->alloc);
+            if (dvl_status st = b.alloc(arrays[k].bytes, arrays[k].what)) return st;
+            *arrays[k].to = b.release();
+            v->bytes += arrays[k].bytes;
+        }
+    }
+    if (v->slab) scratch->spare_bytes = v->slab_size - (size_t)(scratch->spare - v->slab);
+    return DVL_OK;
+}
+
+// Fill the sorted arrays and statistics of a volume in one pass from the given
+// arrays (original order, or a contiguous range of another volume's sorted
+// arrays: perm NULL).  `ranges` (host-readable, a uint2 per field and one
+// more) receives the data ranges and `flag`; `range_part` is device scratch of
+// 8 bytes per field and tile.
 static dvl_status place_volume(dvl_volume* v, const uint32_t* perm, const uint8_t* level, const void* const* fields,
-                               uint2* range_part, unsigned int* ranges, hipStream_t s) {
-    const Alloc& A = v->alloc;
-    const int eb = elem_bytes_of(v->dtype);
-    const int64_t n_steps = v->n_pad / kStepCells;
+                               uint2* range_part, uint2* ranges, const unsigned long long* flag, hipStream_t s) {
     PlaceArrays pa{};
     pa.n_fields = v->M;
-    {
-        DevBuf lv(A), lc(A);
-        if (dvl_status st = lv.alloc((size_t)v->n_pad, "sorted levels")) return st;
-        v->level_s = (uint8_t*)lv.release();
-        v->bytes += (size_t)v->n_pad;
-        if (dvl_status st = lc.alloc((size_t)n_steps * 4, "level codes")) return st;
-        v->lcode_s = (uint32_t*)lc.release();
-        v->bytes += (size_t)n_steps * 4;
-    }
     pa.level_src = level;
     pa.level_dst = v->level_s;
     pa.codes = v->lcode_s;
     for (int m = 0; m < v->M; ++m) {
-        DevBuf fb(A);
-        if (dvl_status st = fb.alloc((size_t)v->n_pad * eb, "sorted field")) return st;
-        v->fields_s[m] = fb.release();
-        v->bytes += (size_t)v->n_pad * eb;
         pa.src[m] = fields[m];
         pa.dst[m] = v->fields_s[m];
     }
-    DevBuf ts(A), ss(A);
-    const size_t tile_bytes = (size_t)v->M * v->n_tiles * sizeof(FieldStat);
-    const size_t seg_bytes = tile_bytes * v->tile_steps * kSegsPerStep;
-    if (dvl_status st = ts.alloc(tile_bytes, "tile statistics")) return st;
-    if (dvl_status st = ss.alloc(seg_bytes, "segment statistics")) return st;
-    v->tile_stat = (FieldStat*)ts.release();
-    v->seg_stat = (FieldStat*)ss.release();
-    v->bytes += tile_bytes + seg_bytes;
-    return launch_place(v->n, v->dtype, v->tile_steps, perm, pa, place_stats(v, range_part), ranges, s);
-}
-
-// scratch of dvl_set_field's range check: the result (4 words), then the partial ranges
-static dvl_status alloc_range_scratch(dvl_volume* v) {
-    DevBuf sr(v->alloc);
-    const size_t bytes = 256 + range_scratch_bytes();
-    if (dvl_status st = sr.alloc(bytes, "range scratch")) return st;
-    v->scratch_range = (unsigned int*)sr.release();
-    v->bytes += bytes;
-    return DVL_OK;
+    return launch_place(v->n, v->dtype, v->tile_steps, perm, pa, place_stats(v, range_part), ranges, flag, s);
 }
 
 extern "C" {
@@ -1205,12 +1282,21 @@ dvl_status dvl_build_order_ex(int64_t n, const int32_t* x, const int32_t* y, con
         v->n_runs = (v->n_tiles + v->tiles_per_run - 1) / v->tiles_per_run;
     }
 
+    HostPage page;
+    if (dvl_status st = page.take()) return st;
+    BuildScratch scratch;
+    if (dvl_status st = alloc_arrays(v, &scratch)) return st;
+    DevBuf small(A), tmp(A);
+    if (!scratch.small) {
+        if (dvl_status st = small.alloc(build_small_bytes(v), "build scratch")) return st;
+        scratch.small = (char*)small.p;
+    }
+
     // extent, validity, grid bits
-    DevBuf ext(A);
-    if (dvl_status st = ext.alloc(256 + extent_scratch_bytes(), "extent")) return st;
-    if (dvl_status st = launch_extent(n, x, y, z, level, (unsigned long long*)ext.p, (char*)ext.p + 256, s)) return st;
-    unsigned long long eh[4] = {};
-    DVL_HIP(hipMemcpyAsync(eh, ext.p, sizeof eh, hipMemcpyDeviceToHost, s));
+    unsigned long long* eh = (unsigned long long*)page.p;
+    unsigned long long* dup = (unsigned long long*)scratch.small;
+    uint2* range_part = (uint2*)(scratch.small + al256(256 + extent_scratch_bytes()));
+    if (dvl_status st = launch_extent(n, x, y, z, level, eh, dup, scratch.small + 256, s)) return st;
     DVL_HIP(hipStreamSynchronize(s));
     if (eh[1]) return fail(DVL_E_RANGE, "a cell has a negative corner or a level above 20");
     int bits = 1;
@@ -1219,43 +1305,40 @@ dvl_status dvl_build_order_ex(int64_t n, const int32_t* x, const int32_t* y, con
     v->bits = bits;
     v->max_level = (int)eh[2];
 
-    // keys + sort
+    // keys + sort, between the volume's own arrays and a second pair of
+    // buffers (the spare arrays where they are large enough, else one
+    // temporary allocation), so that the sorted pair ends in the volume's
     const SortPlan sp = sort_plan(n, 3 * bits);
-    DevBuf ka(A), kb(A), va(A), vb(A), counts(A);
-    if (dvl_status st = ka.alloc((size_t)n * 8, "keys")) return st;
-    if (dvl_status st = kb.alloc((size_t)n * 8, "keys (sort buffer)")) return st;
-    if (dvl_status st = va.alloc((size_t)n * 4, "permutation")) return st;
-    if (!sp.packed)
-        if (dvl_status st = vb.alloc((size_t)n * 4, "permutation (sort buffer)")) return st;
-    if (dvl_status st = counts.alloc(sp.scratch_bytes, "sort counts")) return st;
+    const size_t key_bytes = al256((size_t)n * 8), idx_bytes = sp.packed ? 0 : al256((size_t)n * 4);
+    char* second = scratch.spare;
+    const size_t second_bytes = key_bytes + idx_bytes + sp.scratch_bytes;
+    if (second_bytes > scratch.spare_bytes) {
+        if (dvl_status st = tmp.alloc(second_bytes, "sort buffers")) return st;
+        second = (char*)tmp.p;
+    }
+    uint64_t* keys_t = (uint64_t*)second;
+    uint32_t* perm_t = sp.packed ? nullptr : (uint32_t*)(second + key_bytes);
+    uint32_t* counts = (uint32_t*)(second + key_bytes + idx_bytes);
+    const bool odd = sp.passes & 1;      // an odd number of passes ends in the second pair
     bool in_second = false;
-    if (dvl_status st = launch_order(sp, n, x, y, z, level, bits, (uint64_t*)ka.p, (uint64_t*)kb.p, (uint32_t*)va.p,
-                                     (uint32_t*)vb.p, (uint32_t*)counts.p, s, &in_second))
+    if (dvl_status st = launch_order(sp, n, x, y, z, level, bits, odd ? keys_t : v->keys_s, odd ? v->keys_s : keys_t,
+                                     odd && !sp.packed ? perm_t : v->perm, odd && !sp.packed ? v->perm : perm_t, counts, s,
+                                     &in_second))
         return st;
-    uint64_t* ksorted = (uint64_t*)(in_second ? kb.p : ka.p);
-    unsigned long long* dup = (unsigned long long*)ext.p + 3;   // zeroed with the extent
-    if (dvl_status st = launch_dup(n, ksorted, dup, s)) return st;
-    // keep the sorted pair, free the other
-    v->keys_s = (uint64_t*)(in_second ? kb.release() : ka.release());
-    v->perm = (uint32_t*)(in_second && !sp.packed ? vb.release() : va.release());
-    v->bytes += (size_t)n * 12;
+    if (in_second != odd) return fail(DVL_E_HIP, "sort passes disagree with their plan");
+    if (dvl_status st = launch_dup(n, v->keys_s, dup, s)) return st;
 
     // sorted arrays (padded to whole tiles), statistics and data ranges
-    DevBuf rng(A), part(A);
-    if (dvl_status st = rng.alloc((size_t)kMaxFields * 4 * sizeof(unsigned int), "ranges")) return st;
-    if (dvl_status st = part.alloc((size_t)M * v->n_tiles * sizeof(uint2), "partial ranges")) return st;
-    if (dvl_status st = place_volume(v, v->perm, level, fields, (uint2*)part.p, (unsigned int*)rng.p, s)) return st;
-    unsigned int rh[kMaxFields * 4] = {};
-    DVL_HIP(hipMemcpyAsync(eh, dup, sizeof eh[0], hipMemcpyDeviceToHost, s));
-    DVL_HIP(hipMemcpyAsync(rh, rng.p, (size_t)M * 4 * sizeof rh[0], hipMemcpyDeviceToHost, s));
+    uint2* rh = (uint2*)page.p;
+    if (dvl_status st = place_volume(v, v->perm, level, fields, range_part, rh, dup, s)) return st;
     DVL_HIP(hipStreamSynchronize(s));
-    if (eh[0]) return fail(DVL_E_OVERLAP, "two cells share a Hilbert key (overlapping AMR cells)");
+    page.idle = small.idle = tmp.idle = true;
+    if (rh[M].x) return fail(DVL_E_OVERLAP, "two cells share a Hilbert key (overlapping AMR cells)");
     for (int m = 0; m < M; ++m) {
-        if (rh[m * 4 + 2]) return fail(DVL_E_RANGE, "field %d holds a NaN", m);
-        v->dmin[m] = unkey(rh[m * 4]);
-        v->dmax[m] = unkey(rh[m * 4 + 1]);
+        if (rh[m].y == kRangeNan) return fail(DVL_E_RANGE, "field %d holds a NaN", m);
+        v->dmin[m] = unkey(rh[m].x);
+        v->dmax[m] = unkey(rh[m].y);
     }
-    if (dvl_status st = alloc_range_scratch(v)) return st;
     DVL_HIP(hipEventCreateWithFlags(&v->cache_ready, hipEventDisableTiming));
 
     // private executor of dvl_update, with the workspace of one request ready
@@ -1281,11 +1364,19 @@ dvl_status dvl_set_field(dvl_volume* v, int32_t m, const void* values, void* str
     // The data range (and the NaN check) does not depend on the order, so it
     // is taken from the new values as given, before anything of the volume
     // changes: a rejected field leaves the volume as it was.
-    unsigned int r[4] = {};
-    if (dvl_status st = launch_range(v->n, v->dtype, values, v->scratch_range, (char*)v->scratch_range + 256, s)) return st;
-    DVL_HIP(hipMemcpyAsync(r, v->scratch_range, sizeof r, hipMemcpyDeviceToHost, s));
+    HostPage page;
+    if (dvl_status st = page.take()) return st;
+    uint2* part = (uint2*)page.p;
+    int n_part = 0;
+    if (dvl_status st = launch_range(v->n, v->dtype, values, part, &n_part, s)) return st;
     DVL_HIP(hipStreamSynchronize(s));
-    if (r[2]) return fail(DVL_E_RANGE, "field %d holds a NaN; the volume is unchanged", m);
+    page.idle = true;
+    uint32_t r_lo = 0xFFFFFFFFu, r_hi = 0u;
+    for (int i = 0; i < n_part; ++i) {
+        r_lo = std::min(r_lo, part[i].x);
+        r_hi = std::max(r_hi, part[i].y);
+    }
+    if (r_hi == kRangeNan) return fail(DVL_E_RANGE, "field %d holds a NaN; the volume is unchanged", m);
     v->idx_valid = false;      // the cached entries describe the old values
     v->cand_set = false;
     PlaceArrays pa{};
@@ -1293,12 +1384,12 @@ dvl_status dvl_set_field(dvl_volume* v, int32_t m, const void* values, void* str
     pa.first_field = m;
     pa.src[0] = values;
     pa.dst[0] = v->fields_s[m];
-    if (dvl_status st = launch_place(v->n, v->dtype, v->tile_steps, v->perm, pa, place_stats(v, nullptr), nullptr, s)) {
+    if (dvl_status st = launch_place(v->n, v->dtype, v->tile_steps, v->perm, pa, place_stats(v, nullptr), nullptr, nullptr, s)) {
         v->sticky = st;
         return st;
     }
-    v->dmin[m] = unkey(r[0]);
-    v->dmax[m] = unkey(r[1]);
+    v->dmin[m] = unkey(r_lo);
+    v->dmax[m] = unkey(r_hi);
     return DVL_OK;
 }
 
@@ -1571,15 +1662,33 @@ dvl_status dvl_select_bins(const dvl_volume* v, const dvl_bins* bins, int32_t W,
     if (dvl_status st = check_bins_of(v, bins, W)) return st;
     if (b0 < 0 || b1 < b0 || b1 >= W) return fail(DVL_E_INVALID, "bin range [%d, %d] outside [0, %d)", b0, b1, W);
     hipStream_t s = (hipStream_t)stream;
+    int dev = -1;
+    DVL_HIP(hipGetDevice(&dev));
     uint32_t f = 0, l = 0;
-    DVL_HIP(hipMemcpyAsync(&f, bins->first_cell + b0, 4, hipMemcpyDeviceToHost, s));
-    DVL_HIP(hipMemcpyAsync(&l, bins->last_cell + b1, 4, hipMemcpyDeviceToHost, s));
-    DVL_HIP(hipStreamSynchronize(s));
-    if (f > l || (int64_t)l >= v->n) return fail(DVL_E_STATE, "the bins do not hold a cell range of this volume");
     uint64_t klo = 0, khi = 0;
-    DVL_HIP(hipMemcpyAsync(&klo, v->keys_s + f, 8, hipMemcpyDeviceToHost, s));
-    DVL_HIP(hipMemcpyAsync(&khi, v->keys_s + l, 8, hipMemcpyDeviceToHost, s));
-    DVL_HIP(hipStreamSynchronize(s));
+    if (dev == v->device) {
+        HostPage page;
+        if (dvl_status st = page.take()) return st;
+        uint64_t* got = (uint64_t*)page.p;
+        if (dvl_status st = launch_pick(bins->first_cell, bins->last_cell, b0, b1, v->n, v->keys_s, got, s)) return st;
+        DVL_HIP(hipStreamSynchronize(s));
+        page.idle = true;
+        f = (uint32_t)got[0];
+        l = (uint32_t)(got[0] >> 32);
+        klo = got[1];
+        khi = got[2];
+    } else {
+        // another device is current: copies find their way, a kernel would not
+        DVL_HIP(hipMemcpyAsync(&f, bins->first_cell + b0, 4, hipMemcpyDeviceToHost, s));
+        DVL_HIP(hipMemcpyAsync(&l, bins->last_cell + b1, 4, hipMemcpyDeviceToHost, s));
+        DVL_HIP(hipStreamSynchronize(s));
+        if (f <= l && (int64_t)l < v->n) {
+            DVL_HIP(hipMemcpyAsync(&klo, v->keys_s + f, 8, hipMemcpyDeviceToHost, s));
+            DVL_HIP(hipMemcpyAsync(&khi, v->keys_s + l, 8, hipMemcpyDeviceToHost, s));
+            DVL_HIP(hipStreamSynchronize(s));
+        }
+    }
+    if (f > l || (int64_t)l >= v->n) return fail(DVL_E_STATE, "the bins do not hold a cell range of this volume");
     if (first) *first = f;
     if (last) *last = l;
     if (key_lo) *key_lo = klo;
@@ -1674,31 +1783,29 @@ dvl_status dvl_zoom(const dvl_volume* v, uint32_t first, uint32_t last, const dv
         z->tiles_per_run = std::max<int64_t>(1, (z->n_tiles + waves - 1) / waves);
         z->n_runs = (z->n_tiles + z->tiles_per_run - 1) / z->tiles_per_run;
     }
-    // the range's keys, an identity permutation (its original order is the range)
-    {
-        DevBuf kb(A), pb(A);
-        if (dvl_status st = kb.alloc((size_t)n * 8, "keys")) return st;
-        if (dvl_status st = pb.alloc((size_t)n * 4, "permutation")) return st;
-        DVL_HIP(hipMemcpyAsync(kb.p, v->keys_s + first, (size_t)n * 8, hipMemcpyDeviceToDevice, s));
-        if (dvl_status st = launch_iota(n, (uint32_t*)pb.p, s)) return st;
-        z->keys_s = (uint64_t*)kb.release();
-        z->perm = (uint32_t*)pb.release();
-        z->bytes += (size_t)n * 12;
+    HostPage page;
+    if (dvl_status st = page.take()) return st;
+    BuildScratch scratch;
+    if (dvl_status st = alloc_arrays(z, &scratch)) return st;
+    DevBuf small(A);
+    if (!scratch.small) {
+        if (dvl_status st = small.alloc(build_small_bytes(z), "build scratch")) return st;
+        scratch.small = (char*)small.p;
     }
-    DevBuf rng(A), part(A);
-    if (dvl_status st = rng.alloc((size_t)kMaxFields * 4 * sizeof(unsigned int), "ranges")) return st;
-    if (dvl_status st = part.alloc((size_t)z->M * z->n_tiles * sizeof(uint2), "partial ranges")) return st;
+    uint2* range_part = (uint2*)(scratch.small + al256(256 + extent_scratch_bytes()));
+    // the range's keys, an identity permutation (its original order is the range)
+    DVL_HIP(hipMemcpyAsync(z->keys_s, v->keys_s + first, (size_t)n * 8, hipMemcpyDeviceToDevice, s));
+    if (dvl_status st = launch_iota(n, z->perm, s)) return st;
     const void* src[kMaxFields] = {};
     for (int m = 0; m < z->M; ++m) src[m] = (const char*)v->fields_s[m] + (size_t)first * eb;
-    if (dvl_status st = place_volume(z, nullptr, v->level_s + first, src, (uint2*)part.p, (unsigned int*)rng.p, s)) return st;
-    unsigned int rh[kMaxFields * 4] = {};
-    DVL_HIP(hipMemcpyAsync(rh, rng.p, (size_t)z->M * 4 * sizeof rh[0], hipMemcpyDeviceToHost, s));
+    uint2* rh = (uint2*)page.p;
+    if (dvl_status st = place_volume(z, nullptr, v->level_s + first, src, range_part, rh, nullptr, s)) return st;
     DVL_HIP(hipStreamSynchronize(s));
+    page.idle = small.idle = true;
     for (int m = 0; m < z->M; ++m) {
-        z->dmin[m] = unkey(rh[m * 4]);
-        z->dmax[m] = unkey(rh[m * 4 + 1]);
+        z->dmin[m] = unkey(rh[m].x);
+        z->dmax[m] = unkey(rh[m].y);
     }
-    if (dvl_status st = alloc_range_scratch(z)) return st;
     DVL_HIP(hipEventCreateWithFlags(&z->cache_ready, hipEventDisableTiming));
     if (dvl_status st = new_executor(A, &z->ex)) return st;
     if (dvl_status st = z->ex->ensure_ws(0, request_ws_bytes(z, 1))) return st;
@@ -1729,11 +1836,10 @@ dvl_status dvl_set_entry_cache(dvl_volume* v, int32_t policy) {
     v->idx_policy = policy;
     if (policy == DVL_ENTRY_CACHE_NEVER) {
         DVL_HIP(hipDeviceSynchronize());   // queued updates may still read it
-        for (int m = 0; m < kMaxFields; ++m) {
-            if (!v->idx_s[m]) continue;
-            v->alloc.put(v->idx_s[m], nullptr);
-            v->idx_s[m] = nullptr;
-            v->bytes -= (size_t)v->n_pad;
+        if (v->idx_s[0]) {
+            v->alloc.put(v->idx_s[0], nullptr);
+            for (int m = 0; m < kMaxFields; ++m) v->idx_s[m] = nullptr;
+            v->bytes -= (size_t)v->n_pad * v->M;
         }
         v->idx_valid = false;
         v->cand_set = false;
@@ -1777,15 +1883,18 @@ void dvl_destroy(dvl_volume* v) {
     (void)hipDeviceSynchronize();
     delete v->ex;
     const Alloc& A = v->alloc;
-    A.put(v->level_s, nullptr);
-    A.put(v->lcode_s, nullptr);
-    for (int m = 0; m < kMaxFields; ++m) A.put(v->fields_s[m], nullptr);
-    A.put(v->keys_s, nullptr);
-    A.put(v->perm, nullptr);
-    A.put(v->tile_stat, nullptr);
-    A.put(v->seg_stat, nullptr);
-    A.put(v->scratch_range, nullptr);
-    for (int m = 0; m < kMaxFields; ++m) A.put(v->idx_s[m], nullptr);
+    if (v->slab) {
+        (void)hipFree(v->slab);
+    } else {
+        A.put(v->level_s, nullptr);
+        A.put(v->lcode_s, nullptr);
+        for (int m = 0; m < kMaxFields; ++m) A.put(v->fields_s[m], nullptr);
+        A.put(v->keys_s, nullptr);
+        A.put(v->perm, nullptr);
+        A.put(v->tile_stat, nullptr);
+        A.put(v->seg_stat, nullptr);
+    }
+    A.put(v->idx_s[0], nullptr);
     if (v->cache_ready) (void)hipEventDestroy(v->cache_ready);
     if (v->read_stage) (void)hipHostFree(v->read_stage);
     delete v;

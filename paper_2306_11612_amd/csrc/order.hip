@@ -21,7 +21,7 @@ namespace dvl {
 // 142 + 6 us like this.)
 // ===================================================================
 constexpr int kReduceThreads = 256;
-constexpr int kReduceBlocks = 2048;   // at most; two words of partial result each
+constexpr int kReduceBlocks = kRangeParts;   // at most
 
 struct ExtentPart {
     unsigned long long upper;    // max(corner + 2^level)
@@ -89,9 +89,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_extent(int64_t n, const int3
     if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
 
-// out: [0] max upper corner, [1] bad, [2] max level, [3] 0 (the duplicate flag of k_dup)
+// out (pinned host memory): [0] max upper corner, [1] bad, [2] max level; dup:
+// the duplicate flag of k_dup, cleared
 __global__ __launch_bounds__(1024) void k_extent_fold(int n_part, const ExtentPart* __restrict__ part,
-                                                      unsigned long long* __restrict__ out) {
+                                                      unsigned long long* __restrict__ out,
+                                                      unsigned long long* __restrict__ dup) {
     int64_t mx = 0;
     uint32_t bad = 0, lmax = 0;
     for (int i = threadIdx.x; i < n_part; i += blockDim.x) {
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(1024) void k_extent_fold(int n_part, const ExtentPa
         out[0] = r.upper;
         out[1] = r.bad;
         out[2] = r.level;
-        out[3] = 0ull;
+        *dup = 0ull;
     }
 }
 
@@ -625,8 +627,6 @@ __global__ __launch_bounds__(256) void k_dup(int64_t n, const uint64_t* __restri
 // ===================================================================
 // data ranges: order-preserving unsigned keys of floats, a NaN above them all
 // ===================================================================
-constexpr uint32_t kRangeNan = 0xFFFFFFFFu;   // above the key of +inf
-
 __device__ __forceinline__ void range_add(float f, uint32_t& lo, uint32_t& hi) {
     uint32_t u = __float_as_uint(f);
     u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
@@ -684,10 +684,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_range(int64_t n, const typen
     if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
 
-// Workgroup m folds the n_part partial ranges part[m * n_part ..] of field m:
-// out[4 m] = min key, [4 m + 1] = max key, [4 m + 2] = NaN seen.
+// Workgroup m folds the n_part partial ranges part[m * n_part ..] of field m
+// into out[m] (pinned host memory); flag (optional): copied behind them.
 __global__ __launch_bounds__(1024) void k_range_fold(int64_t n_part, const uint2* __restrict__ part,
-                                                     unsigned int* __restrict__ out) {
+                                                     uint2* __restrict__ out,
+                                                     const unsigned long long* __restrict__ flag) {
     __shared__ uint2 sh[1024 / kWave];
     const uint2* p = part + (int64_t)blockIdx.x * n_part;
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
@@ -698,9 +699,8 @@ __global__ __launch_bounds__(1024) void k_range_fold(int64_t n_part, const uint2
     }
     const uint2 r = range_block(lo, hi, sh);
     if (threadIdx.x == 0) {
-        out[4 * blockIdx.x] = r.x;
-        out[4 * blockIdx.x + 1] = r.y;
-        out[4 * blockIdx.x + 2] = r.y == kRangeNan;
+        out[blockIdx.x] = r;
+        if (blockIdx.x == 0 && flag) out[gridDim.x] = make_uint2((uint32_t)(*flag != 0ull), 0u);
     }
 }
 
@@ -897,15 +897,15 @@ static bool vec4_inputs(const int32_t* x, const int32_t* y, const int32_t* z, co
 
 size_t extent_scratch_bytes() { return (size_t)kReduceBlocks * sizeof(ExtentPart); }
 
-dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
-                         const uint8_t* level, unsigned long long* out, void* scratch, hipStream_t s) {
+dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z, const uint8_t* level,
+                         unsigned long long* out, unsigned long long* dup, void* scratch, hipStream_t s) {
     ExtentPart* part = reinterpret_cast<ExtentPart*>(scratch);
     const unsigned grid = grid_for((n + 3) / 4, kReduceThreads, kReduceBlocks);
     if (vec4_inputs(x, y, z, level))
         hipLaunchKernelGGL(k_extent<true>, dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
     else
         hipLaunchKernelGGL(k_extent<false>, dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
-    hipLaunchKernelGGL(k_extent_fold, dim3(1), dim3(1024), 0, s, (int)grid, part, out);
+    hipLaunchKernelGGL(k_extent_fold, dim3(1), dim3(1024), 0, s, (int)grid, part, out, dup);
     DVL_HIP(hipGetLastError());
     return DVL_OK;
 }
@@ -996,8 +996,6 @@ dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sort
     return DVL_OK;
 }
 
-size_t range_scratch_bytes() { return (size_t)kReduceBlocks * sizeof(uint2); }
-
 template <typename S>
 static void range_of(int64_t n, const void* v, uint2* part, unsigned grid, hipStream_t s) {
     const auto* p = reinterpret_cast<const typename S::raw*>(v);
@@ -1007,8 +1005,7 @@ static void range_of(int64_t n, const void* v, uint2* part, unsigned grid, hipSt
         hipLaunchKernelGGL((k_range<S, false>), dim3(grid), dim3(kReduceThreads), 0, s, n, p, part);
 }
 
-dvl_status launch_range(int64_t n, int dtype, const void* v, unsigned int* out, void* scratch, hipStream_t s) {
-    uint2* part = reinterpret_cast<uint2*>(scratch);
+dvl_status launch_range(int64_t n, int dtype, const void* v, uint2* part, int* n_part, hipStream_t s) {
     const unsigned grid = grid_for((n + 3) / 4, kReduceThreads, kReduceBlocks);
     if (dtype == DVL_F32)
         range_of<F32>(n, v, part, grid, s);
@@ -1016,8 +1013,8 @@ dvl_status launch_range(int64_t n, int dtype, const void* v, unsigned int* out, 
         range_of<F16>(n, v, part, grid, s);
     else
         range_of<BF16>(n, v, part, grid, s);
-    hipLaunchKernelGGL(k_range_fold, dim3(1), dim3(1024), 0, s, (int64_t)grid, part, out);
     DVL_HIP(hipGetLastError());
+    *n_part = (int)grid;
     return DVL_OK;
 }
 
@@ -1032,7 +1029,7 @@ static void place_typed(int64_t n, int tile_steps, const uint32_t* perm, const P
 }
 
 dvl_status launch_place(int64_t n, int dtype, int tile_steps, const uint32_t* perm, const PlaceArrays& a,
-                        const PlaceStats& st, unsigned int* ranges, hipStream_t s) {
+                        const PlaceStats& st, uint2* ranges, const unsigned long long* flag, hipStream_t s) {
     const int64_t units = st.n_tiles * (a.n_fields + (a.level_src ? 1 : 0));
     const unsigned grid = (unsigned)std::min<int64_t>(units, (int64_t)1 << 23);   // below 2^32 work-items
     if (dtype == DVL_F32)
@@ -1043,7 +1040,7 @@ dvl_status launch_place(int64_t n, int dtype, int tile_steps, const uint32_t* pe
         place_typed<BF16>(n, tile_steps, perm, a, st, grid, s);
     DVL_HIP(hipGetLastError());
     if (ranges) {
-        hipLaunchKernelGGL(k_range_fold, dim3(a.n_fields), dim3(1024), 0, s, st.n_tiles, st.range, ranges);
+        hipLaunchKernelGGL(k_range_fold, dim3(a.n_fields), dim3(1024), 0, s, st.n_tiles, st.range, ranges, flag);
         DVL_HIP(hipGetLastError());
     }
     return DVL_OK;

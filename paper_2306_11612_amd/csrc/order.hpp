@@ -5,11 +5,12 @@
 
 namespace dvl {
 
-// out: [0] max(corner + 2^level), [1] a cell fails the checks, [2] max level, [3] zeroed;
-// scratch: extent_scratch_bytes() of device memory
+// out (memory the host can read once the stream is synchronised):
+// [0] max(corner + 2^level), [1] a cell fails the checks, [2] max level;
+// dup: device word, zeroed; scratch: extent_scratch_bytes() of device memory
 size_t extent_scratch_bytes();
-dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
-                         const uint8_t* level, unsigned long long* out, void* scratch, hipStream_t s);
+dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const int32_t* z, const uint8_t* level,
+                         unsigned long long* out, unsigned long long* dup, void* scratch, hipStream_t s);
 // The ordering of n cells with keys of key_bits bits: sort layout and scratch.
 struct SortPlan {
     int64_t n_tiles, n_chunks;
@@ -31,10 +32,12 @@ dvl_status launch_order(const SortPlan& p, int64_t n, const int32_t* x, const in
 dvl_status launch_dup(int64_t n, const uint64_t* keys, unsigned long long* flag, hipStream_t s);
 dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sorted, void* orig,
                                int elem_bytes, hipStream_t s);
-// out[0] = min, out[1] = max as order-preserving uint keys, out[2] = NaN seen;
-// scratch: range_scratch_bytes() of device memory
-size_t range_scratch_bytes();
-dvl_status launch_range(int64_t n, int dtype, const void* v, unsigned int* out, void* scratch, hipStream_t s);
+// Partial ranges of n values: part[i] = (min, max) as order-preserving uint
+// keys for i < *n_part <= kRangeParts, max = kRangeNan where there is a NaN.
+// part: memory the host can read once the stream is synchronised.
+constexpr int kRangeParts = 1024;
+constexpr uint32_t kRangeNan = 0xFFFFFFFFu;   // above the key of +inf
+dvl_status launch_range(int64_t n, int dtype, const void* v, uint2* part, int* n_part, hipStream_t s);
 
 // The sorted arrays of a volume: fields src -> dst (statistics rows
 // first_field ..) and, when level_src is not NULL, the levels and their codes.
@@ -56,8 +59,10 @@ struct PlaceStats {
     uint2* range;            // [n_fields][n_tiles] range keys per tile, or NULL
 };
 // sorted cell i from original cell perm[i], or from src[i] when perm is NULL;
-// ranges (optional, needs st.range and first_field 0): per field as launch_range
+// ranges (optional, needs st.range and first_field 0): per field as
+// launch_range, then, with `flag`, whether that device word is set; memory the
+// host can read once the stream is synchronised
 dvl_status launch_place(int64_t n, int dtype, int tile_steps, const uint32_t* perm, const PlaceArrays& a,
-                        const PlaceStats& st, unsigned int* ranges, hipStream_t s);
+                        const PlaceStats& st, uint2* ranges, const unsigned long long* flag, hipStream_t s);
 
 }  // namespace dvl

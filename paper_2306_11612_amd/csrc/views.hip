@@ -145,6 +145,25 @@ dvl_status launch_select_mask(int64_t n, const uint64_t* keys_sorted, const uint
     return DVL_OK;
 }
 
+// The cell range of bins b0 .. b1 and its keys, into memory the host can read
+// once the stream is synchronised: out[0] = first | last << 32, [1], [2] = keys
+// (0 when the range is no range of the volume).
+__global__ void k_pick(const uint32_t* first_cell, const uint32_t* last_cell, int b0, int b1, int64_t n,
+                       const uint64_t* keys_sorted, uint64_t* out) {
+    const uint32_t f = first_cell[b0], l = last_cell[b1];
+    const bool ok = f <= l && (int64_t)l < n;
+    out[0] = (uint64_t)f | ((uint64_t)l << 32);
+    out[1] = ok ? keys_sorted[f] : 0ull;
+    out[2] = ok ? keys_sorted[l] : 0ull;
+}
+
+dvl_status launch_pick(const uint32_t* first_cell, const uint32_t* last_cell, int b0, int b1, int64_t n,
+                       const uint64_t* keys_sorted, uint64_t* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_pick, dim3(1), dim3(1), 0, st, first_cell, last_cell, b0, b1, n, keys_sorted, out);
+    DVL_HIP(hipGetLastError());
+    return DVL_OK;
+}
+
 // ------------------------------------------------------------------ bins to the host
 
 // The arrays of an update's bins written one after another into pinned host

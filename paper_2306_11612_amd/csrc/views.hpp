@@ -25,6 +25,9 @@ dvl_status launch_select_mask(int64_t n, const uint64_t* keys_sorted, const uint
 // out[i] = i
 dvl_status launch_iota(int64_t n, uint32_t* out, hipStream_t st);
 
+// out[0] = first_cell[b0] | last_cell[b1] << 32, out[1], out[2] = their keys
+dvl_status launch_pick(const uint32_t* first_cell, const uint32_t* last_cell, int b0, int b1, int64_t n,
+                       const uint64_t* keys_sorted, uint64_t* out, hipStream_t st);
 // n arrays of 32-bit words, array a copied to out + at[a] (out: host memory
 // the device can write, complete once the stream is synchronised)
 struct PackList {

@@ -181,8 +181,13 @@ def _check(status: int, where: str):
         raise DvlError(status, where, lib().dvl_last_error().decode(errors="replace"))
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream):
     if stream is None:
+        if _raw_stream is not None:      # the handle without a Stream object around it
+            return C.c_void_p(_raw_stream(torch.cuda.current_device()))
         stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
@@ -264,8 +269,7 @@ def build_order(x, y, z, level, fields, stream=None, tile_steps: int = 0, run_wa
 def set_tf(vol: "Volume", m: int, alpha, lo: float, hi: float):
     """dvl_set_tf: alpha TF of field m with normalisation window [lo, hi]."""
     a = np.ascontiguousarray(np.asarray(alpha, dtype=np.float32))
-    _check(lib().dvl_set_tf(vol.handle, int(m), a.ctypes.data_as(C.c_void_p), a.size,
-                            float(lo), float(hi)), "dvl_set_tf")
+    _check(lib().dvl_set_tf(vol.handle, int(m), a.ctypes.data, a.size, float(lo), float(hi)), "dvl_set_tf")
 
 
 def update(vol: "Volume", p: dvl_params, bins: Bins, stream=None):
