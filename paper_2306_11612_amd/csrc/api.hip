@@ -1720,7 +1720,7 @@ dvl_status dvl_bin_histograms(const dvl_volume* v, const dvl_bins* bins, int32_t
     float qs, qb;
     quantiser(n_buckets, lo, hi, &qs, &qb);
     if (!isfinite(qs) || !isfinite(qb)) return fail(DVL_E_INVALID, "window [%g, %g] is too narrow for fp32", lo, hi);
-    return launch_bin_histograms(v->dtype, v->fields_s[m], W, bins->first_cell, bins->last_cell, n_buckets, qs, qb,
+    return launch_bin_histograms(v->dtype, v->fields_s[m], v->n, W, bins->first_cell, bins->last_cell, n_buckets, qs, qb,
                                  counts, v->n_cu, (hipStream_t)stream);
 }
 

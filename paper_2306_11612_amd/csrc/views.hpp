@@ -11,7 +11,7 @@ constexpr int kRasterBars = 1;       // column b spans rows 0 .. the row of heig
 
 // counts[b * H + k]: cells first[b]..last[b] of the sorted field whose
 // entry under the quantiser (s, b) of H buckets is k
-dvl_status launch_bin_histograms(int dtype, const void* field, int32_t W, const uint32_t* first,
+dvl_status launch_bin_histograms(int dtype, const void* field, int64_t n, int32_t W, const uint32_t* first,
                                  const uint32_t* last, int32_t H, float s, float b, uint32_t* counts,
                                  int n_cu, hipStream_t st);
 // img[l][r][b] for `lines` lines of W heights each, H rows
