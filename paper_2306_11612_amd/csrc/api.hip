@@ -1793,9 +1793,7 @@ dvl_status dvl_zoom(const dvl_volume* v, uint32_t first, uint32_t last, const dv
         scratch.small = (char*)small.p;
     }
     uint2* range_part = (uint2*)(scratch.small + al256(256 + extent_scratch_bytes()));
-    // the range's keys, an identity permutation (its original order is the range)
-    DVL_HIP(hipMemcpyAsync(z->keys_s, v->keys_s + first, (size_t)n * 8, hipMemcpyDeviceToDevice, s));
-    if (dvl_status st = launch_iota(n, z->perm, s)) return st;
+    if (dvl_status st = launch_range_order(n, v->keys_s + first, z->keys_s, z->perm, s)) return st;
     const void* src[kMaxFields] = {};
     for (int m = 0; m < z->M; ++m) src[m] = (const char*)v->fields_s[m] + (size_t)first * eb;
     uint2* rh = (uint2*)page.p;

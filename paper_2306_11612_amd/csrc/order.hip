@@ -236,9 +236,9 @@ __device__ __forceinline__ void hilbert_keys(const uint16_t* table, uint32_t sta
 //              digits written to digit base + column scan + chunk row
 // Rows are tile-major, so counting writes and scattering reads whole rows.
 //
-// 50 M cells, 33-bit keys, MI355X: 4 passes of 102 (count) + 15 (columns) +
+// 50 M cells, 33-bit keys, MI355X: 4 passes of 102 (count) + 8 (columns) +
 // 187 us (scatter: 16 bytes per cell at 4.3 TB/s) after 242 us for the keys,
-// the first of them without its count: 1.35 ms.  With 12-byte pairs, 8-bit
+// the first of them without its count: 1.33 ms.  With 12-byte pairs, 8-bit
 // digits, counts in digit-major order and a scan over all of them it was 5
 // passes of 167 + 33 + 405 us after 285: 3.31 ms.
 // ===================================================================
@@ -423,28 +423,33 @@ __device__ __forceinline__ uint32_t block_excl_scan_u32(uint32_t v, uint32_t* sh
 }
 
 // Column scan of the chunk totals [n_chunks][1 << D], in place, and the digit
-// totals.  A workgroup takes 64 digits; its 16 waves take a sixteenth of the
-// rows each: sums first, then the exclusive prefixes.
-constexpr int kColumnWaves = 16;
+// totals.  A workgroup takes 16 digits (64-byte pieces of the rows); its 64
+// groups of 16 lanes take a 64th of the rows each: sums first, then the
+// exclusive prefixes.  Bound by the latency of its loads, so many groups with
+// 8 loads in flight each: 1110 rows of 512 digits 7.6 us (14.8 with 64 digits
+// per workgroup and 16 groups).
+constexpr int kColumnDigits = 16, kColumnGroups = 64;
 template <int D>
-__global__ __launch_bounds__(kColumnWaves * kWave) void k_columns(int64_t n_chunks, uint32_t* __restrict__ totals,
-                                                                  uint32_t* __restrict__ digits) {
-    __shared__ uint32_t part[kColumnWaves][kWave];
-    const int w = threadIdx.x / kWave, lane = lane_id();
-    const int d = blockIdx.x * kWave + lane;
-    const int64_t per = (n_chunks + kColumnWaves - 1) / kColumnWaves;
-    const int64_t r0 = min((int64_t)w * per, n_chunks), r1 = min(r0 + per, n_chunks);
+__global__ __launch_bounds__(kColumnDigits * kColumnGroups) void k_columns(int64_t n_chunks,
+                                                                           uint32_t* __restrict__ totals,
+                                                                           uint32_t* __restrict__ digits) {
+    __shared__ uint32_t part[kColumnGroups][kColumnDigits];
+    const int g = threadIdx.x / kColumnDigits, j = threadIdx.x % kColumnDigits;
+    const int d = blockIdx.x * kColumnDigits + j;
+    const int64_t per = (n_chunks + kColumnGroups - 1) / kColumnGroups;
+    const int64_t r0 = min(g * per, n_chunks), r1 = min(r0 + per, n_chunks);
     uint32_t sum = 0;
 #pragma unroll 8
     for (int64_t r = r0; r < r1; ++r) sum += totals[(r << D) + d];
-    part[w][lane] = sum;
+    part[g][j] = sum;
     __syncthreads();
     uint32_t run = 0, all = 0;
-    for (int q = 0; q < kColumnWaves; ++q) {
-        if (q < w) run += part[q][lane];
-        all += part[q][lane];
+#pragma unroll 16
+    for (int q = 0; q < kColumnGroups; ++q) {
+        if (q < g) run += part[q][j];
+        all += part[q][j];
     }
-    if (w == 0) digits[d] = all;
+    if (g == 0) digits[d] = all;
     int64_t r = r0;
     for (; r + 8 <= r1; r += 8) {
         uint32_t v[8];
@@ -949,7 +954,7 @@ static dvl_status sort_typed(const SortPlan& p, int64_t n, const int32_t* x, con
             hipLaunchKernelGGL(k_count<D>, chunks, thr, 0, s, n, ka, shift, p.chunk, p.n_tiles, rows, totals);
             DVL_HIP(hipGetLastError());
         }
-        hipLaunchKernelGGL(k_columns<D>, dim3((1 << D) / kWave), dim3(kColumnWaves * kWave), 0, s, p.n_chunks, totals,
+        hipLaunchKernelGGL(k_columns<D>, dim3((1 << D) / kColumnDigits), dim3(kColumnDigits * kColumnGroups), 0, s, p.n_chunks, totals,
                            digits);
         if (i + 1 == p.passes)
             hipLaunchKernelGGL((k_scatter<D, PACKED, true>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,

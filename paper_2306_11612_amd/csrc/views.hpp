@@ -22,8 +22,8 @@ dvl_status launch_rasterize(const float* y, int32_t W, int32_t H, int32_t lines,
 constexpr int kMaxSelectRanges = 128;
 dvl_status launch_select_mask(int64_t n, const uint64_t* keys_sorted, const uint32_t* perm, int32_t n_ranges,
                               const uint64_t* ranges, uint8_t* mask, hipStream_t st);
-// out[i] = i
-dvl_status launch_iota(int64_t n, uint32_t* out, hipStream_t st);
+// keys[i] = src[i], perm[i] = i
+dvl_status launch_range_order(int64_t n, const uint64_t* src, uint64_t* keys, uint32_t* perm, hipStream_t st);
 
 // out[0] = first_cell[b0] | last_cell[b1] << 32, out[1], out[2] = their keys
 dvl_status launch_pick(const uint32_t* first_cell, const uint32_t* last_cell, int b0, int b1, int64_t n,
