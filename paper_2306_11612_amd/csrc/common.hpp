@@ -64,7 +64,7 @@ __device__ __forceinline__ float dpp_row_shr_f(float v, int n) {
 // Inclusive wave64 sum scan: Hillis-Steele inside each row of 16 lanes via
 // DPP row shifts, then row totals combined through readlane.  The result is
 // NOT guaranteed monotone under rounding; callers that need monotone
-// prefixes follow it with wave_max_scan.
+// prefixes follow it with wave_incl_max.
 __device__ __forceinline__ float wave_incl_sum(float v) {
     v += dpp_row_shr_f(v, 1);
     v += dpp_row_shr_f(v, 2);
@@ -77,36 +77,34 @@ __device__ __forceinline__ float wave_incl_sum(float v) {
     return v + off;
 }
 
-__device__ __forceinline__ float dpp_row_shr_max(float v, int n) {
-    // source outside the row yields -0.0f-free neutral element: use the lane's own value
-    int r;
+// Inclusive wave64 running maximum of values that are no NaN and not below
+// -0.0f: they order as signed integers, whose maximum takes the row shift as
+// its operand (a float's needs a move beside it) and, for the row totals, runs
+// on the scalar unit.
+__device__ __forceinline__ int dpp_row_shr_lowest(int v, int n) {
     switch (n) {
-        case 1: r = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), DVL_DPP_ROW_SHR(1), 0xF, 0xF, false); break;
-        case 2: r = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), DVL_DPP_ROW_SHR(2), 0xF, 0xF, false); break;
-        case 4: r = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), DVL_DPP_ROW_SHR(4), 0xF, 0xF, false); break;
-        default: r = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), DVL_DPP_ROW_SHR(8), 0xF, 0xF, false); break;
+        case 1: return __builtin_amdgcn_update_dpp(INT32_MIN, v, DVL_DPP_ROW_SHR(1), 0xF, 0xF, false);
+        case 2: return __builtin_amdgcn_update_dpp(INT32_MIN, v, DVL_DPP_ROW_SHR(2), 0xF, 0xF, false);
+        case 4: return __builtin_amdgcn_update_dpp(INT32_MIN, v, DVL_DPP_ROW_SHR(4), 0xF, 0xF, false);
+        default: return __builtin_amdgcn_update_dpp(INT32_MIN, v, DVL_DPP_ROW_SHR(8), 0xF, 0xF, false);
     }
-    return __int_as_float(r);
 }
-
-// Inclusive wave64 running maximum.
-__device__ __forceinline__ float wave_incl_max(float v) {
-    v = fmaxf(v, dpp_row_shr_max(v, 1));
-    v = fmaxf(v, dpp_row_shr_max(v, 2));
-    v = fmaxf(v, dpp_row_shr_max(v, 4));
-    v = fmaxf(v, dpp_row_shr_max(v, 8));
-    const float r0 = readlane(v, 15), r1 = readlane(v, 31), r2 = readlane(v, 47);
+__device__ __forceinline__ float wave_incl_max(float f) {
+    int v = __float_as_int(f);
+    v = max(v, dpp_row_shr_lowest(v, 1));
+    v = max(v, dpp_row_shr_lowest(v, 2));
+    v = max(v, dpp_row_shr_lowest(v, 4));
+    v = max(v, dpp_row_shr_lowest(v, 8));
+    const int r0 = readlane(v, 15), r1 = readlane(v, 31), r2 = readlane(v, 47);
     const int row = lane_id() >> 4;
-    const float o2 = fmaxf(r0, r1), o3 = fmaxf(o2, r2);
-    const float off = row == 0 ? v : (row == 1 ? r0 : (row == 2 ? o2 : o3));
-    return fmaxf(v, off);
+    const int o2 = max(r0, r1), o3 = max(o2, r2);
+    const int off = row == 0 ? INT32_MIN : (row == 1 ? r0 : (row == 2 ? o2 : o3));
+    return __int_as_float(max(v, off));
 }
 
-// value of lane - 1 (lane 0 gets `first`)
-__device__ __forceinline__ float shfl_up1(float v, float first) {
-    const int l = lane_id();
-    int r = __builtin_amdgcn_ds_bpermute((l == 0 ? 0 : l - 1) << 2, __float_as_int(v));
-    return l == 0 ? first : __int_as_float(r);
+// value of lane - 1 (lane 0 gets `first`): the wave shift of the DPP
+__device__ __forceinline__ float wave_shr1(float v, float first) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(first), __float_as_int(v), 0x138, 0xF, 0xF, false));
 }
 
 __device__ __forceinline__ int shfl_up_i(int v, int d) {

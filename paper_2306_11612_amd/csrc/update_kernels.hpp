@@ -56,17 +56,23 @@ struct ImpCtx {
     int lshift;
 };
 
-__device__ __forceinline__ ImpCtx make_ctx(const ReqDev& q) {
+// In two steps: what the descriptor holds, read with a kernel's first loads,
+// and max V, whose load hangs behind them; a kernel issues it early too and
+// takes the value once its cells are on their way (read after the barrier that
+// follows the tables, both cost every workgroup two cold loads in a row).
+__device__ __forceinline__ ImpCtx ctx_params(const ReqDev& q) {
     ImpCtx c;
-    const float vm = uni(gload<float>(q.vmax_dev, 0));
-    c.inv_vmax = vm > 0.0f ? 1.0f / vm : 0.0f;
     c.fmin = uni(q.fmin);
     c.p = uni(q.exponent);
     c.exp_is_one = uni(q.exp_is_one);
     c.clamp_mode = uni(q.clamp_mode);
     c.lshift = uni(q.level_shift);
-    c.scalable = uni((int)(ldexpf(c.inv_vmax, 60) <= 3.0e38f)) != 0;
     return c;
+}
+__device__ __forceinline__ void ctx_vmax(ImpCtx& c, float vmax) {
+    const float vm = uni(vmax);
+    c.inv_vmax = vm > 0.0f ? 1.0f / vm : 0.0f;
+    c.scalable = uni((int)(ldexpf(c.inv_vmax, 60) <= 3.0e38f)) != 0;
 }
 
 // TF entry: clamp(floor(fma(x, s, b)), 0, n_tf - 1); the clamp is one
@@ -644,6 +650,13 @@ __device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, in
     const int64_t n = uni(vol.n);
     const int last_group = (nsteps - 1) / G * G;
     const RunView<MT> view = run_view<MT, D>(vol, M, c_begin);
+    const float vmax = gload<float>(q.vmax_dev, 0);
+    ImpCtx ctx = ctx_params(q);
+    float* const fst = uni(q.ws.fstore);      // where f of every cell is kept for the projection, or NULL
+    double* const lpre = uni(q.ws.local_prefix);
+    const int mode = uni(q.scan_mode);
+    Quant<MT> qn;
+    qn.load(q);
     // Two groups in flight, in buffers A and B that take turns: a buffer is
     // loaded again (unconditionally; past the run's end the last step is
     // reloaded) right after its group was used, so no loaded value is ever
@@ -663,13 +676,7 @@ __device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, in
         for (int g = 0; g < G; ++g) B[g].load(view, M, min(G + g, nsteps - 1), c1.c[g]);
     }
     tables();
-
-    Quant<MT> qn;
-    qn.load(q);
-    const ImpCtx ctx = make_ctx(q);
-    float* const fst = uni(q.ws.fstore);      // where f of every cell is kept for the projection, or NULL
-    double* const lpre = uni(q.ws.local_prefix);
-    const int mode = uni(q.scan_mode);
+    ctx_vmax(ctx, vmax);
     ModeSum run, tacc;
     run.init();
     tacc.init();
@@ -854,10 +861,12 @@ struct StepPrefix {
 // definition.  16 bytes per lane and step.
 struct Stage {
     f32x4* ex_p;
-    __device__ void put(int s, const StepPrefix& p) {
-        f32x4 v = p.ex_p;
-        const float total = readlane(p.B, kWave - 1);
-        if (lane_id() == 0) v.x = total;
+    __device__ void put(int s, float B, float p1, float p2, float p3) {
+        f32x4 v;
+        v.x = wave_shr1(B, readlane(B, kWave - 1));
+        v.y = p1;
+        v.z = p2;
+        v.w = p3;
         ex_p[s * kWave + lane_id()] = v;
     }
     __device__ StepPrefix get(int s) const {
@@ -884,8 +893,12 @@ constexpr size_t kStageBytesPerStep = (size_t)kWave * sizeof(f32x4);
 // POW: the importance needs powf or the other clamp; its steps go one after
 // another in a rolled loop (six copies of four powf were 20 KB of code, run
 // cold by every workgroup).
+// One branch a step for the two special cases (total importance 0, cells past
+// the end): a test per cell kept each cell's lookups in a block of their own,
+// waited for one after another.
 template <int MT, typename D, bool POW, typename Tables>
-__device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float* tf_lds, Stage stage, Tables tables) {
+__device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, float vmax, double degenerate_d,
+                                             const float* tf_lds, Stage stage, Tables tables) {
     const int lane = lane_id();
     const int w = uni((int)(thread_x() / kWave));
     const VolDev& vol = q.v;
@@ -893,41 +906,43 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float
     const int64_t n = uni(vol.n);
     const int tile_steps = uni(vol.tile_steps);
     const int64_t tbase = (int64_t)t * tile_steps * kStepCells;
-    const int nsteps = (int)((min(tbase + (int64_t)tile_steps * kStepCells, n) - tbase + kStepCells - 1) / kStepCells);
+    const int here = (int)min((int64_t)tile_steps * kStepCells, n - tbase);    // cells of the tile
+    const int nsteps = (here + kStepCells - 1) / kStepCells;
     constexpr bool kStored = std::is_same<D, StepF<MT>>::value;
     RunView<MT> view = run_view<MT, D>(vol, kStored ? 0 : M, tbase);
     if constexpr (kStored) view.base[0] = reinterpret_cast<const char*>(uni(q.ws.fstore)) + tbase * 4;
-    const double degenerate_d = gload<double>(q.ws.scal, 1);
     ImpCtx c;
     Quant<MT> qn;
+    if constexpr (!kStored) {
+        c = ctx_params(q);
+        qn.load(q);
+    }
     bool degenerate = false;
     auto process = [&](const D& cur, int s) {
-        const int64_t quad = ((tbase + (int64_t)s * kStepCells) >> 2) + lane;
         float f[4];
+        if (degenerate) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float fk = 1.0f;
-            if constexpr (kStored) {
-                if (!degenerate) fk = k == 0 ? cur.fv.x : (k == 1 ? cur.fv.y : (k == 2 ? cur.fv.z : cur.fv.w));
-            } else {
-                if (!degenerate) {
-                    const float v = cell_v<MT>(cur, k, M, tf_lds, qn);
-                    fk = POW ? importance_from_v(v, cur.lv.get(k), c) : importance_p1(v, cur.lv.get(k), c);
-                }
-            }
-            f[k] = ((quad << 2) + k < n) ? fk : 0.0f;
+            for (int k = 0; k < 4; ++k) f[k] = 1.0f;
+        } else if constexpr (kStored) {
+            f[0] = cur.fv.x;
+            f[1] = cur.fv.y;
+            f[2] = cur.fv.z;
+            f[3] = cur.fv.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[k] = cell_v<MT>(cur, k, M, tf_lds, qn);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                f[k] = POW ? importance_from_v(f[k], cur.lv.get(k), c) : importance_p1(f[k], cur.lv.get(k), c);
+        }
+        if ((s + 1) * kStepCells > here) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[k] = s * kStepCells + 4 * lane + k < here ? f[k] : 0.0f;
         }
         // monotone in-tile prefix: lane-serial over 4 cells, wave sum scan,
         // running max to undo rounding steps back
         const float p1 = f[0], p2 = p1 + f[1], p3 = p2 + f[2], tl = p3 + f[3];
-        const float B = wave_incl_max(wave_incl_sum(tl));
-        StepPrefix sp;
-        sp.ex_p.x = shfl_up1(B, 0.0f);
-        sp.ex_p.y = p1;
-        sp.ex_p.z = p2;
-        sp.ex_p.w = p3;
-        sp.B = B;
-        stage.put(s, sp);
+        stage.put(s, wave_incl_max(wave_incl_sum(tl)), p1, p2, p3);
     };
     constexpr int kAhead = POW ? 1 : (MT * D::kQuadBytes >= 64 ? 2 : 4);
     const int cnt = nsteps > w ? (nsteps - w + kBinWaves - 1) / kBinWaves : 0;
@@ -941,10 +956,7 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, const float
         if (first) {
             tables();
             degenerate = uni((int)(degenerate_d != 0.0)) != 0;
-            if constexpr (!kStored) {
-                c = make_ctx(q);
-                qn.load(q);
-            }
+            if constexpr (!kStored) ctx_vmax(c, vmax);
             first = false;
         }
 #pragma unroll
@@ -1010,15 +1022,15 @@ __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0
     // step order), the first bin of its first cell and the last bin of its
     // last cell.
     const int ls = min(lane, nsteps - 1);
+    const float total = stage.ex_p[ls * kWave].x;         // the step total (lane 0's Bex slot): B of lane 63
     float run_v = 0.0f;
-    for (int k = 0; k < nsteps; ++k) {
-        const float st_k = stage.ex_p[k * kWave].x;   // step k's total (lane 0's Bex slot)
-        if (k < ls) run_v = run_v + st_k;
+    for (int k = 0; k < nsteps - 1; ++k) {
+        const float st_k = readlane(total, k);
+        run_v = k < ls ? run_v + st_k : run_v;
     }
     int key0_v, key_end_v;
     {
         const int64_t c0 = tbase + (int64_t)ls * kStepCells;
-        const float total = stage.ex_p[ls * kWave].x;     // the step total: B of lane 63
         const float B0 = stage.ex_p[ls * kWave + 1].x;    // B of lane 0: Bex of lane 1
         const float x_first = fminf(fmaf(run_v + fminf(0.0f, B0), scale_f, X0), X1);
         key0_v = max(0, min((int)floorf(x_first), W1));
@@ -1111,10 +1123,10 @@ __device__ __forceinline__ int bin_of(float x, int W1) { return max(0, min((int)
 // of the steps that hold an edge (phase 2).  Bound by latency on a large
 // volume (a chain of kernel arguments, descriptor, edge and cells), by the
 // arithmetic of phase 1 when most tiles are rescanned.  From cached entries:
-// 64^3 cells W 1024 13.6 -> 9.8 us, 11.8 M cells 21 -> 18.9, eight requests on
-// two 20 M-cell volumes 102 -> 89 us against three waves a tile that found
-// their tile through the per-bin bounds, read levels through their codes and
-// looked entries up in the request's own table layout.
+// 64^3 cells W 1024 13.6 -> 8.4 us, 11.8 M cells 21 -> 16.2, 501 M 22.4 -> 19.2,
+// eight requests on two 20 M-cell volumes 102 -> 78 us, eight volumes of 8
+// fields 48 -> 42; 16-bit values 33 -> 26: three waves a tile found their tile
+// through the per-bin bounds, and tests per cell held the lookups apart.
 // IDX: this instance serves the requests whose projection reads values (0),
 // cached entries (1) or the f the importance pass stored (2).  LDS: the
 // request's tables (as in the importance pass; none for stored f), then the
@@ -1125,6 +1137,10 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
     const ReqDev& q = bd.reqs[block_y()];
     if (uni(q.bin_path) != IDX) return;
     const int W1 = uni(q.W) - 1;
+    const double* const scal = uni(q.ws.scal);
+    const double degenerate_d = gload<double>(scal, 1), scale_d = gload<double>(scal, 2);
+    float vmax = 0.0f;
+    if constexpr (IDX != 2) vmax = gload<float>(q.vmax_dev, 0);
     int t = block_x();
     float X0, X1;
     if (uni(q.by_tile)) {
@@ -1140,7 +1156,6 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
         X0 = uni(__uint_as_float(e.y));
         X1 = uni(__uint_as_float(e.z));
     }
-    const float scale_f = (float)gload<double>(q.ws.scal, 2);
     float* tf_lds = reinterpret_cast<float*>(bin_lds);
     Stage stage;
     stage.ex_p = IDX == 2 ? bin_lds : bin_lds + ((IDX == 1 ? bd.max_fields * kIdxTable : bd.max_req_tf) + 3) / 4;
@@ -1152,13 +1167,13 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
     const bool pow = uni((int)!(q.exp_is_one && q.clamp_mode == 0)) != 0;
     using D = typename std::conditional<IDX == 1, BinIdx<MT>, BinData<MT, S>>::type;
     if constexpr (IDX == 2)
-        rescan_stage<MT, StepF<MT>, false>(q, t, tf_lds, stage, tables);
+        rescan_stage<MT, StepF<MT>, false>(q, t, vmax, degenerate_d, tf_lds, stage, tables);
     else if (pow)
-        rescan_stage<MT, D, true>(q, t, tf_lds, stage, tables);
+        rescan_stage<MT, D, true>(q, t, vmax, degenerate_d, tf_lds, stage, tables);
     else
-        rescan_stage<MT, D, false>(q, t, tf_lds, stage, tables);
+        rescan_stage<MT, D, false>(q, t, vmax, degenerate_d, tf_lds, stage, tables);
     __syncthreads();
-    rescan_bins(q, t, X0, X1, uni(scale_f), stage);
+    rescan_bins(q, t, X0, X1, uni((float)scale_d), stage);
 }
 
 // ------------------------------------------------------------------ K4
