@@ -26,7 +26,7 @@ ARCH = os.environ.get("DVL_OFFLOAD_ARCH", "gfx950")
 # values) drop IEEE NaN handling of min/max, which otherwise doubles every
 # fminf/fmaxf with canonicalisations.  Host code keeps full IEEE semantics.
 _NO_NAN = ["-Xarch_device", "-fno-honor-nans", "-Xarch_device", "-mno-amdgpu-ieee"]
-TYPED_UNITS = [(t, m) for t in ("F32", "F16", "BF16") for m in (1, 2, 4, 8, 16)]
+TYPED_UNITS = [(t, m) for t in ("F32", "F16", "BF16") for m in (1, 2, 3, 4, 5, 6, 7, 8, 16)]
 FILE_FLAGS = {"update.hip": _NO_NAN}
 FILE_FLAGS.update({f"update_{t.lower()}_m{m}.hip": _NO_NAN for t, m in TYPED_UNITS})
 

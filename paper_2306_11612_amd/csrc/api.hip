@@ -531,7 +531,7 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         P.groups.push_back(g);
     }
     // The kernels are specialised on the field count: batches whose volumes
-    // all have 1, 2, 4 or 8 fields run that variant; others the general one,
+    // all have the same 1 to 8 fields run that variant; others the general one,
     // which reads M per volume.
     P.max_m = P.reqs[0].v->M;
     P.rdev.resize(P.reqs.size());

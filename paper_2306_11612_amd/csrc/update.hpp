@@ -143,7 +143,7 @@ constexpr uint64_t kDescriptorLayout =
 
 // Launch the five phases for the batch described by `b` (descriptors already
 // resident on the device).  `max_m`: the field count when every volume has
-// the same (1, 2, 4 or 8), else kMaxFields.  `layout`: the caller's
+// the same (1 to 8), else kMaxFields.  `layout`: the caller's
 // kDescriptorLayout.  ev (optional): kPhases + 1 events.
 dvl_status launch_batch(const BatchDev& b, int dtype, int max_m, int n_cu, hipStream_t s, uint64_t layout,
                         hipEvent_t* ev = nullptr);
