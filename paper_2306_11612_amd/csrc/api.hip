@@ -456,10 +456,16 @@ static dvl_status check_range(const ReqHost& r, float vmax) {
 
 // ================================================================== batch plans
 
+// The requests on one volume, consecutive in the batch.
+struct VolReqs {
+    int req0, n_req;
+};
+
 struct Plan {
     std::vector<ReqHost> reqs;       // grouped by volume
     std::vector<int> where;          // caller's request index -> index in `reqs`
-    std::vector<GroupDev> groups;    // one per volume
+    std::vector<VolReqs> groups;     // one per volume
+    std::vector<int64_t> unit0;      // each request's first importance-pass unit
     std::vector<ReqDev> rdev;
     std::vector<float*> fstore;      // where each request may store f, or NULL
     int dtype = DVL_F32;
@@ -474,7 +480,7 @@ struct Plan {
     int64_t k1_units = 0;
     size_t tf_floats = 0;
     // descriptor block, uploaded before every launch:
-    //   [GroupDev x groups][ReqDev x reqs][max V x reqs][tables]
+    //   [unit0 x reqs][ReqDev x reqs][max V x reqs][tables]
     size_t off_reqs = 0, off_vmax = 0, off_tf = 0, block_bytes = 0;
 };
 
@@ -514,8 +520,7 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
     P.where.assign(reqs.size(), 0);
     for (size_t i = 0; i < reqs.size(); ++i) {
         if (taken[i]) continue;
-        GroupDev g{};
-        g.unit0 = P.k1_units;
+        VolReqs g{};
         g.req0 = (int)P.reqs.size();
         dvl_volume* v = reqs[i].v;
         for (size_t k = i; k < reqs.size(); ++k)
@@ -525,9 +530,6 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
                 taken[k] = true;
             }
         g.n_req = (int)P.reqs.size() - g.req0;
-        // one importance-pass unit is one workgroup: a run per wave, or a tile
-        const VolDev d = vol_dev(v);
-        P.k1_units += (int64_t)g.n_req * (d.split ? d.n_runs : (d.n_runs + kUpdWaves - 1) / kUpdWaves);
         P.groups.push_back(g);
     }
     // The kernels are specialised on the field count: batches whose volumes
@@ -555,6 +557,11 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         d.clamp_mode = r.p.clamp_mode;
         d.level_shift = r.p.level_scale;
         d.scan_mode = r.p.scan_mode;
+        // the other scan arithmetics' sums depend on their order: a wave per run
+        d.v.split = d.v.split && d.scan_mode == DVL_SCAN_FP64;
+        // a unit of the importance pass: a run per wave, or a tile
+        P.unit0.push_back(P.k1_units);
+        P.k1_units += d.v.split ? d.v.n_runs : (d.v.n_runs + kUpdWaves - 1) / kUpdWaves;
         d.vmax_exact = r.p.vmax_mode == DVL_VMAX_EXACT;
         // a workgroup of k_bin per tile when there are no more tiles than
         // bins, else per bin edge
@@ -577,7 +584,7 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         P.any_exact |= d.vmax_exact;
     }
     if (P.max_m > 8) P.max_m = kMaxFields;
-    P.off_reqs = (P.groups.size() * sizeof(GroupDev) + 63) & ~(size_t)63;
+    P.off_reqs = (P.unit0.size() * sizeof(int64_t) + 63) & ~(size_t)63;
     P.off_vmax = P.off_reqs + P.rdev.size() * sizeof(ReqDev);
     P.off_tf = (P.off_vmax + P.rdev.size() * sizeof(float) + 63) & ~(size_t)63;
     P.block_bytes = al256(P.off_tf + P.tf_floats * sizeof(float));
@@ -603,7 +610,7 @@ static dvl_status fill_block(Plan& P, char* h, char* d) {
         P.rdev[q].tf = (const float*)(d + P.off_tf) + r.tf_pos;
         P.rdev[q].vmax_dev = (float*)(d + P.off_vmax) + q;
     }
-    memcpy(h, P.groups.data(), P.groups.size() * sizeof(GroupDev));
+    memcpy(h, P.unit0.data(), P.unit0.size() * sizeof(int64_t));
     memcpy(h + P.off_reqs, P.rdev.data(), P.rdev.size() * sizeof(ReqDev));
     return DVL_OK;
 }
@@ -629,7 +636,7 @@ struct CacheBuild {
 };
 
 // the requests of group g read their volume's entry cache
-static void use_cache(Plan& P, const GroupDev& g) {
+static void use_cache(Plan& P, const VolReqs& g) {
     const dvl_volume* v = P.reqs[g.req0].v;
     for (int k = 0; k < g.n_req; ++k) {
         ReqDev& d = P.rdev[g.req0 + k];
@@ -645,7 +652,7 @@ static void use_cache(Plan& P, const GroupDev& g) {
 // per launch.
 static dvl_status decide_cache(Plan& P, std::vector<CacheBuild>& builds) {
     builds.clear();
-    for (const GroupDev& g : P.groups) {
+    for (const VolReqs& g : P.groups) {
         for (int k = 0; k < g.n_req; ++k) P.rdev[g.req0 + k].entries = 0;
         dvl_volume* v = P.reqs[g.req0].v;
         if (v->idx_policy == DVL_ENTRY_CACHE_NEVER) continue;
@@ -742,7 +749,7 @@ static dvl_status run_cache_builds(const std::vector<CacheBuild>& builds, hipStr
 // for their latest rebuild when it ran on another stream (on s itself the
 // stream order already follows it).
 static dvl_status cache_wait(const Plan& P, hipStream_t s) {
-    for (const GroupDev& g : P.groups) {
+    for (const VolReqs& g : P.groups) {
         if (!P.rdev[g.req0].entries) continue;
         dvl_volume* v = P.reqs[g.req0].v;
         if (v->cache_ready_recorded && v->cache_ready_stream != s)
@@ -755,7 +762,7 @@ static dvl_status cache_wait(const Plan& P, hipStream_t s) {
 // whether any request read a cache).  The caller records s's reader event.
 static bool cache_add_readers(const Plan& P, hipStream_t s) {
     bool any = false;
-    for (const GroupDev& g : P.groups) {
+    for (const VolReqs& g : P.groups) {
         if (!P.rdev[g.req0].entries) continue;
         dvl_volume* v = P.reqs[g.req0].v;
         if (std::find(v->cache_readers.begin(), v->cache_readers.end(), s) == v->cache_readers.end())
@@ -797,12 +804,12 @@ static int plan_paths(Plan& P) {
 // `paths`: the variants to launch (plan_paths)
 static BatchDev batch_dev(const Plan& P, char* d, int paths) {
     BatchDev b{};
-    b.groups = (const GroupDev*)d;
+    b.unit0 = (const int64_t*)d;
     b.reqs = (const ReqDev*)(d + P.off_reqs);
-    b.n_groups = (int)P.groups.size();
     b.n_reqs = (int)P.rdev.size();
     b.k1_units = P.k1_units;
     b.any_exact = P.any_exact;
+    b.chain = 1;
     b.paths = paths;
     b.max_req_tf = P.max_req_tf;
     b.max_fields = P.max_fields;
@@ -1476,7 +1483,7 @@ static dvl_status scratch_address(int dev, char** out) {
 // volume's reader streams (its reader event exists and is re-recorded below,
 // creating nothing), so a later rebuild elsewhere still waits for this launch.
 static void use_existing_cache(Plan& P, hipStream_t s) {
-    for (const GroupDev& g : P.groups) {
+    for (const VolReqs& g : P.groups) {
         P.rdev[g.req0].entries = 0;      // one request per plan here
         dvl_volume* v = P.reqs[g.req0].v;
         if (v->idx_policy == DVL_ENTRY_CACHE_NEVER || !v->idx_valid) continue;

@@ -105,25 +105,18 @@ struct ReqDev {
     int tf_off[kMaxFields];   // start of field m's table inside this request's block
 };
 
-// The requests on one volume, consecutive in the batch.  Their units of the
-// importance pass take turns (unit u: request u % n_req), so that the same
-// cells are read by neighbouring workgroups at about the same time and come
-// from the caches after the first.  (A kernel that evaluated up to 8 requests
-// per read of a cell held 183 KB of code against 64 KB of instruction cache:
-// 341 us for 4 requests on each of two 20 M-cell volumes, cached entries; one
-// request at a time takes 141 us.)
-struct GroupDev {
-    int64_t unit0;            // first unit
-    int req0;
-    int n_req;
-};
-
+// The importance pass's units of work are numbered request after request
+// (unit0: each request's first).  Requests on one volume run at the same pace
+// side by side, so that their cells come from the caches after the first.  (A
+// kernel that evaluated up to 8 requests per read of a cell held 183 KB of code
+// against 64 KB of instruction cache: 341 us for 4 requests on each of two 20
+// M-cell volumes, cached entries; one request at a time takes 119 us.)
 struct BatchDev {
-    const GroupDev* groups;
+    const int64_t* unit0;     // [n_reqs]
     const ReqDev* reqs;
-    int n_groups;
     int n_reqs;
     int64_t k1_units;
+    int64_t chain;            // consecutive units a workgroup of the importance pass takes
     int any_exact;
     int paths;                // kPath*: which variants of the importance pass and the projection to launch
     int max_req_tf;           // largest request table block (floats)

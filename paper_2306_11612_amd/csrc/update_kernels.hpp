@@ -20,27 +20,29 @@ namespace dvl {
 struct Unit {
     int req;                  // request
     int local;                // unit of that request
+    int left;                 // units of the request from it on
 };
 
-// The request and its unit of importance-pass unit u: its volume's group by
-// one load of 64 groups' first units at a time (a binary search is a chain of
-// dependent loads), then turn by turn among the group's requests.
+// The request and its unit of importance-pass unit u: by one load of 64
+// requests' first units at a time (a binary search is a chain of dependent
+// loads).
 __device__ __forceinline__ Unit find_unit(const BatchDev& b, int64_t u) {
-    int g = 0;
-    if (b.n_groups > 1) {
-        for (int base = 0; base < b.n_groups; base += kWave) {
+    Unit r;
+    r.req = 0;
+    int64_t first = 0, end = b.k1_units;
+    if (b.n_reqs > 1) {
+        for (int base = 0; base < b.n_reqs; base += kWave) {
             const int i = base + lane_id();
-            const uint64_t below = __ballot(i < b.n_groups && gload<int64_t>(&b.groups[min(i, b.n_groups - 1)].unit0, 0) <= u);
-            g = base + (int)__popcll(below) - 1;
+            const uint64_t below = __ballot(i < b.n_reqs && gload<int64_t>(b.unit0, min(i, b.n_reqs - 1)) <= u);
+            r.req = base + (int)__popcll(below) - 1;
             if (below != ~0ull) break;
         }
-        g = uni(g);
+        r.req = uni(r.req);
+        first = uni(gload<int64_t>(b.unit0, r.req));
+        if (r.req + 1 < b.n_reqs) end = uni(gload<int64_t>(b.unit0, r.req + 1));
     }
-    const GroupDev& gd = b.groups[g];
-    const uint32_t l = (uint32_t)(u - gd.unit0), n_req = (uint32_t)gd.n_req;
-    Unit r;
-    r.req = gd.req0 + (int)(n_req > 1 ? l % n_req : 0u);
-    r.local = (int)(n_req > 1 ? l / n_req : l);
+    r.local = (int)(u - first);
+    r.left = (int)(end - u);
     return r;
 }
 
@@ -613,47 +615,56 @@ struct ModeSum {
     }
 };
 
-// One wave's part of the importance pass: the steps [s_begin, s_end) of the
-// tiles [t_begin, t_end) (all of them, unless the workgroup's waves share one
-// tile).  Stream the cells once (values, or cached entries), evaluate f, sum f
-// over each tile (per lane, 4 cells per step as (f0 + f1) + (f2 + f3) in fp32,
-// accumulated over the tile's steps and then over the wave in the request's
-// scan arithmetic: fp64, compensated fp32 or plain fp32) and record, per tile,
-// the non-decreasing sum of the earlier tiles of the run.  Both sources give
-// the same f bit for bit.  `tables()` puts the tables into LDS after the first
-// loads are on their way; it is called exactly once, by every wave (also one
-// without work, nsteps <= 0).  The result: the sum of the last tile (split)
-// or the run's total (else).
+// One wave's part of the importance pass: `nsteps` steps of one request.  Not
+// split: consecutive, whole runs from run `first` (tile t_begin) on; the sum of
+// every run, and per tile the non-decreasing sum of the earlier tiles of its
+// run, are recorded.  Split: `part` steps of every tile from tile `first` on
+// (c_begin: the wave's first cell there); the wave's sum of tile first + k goes
+// to part_sums[k * kUpdWaves].  Either way the cells are one stream: the next
+// steps are on their way while a tile ends and the next begins.
+// f of the cells is evaluated from values or cached entries (the same bits) and
+// summed over each tile per lane, 4 cells per step as (f0 + f1) + (f2 + f3) in
+// fp32, accumulated over the tile's steps and then over the wave in the
+// request's scan arithmetic: fp64, compensated fp32 or plain fp32.  `tables()`
+// puts the tables into LDS after the first loads are on their way; it is called
+// exactly once, by every wave (also one without work, nsteps <= 0).
 //
-// PLAIN: fp64 sums, P = 1 with the importance clamp, f not stored, every cell
-// of the run inside the volume (whole groups of steps): nothing is tested per
-// step but whether its levels are mixed.  In a step without mixed segments a
-// lane's four cells share a level, so the level scale is folded into 1 / max V
-// (a power of two: the product has the same bits).  75 vector and 30 scalar
-// instructions per step became 62 and 8, and a step's 16 lookups are in flight
-// together: 432 -> 417 us for 501 M cells of 4 fields (vector units now busy
-// 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s), 141 -> 133 us for 8
-// requests on two 20 M-cell volumes, 8.3 -> 6.9 us for 64^3 cells.
-enum RunKind { kRunPlain, kRunP1, kRunPow };
+// kRunPlain, kRunSplit: fp64 sums, P = 1 with the importance clamp, f not
+// stored, every cell inside the volume (whole groups of steps): nothing is
+// tested per step but whether its levels are mixed.  In a step without mixed
+// segments a lane's four cells share a level, so the level scale is folded into
+// 1 / max V (a power of two: the product has the same bits).  75 vector and 30
+// scalar instructions per step became 62 and 8, and a step's 16 lookups are in
+// flight together: 432 -> 417 us for 501 M cells of 4 fields (vector units now
+// busy 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s).
+// kRunSplitAny: fp64 sums; kRunP1, kRunPow: anything.
+enum RunKind { kRunPlain, kRunP1, kRunPow, kRunSplit, kRunSplitAny };
 template <int MT, typename D, int KIND, typename Tables>
-__device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, int64_t c_begin, int nsteps, bool split,
-                                                const float* tf_lds, Tables tables) {
+__device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_begin, int64_t c_begin, int nsteps,
+                                              int part, double* part_sums, const float* tf_lds, Tables tables) {
     constexpr int G = Group<D>::n;
+    constexpr bool kSplit = KIND == kRunSplit || KIND == kRunSplitAny;
+    constexpr bool kPlain = KIND == kRunPlain || KIND == kRunSplit;
     if (nsteps <= 0) {
         tables();
-        return 0.0;
+        return;
     }
     const int lane = lane_id();
     const VolDev& vol = q.v;
     const int M = uni(fields_of<MT>(vol.M));
     const int tile_steps = uni(vol.tile_steps);
+    const int tile_shift = __builtin_ctz((unsigned)tile_steps), part_shift = kSplit ? __builtin_ctz((unsigned)part) : 0;
+    const int tpr = uni(vol.tiles_per_run);
     const int64_t n = uni(vol.n);
     const int last_group = (nsteps - 1) / G * G;
     const RunView<MT> view = run_view<MT, D>(vol, M, c_begin);
+    // where step s of the stream lies, counted from c_begin
+    auto at = [&](int s) { return kSplit ? ((s >> part_shift) << tile_shift) + (s & (part - 1)) : s; };
     const float vmax = gload<float>(q.vmax_dev, 0);
     ImpCtx ctx = ctx_params(q);
     float* const fst = uni(q.ws.fstore);      // where f of every cell is kept for the projection, or NULL
     double* const lpre = uni(q.ws.local_prefix);
+    double* const run_total = uni(q.ws.run_total);
     const int mode = uni(q.scan_mode);
     Quant<MT> qn;
     qn.load(q);
@@ -667,13 +678,13 @@ __device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, in
     StepCodes<G> cA, cB;
     {
         const StepCodes<G> c0 = load_codes<G>(view.lcode, 0);
-        const StepCodes<G> c1 = load_codes<G>(view.lcode, min(G, last_group));
-        cA = load_codes<G>(view.lcode, min(2 * G, last_group));
+        const StepCodes<G> c1 = load_codes<G>(view.lcode, at(min(G, last_group)));
+        cA = load_codes<G>(view.lcode, at(min(2 * G, last_group)));
 #pragma unroll
         for (int g = 0; g < G; ++g) A[g].load(view, M, g, c0.c[g]);
-        cB = load_codes<G>(view.lcode, min(3 * G, last_group));
+        cB = load_codes<G>(view.lcode, at(min(3 * G, last_group)));
 #pragma unroll
-        for (int g = 0; g < G; ++g) B[g].load(view, M, min(G + g, nsteps - 1), c1.c[g]);
+        for (int g = 0; g < G; ++g) B[g].load(view, M, at(min(G + g, nsteps - 1)), c1.c[g]);
     }
     tables();
     ctx_vmax(ctx, vmax);
@@ -681,12 +692,40 @@ __device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, in
     run.init();
     tacc.init();
     double prev = 0.0;
-    int64_t t = t_begin;
-    int in_tile = 0;
+    int t = t_begin, r = first;               // tile, and run (split: the tile again)
+    int in_tile = 0, in_run = 0;
+    auto end_run = [&]() {
+        if (lane == 0) gstore<double>(run_total, r, fmax(prev, kPlain ? run.d : run.value(mode)));
+        run.init();
+        prev = 0.0;
+        in_run = 0;
+        ++r;
+    };
+    auto end_tile = [&]() {
+        if constexpr (kPlain || kSplit)
+            tacc.d = wave_total_d(tacc.d);
+        else
+            tacc.wave_total(mode);
+        if constexpr (kSplit) {
+            if (lane == 0) *part_sums = tacc.d;
+            part_sums += kUpdWaves;
+        } else {
+            prev = fmax(prev, kPlain ? run.d : run.value(mode));
+            if (lane == 0) gstore<double>(lpre, t, prev);
+            if constexpr (kPlain)
+                run.d += tacc.d;
+            else
+                run.add(mode, tacc);
+            ++t;
+            if (++in_run == tpr) end_run();
+        }
+        tacc.init();
+        in_tile = 0;
+    };
 
-    // the steps s .. s + G - 1 of the run, loaded into `cur`
+    // the steps s .. s + G - 1 of the stream, loaded into `cur`
     auto process = [&](const D (&cur)[G], int s) {
-        if constexpr (KIND == kRunPlain) {
+        if constexpr (kPlain) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float f[4];
@@ -703,30 +742,21 @@ __device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, in
                 tacc.d += (double)((f[0] + f[1]) + (f[2] + f[3]));
             }
             in_tile += G;
-            if (in_tile == tile_steps) {
-                tacc.d = wave_total_d(tacc.d);
-                if (!split) {
-                    prev = fmax(prev, run.d);
-                    if (lane == 0) gstore<double>(lpre, t, prev);
-                }
-                run.d += tacc.d;
-                tacc.d = 0.0;
-                ++t;
-                in_tile = 0;
-            }
+            if (in_tile == (kSplit ? part : tile_steps)) end_tile();
             return;
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (s + g >= nsteps) break;
-            const int64_t quad = ((c_begin + (int64_t)(s + g) * kStepCells) >> 2) + lane;
-            const bool full = c_begin + (int64_t)(s + g + 1) * kStepCells <= n;   // no cell past the end
+            const int64_t c0 = c_begin + (int64_t)at(s + g) * kStepCells;
+            const int64_t quad = (c0 >> 2) + lane;
+            const bool full = c0 + kStepCells <= n;   // no cell past the end
             float f[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const float v = cell_v<MT>(cur[g], k, M, tf_lds, qn);
                 const uint32_t L = cur[g].lv.get(k);
-                f[k] = KIND != kRunPow ? importance_p1(v, L, ctx) : importance_from_v(v, L, ctx);
+                const float v = cell_v<MT>(cur[g], k, M, tf_lds, qn);
+                f[k] = KIND == kRunP1 ? importance_p1(v, L, ctx) : importance_from_v(v, L, ctx);
             }
             if (!full) {
 #pragma unroll
@@ -740,104 +770,118 @@ __device__ __forceinline__ double tile_sums_run(const ReqDev& q, int t_begin, in
                 fv.w = f[3];
                 gstore<f32x4>(fst, quad, fv);
             }
-            tacc.add_f(mode, (f[0] + f[1]) + (f[2] + f[3]));
-            if (++in_tile == tile_steps || s + g + 1 == nsteps) {
-                tacc.wave_total(mode);
-                if (!split) {
-                    prev = fmax(prev, run.value(mode));
-                    if (lane == 0) gstore<double>(lpre, t, prev);
-                }
-                run.add(mode, tacc);
-                tacc.init();
-                ++t;
-                in_tile = 0;
-            }
+            const float sum = (f[0] + f[1]) + (f[2] + f[3]);
+            if constexpr (kSplit)
+                tacc.d += (double)sum;
+            else
+                tacc.add_f(mode, sum);
+            if (++in_tile == (kSplit ? part : tile_steps) || s + g + 1 == nsteps) end_tile();
         }
     };
 
     for (int s = 0; s < nsteps; s += 2 * G) {
         process(A, s);
         {
-            const StepCodes<G> c2 = load_codes<G>(view.lcode, min(s + 4 * G, last_group));
+            const StepCodes<G> c2 = load_codes<G>(view.lcode, at(min(s + 4 * G, last_group)));
 #pragma unroll
-            for (int g = 0; g < G; ++g) A[g].load(view, M, min(s + 2 * G + g, nsteps - 1), cA.c[g]);
+            for (int g = 0; g < G; ++g) A[g].load(view, M, at(min(s + 2 * G + g, nsteps - 1)), cA.c[g]);
             cA = c2;
         }
         if (s + G >= nsteps) break;
         process(B, s + G);
         {
-            const StepCodes<G> c3 = load_codes<G>(view.lcode, min(s + 5 * G, last_group));
+            const StepCodes<G> c3 = load_codes<G>(view.lcode, at(min(s + 5 * G, last_group)));
 #pragma unroll
-            for (int g = 0; g < G; ++g) B[g].load(view, M, min(s + 3 * G + g, nsteps - 1), cB.c[g]);
+            for (int g = 0; g < G; ++g) B[g].load(view, M, at(min(s + 3 * G + g, nsteps - 1)), cB.c[g]);
             cB = c3;
         }
     }
-    if constexpr (KIND == kRunPlain) {
-        if (split) return wave_total_d(tacc.d);      // a quarter of a tile: no tile ended
-        return fmax(prev, run.d);
-    }
-    return split ? run.value(mode) : fmax(prev, run.value(mode));
+    if constexpr (!kSplit)
+        if (in_run > 0) end_run();                // the volume's last run may have fewer tiles
 }
 
-// A workgroup takes 4 consecutive runs of a request, a wave each; run r owns
-// the tiles [r k, (r + 1) k).  When the volume is so small that a run is one
-// tile and the tiles do not fill the chip with workgroups (VolDev::split), the
-// four waves share one tile instead, a quarter of its steps each, and their
-// fp64 sums are added in order (sums of fp32 values over a tile are exact in
-// fp64 unless f spans more than about 2^20, so the split changes no bit
-// then); the other scan arithmetics, whose sums depend on the order, leave
-// the tile to the first wave.
+// A unit is 4 runs of a request, a wave each; run r owns the tiles [r k,
+// (r + 1) k).  When the volume is so small that a run is one tile and the tiles
+// do not fill the chip (VolDev::split), a unit is one tile, a quarter of its
+// steps each wave, and their fp64 sums are added in order (sums of fp32 values
+// over a tile are exact in fp64 unless f spans more than about 2^20, so the
+// split changes no bit then).  A workgroup takes b.chain consecutive units, and
+// those that belong to one request as one stream: the tables are staged once
+// and only the first loads are waited for.  Eight requests on two 20 M-cell
+// volumes 131 -> 119 us, eight volumes of 2.3 M cells and 8 fields 60.5 -> 45
+// against unit by unit, the requests in turns.
+constexpr int kMaxChain = 16;           // units of one stream
+constexpr size_t kSumsPartBytes = (size_t)kMaxChain * kUpdWaves * sizeof(double);
+constexpr int kMaxStreamSteps = 1 << 20;    // a wave's offsets stay below 2^32 bytes
 template <int MT, typename S, int IDX>
 __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
     extern __shared__ float tf_lds[];
+    double* const part_sums = reinterpret_cast<double*>(tf_lds + sums_lds<IDX != 0>(b));   // [kMaxChain][kUpdWaves]
     const int wv = uni((int)(thread_x() / kWave));
     int loaded = -1;
-    for (int64_t u = block_x(); u < b.k1_units; u += grid_dim_x()) {
-        const Unit un = find_unit(b, u);
-        const ReqDev& q = b.reqs[un.req];
-        if (uni(q.entries) != IDX) continue;
-        const VolDev& vol = q.v;
-        const int tile_steps = uni(vol.tile_steps);
-        const int64_t n = uni(vol.n);
-        const bool split = uni(vol.split) != 0;
-        const int part = uni(q.scan_mode) == DVL_SCAN_FP64 ? tile_steps / kUpdWaves : (wv == 0 ? tile_steps : 0);
-        const WaveSteps ws = wave_steps(vol, un.local, wv, split, part);
-        const int t0 = ws.t0, nsteps = ws.nsteps;
-        const int64_t c_begin = ws.c_begin;
-        auto tables = [&]() {
-            if (un.req == loaded) return;
-            if (loaded >= 0) __syncthreads();   // the other waves are done with the previous tables
-            load_tables<MT, IDX != 0>(q, uni(fields_of<MT>(vol.M)), tf_lds);
-            __syncthreads();
-            loaded = un.req;
-        };
-        using D = typename std::conditional<IDX != 0, StepIdx<MT>, StepData<MT, S>>::type;
-        // P = 1 with the importance clamp: no pow
-        const bool p1 = uni((int)(q.exp_is_one && q.clamp_mode == 0)) != 0;
-        const bool plain = p1 && uni(q.scan_mode) == DVL_SCAN_FP64 && uni(q.ws.fstore) == nullptr &&
-                           nsteps % Group<D>::n == 0 && c_begin + (int64_t)nsteps * kStepCells <= n &&
-                           (split || nsteps % tile_steps == 0);
-        double total;
-        if (plain)
-            total = tile_sums_run<MT, D, kRunPlain>(q, t0, c_begin, nsteps, split, tf_lds, tables);
-        else if (p1)
-            total = tile_sums_run<MT, D, kRunP1>(q, t0, c_begin, nsteps, split, tf_lds, tables);
-        else
-            total = tile_sums_run<MT, D, kRunPow>(q, t0, c_begin, nsteps, split, tf_lds, tables);
-        if (split) {
-            // a partial sum per wave behind the tables (see sums_lds)
-            double* part = reinterpret_cast<double*>(tf_lds + sums_lds<IDX != 0>(b));
-            if (lane_id() == 0) part[wv] = total;
-            __syncthreads();
-            if (thread_x() == 0) {
-                double sum = part[0];
-                for (int k = 1; k < kUpdWaves; ++k) sum += part[k];
-                gstore<double>(q.ws.local_prefix, t0, 0.0);
-                gstore<double>(q.ws.run_total, t0, fmax(0.0, sum));
+    for (int64_t u0 = block_x() * b.chain; u0 < b.k1_units; u0 += grid_dim_x() * b.chain) {
+        const int64_t u1 = min(u0 + b.chain, b.k1_units);
+        for (int64_t u = u0; u < u1;) {
+            const Unit un = find_unit(b, u);
+            const ReqDev& q = b.reqs[un.req];
+            int k = (int)min(u1 - u, (int64_t)un.left);
+            if (uni(q.entries) != IDX) {
+                u += k;
+                continue;
             }
-            __syncthreads();
-        } else if (lane_id() == 0 && nsteps > 0) {
-            gstore<double>(q.ws.run_total, un.local * kUpdWaves + wv, total);
+            const VolDev& vol = q.v;
+            const int tile_steps = uni(vol.tile_steps), tpr = uni(vol.tiles_per_run), n_runs = uni(vol.n_runs);
+            const int64_t n = uni(vol.n), tile_cells = (int64_t)tile_steps * kStepCells;
+            const bool split = uni(vol.split) != 0;
+            auto tables = [&]() {
+                if (un.req == loaded) return;
+                if (loaded >= 0) __syncthreads();   // the other waves are done with the previous tables
+                load_tables<MT, IDX != 0>(q, uni(fields_of<MT>(vol.M)), tf_lds);
+                __syncthreads();
+                loaded = un.req;
+            };
+            using D = typename std::conditional<IDX != 0, StepIdx<MT>, StepData<MT, S>>::type;
+            // P = 1 with the importance clamp: no pow
+            const bool p1 = uni((int)(q.exp_is_one && q.clamp_mode == 0)) != 0;
+            const bool stored = uni(q.ws.fstore) != nullptr;
+            k = max(1, min(min(k, kMaxChain), kMaxStreamSteps / (tpr * tile_steps)));
+            if (!split) {
+                const int r0 = un.local * kUpdWaves + wv * k, r1 = min(r0 + k, n_runs);
+                const int64_t c_begin = (int64_t)r0 * tpr * tile_cells;
+                const int64_t c_end = min(n, (int64_t)r1 * tpr * tile_cells);
+                const int nsteps = r1 > r0 ? (int)((c_end - c_begin + kStepCells - 1) / kStepCells) : 0;
+                const bool plain = p1 && uni(q.scan_mode) == DVL_SCAN_FP64 && !stored &&
+                                   c_begin + (int64_t)nsteps * kStepCells <= n && nsteps % tile_steps == 0;
+                if (plain)
+                    tile_sums_run<MT, D, kRunPlain>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
+                else if (p1)
+                    tile_sums_run<MT, D, kRunP1>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
+                else
+                    tile_sums_run<MT, D, kRunPow>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
+            } else {
+                // whole tiles as one stream, a ragged last tile by itself
+                const int t0 = un.local, part = tile_steps / kUpdWaves;
+                const int whole = min(k, (int)(n / tile_cells) - t0);
+                k = max(1, whole);
+                const int64_t c_begin = ((int64_t)t0 * tile_steps + wv * part) * kStepCells;
+                const int64_t here = n - c_begin;       // cells left in the volume
+                const int nsteps = whole > 0 ? k * part : (int)max((int64_t)0, min((int64_t)part, (here + kStepCells - 1) / kStepCells));
+                if (nsteps == 0 && lane_id() == 0) part_sums[wv] = 0.0;
+                if (whole > 0 && p1 && !stored)
+                    tile_sums_run<MT, D, kRunSplit>(q, t0, t0, c_begin, nsteps, part, part_sums + wv, tf_lds, tables);
+                else
+                    tile_sums_run<MT, D, kRunSplitAny>(q, t0, t0, c_begin, nsteps, part, part_sums + wv, tf_lds, tables);
+                __syncthreads();
+                if ((int)thread_x() < k) {
+                    const double* p = part_sums + thread_x() * kUpdWaves;
+                    double sum = p[0];
+                    for (int w = 1; w < kUpdWaves; ++w) sum += p[w];
+                    gstore<double>(q.ws.local_prefix, t0 + thread_x(), 0.0);
+                    gstore<double>(q.ws.run_total, t0 + thread_x(), fmax(0.0, sum));
+                }
+                __syncthreads();
+            }
+            u += k;
         }
     }
 }
@@ -1406,20 +1450,17 @@ static dvl_status check_no_static_lds(const char* name) {
     return DVL_OK;
 }
 
-// Grid of the importance pass.  When the units split evenly over the
-// workgroups that fit the chip at once with `lds` bytes of LDS each (or
-// number no more than them), or belong to several requests (units of unequal
-// length: the 32-volume batch's pass took 612 instead of 735 us), one round
-// of that many: a workgroup that finishes its unit takes the next one with
-// its tables already in LDS, instead of a second round of workgroups
-// starting cold (descriptors, tables, the first loads: a few dependent memory
-// round trips each), 5 % faster for the 501 M-cell cached-entry pass.  Otherwise 8 workgroups per
-// compute unit, whose later rounds the hardware hands to whichever compute
-// unit frees a slot (a fixed uneven split, 2048 units over 1280 resident
-// workgroups of the value path, was 3 % slower).  The occupancy is queried
-// once per kernel and LDS size; any grid gives the same results.
+// Grid of the importance pass.  Units of several requests go in equal chains to
+// as many workgroups as fit the chip at once.  One large request: as many workgroups as fit when that splits them evenly (or
+// there are no more); a workgroup that finishes its unit takes the next one
+// with its tables in LDS, 5 % faster for 501 M cells from cached entries than a
+// second round starting cold.  Else 8 workgroups per compute unit, whose later
+// rounds the hardware hands to whichever compute unit frees a slot (a fixed
+// uneven split, 2048 units over 1280 resident workgroups of the value path, was
+// 3 % slower).  The occupancy is queried once per kernel and LDS size; any grid
+// gives the same results.
 template <void (*Kernel)(BatchDev)>
-static int64_t resident_grid(size_t lds, int n_cu, int64_t units, int n_reqs) {
+static dvl_status launch_sums(const BatchDev& b, size_t lds, int n_cu, hipStream_t s) {
     static std::atomic<uint64_t> cache{0};   // (lds << 8) | blocks per compute unit, 0: none
     uint64_t c = cache.load(std::memory_order_relaxed);
     int nb = (c >> 8) == (uint64_t)lds && c != 0 ? (int)(c & 0xFF) : 0;
@@ -1432,9 +1473,20 @@ static int64_t resident_grid(size_t lds, int n_cu, int64_t units, int n_reqs) {
         nb = std::min(nb, 255);
         cache.store(((uint64_t)lds << 8) | (uint64_t)nb, std::memory_order_relaxed);
     }
-    const int64_t resident = (int64_t)n_cu * nb;
-    if (units <= resident) return std::max<int64_t>(1, units);
-    return units % resident == 0 || n_reqs > 1 ? resident : std::min<int64_t>(units, (int64_t)n_cu * 8);
+    const int64_t resident = (int64_t)n_cu * nb, units = b.k1_units;
+    BatchDev d = b;
+    int64_t grid = units;
+    if (units > resident) {
+        if (b.n_reqs > 1) {
+            d.chain = (units + resident - 1) / resident;
+            grid = (units + d.chain - 1) / d.chain;
+        } else {
+            grid = units % resident == 0 ? resident : std::min<int64_t>(units, (int64_t)n_cu * 8);
+        }
+    }
+    hipLaunchKernelGGL(Kernel, dim3((unsigned)std::max<int64_t>(1, grid)), dim3(kUpdThreads), lds, s, d);
+    DVL_HIP(hipGetLastError());
+    return DVL_OK;
 }
 
 // Kernels with a request per grid row: at most kMaxGridY rows a launch.
@@ -1462,8 +1514,8 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
         if (ev && ev[i]) DVL_HIP(hipEventRecord(ev[i], s));
         return DVL_OK;
     };
-    const size_t lds1 = (size_t)sums_lds<false>(b) * sizeof(float) + kUpdWaves * sizeof(double);
-    const size_t lds1i = (size_t)sums_lds<true>(b) * sizeof(float) + kUpdWaves * sizeof(double);
+    const size_t lds1 = (size_t)sums_lds<false>(b) * sizeof(float) + kSumsPartBytes;
+    const size_t lds1i = (size_t)sums_lds<true>(b) * sizeof(float) + kSumsPartBytes;
     if (dvl_status st = mark(0)) return st;
     if (b.any_exact) {
         // few enough workgroups that their atomics on one word stay a few us
@@ -1479,14 +1531,10 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
     }
     if (dvl_status st = mark(1)) return st;
     if (b.paths & kPathValues) {
-        const unsigned g = (unsigned)resident_grid<k_tile_sums<MT, S, 0>>(lds1, n_cu, b.k1_units, b.n_reqs);
-        hipLaunchKernelGGL((k_tile_sums<MT, S, 0>), dim3(g), dim3(kUpdThreads), lds1, s, b);
-        DVL_HIP(hipGetLastError());
+        if (dvl_status st = launch_sums<k_tile_sums<MT, S, 0>>(b, lds1, n_cu, s)) return st;
     }
     if (b.paths & kPathEntries) {
-        const unsigned g = (unsigned)resident_grid<k_tile_sums<MT, S, 1>>(lds1i, n_cu, b.k1_units, b.n_reqs);
-        hipLaunchKernelGGL((k_tile_sums<MT, S, 1>), dim3(g), dim3(kUpdThreads), lds1i, s, b);
-        DVL_HIP(hipGetLastError());
+        if (dvl_status st = launch_sums<k_tile_sums<MT, S, 1>>(b, lds1i, n_cu, s)) return st;
     }
     if (dvl_status st = mark(2)) return st;
     if (dvl_status st = launch_carry_classify(b, s)) return st;
