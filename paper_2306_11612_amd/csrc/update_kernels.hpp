@@ -1222,106 +1222,144 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
 
 // ------------------------------------------------------------------ K4
 
-// Field statistics of the sorted cells [first, last] for the fields m0 ..
-// m0 + FC - 1, by one wave: the stored values of the partial 64-cell segments
-// at the two ends (16 lanes each), the statistics of the whole segments next
-// to them and of the whole tiles in between (a segment or tile is whole when
-// the range holds all of its cells below n).  Bound by the latency of cold
-// loads, above all their address translation: with the values of 256-cell
-// end steps and six statistics arrays per field a wave issued 32 loads from
-// as many pages, 4 us of the kernel's 8 at 11.8 M cells; now about 16 loads
-// from 10 pages, and on dense bins a third of the bytes: eight volumes of 8
-// fields, W 2048, 60 -> 40 us; 501 M cells, W 1920, 16.1 -> 12.7 us.  All are issued
-// before the first is used.  Sums are fp64; every lane ends with the result.
-template <int FC, typename S>
-__device__ __forceinline__ void bin_range_stats(const VolDev& j, int m0, int M, uint32_t first, uint32_t last,
-                                                double (&sum)[FC], float (&mn)[FC], float (&mx)[FC]) {
-    const int lane = lane_id();
+// Lanes of a wave's classes: lane l serves field l % P, P the power of two not
+// below the field count (a function of M alone, so that the sums of a volume
+// associate alike in every variant).
+__host__ __device__ constexpr int stat_classes(int M) { return M <= 1 ? 1 : (M <= 2 ? 2 : (M <= 4 ? 4 : (M <= 8 ? 8 : 16))); }
+
+// v combined over the lanes of each class, in every lane: rotations inside the
+// rows of 16, then across the rows
+template <int P, int N, typename Op>
+__device__ __forceinline__ void class_reduce(uint32_t (&v)[N], Op op) {
+    auto with = [&](auto move) {
+        uint32_t o[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) o[i] = move(v[i]);
+        op(v, o);
+    };
+    if constexpr (P <= 1) with([](uint32_t x) { return dpp_move<0x121, 0xF>(x, x); });    // row_ror:1
+    if constexpr (P <= 2) with([](uint32_t x) { return dpp_move<0x122, 0xF>(x, x); });
+    if constexpr (P <= 4) with([](uint32_t x) { return dpp_move<0x124, 0xF>(x, x); });
+    if constexpr (P <= 8) with([](uint32_t x) { return dpp_move<0x128, 0xF>(x, x); });
+    const int l = lane_id();
+    with([l](uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_bpermute((l ^ 16) << 2, (int)x); });
+    with([l](uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_bpermute((l ^ 32) << 2, (int)x); });
+}
+
+// Field statistics of the sorted cells [first, last], by one wave, field l % P
+// by lane l (`field`: its values; `act`: the volume has it): the stored values
+// of the partial 64-cell segments at the two ends, the statistics of the whole
+// segments next to them and of the whole tiles in between (a segment or tile is
+// whole when the range holds all of its cells below n).  A stretch's statistics
+// lie field after field, so a load covers 64 / P neighbouring stretches in one
+// piece and every lane sums one field.  (A field after another, 64 lanes each,
+// left three lanes of four idle on dense bins and reduced every field over the
+// whole wave, some 2700 instructions a bin of 8 fields: eight volumes of 8
+// fields, W 2048, 39 us against 21; eight requests on two 20 M-cell volumes 29
+// against 22; 64^3 cells 5.7 against 4.6; 501 M, W 1920, 13.3 against 12.2.)
+// Bound by the latency of cold loads, above all their address translation, on
+// few or large bins.  All loads of a round are issued before the first is used.  Sums are fp64; every lane
+// ends with its class's result.
+template <int P, typename S>
+__device__ __forceinline__ FieldStat bin_range_stats(const VolDev& j, int M, bool act, const char* field,
+                                                     uint32_t first, uint32_t last) {
+    constexpr int L = kWave / P;                      // lanes of a class
+    constexpr int KQ = L >= 32 ? 1 : 32 / L;          // 4-cell vectors of the two end segments per lane
+    constexpr int KS = P < 4 ? 2 : 4;                 // stretches of each kind per lane and round
+    const int lane = lane_id(), li = lane / P, m = lane % P;
     const int64_t n = uni(j.n);
     const int shift = __builtin_ctz((unsigned)uni(j.tile_steps)) + 2;     // segments per tile: a power of two
     const int64_t f = first, l = last;
     auto whole = [&](int64_t sg) { return f <= sg * kSegCells && l >= min(n, sg * kSegCells + kSegCells) - 1; };
     const int64_t sf = f / kSegCells, sl = l / kSegCells;
-    const bool wf = whole(sf), wl = whole(sl);
-    // partial end segments: lanes 0-15 the first, 16-31 the last, 4 cells each;
-    // lanes with no cell of the range fetch nothing
-    const int64_t c = (lane < 16 ? sf : sl) * kSegCells + 4 * (lane & 15);
-    const bool need = (lane < 16 ? !wf : lane < 32 && !wl && sl != sf) && c + 3 >= f && c <= l;
+    const bool wf = whole(sf), wl = whole(sl) || sl == sf;
     // whole segments [a, b]; whole tiles [ta, tb] among them; the segments
-    // outside whole tiles: [s0, s0 + n0) and [s2, s2 + n1)
-    const int64_t a = wf ? sf : sf + 1, b = wl ? sl : sl - 1;
-    int64_t ta = 1, tb = 0, s2 = 0;
-    int n0 = 0, n1 = 0;
+    // outside whole tiles: [a, a + n0) and [s2, s2 + n1)
+    const int a = (int)(wf ? sf : sf + 1), b = (int)(whole(sl) ? sl : sl - 1);
+    int ta = 1, tb = 0, s2 = 0, n0 = 0, n1 = 0;
     if (a <= b) {
         ta = (a + (1 << shift) - 1) >> shift;
         tb = ((b + 1) >> shift) - 1;
         if (ta <= tb) {
-            n0 = (int)((ta << shift) - a);
+            n0 = (ta << shift) - a;
             s2 = (tb + 1) << shift;
-            n1 = (int)(b + 1 - s2);
+            n1 = b + 1 - s2;
         } else {
-            n0 = (int)(b + 1 - a);      // less than two tiles
+            n0 = b + 1 - a;             // less than two tiles
         }
     }
+    const int ns = n0 + n1, nt = tb - ta + 1;
+    const FieldStat* const tile_stat = uni(j.tile_stat) + m;
+    const FieldStat* const seg_stat = uni(j.seg_stat) + m;
     auto segment = [&](int i) { return i < n0 ? a + i : s2 + (i - n0); };
-    constexpr int kAhead = 2;           // segments per lane loaded at once (all of 16-step tiles)
-    const bool tile = ta + lane <= tb;
-    Quad<S> qd[FC];
-    FieldStat ts[FC], ss[kAhead][FC];
-    const FieldStat* const tile_stat = uni(j.tile_stat) + m0;
-    const FieldStat* const seg_stat = uni(j.seg_stat) + m0;
     auto stat = [](const FieldStat* p, int64_t i) {
         return __builtin_bit_cast(FieldStat, gload<u32x4>(p + i, 0));
     };
+    FieldStat r{0.0, INFINITY, -INFINITY};
+    auto add = [&](double sum, float mn, float mx) {
+        r.sum += sum;
+        r.mn = fminf(r.mn, mn);
+        r.mx = fmaxf(r.mx, mx);
+    };
+    Quad<S> qd[KQ];
+    uint32_t c[KQ];
+    bool need[KQ];
+    FieldStat ss[KS], ts[KS];
 #pragma unroll
-    for (int m = 0; m < FC; ++m)
-        if (m0 + m < M && need) qd[m].load(j.fields[m0 + m], c >> 2);
-#pragma unroll
-    for (int m = 0; m < FC; ++m)
-        if (m0 + m < M && tile) ts[m] = stat(tile_stat, (ta + lane) * M + m);
-#pragma unroll
-    for (int k = 0; k < kAhead; ++k) {
-        const int i = lane + k * kWave;
-#pragma unroll
-        for (int m = 0; m < FC; ++m)
-            if (m0 + m < M && i < n0 + n1) ss[k][m] = stat(seg_stat, segment(i) * M + m);
+    for (int k = 0; k < KQ; ++k) {
+        const int e = li + k * L;                     // vectors 0-15: the first segment's, 16-31: the last's
+        c[k] = (uint32_t)(e < 16 ? sf : sl) * kSegCells + 4 * (e & 15);
+        need[k] = act && e < 32 && !(e < 16 ? wf : wl) && c[k] + 3 >= first && c[k] <= last;
+        if (need[k]) qd[k].load(field, c[k] >> 2);
     }
+    for (int i0 = 0; i0 == 0 || i0 < ns || i0 < nt; i0 += KS * L) {
 #pragma unroll
-    for (int m = 0; m < FC; ++m) {
-        sum[m] = 0.0;
-        mn[m] = INFINITY;
-        mx[m] = -INFINITY;
-        if (m0 + m < M) {
-            auto add = [&](const FieldStat& x) {
-                sum[m] += x.sum;
-                mn[m] = fminf(mn[m], x.mn);
-                mx[m] = fmaxf(mx[m], x.mx);
-            };
-            if (need) {
+        for (int k = 0; k < KS; ++k) {
+            const int i = i0 + li + k * L;
+            if (act && i < ns) ss[k] = stat(seg_stat, (int64_t)segment(i) * M);
+            if (act && i < nt) ts[k] = stat(tile_stat, (int64_t)(ta + i) * M);
+        }
+        if (i0 == 0) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if (c + k >= f && c + k <= l) {
-                        const float v = qd[m].get(k);
-                        add(FieldStat{(double)v, v, v});
-                    }
+            for (int k = 0; k < KQ; ++k) {
+                if (!need[k]) continue;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const bool in = c[k] + x - first <= last - first;
+                    const float v = qd[k].get(x);
+                    add(in ? (double)v : 0.0, in ? v : INFINITY, in ? v : -INFINITY);
                 }
             }
-            if (tile) add(ts[m]);
-            for (int64_t t = ta + lane + kWave; t <= tb; t += kWave) add(stat(tile_stat, t * M + m));
+        }
 #pragma unroll
-            for (int k = 0; k < kAhead; ++k)
-                if (lane + k * kWave < n0 + n1) add(ss[k][m]);
-            for (int i = lane + kAhead * kWave; i < n0 + n1; i += kWave) add(stat(seg_stat, segment(i) * M + m));
+        for (int k = 0; k < KS; ++k) {
+            const int i = i0 + li + k * L;
+            if (act && i < ns) add(ss[k].sum, ss[k].mn, ss[k].mx);
+            if (act && i < nt) add(ts[k].sum, ts[k].mn, ts[k].mx);
         }
     }
-#pragma unroll
-    for (int m = 0; m < FC; ++m) {
-        if (m0 + m < M) {
-            sum[m] = wave_total_d(sum[m]);
-            mn[m] = wave_lowest_f(mn[m]);
-            mx[m] = wave_highest_f(mx[m]);
-        }
+    uint32_t w[4];
+    {
+        const u32x4 u = __builtin_bit_cast(u32x4, r);
+        w[0] = u.x;
+        w[1] = u.y;
+        w[2] = u.z;
+        w[3] = u.w;
     }
+    class_reduce<P>(w, [](uint32_t (&x)[4], const uint32_t (&o)[4]) {
+        auto d = [](const uint32_t (&y)[4]) { return __longlong_as_double(((uint64_t)y[1] << 32) | y[0]); };
+        const uint64_t sum = (uint64_t)__double_as_longlong(d(x) + d(o));
+        x[0] = (uint32_t)sum;
+        x[1] = (uint32_t)(sum >> 32);
+        x[2] = __float_as_uint(fminf(__uint_as_float(x[2]), __uint_as_float(o[2])));
+        x[3] = __float_as_uint(fmaxf(__uint_as_float(x[3]), __uint_as_float(o[3])));
+    });
+    u32x4 u;
+    u.x = w[0];
+    u.y = w[1];
+    u.z = w[2];
+    u.w = w[3];
+    return __builtin_bit_cast(FieldStat, u);
 }
 
 // K4: one wave per (request, bin).  The bin's cell range: written by the
@@ -1342,6 +1380,12 @@ __global__ __launch_bounds__(kUpdThreads) void k_bin_stats(BatchDev bd) {
         gstore<double>(q.f_total, 0, gload<double>(q.ws.scal, 0));
         gstore<float>(q.vmax_used, 0, gload<float>(q.vmax_dev, 0));
     }
+    // the lane's field: its values, quantiser and table (P divides the wave, so
+    // lanes below M serve the field of their number)
+    const int mine = min(lane % stat_classes(M), M - 1);
+    const char* const field = reinterpret_cast<const char*>(gload<uint64_t>(j.fields, mine));
+    const float qs = gload<float>(q.s, mine), qb = gload<float>(q.b, mine), qn = gload<float>(q.nmax, mine);
+    const int qo = gload<int32_t>(q.tf_off, mine);
     const int64_t T = uni(j.n_tiles);
     const int32_t* hb = q.ws.head_bin;
     const int32_t* tb = q.ws.tail_bin;
@@ -1399,33 +1443,32 @@ __global__ __launch_bounds__(kUpdThreads) void k_bin_stats(BatchDev bd) {
         gstore<uint32_t>(q.first_cell, b, first);
         gstore<uint32_t>(q.last_cell, b, last);
     }
-    const uint32_t cnt = last - first + 1u;
-    constexpr int FC = MT < 4 ? MT : 4;
-#pragma unroll
-    for (int m0 = 0; m0 < MT; m0 += FC) {
-        if (m0 >= M) break;
-        double sm[FC];
-        float mn[FC], mx[FC];
-        bin_range_stats<FC, S>(j, m0, M, first, last, sm, mn, mx);
-        // a lane per field
-        double ls = sm[0];
-        float lmn = mn[0], lmx = mx[0];
-#pragma unroll
-        for (int m = 1; m < FC; ++m) {
-            ls = lane == m ? sm[m] : ls;
-            lmn = lane == m ? mn[m] : lmn;
-            lmx = lane == m ? mx[m] : lmx;
+    first = uni(first);
+    last = uni(last);
+    auto stats = [&](auto classes) {
+        constexpr int P = decltype(classes)::value;
+        return bin_range_stats<P, S>(j, M, lane % P < M, field, first, last);
+    };
+    FieldStat r;
+    if constexpr (MT <= 8) {
+        r = stats(std::integral_constant<int, stat_classes(MT)>{});
+    } else {
+        switch (stat_classes(M)) {
+            case 1: r = stats(std::integral_constant<int, 1>{}); break;
+            case 2: r = stats(std::integral_constant<int, 2>{}); break;
+            case 4: r = stats(std::integral_constant<int, 4>{}); break;
+            case 8: r = stats(std::integral_constant<int, 8>{}); break;
+            default: r = stats(std::integral_constant<int, 16>{}); break;
         }
-        const int m = m0 + lane;
-        if (lane < FC && m < M) {
-            const float mean = (float)(ls / (double)cnt);
-            const int e = tf_entry(mean, q.s[m], q.b[m], q.nmax[m]);
-            const int64_t o = (int64_t)m * q.W + b;
-            gstore<float>(q.mean, o, mean);
-            gstore<float>(q.vmin, o, lmn);
-            gstore<float>(q.vmax, o, lmx);
-            gstore<float>(q.y, o, gload<float>(q.tf, q.tf_off[m] + e));
-        }
+    }
+    if (lane < M) {
+        const float mean = (float)(r.sum / (double)(last - first + 1u));
+        const int e = tf_entry(mean, qs, qb, qn);
+        const int64_t o = (int64_t)lane * q.W + b;
+        gstore<float>(q.mean, o, mean);
+        gstore<float>(q.vmin, o, r.mn);
+        gstore<float>(q.vmax, o, r.mx);
+        gstore<float>(q.y, o, gload<float>(q.tf, qo + e));
     }
 }
 
