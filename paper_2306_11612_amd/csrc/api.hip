@@ -478,6 +478,7 @@ struct Plan {
     int max_bin_units = 1;
     int any_exact = 0;
     int64_t k1_units = 0;
+    int64_t n_steps = 0;
     size_t tf_floats = 0;
     // descriptor block, uploaded before every launch:
     //   [unit0 x reqs][ReqDev x reqs][max V x reqs][tables]
@@ -561,6 +562,7 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         d.v.split = d.v.split && d.scan_mode == DVL_SCAN_FP64;
         // a unit of the importance pass: a run per wave, or a tile
         P.unit0.push_back(P.k1_units);
+        P.n_steps += (int64_t)d.v.n_tiles * d.v.tile_steps;
         P.k1_units += d.v.split ? d.v.n_runs : (d.v.n_runs + kUpdWaves - 1) / kUpdWaves;
         d.vmax_exact = r.p.vmax_mode == DVL_VMAX_EXACT;
         // a workgroup of k_bin per tile when there are no more tiles than
@@ -808,6 +810,7 @@ static BatchDev batch_dev(const Plan& P, char* d, int paths) {
     b.reqs = (const ReqDev*)(d + P.off_reqs);
     b.n_reqs = (int)P.rdev.size();
     b.k1_units = P.k1_units;
+    b.n_steps = P.n_steps;
     b.any_exact = P.any_exact;
     b.chain = 1;
     b.paths = paths;

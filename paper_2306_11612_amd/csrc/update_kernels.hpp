@@ -452,11 +452,19 @@ __host__ __device__ __forceinline__ int sums_lds(const BatchDev& b) {
 
 // ------------------------------------------------------------------ K0
 
-// max V over nsteps steps from cell c_begin, by one wave (per lane); eight
-// steps of cached entries (two of values) in flight
-template <int MT, typename D>
-__device__ __forceinline__ float vmax_run(const ReqDev& q, int64_t c_begin, int nsteps, const float* tf_lds) {
-    constexpr int G = 2 * Group<D>::n;
+constexpr int kMaxStreamSteps = 1 << 20;    // steps of one wave's stream: its offsets stay below 2^32 bytes
+
+// max V over nsteps steps from cell c_begin, by one wave (per lane): two groups
+// of steps in flight, the first ones while `tables()` waits for the tables
+// (called once, by a wave without work too)
+template <int MT, typename D, typename Tables>
+__device__ __forceinline__ float vmax_run(const ReqDev& q, int64_t c_begin, int nsteps, const float* tf_lds,
+                                          Tables tables) {
+    constexpr int G = Group<D>::n;
+    if (nsteps <= 0) {
+        tables();
+        return 0.0f;
+    }
     const int lane = lane_id();
     const VolDev& vol = q.v;
     const int M = uni(fields_of<MT>(vol.M));
@@ -465,52 +473,46 @@ __device__ __forceinline__ float vmax_run(const ReqDev& q, int64_t c_begin, int 
     qn.load(q);
     float vmax = 0.0f;
     const RunView<MT> view = run_view<MT, D>(vol, M, c_begin);
-    for (int s = 0; s < nsteps; s += G) {
-        D d[G];
+    D A[G], B[G];
+    auto load = [&](D (&d)[G], int s) {
 #pragma unroll
         for (int g = 0; g < G; ++g) d[g].load(view, M, min(s + g, nsteps - 1), 0u);   // levels unused
+    };
+    auto process = [&](const D (&d)[G], int s) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (s + g >= nsteps) break;
-            const int64_t quad = ((c_begin + (int64_t)(s + g) * kStepCells) >> 2) + lane;
+            float v[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if ((quad << 2) + k < n) vmax = fmaxf(vmax, cell_v<MT>(d[g], k, M, tf_lds, qn));
+            for (int k = 0; k < 4; ++k) v[k] = cell_v<MT>(d[g], k, M, tf_lds, qn);
+            const int64_t c0 = c_begin + (int64_t)(s + g) * kStepCells;
+            if (c0 + kStepCells <= n) {
+                vmax = fmaxf(vmax, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (c0 + 4 * lane + k < n) vmax = fmaxf(vmax, v[k]);
+            }
         }
+    };
+    load(A, 0);
+    load(B, G);
+    tables();
+    for (int s = 0; s < nsteps; s += 2 * G) {
+        process(A, s);
+        load(A, s + 2 * G);
+        if (s + G >= nsteps) break;
+        process(B, s + G);
+        load(B, s + 3 * G);
     }
     return vmax;
 }
 
-// The steps of wave wv in unit `local` of a request: four runs a workgroup, a
-// wave each, or (VolDev::split) one tile, `part` steps a wave.
-struct WaveSteps {
-    int t0;                   // first tile
-    int64_t c_begin;
-    int nsteps;
-};
-__device__ __forceinline__ WaveSteps wave_steps(const VolDev& vol, int local, int wv, bool split, int part) {
-    const int tile_steps = uni(vol.tile_steps), tpr = uni(vol.tiles_per_run), n_tiles = uni(vol.n_tiles);
-    const int64_t n = uni(vol.n);
-    WaveSteps w;
-    int s0 = 0;
-    int64_t c_end;
-    if (split) {
-        w.t0 = local;
-        s0 = wv * part;
-        c_end = min(n, ((int64_t)w.t0 * tile_steps + s0 + part) * kStepCells);
-    } else {
-        const int r = local * kUpdWaves + wv;
-        w.t0 = r < uni(vol.n_runs) ? r * tpr : n_tiles;
-        c_end = min(n, (int64_t)min(n_tiles, w.t0 + tpr) * tile_steps * kStepCells);
-    }
-    w.c_begin = ((int64_t)w.t0 * tile_steps + s0) * kStepCells;
-    w.nsteps = c_end > w.c_begin ? (int)((c_end - w.c_begin + kStepCells - 1) / kStepCells) : 0;
-    return w;
-}
-
-// A workgroup keeps the maximum of its units and publishes it with one atomic
-// per request (an atomic per wave on the one word cost 12 ns each: 15 of 24 us
-// for 5.2 M cells).
+// A workgroup takes b.chain consecutive units, the cells of one request among
+// them as one stretch in four parts, and publishes the request's maximum with
+// one atomic (atomics on one word follow each other at 12 ns: 5.2 M cells took
+// 24 us with one per wave, 19 with one for each of 1024 workgroups, 13 with
+// 316 workgroups).
 // IDX: this instance serves the requests that read cached entries (1) or values (0)
 template <int MT, typename S, int IDX>
 __global__ __launch_bounds__(kUpdThreads) void k_vmax_exact(BatchDev b) {
@@ -531,22 +533,31 @@ __global__ __launch_bounds__(kUpdThreads) void k_vmax_exact(BatchDev b) {
         __syncthreads();
         vmax = 0.0f;
     };
-    for (int64_t u = block_x(); u < b.k1_units; u += grid_dim_x()) {
+    using D = typename std::conditional<IDX != 0, StepIdx<MT>, StepData<MT, S>>::type;
+    const int64_t u1 = min((block_x() + 1) * b.chain, b.k1_units);
+    for (int64_t u = block_x() * b.chain; u < u1;) {
         const Unit un = find_unit(b, u);
         const ReqDev& q = b.reqs[un.req];
-        if (uni(q.entries) != IDX || !uni(q.vmax_exact)) continue;
-        if (un.req != loaded) {
-            if (loaded >= 0) publish();             // also: every wave is done with the tables
+        int k = (int)min(u1 - u, (int64_t)un.left);
+        if (uni(q.entries) != IDX || !uni(q.vmax_exact)) {
+            u += k;
+            continue;
+        }
+        auto tables = [&]() {
+            if (un.req == loaded) return;
             load_tables<MT, IDX != 0>(q, uni(fields_of<MT>(q.v.M)), tf_lds);
             __syncthreads();
             loaded = un.req;
-        }
-        const WaveSteps ws = wave_steps(q.v, un.local, wv, uni(q.v.split) != 0, uni(q.v.tile_steps) / kUpdWaves);
-        if (ws.nsteps <= 0) continue;
-        if constexpr (IDX != 0)
-            vmax = fmaxf(vmax, vmax_run<MT, StepIdx<MT>>(q, ws.c_begin, ws.nsteps, tf_lds));
-        else
-            vmax = fmaxf(vmax, vmax_run<MT, StepData<MT, S>>(q, ws.c_begin, ws.nsteps, tf_lds));
+        };
+        if (un.req != loaded && loaded >= 0) publish();      // also: every wave is done with the tables
+        const int unit_steps = uni(q.v.tile_steps) * (uni(q.v.split) ? 1 : kUpdWaves * uni(q.v.tiles_per_run));
+        k = max(1, min(k, kUpdWaves * kMaxStreamSteps / unit_steps));
+        const int64_t n_steps = (uni(q.v.n) + kStepCells - 1) / kStepCells;
+        const int64_t s0 = (int64_t)un.local * unit_steps, s1 = min(n_steps, s0 + (int64_t)k * unit_steps);
+        const int64_t part = (s1 - s0 + kUpdWaves - 1) / kUpdWaves;
+        const int64_t w0 = s0 + wv * part, w1 = min(s1, w0 + part);
+        vmax = fmaxf(vmax, vmax_run<MT, D>(q, w0 * kStepCells, (int)(w1 - w0), tf_lds, tables));
+        u += k;
     }
     if (loaded >= 0) publish();
 }
@@ -812,7 +823,6 @@ __device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_
 // against unit by unit, the requests in turns.
 constexpr int kMaxChain = 16;           // units of one stream
 constexpr size_t kSumsPartBytes = (size_t)kMaxChain * kUpdWaves * sizeof(double);
-constexpr int kMaxStreamSteps = 1 << 20;    // a wave's offsets stay below 2^32 bytes
 template <int MT, typename S, int IDX>
 __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
     extern __shared__ float tf_lds[];
@@ -1561,14 +1571,19 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
     const size_t lds1i = (size_t)sums_lds<true>(b) * sizeof(float) + kSumsPartBytes;
     if (dvl_status st = mark(0)) return st;
     if (b.any_exact) {
-        // few enough workgroups that their atomics on one word stay a few us
-        const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(b.k1_units, (int64_t)n_cu * 4));
+        // 16 steps a wave, so that the atomics on one word stay a few us, but a
+        // workgroup for every compute unit; at most four, whose loads in flight
+        // fill the memory
+        const int64_t want = std::min<int64_t>(std::max<int64_t>(b.n_steps / (16 * kUpdWaves), n_cu), (int64_t)n_cu * 4);
+        BatchDev d = b;
+        d.chain = std::max<int64_t>(1, (b.k1_units + want - 1) / want);
+        const dim3 g((unsigned)std::max<int64_t>(1, (b.k1_units + d.chain - 1) / d.chain));
         if (b.paths & kPathValues) {
-            hipLaunchKernelGGL((k_vmax_exact<MT, S, 0>), dim3(g), dim3(kUpdThreads), lds1, s, b);
+            hipLaunchKernelGGL((k_vmax_exact<MT, S, 0>), g, dim3(kUpdThreads), lds1, s, d);
             DVL_HIP(hipGetLastError());
         }
         if (b.paths & kPathEntries) {
-            hipLaunchKernelGGL((k_vmax_exact<MT, S, 1>), dim3(g), dim3(kUpdThreads), lds1i, s, b);
+            hipLaunchKernelGGL((k_vmax_exact<MT, S, 1>), g, dim3(kUpdThreads), lds1i, s, d);
             DVL_HIP(hipGetLastError());
         }
     }
