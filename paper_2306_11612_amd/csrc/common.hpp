@@ -247,6 +247,14 @@ __device__ __forceinline__ T gload_at(const char* base, uint32_t byte_off) {
     return *(const DVL_GLOBAL T*)(g + byte_off);
 }
 
+// The same for streams too large to be found in the caches again: marked
+// non-temporal.
+template <typename T>
+__device__ __forceinline__ T gstream_at(const char* base, uint32_t byte_off) {
+    const DVL_GLOBAL char* g = (const DVL_GLOBAL char*)base;
+    return __builtin_nontemporal_load((const DVL_GLOBAL T*)(g + byte_off));
+}
+
 // The constant address space (kernel arguments are read through it).
 #define DVL_CONST __attribute__((address_space(4)))
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -303,6 +311,7 @@ struct Quad<F32> {
     f32x4 v;
     __device__ __forceinline__ void load(const void* base, int64_t i4) { v = gload<f32x4>(base, i4); }
     __device__ __forceinline__ void load_at(const char* base, uint32_t off) { v = gload_at<f32x4>(base, off); }
+    __device__ __forceinline__ void stream_at(const char* base, uint32_t off) { v = gstream_at<f32x4>(base, off); }
     __device__ __forceinline__ float get(int k) const {
         return k == 0 ? v.x : (k == 1 ? v.y : (k == 2 ? v.z : v.w));
     }
@@ -313,6 +322,7 @@ struct Quad16 {
     u32x2 v;
     __device__ __forceinline__ void load(const void* base, int64_t i4) { v = gload<u32x2>(base, i4); }
     __device__ __forceinline__ void load_at(const char* base, uint32_t off) { v = gload_at<u32x2>(base, off); }
+    __device__ __forceinline__ void stream_at(const char* base, uint32_t off) { v = gstream_at<u32x2>(base, off); }
     __device__ __forceinline__ float get(int k) const {
         const uint32_t w = k < 2 ? v.x : v.y;
         const uint16_t h = (uint16_t)((k & 1) ? (w >> 16) : (w & 0xFFFF));

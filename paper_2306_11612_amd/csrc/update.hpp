@@ -118,6 +118,7 @@ struct BatchDev {
     int64_t k1_units;
     int64_t chain;            // consecutive units a workgroup of the importance pass or K0 takes
     int64_t n_steps;          // 256-cell steps of all requests
+    int stream;               // read the cells as streams that bypass the caches (see batch_dev)
     int any_exact;
     int paths;                // kPath*: which variants of the importance pass and the projection to launch
     int max_req_tf;           // largest request table block (floats)

@@ -198,12 +198,19 @@ struct StepData {
     Quad<S> q[MT];
     LaneLevels lv;
     __device__ static const void* source(const VolDev& v, int m) { return v.fields[m]; }
-    // step: index from the run's first step; code: its level code
+    // step: index from the run's first step; code: its level code; STREAM: a
+    // volume too large for the caches (common.hpp)
+    template <bool STREAM>
     __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step, uint32_t code) {
         const uint32_t qd = (uint32_t)(step * kWave + lane_id());
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
-            if (m < M) q[m].load_at(v.base[m], qd * kQuadBytes);
+        for (int m = 0; m < MT; ++m) {
+            if (m >= M) continue;
+            if constexpr (STREAM)
+                q[m].stream_at(v.base[m], qd * kQuadBytes);
+            else
+                q[m].load_at(v.base[m], qd * kQuadBytes);
+        }
         lv.load(v.lev, qd, code);
     }
 };
@@ -216,11 +223,12 @@ struct StepIdx {
     uint32_t e[MT];
     LaneLevels lv;
     __device__ static const void* source(const VolDev& v, int m) { return v.idx[m]; }
+    template <bool STREAM>
     __device__ __forceinline__ void load(const RunView<MT>& v, int M, int step, uint32_t code) {
         const uint32_t qd = (uint32_t)(step * kWave + lane_id());
 #pragma unroll
         for (int m = 0; m < MT; ++m)
-            if (m < M) e[m] = gload_at<uint32_t>(v.base[m], qd * 4u);
+            if (m < M) e[m] = STREAM ? gstream_at<uint32_t>(v.base[m], qd * 4u) : gload_at<uint32_t>(v.base[m], qd * 4u);
         lv.load(v.lev, qd, code);
     }
 };
@@ -457,7 +465,7 @@ constexpr int kMaxStreamSteps = 1 << 20;    // steps of one wave's stream: its o
 // max V over nsteps steps from cell c_begin, by one wave (per lane): two groups
 // of steps in flight, the first ones while `tables()` waits for the tables
 // (called once, by a wave without work too)
-template <int MT, typename D, typename Tables>
+template <int MT, typename D, bool STREAM, typename Tables>
 __device__ __forceinline__ float vmax_run(const ReqDev& q, int64_t c_begin, int nsteps, const float* tf_lds,
                                           Tables tables) {
     constexpr int G = Group<D>::n;
@@ -476,7 +484,7 @@ __device__ __forceinline__ float vmax_run(const ReqDev& q, int64_t c_begin, int 
     D A[G], B[G];
     auto load = [&](D (&d)[G], int s) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) d[g].load(view, M, min(s + g, nsteps - 1), 0u);   // levels unused
+        for (int g = 0; g < G; ++g) d[g].template load<STREAM>(view, M, min(s + g, nsteps - 1), 0u);   // levels unused
     };
     auto process = [&](const D (&d)[G], int s) {
 #pragma unroll
@@ -556,7 +564,8 @@ __global__ __launch_bounds__(kUpdThreads) void k_vmax_exact(BatchDev b) {
         const int64_t s0 = (int64_t)un.local * unit_steps, s1 = min(n_steps, s0 + (int64_t)k * unit_steps);
         const int64_t part = (s1 - s0 + kUpdWaves - 1) / kUpdWaves;
         const int64_t w0 = s0 + wv * part, w1 = min(s1, w0 + part);
-        vmax = fmaxf(vmax, vmax_run<MT, D>(q, w0 * kStepCells, (int)(w1 - w0), tf_lds, tables));
+        vmax = fmaxf(vmax, b.stream ? vmax_run<MT, D, true>(q, w0 * kStepCells, (int)(w1 - w0), tf_lds, tables)
+                                    : vmax_run<MT, D, false>(q, w0 * kStepCells, (int)(w1 - w0), tf_lds, tables));
         u += k;
     }
     if (loaded >= 0) publish();
@@ -649,13 +658,17 @@ struct ModeSum {
 // flight together: 432 -> 417 us for 501 M cells of 4 fields (vector units now
 // busy 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s).
 // kRunSplitAny: fp64 sums; kRunP1, kRunPow: anything.
-enum RunKind { kRunPlain, kRunP1, kRunPow, kRunSplit, kRunSplitAny };
+// kRunStream, kRunP1Stream: kRunPlain and kRunP1 over a volume too large for the
+// caches (BatchDev::stream).
+enum RunKind { kRunPlain, kRunStream, kRunP1, kRunP1Stream, kRunPow, kRunSplit, kRunSplitAny };
 template <int MT, typename D, int KIND, typename Tables>
 __device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_begin, int64_t c_begin, int nsteps,
                                               int part, double* part_sums, const float* tf_lds, Tables tables) {
     constexpr int G = Group<D>::n;
     constexpr bool kSplit = KIND == kRunSplit || KIND == kRunSplitAny;
-    constexpr bool kPlain = KIND == kRunPlain || KIND == kRunSplit;
+    constexpr bool kStream = KIND == kRunStream || KIND == kRunP1Stream;
+    constexpr bool kPlain = KIND == kRunPlain || KIND == kRunStream || KIND == kRunSplit;
+    constexpr bool kP1 = KIND == kRunP1 || KIND == kRunP1Stream;
     if (nsteps <= 0) {
         tables();
         return;
@@ -692,10 +705,10 @@ __device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_
         const StepCodes<G> c1 = load_codes<G>(view.lcode, at(min(G, last_group)));
         cA = load_codes<G>(view.lcode, at(min(2 * G, last_group)));
 #pragma unroll
-        for (int g = 0; g < G; ++g) A[g].load(view, M, g, c0.c[g]);
+        for (int g = 0; g < G; ++g) A[g].template load<kStream>(view, M, g, c0.c[g]);
         cB = load_codes<G>(view.lcode, at(min(3 * G, last_group)));
 #pragma unroll
-        for (int g = 0; g < G; ++g) B[g].load(view, M, at(min(G + g, nsteps - 1)), c1.c[g]);
+        for (int g = 0; g < G; ++g) B[g].template load<kStream>(view, M, at(min(G + g, nsteps - 1)), c1.c[g]);
     }
     tables();
     ctx_vmax(ctx, vmax);
@@ -767,7 +780,7 @@ __device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_
             for (int k = 0; k < 4; ++k) {
                 const uint32_t L = cur[g].lv.get(k);
                 const float v = cell_v<MT>(cur[g], k, M, tf_lds, qn);
-                f[k] = KIND == kRunP1 ? importance_p1(v, L, ctx) : importance_from_v(v, L, ctx);
+                f[k] = kP1 ? importance_p1(v, L, ctx) : importance_from_v(v, L, ctx);
             }
             if (!full) {
 #pragma unroll
@@ -795,7 +808,7 @@ __device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_
         {
             const StepCodes<G> c2 = load_codes<G>(view.lcode, at(min(s + 4 * G, last_group)));
 #pragma unroll
-            for (int g = 0; g < G; ++g) A[g].load(view, M, at(min(s + 2 * G + g, nsteps - 1)), cA.c[g]);
+            for (int g = 0; g < G; ++g) A[g].template load<kStream>(view, M, at(min(s + 2 * G + g, nsteps - 1)), cA.c[g]);
             cA = c2;
         }
         if (s + G >= nsteps) break;
@@ -803,7 +816,7 @@ __device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_
         {
             const StepCodes<G> c3 = load_codes<G>(view.lcode, at(min(s + 5 * G, last_group)));
 #pragma unroll
-            for (int g = 0; g < G; ++g) B[g].load(view, M, at(min(s + 3 * G + g, nsteps - 1)), cB.c[g]);
+            for (int g = 0; g < G; ++g) B[g].template load<kStream>(view, M, at(min(s + 3 * G + g, nsteps - 1)), cB.c[g]);
             cB = c3;
         }
     }
@@ -862,8 +875,12 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
                 const int nsteps = r1 > r0 ? (int)((c_end - c_begin + kStepCells - 1) / kStepCells) : 0;
                 const bool plain = p1 && uni(q.scan_mode) == DVL_SCAN_FP64 && !stored &&
                                    c_begin + (int64_t)nsteps * kStepCells <= n && nsteps % tile_steps == 0;
-                if (plain)
+                if (plain && b.stream)
+                    tile_sums_run<MT, D, kRunStream>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
+                else if (plain)
                     tile_sums_run<MT, D, kRunPlain>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
+                else if (p1 && b.stream)
+                    tile_sums_run<MT, D, kRunP1Stream>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
                 else if (p1)
                     tile_sums_run<MT, D, kRunP1>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
                 else

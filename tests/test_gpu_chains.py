@@ -60,3 +60,34 @@ def test_chains_of_units(n_requests, entry_cache):
         ex.close()
         for V in Vs:
             V.close()
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(vmax_mode=2), dict(scan_mode=1), dict(exponent=2.0)])
+def test_cells_read_as_streams(kw):
+    """280 MB of cells alone are read past the caches, two requests on them in
+    one batch are not: the same bits either way, with few and with many bins."""
+    D = dvl()
+    s = 260
+    g = torch.Generator(device="cuda").manual_seed(5)
+    i = torch.arange(s ** 3, device="cuda")
+    fields = [torch.rand(s ** 3, device="cuda", generator=g) for _ in range(4)]
+    V = D.build_order((i % s).int(), ((i // s) % s).int(), (i // (s * s)).int(),
+                      torch.zeros(s ** 3, dtype=torch.uint8, device="cuda"), fields, entry_cache=2)
+    ex = D.Executor()
+    try:
+        A = tfs(77, 4)
+        for W in (16, 1920):
+            reqs = [D.Request(V, A, D.Bins(W, 4), **kw) for _ in range(2)]
+            ex.update_batch(reqs)
+            for m in range(4):
+                V.set_tf(m, A[m])
+            b = D.Bins(W, 4)
+            V.update(b, **kw)
+            alone = V.read_bins(b)
+            for r in reqs:
+                got = V.read_bins(r.bins)
+                for k in KEYS:
+                    assert np.asarray(got[k]).tobytes() == np.asarray(alone[k]).tobytes(), (W, k)
+    finally:
+        ex.close()
+        V.close()
