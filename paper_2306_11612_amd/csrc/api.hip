@@ -1656,10 +1656,19 @@ dvl_status dvl_export_order(const dvl_volume* v, uint64_t* keys, uint32_t* perm,
     g_err.clear();
     if (dvl_status st = check_volume(v)) return st;
     hipStream_t s = (hipStream_t)stream;
-    if (keys) {
-        if (dvl_status st = launch_scatter_back(v->n, v->perm, v->keys_s, keys, 8, s)) return st;
+    // the permutation, read for the keys anyway, leaves in the same pass (50 M
+    // cells: 318 us apart, 221 together) if the kernel can write to it
+    bool together = false;
+    if (keys && perm) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, perm) == hipSuccess)
+            together = a.type == hipMemoryTypeDevice && a.device == v->device;
+        else
+            (void)hipGetLastError();
     }
-    if (perm) DVL_HIP(hipMemcpyAsync(perm, v->perm, (size_t)v->n * 4, hipMemcpyDeviceToDevice, s));
+    if (keys)
+        if (dvl_status st = launch_keys_back(v->n, v->perm, v->keys_s, keys, together ? perm : nullptr, s)) return st;
+    if (perm && !together) DVL_HIP(hipMemcpyAsync(perm, v->perm, (size_t)v->n * 4, hipMemcpyDeviceToDevice, s));
     return DVL_OK;
 }
 

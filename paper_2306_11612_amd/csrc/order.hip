@@ -18,10 +18,25 @@ namespace dvl {
 // Each workgroup writes its own maximum and flags; k_extent_fold takes them
 // together.  (Every wave's atomicMax on one word cost about 12 ns each
 // whatever the cell count, 32768 waves x 2 atomics: 771 us for 50 M cells;
-// 142 + 6 us like this.)
+// 98 + 4 us like this.)
 // ===================================================================
 constexpr int kReduceThreads = 256;
 constexpr int kReduceBlocks = kRangeParts;   // at most
+
+// Above this many cells the passes read their arrays as non-temporal streams and
+// write the sorted fields so: the 8-byte words of the sort alone exceed the 256
+// MB Infinity Cache, nothing is left of them for the next pass, and they stream
+// faster past the caches (50 M cells: extent 136 -> 98 us, a count 103 -> 78, a
+// scatter 187 -> 182, the sorted arrays 519 -> 512; the keys' pass, which writes
+// after the scattered writes of whatever ran before, gained nothing).  Volumes
+// that fit read what the pass before left there (1.1 M cells, the keys' pass
+// 12.2 us against 14.4).
+constexpr int64_t kStreamCells = (int64_t)1 << 25;
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+template <bool STREAM, typename T>
+__device__ __forceinline__ T read(const T* p) {
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
 
 struct ExtentPart {
     unsigned long long upper;    // max(corner + 2^level)
@@ -61,7 +76,7 @@ __device__ __forceinline__ ExtentPart extent_block(int64_t mx, uint32_t bad, uin
 // Four consecutive cells per thread and iteration with vector loads when the
 // caller's arrays allow it (V4: x, y, z 16-byte and level 4-byte aligned,
 // checked by the launcher); the last n % 4 cells, or all, one by one.
-template <bool V4>
+template <bool V4, bool STREAM>
 __global__ __launch_bounds__(kReduceThreads) void k_extent(int64_t n, const int32_t* __restrict__ x,
                                                            const int32_t* __restrict__ y,
                                                            const int32_t* __restrict__ z,
@@ -74,10 +89,10 @@ __global__ __launch_bounds__(kReduceThreads) void k_extent(int64_t n, const int3
     const int64_t nq = V4 ? n >> 2 : 0;
     if constexpr (V4) {
         for (int64_t q = tid; q < nq; q += stride) {
-            const int4 cx = reinterpret_cast<const int4*>(x)[q];
-            const int4 cy = reinterpret_cast<const int4*>(y)[q];
-            const int4 cz = reinterpret_cast<const int4*>(z)[q];
-            const uint32_t lw = reinterpret_cast<const uint32_t*>(level)[q];
+            const i32x4 cx = read<STREAM>(reinterpret_cast<const i32x4*>(x) + q);
+            const i32x4 cy = read<STREAM>(reinterpret_cast<const i32x4*>(y) + q);
+            const i32x4 cz = read<STREAM>(reinterpret_cast<const i32x4*>(z) + q);
+            const uint32_t lw = read<STREAM>(reinterpret_cast<const uint32_t*>(level) + q);
             extent_add(cx.x, cy.x, cz.x, lw & 0xFFu, mx, bad, lmax);
             extent_add(cx.y, cy.y, cz.y, (lw >> 8) & 0xFFu, mx, bad, lmax);
             extent_add(cx.z, cy.z, cz.z, (lw >> 16) & 0xFFu, mx, bad, lmax);
@@ -236,9 +251,9 @@ __device__ __forceinline__ void hilbert_keys(const uint16_t* table, uint32_t sta
 //              digits written to digit base + column scan + chunk row
 // Rows are tile-major, so counting writes and scattering reads whole rows.
 //
-// 50 M cells, 33-bit keys, MI355X: 4 passes of 102 (count) + 8 (columns) +
-// 187 us (scatter: 16 bytes per cell at 4.3 TB/s) after 242 us for the keys,
-// the first of them without its count: 1.33 ms.  With 12-byte pairs, 8-bit
+// 50 M cells, 33-bit keys, MI355X: 4 passes of 78 (count) + 8 (columns) + 182 us
+// (scatter: 16 bytes per cell at 4.4 TB/s) after 242 us for the keys, the first
+// of them without its count: 1.24 ms.  With 12-byte pairs, 8-bit
 // digits, counts in digit-major order and a scan over all of them it was 5
 // passes of 167 + 33 + 405 us after 285: 3.31 ms.
 // ===================================================================
@@ -339,9 +354,9 @@ __global__ __launch_bounds__(kSortThreads) void k_words(int64_t n, const int32_t
         for (int r = 0; r < kSortItems / 4; ++r) {
             const int64_t i = t * kSortTile + 4 * ((int64_t)r * kSortThreads + threadIdx.x);
             if (V4 && i + 3 < n) {
-                const int4 cx = *reinterpret_cast<const int4*>(x + i);
-                const int4 cy = *reinterpret_cast<const int4*>(y + i);
-                const int4 cz = *reinterpret_cast<const int4*>(z + i);
+                const i32x4 cx = *reinterpret_cast<const i32x4*>(x + i);
+                const i32x4 cy = *reinterpret_cast<const i32x4*>(y + i);
+                const i32x4 cz = *reinterpret_cast<const i32x4*>(z + i);
                 const uint32_t lw = *reinterpret_cast<const uint32_t*>(level + i);
                 const uint32_t h[4] = {half(lw & 0xFFu), half((lw >> 8) & 0xFFu), half((lw >> 16) & 0xFFu), half(lw >> 24)};
                 const uint32_t xs[4] = {cx.x + h[0], cx.y + h[1], cx.z + h[2], cx.w + h[3]};
@@ -372,7 +387,7 @@ __global__ __launch_bounds__(kSortThreads) void k_words(int64_t n, const int32_t
     count_totals<D>(run, totals + ((int64_t)blockIdx.x << D));
 }
 
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(kSortThreads) void k_count(int64_t n, const uint64_t* __restrict__ words, int shift,
                                                         int chunk, int64_t n_tiles, uint32_t* __restrict__ rows,
                                                         uint32_t* __restrict__ totals) {
@@ -386,7 +401,7 @@ __global__ __launch_bounds__(kSortThreads) void k_count(int64_t n, const uint64_
             u64x2 v[kSortItems / 2];
 #pragma unroll
             for (int r = 0; r < kSortItems / 2; ++r)
-                v[r] = reinterpret_cast<const u64x2*>(words + base)[r * kSortThreads + threadIdx.x];
+                v[r] = read<STREAM>(reinterpret_cast<const u64x2*>(words + base) + r * kSortThreads + threadIdx.x);
 #pragma unroll
             for (int r = 0; r < kSortItems / 2; ++r) {
                 l.add(digit_of<D>(v[r].x, shift));
@@ -470,7 +485,7 @@ __global__ __launch_bounds__(kColumnDigits * kColumnGroups) void k_columns(int64
 
 // PACKED: words hold key and index (LAST: split them into kout and vout);
 // otherwise the indices travel as vin -> vout.
-template <int D, bool PACKED, bool LAST>
+template <int D, bool PACKED, bool LAST, bool STREAM>
 __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint64_t* __restrict__ kin,
                                                           const uint32_t* __restrict__ vin, int shift, int idx_bits,
                                                           int chunk, const uint32_t* __restrict__ rows,
@@ -505,8 +520,8 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint6
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
         const int li = li0 + r * kWave;
-        key[r] = li < n_here ? kin[tbeg + li] : 0ull;
-        if constexpr (!PACKED) val[r] = li < n_here ? vin[tbeg + li] : 0u;
+        key[r] = li < n_here ? read<STREAM>(kin + tbeg + li) : 0ull;
+        if constexpr (!PACKED) val[r] = li < n_here ? read<STREAM>(vin + tbeg + li) : 0u;
     }
     // this tile's digit positions, consecutive digits per thread
     uint32_t row[per_thread], col[per_thread], tot[per_thread];
@@ -619,13 +634,39 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint6
     }
 }
 
-// flag adjacent equal keys
+// Flag adjacent equal keys: two keys a thread, the one before them from the
+// lane before, four such pairs in flight.  50 M keys: 74 us (one key and its
+// neighbour at a time: 86; the neighbour of four keys by a load of its own: 95).
+template <bool STREAM>
 __global__ __launch_bounds__(256) void k_dup(int64_t n, const uint64_t* __restrict__ k,
                                              unsigned long long* __restrict__ flag) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    constexpr int kAhead = 4;
+    const int64_t np = n >> 1, stride = (int64_t)gridDim.x * 256;
+    const int64_t p0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool first_lane = lane_id() == 0;
     uint32_t d = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x + 1; i < n; i += stride)
-        d |= (k[i] == k[i - 1]);
+    // every lane of a wave stays while one of them has keys
+    for (int64_t p = p0; p - lane_id() < np; p += kAhead * stride) {
+        u64x2 v[kAhead];
+        uint64_t before[kAhead];
+#pragma unroll
+        for (int g = 0; g < kAhead; ++g) {
+            const int64_t i = p + g * stride;
+            v[g] = u64x2{0ull, 0ull};
+            before[g] = 0ull;
+            if (i < np) v[g] = read<STREAM>(reinterpret_cast<const u64x2*>(k) + i);
+            if (first_lane && i > 0 && i < np) before[g] = k[2 * i - 1];
+        }
+#pragma unroll
+        for (int g = 0; g < kAhead; ++g) {
+            const int64_t i = p + g * stride;
+            const uint32_t lo = __float_as_uint(wave_shr1(__uint_as_float((uint32_t)v[g].y), __uint_as_float((uint32_t)before[g])));
+            const uint32_t hi = __float_as_uint(wave_shr1(__uint_as_float((uint32_t)(v[g].y >> 32)), __uint_as_float((uint32_t)(before[g] >> 32))));
+            const uint64_t left = ((uint64_t)hi << 32) | lo;
+            if (i < np) d |= (i > 0 && v[g].x == left) | (v[g].y == v[g].x);
+        }
+    }
+    if (p0 == 0 && (n & 1) && n > 1) d |= k[n - 1] == k[n - 2];
     if (__ballot(d) != 0ull && lane_id() == 0) atomicOr(flag, 1ull);
 }
 
@@ -745,7 +786,16 @@ __device__ __forceinline__ Four<uint32_t> source_quad(const uint32_t* perm, int6
     return r;
 }
 
-template <typename S, int G>
+template <bool STREAM, typename T>
+__device__ __forceinline__ void put(T* dst, const Four<T>& v) {
+    using W = typename std::conditional<sizeof(T) == 4, u32x4, u32x2>::type;
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(__builtin_bit_cast(W, v), reinterpret_cast<W*>(dst));
+    else
+        *reinterpret_cast<Four<T>*>(dst) = v;
+}
+
+template <typename S, int G, bool STREAM>
 __device__ __forceinline__ void place_field(int64_t n, int64_t t, int tile_steps, const uint32_t* __restrict__ perm,
                                             const typename S::raw* __restrict__ src, typename S::raw* __restrict__ dst,
                                             int64_t stat, const PlaceStats& st) {
@@ -772,7 +822,7 @@ __device__ __forceinline__ void place_field(int64_t n, int64_t t, int tile_steps
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int64_t c = (step0 + s + g) * kStepCells + 4 * lane;
-            *reinterpret_cast<Four<raw>*>(dst + c) = r[g];
+            put<STREAM>(dst + c, r[g]);
             float s4 = 0.0f, slo = INFINITY, shi = -INFINITY;
             double d4 = 0.0;
 #pragma unroll
@@ -852,7 +902,7 @@ __device__ __forceinline__ void place_levels(int64_t n, int64_t t, int tile_step
     }
 }
 
-template <typename S, int G>
+template <typename S, int G, bool STREAM>
 __global__ __launch_bounds__(kReduceThreads) void k_place(int64_t n, int tile_steps, const uint32_t* __restrict__ perm,
                                                           PlaceArrays a, PlaceStats st) {
     const int n_arrays = a.n_fields + (a.level_src ? 1 : 0);
@@ -865,7 +915,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_place(int64_t n, int tile_st
         const int64_t t = u / n_arrays;
         const int m = (int)(u - t * n_arrays);
         if (m < a.n_fields)
-            place_field<S, G>(n, t, tile_steps, perm, reinterpret_cast<const typename S::raw*>(a.src[m]),
+            place_field<S, G, STREAM>(n, t, tile_steps, perm, reinterpret_cast<const typename S::raw*>(a.src[m]),
                               reinterpret_cast<typename S::raw*>(a.dst[m]), a.first_field + m, st);
         else
             place_levels<G>(n, t, tile_steps, perm, a.level_src, a.level_dst, a.codes);
@@ -873,13 +923,22 @@ __global__ __launch_bounds__(kReduceThreads) void k_place(int64_t n, int tile_st
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_scatter_back(int64_t n, const uint32_t* __restrict__ perm,
-                                                      const T* __restrict__ sorted, T* __restrict__ orig) {
+// orig[perm[i]] = sorted[i]; the permutation itself to perm_out (or NULL) in the
+// same pass
+template <bool STREAM>
+__global__ __launch_bounds__(256) void k_keys_back(int64_t n, const uint32_t* __restrict__ perm,
+                                                   const uint64_t* __restrict__ sorted, uint64_t* __restrict__ orig,
+                                                   uint32_t* __restrict__ perm_out) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint32_t p = perm[i];
-        if (p < (uint64_t)n) orig[p] = sorted[i];
+        const uint32_t p = read<STREAM>(perm + i);
+        if (p < (uint64_t)n) orig[p] = read<STREAM>(sorted + i);
+        if (perm_out) {
+            if constexpr (STREAM)
+                __builtin_nontemporal_store(p, perm_out + i);
+            else
+                perm_out[i] = p;
+        }
     }
 }
 
@@ -906,10 +965,12 @@ dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const in
                          unsigned long long* out, unsigned long long* dup, void* scratch, hipStream_t s) {
     ExtentPart* part = reinterpret_cast<ExtentPart*>(scratch);
     const unsigned grid = grid_for((n + 3) / 4, kReduceThreads, kReduceBlocks);
-    if (vec4_inputs(x, y, z, level))
-        hipLaunchKernelGGL(k_extent<true>, dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
+    if (vec4_inputs(x, y, z, level) && n > kStreamCells)
+        hipLaunchKernelGGL((k_extent<true, true>), dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
+    else if (vec4_inputs(x, y, z, level))
+        hipLaunchKernelGGL((k_extent<true, false>), dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
     else
-        hipLaunchKernelGGL(k_extent<false>, dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
+        hipLaunchKernelGGL((k_extent<false, false>), dim3(grid), dim3(kReduceThreads), 0, s, n, x, y, z, level, part);
     hipLaunchKernelGGL(k_extent_fold, dim3(1), dim3(1024), 0, s, (int)grid, part, out, dup);
     DVL_HIP(hipGetLastError());
     return DVL_OK;
@@ -931,7 +992,7 @@ SortPlan sort_plan(int64_t n, int key_bits) {
     return p;
 }
 
-template <int D, bool PACKED>
+template <int D, bool PACKED, bool STREAM>
 static dvl_status sort_typed(const SortPlan& p, int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
                              const uint8_t* level, int bits, uint64_t* ka, uint64_t* kb, uint32_t* va, uint32_t* vb,
                              uint32_t* scratch, hipStream_t s, bool* in_second) {
@@ -951,16 +1012,16 @@ static dvl_status sort_typed(const SortPlan& p, int64_t n, const int32_t* x, con
     for (int i = 0; i < p.passes; ++i) {
         const int shift = low + D * i;
         if (i > 0) {
-            hipLaunchKernelGGL(k_count<D>, chunks, thr, 0, s, n, ka, shift, p.chunk, p.n_tiles, rows, totals);
+            hipLaunchKernelGGL((k_count<D, STREAM>), chunks, thr, 0, s, n, ka, shift, p.chunk, p.n_tiles, rows, totals);
             DVL_HIP(hipGetLastError());
         }
         hipLaunchKernelGGL(k_columns<D>, dim3((1 << D) / kColumnDigits), dim3(kColumnDigits * kColumnGroups), 0, s, p.n_chunks, totals,
                            digits);
         if (i + 1 == p.passes)
-            hipLaunchKernelGGL((k_scatter<D, PACKED, true>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
+            hipLaunchKernelGGL((k_scatter<D, PACKED, true, STREAM>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
                                rows, totals, digits, kb, PACKED ? va : vb);   // packed: vin is not read
         else
-            hipLaunchKernelGGL((k_scatter<D, PACKED, false>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
+            hipLaunchKernelGGL((k_scatter<D, PACKED, false, STREAM>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
                                rows, totals, digits, kb, vb);
         DVL_HIP(hipGetLastError());
         std::swap(ka, kb);
@@ -973,30 +1034,35 @@ static dvl_status sort_typed(const SortPlan& p, int64_t n, const int32_t* x, con
 dvl_status launch_order(const SortPlan& p, int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
                         const uint8_t* level, int bits, uint64_t* ka, uint64_t* kb, uint32_t* va, uint32_t* vb,
                         uint32_t* scratch, hipStream_t s, bool* in_second) {
-#define DVL_SORT(D)                                                                                                \
-    if (p.digit_bits == D)                                                                                         \
-        return p.packed ? sort_typed<D, true>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s, in_second)    \
-                        : sort_typed<D, false>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s, in_second);
-    DVL_SORT(8)
-    DVL_SORT(9)
+#define DVL_SORT(D, STREAM)                                                                                            \
+    if (p.digit_bits == D && (n > kStreamCells) == STREAM)                                                             \
+        return p.packed ? sort_typed<D, true, STREAM>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s, in_second) \
+                        : sort_typed<D, false, STREAM>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s, in_second);
+    DVL_SORT(8, false)
+    DVL_SORT(9, false)
+    DVL_SORT(8, true)
+    DVL_SORT(9, true)
 #undef DVL_SORT
     set_error("sort digits of %d bits", p.digit_bits);
     return DVL_E_INVALID;
 }
 
 dvl_status launch_dup(int64_t n, const uint64_t* keys, unsigned long long* flag, hipStream_t s) {
-    hipLaunchKernelGGL(k_dup, dim3(grid_for(n)), dim3(256), 0, s, n, keys, flag);
+    const dim3 grid(grid_for((n + 7) / 8, 256, 2048));
+    if (n > kStreamCells)
+        hipLaunchKernelGGL(k_dup<true>, grid, dim3(256), 0, s, n, keys, flag);
+    else
+        hipLaunchKernelGGL(k_dup<false>, grid, dim3(256), 0, s, n, keys, flag);
     DVL_HIP(hipGetLastError());
     return DVL_OK;
 }
 
-dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sorted, void* orig,
-                               int elem_bytes, hipStream_t s) {
-    if (elem_bytes == 8)
-        hipLaunchKernelGGL(k_scatter_back<uint64_t>, dim3(grid_for(n)), dim3(256), 0, s, n, perm,
-                           (const uint64_t*)sorted, (uint64_t*)orig);
+dvl_status launch_keys_back(int64_t n, const uint32_t* perm, const uint64_t* sorted, uint64_t* orig, uint32_t* perm_out,
+                            hipStream_t s) {
+    if (n > kStreamCells)
+        hipLaunchKernelGGL(k_keys_back<true>, dim3(grid_for(n)), dim3(256), 0, s, n, perm, sorted, orig, perm_out);
     else
-        return DVL_E_INVALID;
+        hipLaunchKernelGGL(k_keys_back<false>, dim3(grid_for(n)), dim3(256), 0, s, n, perm, sorted, orig, perm_out);
     DVL_HIP(hipGetLastError());
     return DVL_OK;
 }
@@ -1028,9 +1094,11 @@ static void place_typed(int64_t n, int tile_steps, const uint32_t* perm, const P
                         unsigned grid, hipStream_t s) {
     // tiles of 8 steps: two steps per wave; 16 and 32: four at a time
     if (tile_steps < 16)
-        hipLaunchKernelGGL((k_place<S, 2>), dim3(grid), dim3(kReduceThreads), 0, s, n, tile_steps, perm, a, st);
+        hipLaunchKernelGGL((k_place<S, 2, false>), dim3(grid), dim3(kReduceThreads), 0, s, n, tile_steps, perm, a, st);
+    else if (n > kStreamCells)
+        hipLaunchKernelGGL((k_place<S, 4, true>), dim3(grid), dim3(kReduceThreads), 0, s, n, tile_steps, perm, a, st);
     else
-        hipLaunchKernelGGL((k_place<S, 4>), dim3(grid), dim3(kReduceThreads), 0, s, n, tile_steps, perm, a, st);
+        hipLaunchKernelGGL((k_place<S, 4, false>), dim3(grid), dim3(kReduceThreads), 0, s, n, tile_steps, perm, a, st);
 }
 
 dvl_status launch_place(int64_t n, int dtype, int tile_steps, const uint32_t* perm, const PlaceArrays& a,

@@ -30,8 +30,9 @@ dvl_status launch_order(const SortPlan& p, int64_t n, const int32_t* x, const in
                         const uint8_t* level, int bits, uint64_t* ka, uint64_t* kb, uint32_t* va, uint32_t* vb,
                         uint32_t* scratch, hipStream_t s, bool* in_second);
 dvl_status launch_dup(int64_t n, const uint64_t* keys, unsigned long long* flag, hipStream_t s);
-dvl_status launch_scatter_back(int64_t n, const uint32_t* perm, const void* sorted, void* orig,
-                               int elem_bytes, hipStream_t s);
+// orig[perm[i]] = sorted[i]; perm_out (or NULL): a copy of perm
+dvl_status launch_keys_back(int64_t n, const uint32_t* perm, const uint64_t* sorted, uint64_t* orig, uint32_t* perm_out,
+                            hipStream_t s);
 // Partial ranges of n values: part[i] = (min, max) as order-preserving uint
 // keys for i < *n_part <= kRangeParts, max = kRangeNan where there is a NaN.
 // part: memory the host can read once the stream is synchronised.

@@ -71,3 +71,52 @@ def test_order_of_a_large_volume_is_a_sorted_permutation():
         assert bool((torch.bincount(perm.long(), minlength=s ** 3) == 1).all())
     finally:
         V.close()
+
+
+def test_duplicates_and_order_past_the_caches():
+    """More than 2^25 cells (passes read as streams): the keys back in the
+    original order belong to the sorted ones, and a repeated cell at either end
+    or in the middle of the sorted order is refused."""
+    D = dvl()
+    s = 324
+    n = s ** 3 + 1
+    i = torch.arange(s ** 3, device="cuda", dtype=torch.int64).flip(0)
+    x, y, z = (torch.cat([c, c.new_full((1,), s)]) for c in ((i % s).int(), ((i // s) % s).int(), (i // (s * s)).int()))
+    level = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    field = torch.arange(n, device="cuda").float()
+    V = D.build_order(x, y, z, level, [field])
+    try:
+        keys, perm = V.export_order()
+        k = keys[perm.long()]
+        assert bool((k[1:] > k[:-1]).all())
+        assert bool((torch.bincount(perm.long(), minlength=n) == 1).all())
+        alone = torch.empty_like(perm)
+        import ctypes as C
+        assert D.lib().dvl_export_order(V.handle, C.c_void_p(0), C.c_void_p(alone.data_ptr()), C.c_void_p(0)) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(alone, perm)
+        assert torch.equal(V.export_sorted()[1][0], field[perm.long()])
+        ends = [int(perm[h]) for h in (0, 1, n // 2, n - 2, n - 1)]
+    finally:
+        V.close()
+    for at in ends:
+        c = [t.clone() for t in (x, y, z)]
+        other = (at + 1) % n
+        for t in c:
+            t[other] = t[at].clone()
+        with pytest.raises(D.DvlError) as e:
+            D.build_order(*c, level, [field])
+        assert e.value.status == D.E_OVERLAP
+
+
+@pytest.mark.parametrize("n", [2, 3, 5, 8, 13, 514, 4099])
+def test_a_repeated_cell_is_found_wherever_it_lies(n):
+    D = dvl()
+    vol = _cells(n, 7, seed=n).to("cuda")
+    for at in range(n) if n < 20 else sorted({0, 1, n - 1, n - 2, *range(63, n, 1 + n // 17)}):
+        c = [t.clone() for t in (vol.x, vol.y, vol.z)]
+        for t in c:
+            t[at] = t[(at + n // 2) % n].clone()
+        with pytest.raises(D.DvlError) as e:
+            D.build_order(*c, vol.level, vol.fields)
+        assert e.value.status == D.E_OVERLAP, at
