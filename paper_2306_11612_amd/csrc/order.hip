@@ -258,8 +258,13 @@ __device__ __forceinline__ void hilbert_keys(const uint16_t* table, uint32_t sta
 // passes of 167 + 33 + 405 us after 285: 3.31 ms.
 // ===================================================================
 constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;                       // per thread
-constexpr int kSortTile = kSortThreads * kSortItems; // 4096 keys
+// Keys per thread: 16, tiles of 4096; 4, tiles of 1024, while the larger ones
+// would give a compute unit one workgroup, whose 16 rounds of ranking follow
+// one another (a scatter of 1.1 M cells 15 -> 10.6 us; building 0.2 M cells 154 ->
+// 127 us, 1.0 M 172 -> 156, 2.0 M and more the same or slower).
+constexpr int kSortItems = 16, kSortItemsSmall = 4;
+constexpr int64_t kSmallCells = (int64_t)3 << 19;
+constexpr int sort_tile(int items) { return kSortThreads * items; }
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with its own L2
 
@@ -328,13 +333,14 @@ __device__ __forceinline__ void count_totals(const uint32_t (&run)[(1 << D) / kS
 // digit counts of the first pass.  Four consecutive cells per thread with
 // vector loads and stores when the caller's arrays allow it (V4: x, y, z
 // 16-byte and level 4-byte aligned, checked by the launcher).
-template <int D, bool PACKED, bool V4>
+template <int D, int ITEMS, bool PACKED, bool V4>
 __global__ __launch_bounds__(kSortThreads) void k_words(int64_t n, const int32_t* __restrict__ x,
                                                         const int32_t* __restrict__ y, const int32_t* __restrict__ z,
                                                         const uint8_t* __restrict__ level, int bits, int idx_bits,
                                                         int chunk, int64_t n_tiles, uint64_t* __restrict__ words,
                                                         uint32_t* __restrict__ idx, uint32_t* __restrict__ rows,
                                                         uint32_t* __restrict__ totals) {
+    constexpr int kTile = sort_tile(ITEMS);
     __shared__ alignas(16) CountLds<D> l;
     __shared__ alignas(16) uint16_t table[kHilbertStates * 64];
     static_assert(sizeof(table) % 4 == 0, "copied in 32-bit words");
@@ -351,8 +357,8 @@ __global__ __launch_bounds__(kSortThreads) void k_words(int64_t n, const int32_t
     auto half = [](uint32_t lev) { return (1u << lev) >> 1; };
     for (int64_t t = t0; t < t1; ++t) {
 #pragma unroll
-        for (int r = 0; r < kSortItems / 4; ++r) {
-            const int64_t i = t * kSortTile + 4 * ((int64_t)r * kSortThreads + threadIdx.x);
+        for (int r = 0; r < ITEMS / 4; ++r) {
+            const int64_t i = t * kTile + 4 * ((int64_t)r * kSortThreads + threadIdx.x);
             if (V4 && i + 3 < n) {
                 const i32x4 cx = *reinterpret_cast<const i32x4*>(x + i);
                 const i32x4 cy = *reinterpret_cast<const i32x4*>(y + i);
@@ -387,23 +393,24 @@ __global__ __launch_bounds__(kSortThreads) void k_words(int64_t n, const int32_t
     count_totals<D>(run, totals + ((int64_t)blockIdx.x << D));
 }
 
-template <int D, bool STREAM>
+template <int D, int ITEMS, bool STREAM>
 __global__ __launch_bounds__(kSortThreads) void k_count(int64_t n, const uint64_t* __restrict__ words, int shift,
                                                         int chunk, int64_t n_tiles, uint32_t* __restrict__ rows,
                                                         uint32_t* __restrict__ totals) {
+    constexpr int kTile = sort_tile(ITEMS);
     __shared__ alignas(16) CountLds<D> l;
     uint32_t run[(1 << D) / kSortThreads];
     count_clear(l, run);
     const int64_t t0 = (int64_t)blockIdx.x * chunk, t1 = min(t0 + chunk, n_tiles);
     for (int64_t t = t0; t < t1; ++t) {
-        const int64_t base = t * kSortTile;
-        if (base + kSortTile <= n) {
-            u64x2 v[kSortItems / 2];
+        const int64_t base = t * kTile;
+        if (base + kTile <= n) {
+            u64x2 v[ITEMS / 2];
 #pragma unroll
-            for (int r = 0; r < kSortItems / 2; ++r)
+            for (int r = 0; r < ITEMS / 2; ++r)
                 v[r] = read<STREAM>(reinterpret_cast<const u64x2*>(words + base) + r * kSortThreads + threadIdx.x);
 #pragma unroll
-            for (int r = 0; r < kSortItems / 2; ++r) {
+            for (int r = 0; r < ITEMS / 2; ++r) {
                 l.add(digit_of<D>(v[r].x, shift));
                 l.add(digit_of<D>(v[r].y, shift));
             }
@@ -485,20 +492,21 @@ __global__ __launch_bounds__(kColumnDigits * kColumnGroups) void k_columns(int64
 
 // PACKED: words hold key and index (LAST: split them into kout and vout);
 // otherwise the indices travel as vin -> vout.
-template <int D, bool PACKED, bool LAST, bool STREAM>
+template <int D, int ITEMS, bool PACKED, bool LAST, bool STREAM>
 __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint64_t* __restrict__ kin,
                                                           const uint32_t* __restrict__ vin, int shift, int idx_bits,
                                                           int chunk, const uint32_t* __restrict__ rows,
                                                           const uint32_t* __restrict__ columns,
                                                           const uint32_t* __restrict__ digits,
                                                           uint64_t* __restrict__ kout, uint32_t* __restrict__ vout) {
+    constexpr int kTile = sort_tile(ITEMS);
     constexpr int R = 1 << D;
     constexpr int per_thread = R / kSortThreads;
     __shared__ alignas(16) uint16_t whist[kSortWaves][R];   // per-wave digit counts, then starts in the tile (<= 4096)
     __shared__ uint32_t gbase[R];               // global position of the digit's first cell here minus its start in the tile
     __shared__ uint32_t wsum[2][kSortWaves];
     // the tile in digit order: keys first, then (in the same space) values
-    __shared__ uint64_t stage[kSortTile];
+    __shared__ uint64_t stage[kTile];
     uint32_t* sval = reinterpret_cast<uint32_t*>(stage);
 
     const int w = threadIdx.x / kWave;
@@ -509,16 +517,16 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint6
     const int64_t nb = gridDim.x, bid = blockIdx.x;
     const int64_t xcd = bid % kXcds, per = nb / kXcds, rem = nb % kXcds;
     const int64_t tile = xcd * per + min(xcd, rem) + bid / kXcds;
-    const int64_t tbeg = tile * kSortTile;
-    const int n_here = (int)min((int64_t)kSortTile, n - tbeg);
+    const int64_t tbeg = tile * kTile;
+    const int n_here = (int)min((int64_t)kTile, n - tbeg);
 
     // each wave owns a contiguous quarter of the tile; round r covers 64 keys
-    uint64_t key[kSortItems];
-    uint32_t val[PACKED ? 1 : kSortItems];
-    uint32_t rank[kSortItems];
-    const int li0 = w * (kWave * kSortItems) + lane;
+    uint64_t key[ITEMS];
+    uint32_t val[PACKED ? 1 : ITEMS];
+    uint32_t rank[ITEMS];
+    const int li0 = w * (kWave * ITEMS) + lane;
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const int li = li0 + r * kWave;
         key[r] = li < n_here ? read<STREAM>(kin + tbeg + li) : 0ull;
         if constexpr (!PACKED) val[r] = li < n_here ? read<STREAM>(vin + tbeg + li) : 0u;
@@ -540,7 +548,7 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint6
 
     const uint64_t lt = lanemask_lt();
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const bool ok = li0 + r * kWave < n_here;
         const uint32_t d = digit_of<D>(key[r], shift);
         // lanes holding the same digit
@@ -594,17 +602,17 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint6
 
     // positions in digit order (kept for the value pass)
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         if (li0 + r * kWave < n_here) {
             rank[r] += whist[w][digit_of<D>(key[r], shift)];
-            stage[rank[r] & (kSortTile - 1)] = key[r];
+            stage[rank[r] & (kTile - 1)] = key[r];
         }
     }
     __syncthreads();
     // out in contiguous runs per digit; remember each slot's destination
-    uint32_t dest[PACKED ? 1 : kSortItems];
+    uint32_t dest[PACKED ? 1 : ITEMS];
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const int i = r * kSortThreads + threadIdx.x;
         if (i < n_here) {
             const uint64_t k = stage[i];
@@ -623,11 +631,11 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(int64_t n, const uint6
     if constexpr (!PACKED) {
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < kSortItems; ++r)
-            if (li0 + r * kWave < n_here) sval[rank[r] & (kSortTile - 1)] = val[r];
+        for (int r = 0; r < ITEMS; ++r)
+            if (li0 + r * kWave < n_here) sval[rank[r] & (kTile - 1)] = val[r];
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < kSortItems; ++r) {
+        for (int r = 0; r < ITEMS; ++r) {
             const int i = r * kSortThreads + threadIdx.x;
             if (i < n_here && (int64_t)dest[r] < n) vout[dest[r]] = sval[i];
         }
@@ -978,7 +986,8 @@ dvl_status launch_extent(int64_t n, const int32_t* x, const int32_t* y, const in
 
 SortPlan sort_plan(int64_t n, int key_bits) {
     SortPlan p{};
-    p.n_tiles = (n + kSortTile - 1) / kSortTile;
+    const int tile = sort_tile(n <= kSmallCells ? kSortItemsSmall : kSortItems);
+    p.n_tiles = (n + tile - 1) / tile;
     p.chunk = sort_chunk(p.n_tiles);
     p.n_chunks = (p.n_tiles + p.chunk - 1) / p.chunk;
     p.idx_bits = 1;
@@ -992,7 +1001,7 @@ SortPlan sort_plan(int64_t n, int key_bits) {
     return p;
 }
 
-template <int D, bool PACKED, bool STREAM>
+template <int D, int ITEMS, bool PACKED, bool STREAM>
 static dvl_status sort_typed(const SortPlan& p, int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
                              const uint8_t* level, int bits, uint64_t* ka, uint64_t* kb, uint32_t* va, uint32_t* vb,
                              uint32_t* scratch, hipStream_t s, bool* in_second) {
@@ -1002,26 +1011,26 @@ static dvl_status sort_typed(const SortPlan& p, int64_t n, const int32_t* x, con
     const dim3 chunks((unsigned)p.n_chunks), tiles((unsigned)p.n_tiles), thr(kSortThreads);
     const int low = PACKED ? p.idx_bits : 0;
     if (vec4_inputs(x, y, z, level))
-        hipLaunchKernelGGL((k_words<D, PACKED, true>), chunks, thr, 0, s, n, x, y, z, level, bits, p.idx_bits, p.chunk,
+        hipLaunchKernelGGL((k_words<D, ITEMS, PACKED, true>), chunks, thr, 0, s, n, x, y, z, level, bits, p.idx_bits, p.chunk,
                            p.n_tiles, ka, va, rows, totals);
     else
-        hipLaunchKernelGGL((k_words<D, PACKED, false>), chunks, thr, 0, s, n, x, y, z, level, bits, p.idx_bits, p.chunk,
+        hipLaunchKernelGGL((k_words<D, ITEMS, PACKED, false>), chunks, thr, 0, s, n, x, y, z, level, bits, p.idx_bits, p.chunk,
                            p.n_tiles, ka, va, rows, totals);
     DVL_HIP(hipGetLastError());
     *in_second = false;
     for (int i = 0; i < p.passes; ++i) {
         const int shift = low + D * i;
         if (i > 0) {
-            hipLaunchKernelGGL((k_count<D, STREAM>), chunks, thr, 0, s, n, ka, shift, p.chunk, p.n_tiles, rows, totals);
+            hipLaunchKernelGGL((k_count<D, ITEMS, STREAM>), chunks, thr, 0, s, n, ka, shift, p.chunk, p.n_tiles, rows, totals);
             DVL_HIP(hipGetLastError());
         }
         hipLaunchKernelGGL(k_columns<D>, dim3((1 << D) / kColumnDigits), dim3(kColumnDigits * kColumnGroups), 0, s, p.n_chunks, totals,
                            digits);
         if (i + 1 == p.passes)
-            hipLaunchKernelGGL((k_scatter<D, PACKED, true, STREAM>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
+            hipLaunchKernelGGL((k_scatter<D, ITEMS, PACKED, true, STREAM>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
                                rows, totals, digits, kb, PACKED ? va : vb);   // packed: vin is not read
         else
-            hipLaunchKernelGGL((k_scatter<D, PACKED, false, STREAM>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
+            hipLaunchKernelGGL((k_scatter<D, ITEMS, PACKED, false, STREAM>), tiles, thr, 0, s, n, ka, va, shift, p.idx_bits, p.chunk,
                                rows, totals, digits, kb, vb);
         DVL_HIP(hipGetLastError());
         std::swap(ka, kb);
@@ -1034,14 +1043,19 @@ static dvl_status sort_typed(const SortPlan& p, int64_t n, const int32_t* x, con
 dvl_status launch_order(const SortPlan& p, int64_t n, const int32_t* x, const int32_t* y, const int32_t* z,
                         const uint8_t* level, int bits, uint64_t* ka, uint64_t* kb, uint32_t* va, uint32_t* vb,
                         uint32_t* scratch, hipStream_t s, bool* in_second) {
-#define DVL_SORT(D, STREAM)                                                                                            \
-    if (p.digit_bits == D && (n > kStreamCells) == STREAM)                                                             \
-        return p.packed ? sort_typed<D, true, STREAM>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s, in_second) \
-                        : sort_typed<D, false, STREAM>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s, in_second);
-    DVL_SORT(8, false)
-    DVL_SORT(9, false)
-    DVL_SORT(8, true)
-    DVL_SORT(9, true)
+    const bool small = n <= kSmallCells, stream = n > kStreamCells;
+#define DVL_SORT(D, ITEMS, STREAM)                                                                                     \
+    if (p.digit_bits == D && small == (ITEMS == kSortItemsSmall) && stream == STREAM)                                  \
+        return p.packed ? sort_typed<D, ITEMS, true, STREAM>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s,    \
+                                                             in_second)                                                 \
+                        : sort_typed<D, ITEMS, false, STREAM>(p, n, x, y, z, level, bits, ka, kb, va, vb, scratch, s,   \
+                                                              in_second);
+    DVL_SORT(8, kSortItemsSmall, false)
+    DVL_SORT(9, kSortItemsSmall, false)
+    DVL_SORT(8, kSortItems, false)
+    DVL_SORT(9, kSortItems, false)
+    DVL_SORT(8, kSortItems, true)
+    DVL_SORT(9, kSortItems, true)
 #undef DVL_SORT
     set_error("sort digits of %d bits", p.digit_bits);
     return DVL_E_INVALID;

@@ -120,3 +120,18 @@ def test_a_repeated_cell_is_found_wherever_it_lies(n):
         with pytest.raises(D.DvlError) as e:
             D.build_order(*c, vol.level, vol.fields)
         assert e.value.status == D.E_OVERLAP, at
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 3 * 1024 + 1, (3 << 19) - 1023, 3 << 19, (3 << 19) + 1, (3 << 19) + 4095])
+def test_tiles_of_both_sizes(n):
+    """Edges of the small tiles, and of the volumes that take the large ones:
+    the permutation sorts the exported keys."""
+    D = dvl()
+    vol = _cells(n, 7 if n < 100000 else 9, seed=n).to("cuda")
+    V = D.build_order(vol.x, vol.y, vol.z, vol.level, vol.fields)
+    try:
+        keys, perm = V.export_order()
+        assert torch.equal(perm.long(), torch.argsort(keys))
+        assert torch.equal(V.export_sorted()[1][0], vol.fields[0][perm.long()])
+    finally:
+        V.close()
