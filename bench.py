@@ -231,18 +231,19 @@ def bench_batch32(args, dt):
     #  tile_sums  every cell's M entries (or values) + level stream, plus 4 B
     #             per cell written where the pass stores f for the rescan
     #  bin        the rescanned tiles (at most min(T, W) per volume); with
-    #             W >= T / 4 the importance pass stored f, which the rescan
-    #             reads (4 B per cell), else it reads what the first pass read
-    #  bin_stats  per bin, the values of its two partial end steps
+    #             W >= T / 4 the importance pass stored f (unless entries are
+    #             cached and f is cheap), which the rescan reads (4 B per
+    #             cell), else it reads what the first pass read
+    #  bin_stats  per bin, the values of its two partial end segments
     kbytes = {"tile_sums": cells * bpc, "bin": 0.0, "bin_stats": 0.0}
     for V, (ts, _) in zip(vols, layouts):
         tile_cells = 256 * ts
         T = -(-V.n // tile_cells)
-        stored_f = W * 4 >= T
+        stored_f = W * 4 >= T and not (cached and M <= 8 and args.exponent == 1.0)
         if stored_f:
             kbytes["tile_sums"] += V.n * 4          # the importance pass writes f of every cell
         kbytes["bin"] += min(T, W) * tile_cells * (4 if stored_f else bpc)
-        kbytes["bin_stats"] += W * 2 * 256 * M * elem
+        kbytes["bin_stats"] += W * 2 * 64 * M * elem
     achieved = kbytes[dom] / (per_launch[dom] * 1e-3) / 1e9
     ms_best = min(ms_batch, ms_graph)
     out = {
@@ -258,7 +259,7 @@ def bench_batch32(args, dt):
                      "bytes_per_cell": kbytes[dom] / cells, "avg_launch_ms": per_launch[dom],
                      "byte_model": {"tile_sums": "M cached entry bytes (or M field values) + level stream per cell, + 4 B of stored f per cell of the dense-bin volumes",
                                     "bin": "rescanned tiles: stored f (4 B per cell) or the first pass's bytes",
-                                    "bin_stats": "per bin: the values of its two partial end steps"}[dom],
+                                    "bin_stats": "per bin: the values of its two partial 64-cell end segments"}[dom],
                      "kernel_bytes": kbytes},
         "dominant_kernel": dom,
         "tuned_layouts": {f"tile_steps={a},run_waves={b or 'default'}": layouts.count((a, b))
@@ -277,18 +278,21 @@ def bench_batch32(args, dt):
 
 
 def sort_passes(bits: int) -> int:
-    """8-bit LSD passes over the 3 * bits significant key bits."""
-    return max(1, (3 * bits + 7) // 8)
+    """LSD passes over the 3 * bits significant key bits: digits of 9 bits where
+    that saves a pass, else of 8."""
+    return max(1, min((3 * bits + 8) // 9, (3 * bits + 7) // 8))
 
 
-def ordering_bytes_per_cell(bits: int, M: int, elem: int) -> float:
+def ordering_bytes_per_cell(n: int, bits: int, M: int, elem: int) -> float:
     """Algorithmic bytes of the one-time ordering per cell: keys (read x, y, z,
-    level: 13 B; write the 8-byte key: 21 B per cell, the 4-byte starting index
-    written beside it not counted), the sort (one 8 B digit read per pass for the counts plus 24 B of
-    key and index read and written per pass), the gather of level and fields
-    (read index, level, fields; write level and fields)."""
+    level: 13 B; write the word), the sort (per pass the word read and written;
+    the key read once more for the counts of every pass but the first), the check
+    for equal keys (8 B), the gather of level and fields (read index, level,
+    fields; write level and fields).  A word is 8 B when key and index fit 64
+    bits together, else 12."""
     p = sort_passes(bits)
-    return 21 + 8 * p + 24 * p + (4 + 1 + M * elem) + (1 + M * elem)
+    word = 8 if 3 * bits + max(1, (n - 1).bit_length()) <= 64 else 12
+    return 13 + word + 2 * word * p + 8 * (p - 1) + 8 + (4 + 1 + M * elem) + (1 + M * elem)
 
 
 def event_times(step, reps: int, flush=None):
@@ -483,20 +487,20 @@ def main():
     n_tiles = (n + 4095) // 4096
 
     def update_bytes_of(bpc):
-        return n * bpc + min(n_tiles, args.bins) * 4096 * bpc + args.bins * 2 * 256 * M * elem
+        return n * bpc + min(n_tiles, args.bins) * 4096 * bpc + args.bins * 2 * 64 * M * elem
 
     update_bytes = update_bytes_of(k1_bpc)
     update_gbps = update_bytes / (ms_per_step * 1e-3) / 1e9
     values_update_bytes = update_bytes_of(value_bpc)
     values_gbps = n * value_bpc / (per_launch_values["tile_sums"] * 1e-3) / 1e9
     plain_bpc = 2 * (M * elem + 1)
-    ord_bpc = ordering_bytes_per_cell(V.bits, M, elem)
+    ord_bpc = ordering_bytes_per_cell(n, V.bits, M, elem)
     model = ("design, TF change with unchanged windows: importance pass over cached TF entries "
-             "(M + level bytes per cell), rescan of the tiles holding a bin edge, bin end steps; per-tile "
-             "and per-step field statistics and the entry cache are built at ordering / data-change time"
+             "(M + level bytes per cell), rescan of the tiles holding a bin edge, bin end segments; per-tile "
+             "and per-segment field statistics and the entry cache are built at ordering / data-change time"
              if cached else
              "design, value path: importance pass over the field values (M*s + level bytes per cell), "
-             "rescan of the tiles holding a bin edge, bin end steps")
+             "rescan of the tiles holding a bin edge, bin end segments")
 
     out = {
         "metric": METRIC,
@@ -576,16 +580,16 @@ def main():
             step(k)
         torch.cuda.synchronize()
         ms_dc = (time.perf_counter() - t0) * 1e3 / args.steps
-        # per field: data range of the new values (s B/cell), gather (4 B index,
-        # s B random read, s B write), per-tile/step statistics (s B/cell read)
-        set_bpc = M * (4 + 4 * elem)
+        # per field: data range of the new values (s B/cell), gather with the
+        # statistics (4 B index, s B random read, s B write)
+        set_bpc = M * (4 + 3 * elem)
         dc_bytes = n * set_bpc + values_update_bytes
         out["data_change"] = {
             "ms_per_step": ms_dc, "value": n / (ms_dc * 1e-3), "set_field_ms_per_step": t_set * 1e3 / args.steps,
             "entry_cache": V.entry_cache_info() is not None,
             "bytes_per_cell": dc_bytes / n,
-            "byte_model": "dvl_set_field x M (range of the new values, gather into sorted order, per-tile and "
-                          "per-step statistics) + value-path update",
+            "byte_model": "dvl_set_field x M (range of the new values, gather into sorted order with the "
+                          "statistics) + value-path update",
             "gbps": dc_bytes / (ms_dc * 1e-3) / 1e9, "frac": dc_bytes / (ms_dc * 1e-3) / 1e9 / HBM_PEAK_GBPS,
             "step": "dvl_set_field for every field from one of two resident copies (original order), "
                     "dvl_set_tf x M with the new data ranges, dvl_update"}

@@ -173,7 +173,7 @@ dvl_status dvl_build_order_ex(int64_t n_cells, const int32_t* x, const int32_t* 
  * First the data range of the new values is taken and checked for NaN
  * (this synchronises `stream` once); a NaN returns DVL_E_RANGE and leaves the
  * volume unchanged.  Then the values are gathered into sorted order and the
- * per-tile / per-step statistics refreshed, asynchronously on `stream`; the
+ * per-tile / per-segment statistics refreshed, asynchronously on `stream`; the
  * TF entry cache is invalidated.  A TF set earlier for m keeps its window.
  * Updates issued later must run on `stream` (or after it).  Errors:
  * DVL_E_INVALID, DVL_E_RANGE, DVL_E_HIP (sticky).

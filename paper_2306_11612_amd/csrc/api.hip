@@ -1131,7 +1131,7 @@ struct dvl_graph {
     bool used[kRing] = {};
     int next = 0;
     // one captured graph per set of projection paths (values, cached
-    // entries, stored f): a replay launches only the kernel variants its jobs
+    // entries, stored f): a replay launches only the kernel variants its requests
     // use, and the set can change between launches as entry caches appear
     struct Captured {
         int paths;
@@ -1472,7 +1472,7 @@ dvl_status dvl_update(dvl_volume* v, const dvl_params* p, const dvl_bins* out, v
 namespace dvl {
 
 // The fixed device scratch of dvl_update_noalloc: the descriptor block
-// (descriptors, tables, rescan queues) followed by the request workspace.
+// (descriptors, tables) followed by the request workspace.
 // Every call on a device shares its copy.  In host code `scratch` names a
 // host-side stand-in, never the device memory: its device address comes
 // from hipGetSymbolAddress, once per device, and only that address is used.
