@@ -123,33 +123,11 @@ __device__ __forceinline__ int shfl_i(int v, int src) {
     return __builtin_amdgcn_ds_bpermute(src << 2, v);
 }
 
-// wave64 butterfly reductions (result in every lane)
-__device__ __forceinline__ double wave_sum_d(double v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        uint64_t u = __double_as_longlong(v);
-        const int l = lane_id() ^ o;
-        int lo = __builtin_amdgcn_ds_bpermute(l << 2, (int)(uint32_t)u);
-        int hi = __builtin_amdgcn_ds_bpermute(l << 2, (int)(uint32_t)(u >> 32));
-        v += __longlong_as_double(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-    }
-    return v;
-}
-__device__ __forceinline__ float wave_min_f(float v) {
-    for (int o = 32; o > 0; o >>= 1)
-        v = fminf(v, __int_as_float(__builtin_amdgcn_ds_bpermute((lane_id() ^ o) << 2, __float_as_int(v))));
-    return v;
-}
-__device__ __forceinline__ float wave_max_f(float v) {
-    for (int o = 32; o > 0; o >>= 1)
-        v = fmaxf(v, __int_as_float(__builtin_amdgcn_ds_bpermute((lane_id() ^ o) << 2, __float_as_int(v))));
-    return v;
-}
-
 // Reductions of a whole wave through the lanes' data paths (DPP): rows of 16
 // by row shifts, then rows 0-1 and 2-3, then both halves by row broadcasts;
 // lane 63 holds the result, which every lane gets from a scalar register.
-// No LDS round trips: six dependent ds_bpermute of the butterflies above are
-// six LDS latencies.  All 64 lanes must be active.
+// No LDS round trips: the six dependent ds_bpermute of a butterfly are six LDS
+// latencies.  All 64 lanes must be active.
 #define DVL_DPP_ROW_BCAST15 0x142
 #define DVL_DPP_ROW_BCAST31 0x143
 

@@ -1,9 +1,8 @@
 // Device code of the per-update kernels that depend on the field storage
-// type (K0 exact max V, K1 importance and tile sums, K3b rescan), their
-// helpers, and the templated launcher.  Each storage type is instantiated in
-// its own translation unit (update_f32.hip, update_f16.hip, update_bf16.hip);
-// the storage-independent kernels and the per-kernel commentary are in
-// update.hip.
+// type and field count (K0 exact max V, K1 importance and tile sums, K3b rescan,
+// K4 bin statistics), their helpers, and the templated launcher.  Each pair of
+// them is instantiated in a generated translation unit of its own; the other
+// kernels and the overview of all are in update.hip.
 #pragma once
 
 #include "update.hpp"
