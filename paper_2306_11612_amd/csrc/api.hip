@@ -1131,10 +1131,12 @@ struct dvl_graph {
     bool used[kRing] = {};
     int next = 0;
     // one captured graph per set of projection paths (values, cached
-    // entries, stored f): a replay launches only the kernel variants its requests
-    // use, and the set can change between launches as entry caches appear
+    // entries, stored f) and way of reading (BatchDev::stream): a replay launches
+    // only the kernel variants its requests use, and both can change between
+    // launches as entry caches appear
     struct Captured {
         int paths;
+        int stream;
         int slot;
         hipGraph_t graph;
         hipGraphExec_t exec;
@@ -2030,22 +2032,22 @@ dvl_status dvl_graph_create(const dvl_request* reqs, int32_t n_reqs, dvl_graph**
     return DVL_OK;
 }
 
-// The executable graph of this path set, captured on first use.
+// The executable graph of this path set and way of reading, captured on first use.
 static dvl_status graph_exec_for(dvl_graph* g, int paths, int slot, hipGraphExec_t* out) {
+    Plan& P = g->plan;
+    const BatchDev b = batch_dev(P, g->dev[slot], paths);
     for (auto& c : g->captured)
-        if (c.paths == paths && c.slot == slot) {
+        if (c.paths == paths && c.stream == b.stream && c.slot == slot) {
             *out = c.exec;
             return DVL_OK;
         }
-    Plan& P = g->plan;
     hipStream_t cs;
     DVL_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     if (hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal)) {
         (void)hipStreamDestroy(cs);
         return hip_fail(e, "hipStreamBeginCapture");
     }
-    const dvl_status cst =
-        launch_batch(batch_dev(P, g->dev[slot], paths), P.dtype, P.max_m, g->n_cu, cs, kDescriptorLayout, nullptr);
+    const dvl_status cst = launch_batch(b, P.dtype, P.max_m, g->n_cu, cs, kDescriptorLayout, nullptr);
     hipGraph_t graph = nullptr;
     const hipError_t ee = hipStreamEndCapture(cs, &graph);
     (void)hipStreamDestroy(cs);
@@ -2059,7 +2061,7 @@ static dvl_status graph_exec_for(dvl_graph* g, int paths, int slot, hipGraphExec
         (void)hipGraphDestroy(graph);
         return hip_fail(e, "hipGraphInstantiate");
     }
-    g->captured.push_back({paths, slot, graph, exec});
+    g->captured.push_back({paths, b.stream, slot, graph, exec});
     *out = exec;
     return DVL_OK;
 }
