@@ -42,7 +42,7 @@ def generated_sources(gen_dir: str) -> list[str]:
                 f"// {t} storage and {m}-field jobs.\n"
                 '#include "update_kernels.hpp"\n\n'
                 "namespace dvl {\n"
-                f"template dvl_status launch_sm<{t}, {m}>(const BatchDev&, int, hipStream_t, uint64_t, hipEvent_t*);\n"
+                f"template dvl_status launch_sm<{t}, {m}>(const BatchLaunch&, int, hipStream_t, uint64_t, hipEvent_t*);\n"
                 "}  // namespace dvl\n")
         old = open(path).read() if os.path.exists(path) else None
         if old != text:

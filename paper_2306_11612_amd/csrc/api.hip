@@ -465,6 +465,7 @@ struct Plan {
     std::vector<ReqHost> reqs;       // grouped by volume
     std::vector<int> where;          // caller's request index -> index in `reqs`
     std::vector<VolReqs> groups;     // one per volume
+    std::vector<Share> shares;       // value readers that share reads (plan_paths)
     std::vector<int64_t> unit0;      // each request's first importance-pass unit
     std::vector<ReqDev> rdev;
     std::vector<float*> fstore;      // where each request may store f, or NULL
@@ -507,6 +508,11 @@ static VolDev vol_dev(const dvl_volume* v) {
     d.tile_stat = v->tile_stat;
     d.seg_stat = v->seg_stat;
     return d;
+}
+
+// Units of the importance pass of one request: a run per wave, or a tile.
+static int64_t request_units(const VolDev& v) {
+    return v.split ? v.n_runs : (v.n_runs + kUpdWaves - 1) / kUpdWaves;
 }
 
 // Group the requests by volume and lay out the work units of every phase and
@@ -560,10 +566,9 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         d.scan_mode = r.p.scan_mode;
         // the other scan arithmetics' sums depend on their order: a wave per run
         d.v.split = d.v.split && d.scan_mode == DVL_SCAN_FP64;
-        // a unit of the importance pass: a run per wave, or a tile
         P.unit0.push_back(P.k1_units);
         P.n_steps += (int64_t)d.v.n_tiles * d.v.tile_steps;
-        P.k1_units += d.v.split ? d.v.n_runs : (d.v.n_runs + kUpdWaves - 1) / kUpdWaves;
+        P.k1_units += request_units(d.v);
         d.vmax_exact = r.p.vmax_mode == DVL_VMAX_EXACT;
         // a workgroup of k_bin per tile when there are no more tiles than
         // bins, else per bin edge
@@ -783,6 +788,27 @@ static dvl_status cache_mark_readers(const Plan& P, hipStream_t s) {
     return DVL_OK;
 }
 
+// The requests that read the values of one volume, in shares of up to 8 (caches
+// decided).  With one field the lookups bound the pass, and on few cells the
+// launch of its own costs what the reads save: from 64 MB of values on every
+// share was faster (two requests on 64 MB 75 -> 67 us, eight 147 -> 105; 8 MB
+// of them +-1 %; one field, 200 MB, five requests 107 -> 115).
+constexpr int kMaxShare = 8;
+constexpr double kShareBytes = 64e6;
+static void plan_shares(Plan& P) {
+    P.shares.clear();
+    for (const VolReqs& g : P.groups) {
+        const ReqDev* r = &P.rdev[g.req0];
+        const bool large = r->v.M > 1 && (double)r->v.n * r->v.M * elem_bytes_of(P.dtype) >= kShareBytes;
+        for (int k = 0, e; k < g.n_req; k = e) {
+            for (e = k + 1; e < g.n_req && e - k < kMaxShare && r[e].entries == r[k].entries && r[e].v.split == r[k].v.split;) ++e;
+            const bool share = large && e - k > 1 && !r[k].entries;
+            for (int i = k; i < e; ++i) P.rdev[g.req0 + i].shared = share;
+            if (share) P.shares.push_back({g.req0 + k, e - k, request_units(r[k].v)});
+        }
+    }
+}
+
 // What each request's projection reads (caches decided), and the kernel
 // variants that have work.  A request whose bins number a quarter of its tiles
 // or more rescans most of the volume; it stores f in the importance pass (4
@@ -792,12 +818,14 @@ static dvl_status cache_mark_readers(const Plan& P, hipStream_t s) {
 // of 820 MB of the importance pass on f.
 static int plan_paths(Plan& P) {
     int paths = 0;
+    plan_shares(P);
     for (size_t q = 0; q < P.rdev.size(); ++q) {
         ReqDev& d = P.rdev[q];
         const bool again = d.entries && d.v.M <= 8 && d.exp_is_one;
         d.ws.fstore = again ? nullptr : P.fstore[q];
         d.bin_path = d.ws.fstore ? 2 : (d.entries ? 1 : 0);
         paths |= d.entries ? kPathEntries : kPathValues;
+        if (!d.entries && !d.shared) paths |= kPathAlone;
         paths |= d.bin_path == 2 ? kPathBinStoredF : (d.bin_path == 1 ? kPathBinEntries : kPathBinValues);
     }
     return paths;
@@ -822,8 +850,11 @@ static bool streams(const Plan& P) {
 }
 
 // `paths`: the variants to launch (plan_paths)
-static BatchDev batch_dev(const Plan& P, char* d, int paths) {
-    BatchDev b{};
+static BatchLaunch batch_dev(const Plan& P, char* d, int paths) {
+    BatchLaunch l;
+    l.shares = P.shares;
+    BatchDev& b = l.dev;
+    b = BatchDev{};
     b.unit0 = (const int64_t*)d;
     b.reqs = (const ReqDev*)(d + P.off_reqs);
     b.n_reqs = (int)P.rdev.size();
@@ -839,7 +870,7 @@ static BatchDev batch_dev(const Plan& P, char* d, int paths) {
     b.max_tiles = P.max_tiles;
     b.max_w = P.max_w;
     b.max_bin_units = P.max_bin_units;
-    return b;
+    return l;
 }
 
 static int64_t fstore_cells(const dvl_volume* v, int n_bins) {
@@ -1131,23 +1162,29 @@ struct dvl_graph {
     bool used[kRing] = {};
     int next = 0;
     // one captured graph per set of projection paths (values, cached
-    // entries, stored f) and way of reading (BatchDev::stream): a replay launches
-    // only the kernel variants its requests use, and both can change between
-    // launches as entry caches appear
+    // entries, stored f) and way of reading (BatchDev::stream, shares): a replay
+    // launches only the kernel variants its requests use, and both can change
+    // between launches as entry caches appear.  At most kKept are kept.
+    static constexpr size_t kKept = 32;
     struct Captured {
         int paths;
         int stream;
+        std::vector<Share> shares;
         int slot;
         hipGraph_t graph;
         hipGraphExec_t exec;
     };
     std::vector<Captured> captured;
-    ~dvl_graph() {
+    void drop_captured() {
         (void)hipDeviceSynchronize();
         for (auto& c : captured) {
             if (c.exec) (void)hipGraphExecDestroy(c.exec);
             if (c.graph) (void)hipGraphDestroy(c.graph);
         }
+        captured.clear();
+    }
+    ~dvl_graph() {
+        drop_captured();
         for (char* d : dev) alloc.put(d, nullptr);
         for (void* w : ws) alloc.put(w, nullptr);
         for (int r = 0; r < kRing; ++r) {
@@ -2035,12 +2072,13 @@ dvl_status dvl_graph_create(const dvl_request* reqs, int32_t n_reqs, dvl_graph**
 // The executable graph of this path set and way of reading, captured on first use.
 static dvl_status graph_exec_for(dvl_graph* g, int paths, int slot, hipGraphExec_t* out) {
     Plan& P = g->plan;
-    const BatchDev b = batch_dev(P, g->dev[slot], paths);
+    const BatchLaunch b = batch_dev(P, g->dev[slot], paths);
     for (auto& c : g->captured)
-        if (c.paths == paths && c.stream == b.stream && c.slot == slot) {
+        if (c.paths == paths && c.stream == b.dev.stream && c.shares == b.shares && c.slot == slot) {
             *out = c.exec;
             return DVL_OK;
         }
+    if (g->captured.size() >= dvl_graph::kKept) g->drop_captured();
     hipStream_t cs;
     DVL_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     if (hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal)) {
@@ -2061,7 +2099,7 @@ static dvl_status graph_exec_for(dvl_graph* g, int paths, int slot, hipGraphExec
         (void)hipGraphDestroy(graph);
         return hip_fail(e, "hipGraphInstantiate");
     }
-    g->captured.push_back({paths, b.stream, slot, graph, exec});
+    g->captured.push_back({paths, b.dev.stream, b.shares, slot, graph, exec});
     *out = exec;
     return DVL_OK;
 }

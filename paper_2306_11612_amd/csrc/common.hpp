@@ -10,6 +10,7 @@
 namespace dvl {
 
 constexpr int kWave = 64;
+constexpr int kXcds = 8;                    // accelerator complex dies of an MI355X, each with its own L2
 constexpr int kMaxFields = 16;
 constexpr int kMaxTfEntries = 4096;
 constexpr int kMaxTfTotal = 16384;          // M * n_tf, lives in LDS (64 KB)

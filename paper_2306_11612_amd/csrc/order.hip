@@ -266,7 +266,6 @@ constexpr int kSortItems = 16, kSortItemsSmall = 4;
 constexpr int64_t kSmallCells = (int64_t)3 << 19;
 constexpr int sort_tile(int items) { return kSortThreads * items; }
 constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with its own L2
 
 // Tiles per counting workgroup: up to 16, fewer while that leaves compute
 // units idle (1.1 M cells in groups of 16 were 17 workgroups, 79 us a pass).

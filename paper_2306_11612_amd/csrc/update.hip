@@ -353,7 +353,7 @@ dvl_status launch_carry_classify(const BatchDev& b, hipStream_t s) {
     return launch_rows<k_carry_classify>(b, (b.max_tiles + kClassifyTiles - 1) / kClassifyTiles, kCarryThreads, 0, s);
 }
 
-dvl_status launch_batch(const BatchDev& b, int dtype, int max_m, int n_cu, hipStream_t s, uint64_t layout,
+dvl_status launch_batch(const BatchLaunch& b, int dtype, int max_m, int n_cu, hipStream_t s, uint64_t layout,
                         hipEvent_t* ev) {
     if (layout != kDescriptorLayout) {
         set_error("descriptor layout mismatch between library objects (%llx vs %llx): rebuild the library",

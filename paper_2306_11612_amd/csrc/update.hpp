@@ -4,6 +4,8 @@
 // TF tables, parameters and outputs.  A single dvl_update is a batch of one.
 #pragma once
 
+#include <vector>
+
 #include "common.hpp"
 
 namespace dvl {
@@ -19,6 +21,7 @@ constexpr int kPathEntries = 2;                  // requests that read cached TF
 constexpr int kPathBinStoredF = 4;               // requests whose projection reads stored f,
 constexpr int kPathBinEntries = 8;               // cached entries,
 constexpr int kPathBinValues = 16;               // or values
+constexpr int kPathAlone = 32;                   // value readers that belong to no Share
 constexpr int kIdxTable = 256;                   // LDS floats per table on the cached-entry path
 
 // A bin edge's tile and its pixel interval, when the edge is the tile's first
@@ -81,6 +84,7 @@ struct ReqDev {
     UpdWorkspace ws;
     int W;
     int entries;              // the importance pass reads cached entries (1) or values (0)
+    int shared;               // the importance pass serves it in a share (see Share)
     int bin_path;             // the projection reads values (0), cached entries (1) or stored f (2)
     int by_tile;              // k_bin: a workgroup per tile (1) or per bin edge (0)
     int tf_total;             // floats in this request's block
@@ -119,6 +123,7 @@ struct BatchDev {
     int64_t chain;            // consecutive units a workgroup of the importance pass or K0 takes
     int64_t n_steps;          // 256-cell steps of all requests
     int stream;               // read the cells as streams that bypass the caches (see batch_dev)
+    int share;                // requests of a share launched by itself, 0: the rest of the batch
     int any_exact;
     int paths;                // kPath*: which variants of the importance pass and the projection to launch
     int max_req_tf;           // largest request table block (floats)
@@ -127,6 +132,21 @@ struct BatchDev {
     int max_tiles;            // most tiles of a volume
     int max_w;                // most bins of a request
     int max_bin_units;        // most k_bin workgroups of a request
+};
+
+// Requests [req0, req0 + n_req) on one volume that read its values in one launch
+// of the importance pass, side by side, so that each cell is fetched from HBM
+// once for all of them; units: importance-pass units of each.
+struct Share {
+    int req0, n_req;
+    int64_t units;
+    bool operator==(const Share& o) const { return req0 == o.req0 && n_req == o.n_req && units == o.units; }
+};
+
+// What launch_batch is given: the batch as the kernels see it, and its shares.
+struct BatchLaunch {
+    BatchDev dev;
+    std::vector<Share> shares;
 };
 
 // The descriptor layout a translation unit was compiled with.  The host
@@ -140,7 +160,7 @@ constexpr uint64_t kDescriptorLayout =
 // resident on the device).  `max_m`: the field count when every volume has
 // the same (1 to 8), else kMaxFields.  `layout`: the caller's
 // kDescriptorLayout.  ev (optional): kPhases + 1 events.
-dvl_status launch_batch(const BatchDev& b, int dtype, int max_m, int n_cu, hipStream_t s, uint64_t layout,
+dvl_status launch_batch(const BatchLaunch& b, int dtype, int max_m, int n_cu, hipStream_t s, uint64_t layout,
                         hipEvent_t* ev = nullptr);
 
 // TF entry of every cell of one sorted field under quantiser (s, b) with

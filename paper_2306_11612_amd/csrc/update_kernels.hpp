@@ -833,6 +833,17 @@ __device__ __forceinline__ void tile_sums_run(const ReqDev& q, int first, int t_
 // and only the first loads are waited for.  Eight requests on two 20 M-cell
 // volumes 131 -> 119 us, eight volumes of 2.3 M cells and 8 fields 60.5 -> 45
 // against unit by unit, the requests in turns.
+//
+// A share (values, several requests on one volume; BatchDev::share): the units
+// are those of one request, a workgroup takes one chain of one request, and the
+// chains of the same cells for the share's requests go to workgroups b, b + 8,
+// b + 16, ...: to one XCD at about the same time, which reads them from HBM
+// once and finds them in its L2 for the others (who runs ahead waits for HBM,
+// who follows catches up).  Past the caches (non-temporal) they would not be
+// found.  Importance pass and rest of 8 requests, W = 64, request after request
+// / shared / shared with non-temporal loads: 300 M fp32 cells of 4 fields 5854
+// / 2780 / 4574 us, 50 M of 8 fields 1976 / 844 / 1362, 50 M bf16 cells of 4
+// fields 539 / 436 / 441, 2 M fp32 cells of 8 fields 147 / 105 / 105.
 constexpr int kMaxChain = 16;           // units of one stream
 constexpr size_t kSumsPartBytes = (size_t)kMaxChain * kUpdWaves * sizeof(double);
 template <int MT, typename S, int IDX>
@@ -841,13 +852,21 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
     double* const part_sums = reinterpret_cast<double*>(tf_lds + sums_lds<IDX != 0>(b));   // [kMaxChain][kUpdWaves]
     const int wv = uni((int)(thread_x() / kWave));
     int loaded = -1;
-    for (int64_t u0 = block_x() * b.chain; u0 < b.k1_units; u0 += grid_dim_x() * b.chain) {
+    int64_t u0 = block_x() * b.chain, next = grid_dim_x() * b.chain;
+    int shared = -1;                        // the workgroup's request of a share
+    if (IDX == 0 && b.share > 0) {
+        const int g = block_x(), row = kXcds * b.share;
+        shared = g % row / kXcds;
+        u0 = (int64_t)(g / row * kXcds + g % kXcds) * b.chain;
+        next = b.k1_units;
+    }
+    for (; u0 < b.k1_units; u0 += next) {
         const int64_t u1 = min(u0 + b.chain, b.k1_units);
         for (int64_t u = u0; u < u1;) {
-            const Unit un = find_unit(b, u);
+            const Unit un = IDX == 0 && shared >= 0 ? Unit{shared, (int)u, (int)(b.k1_units - u)} : find_unit(b, u);
             const ReqDev& q = b.reqs[un.req];
             int k = (int)min(u1 - u, (int64_t)un.left);
-            if (uni(q.entries) != IDX) {
+            if (uni(q.entries) != IDX || (IDX == 0 && shared < 0 && uni(q.shared))) {   // another launch's
                 u += k;
                 continue;
             }
@@ -1526,7 +1545,8 @@ static dvl_status check_no_static_lds(const char* name) {
 // second round starting cold.  Else 8 workgroups per compute unit, whose later
 // rounds the hardware hands to whichever compute unit frees a slot (a fixed
 // uneven split, 2048 units over 1280 resident workgroups of the value path, was
-// 3 % slower).  The occupancy is queried once per kernel and LDS size; any grid
+// 3 % slower).  A share: chains so long that the workgroups of all its
+// requests fit the chip at once.  The occupancy is queried once per kernel and LDS size; any grid
 // gives the same results.
 template <void (*Kernel)(BatchDev)>
 static dvl_status launch_sums(const BatchDev& b, size_t lds, int n_cu, hipStream_t s) {
@@ -1545,7 +1565,12 @@ static dvl_status launch_sums(const BatchDev& b, size_t lds, int n_cu, hipStream
     const int64_t resident = (int64_t)n_cu * nb, units = b.k1_units;
     BatchDev d = b;
     int64_t grid = units;
-    if (units > resident) {
+    if (b.share > 0) {
+        const int64_t row = (int64_t)kXcds * b.share, slots = std::max<int64_t>(1, resident / row) * kXcds;
+        d.chain = (units + slots - 1) / slots;
+        const int64_t chains = (units + d.chain - 1) / d.chain;
+        grid = (chains + kXcds - 1) / kXcds * row;
+    } else if (units > resident) {
         if (b.n_reqs > 1) {
             d.chain = (units + resident - 1) / resident;
             grid = (units + d.chain - 1) / d.chain;
@@ -1573,7 +1598,8 @@ static dvl_status launch_rows(const BatchDev& b, int64_t blocks, int threads, si
 }
 
 template <int MT, typename S>
-static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEvent_t* ev) {
+static dvl_status launch_typed(const BatchLaunch& batch, int n_cu, hipStream_t s, hipEvent_t* ev) {
+    const BatchDev& b = batch.dev;
     if (b.paths & kPathEntries) {
         if (dvl_status st = check_no_static_lds<k_tile_sums<MT, S, 1>>("k_tile_sums")) return st;
         if (dvl_status st = check_no_static_lds<k_vmax_exact<MT, S, 1>>("k_vmax_exact")) return st;
@@ -1604,7 +1630,15 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
         }
     }
     if (dvl_status st = mark(1)) return st;
-    if (b.paths & kPathValues) {
+    for (const Share& sh : batch.shares) {
+        BatchDev d = b;
+        d.reqs = b.reqs + sh.req0;
+        d.n_reqs = d.share = sh.n_req;
+        d.k1_units = sh.units;
+        d.stream = 0;
+        if (dvl_status st = launch_sums<k_tile_sums<MT, S, 0>>(d, lds1, n_cu, s)) return st;
+    }
+    if (b.paths & kPathAlone) {
         if (dvl_status st = launch_sums<k_tile_sums<MT, S, 0>>(b, lds1, n_cu, s)) return st;
     }
     if (b.paths & kPathEntries) {
@@ -1632,7 +1666,7 @@ static dvl_status launch_typed(const BatchDev& b, int n_cu, hipStream_t s, hipEv
 // parallel); elsewhere the declarations below keep the compiler from
 // instantiating them.
 template <typename S, int MT>
-dvl_status launch_sm(const BatchDev& b, int n_cu, hipStream_t s, uint64_t layout, hipEvent_t* ev) {
+dvl_status launch_sm(const BatchLaunch& b, int n_cu, hipStream_t s, uint64_t layout, hipEvent_t* ev) {
     if (layout != kDescriptorLayout) {
         set_error("descriptor layout mismatch between library objects (%llx vs %llx): rebuild the library",
                   (unsigned long long)layout, (unsigned long long)kDescriptorLayout);
@@ -1643,7 +1677,7 @@ dvl_status launch_sm(const BatchDev& b, int n_cu, hipStream_t s, uint64_t layout
 
 #define DVL_FOR_EACH_COUNT(X, S) X(S, 1) X(S, 2) X(S, 3) X(S, 4) X(S, 5) X(S, 6) X(S, 7) X(S, 8) X(S, 16)
 #define DVL_EXTERN_LAUNCH(S, MT) \
-    extern template dvl_status launch_sm<S, MT>(const BatchDev&, int, hipStream_t, uint64_t, hipEvent_t*);
+    extern template dvl_status launch_sm<S, MT>(const BatchLaunch&, int, hipStream_t, uint64_t, hipEvent_t*);
 DVL_FOR_EACH_COUNT(DVL_EXTERN_LAUNCH, F32)
 DVL_FOR_EACH_COUNT(DVL_EXTERN_LAUNCH, F16)
 DVL_FOR_EACH_COUNT(DVL_EXTERN_LAUNCH, BF16)
@@ -1656,7 +1690,7 @@ DVL_FOR_EACH_COUNT(DVL_EXTERN_LAUNCH, BF16)
 // Importance pass of 20 M fp32 cells, own variant / general: 3 fields from
 // entries 24.5 / 118 us, from values 64 / 171; 6 fields 38 / 145 and 118 / 253.
 template <typename S>
-static dvl_status launch_s(const BatchDev& b, int max_m, int n_cu, hipStream_t s, uint64_t layout, hipEvent_t* ev) {
+static dvl_status launch_s(const BatchLaunch& b, int max_m, int n_cu, hipStream_t s, uint64_t layout, hipEvent_t* ev) {
     switch (max_m) {
         case 1: return launch_sm<S, 1>(b, n_cu, s, layout, ev);
         case 2: return launch_sm<S, 2>(b, n_cu, s, layout, ev);

@@ -29,3 +29,34 @@ def test_graph_is_captured_again_when_its_reads_change(tmp_path):
     for v in (A, B):
         L.dvl_destroy(v)
     ''')
+
+
+def test_value_readers_of_one_volume_share_a_launch(tmp_path):
+    """Requests that read the values of one large volume (320 MB): up to 8 in a
+    launch, whose workgroups number a multiple of 8 (one per XCD) per request
+    and fit the chip (5 to a compute unit here); the rest as before."""
+    fake_hip.run(tmp_path, '''
+    V, small = build(20_000_000, entry_cache=2), build(100_000, entry_cache=2)
+    ex = executor()
+
+    def sums(reqs):
+        H.fake_reset()
+        batch(ex, reqs)
+        return [x for _, x, _ in launched("k_tile_sums")]
+
+    for k in (2, 3, 8):
+        g = sums([request(V, 64) for _ in range(k)])
+        assert len(g) == 1 and g[0] % (8 * k) == 0 and 1000 <= g[0] <= 1280, (k, g)
+    g = sums([request(V, 64) for _ in range(9)])
+    assert len(g) == 2 and g[0] % 64 == 0, g                 # 8, and one alone
+    assert len(sums([request(V, 64) for _ in range(16)])) == 2
+    assert len(sums([request(small, 64) for _ in range(4)])) == 1
+    assert len(sums([request(V, 64), request(small, 64), request(V, 64, scan_mode=1)])) == 2
+    # readers of cached entries have their own launch
+    ok(L.dvl_set_entry_cache(V, D.ENTRY_CACHE_ALWAYS))
+    g = sums([request(V, 64) for _ in range(4)])
+    assert [n for n, _, _ in launched("k_tile_sums")] == ["_ZN3dvl11k_tile_sumsILi4ENS_3F32ELi1EEEvNS_8BatchDevE"], launched()
+    L.dvl_executor_destroy(ex)
+    for v in (V, small):
+        L.dvl_destroy(v)
+    ''')
