@@ -454,6 +454,23 @@ static dvl_status check_range(const ReqHost& r, float vmax) {
     return DVL_OK;
 }
 
+// Whether the importance pass may scale 1 / max V by the level scale instead of
+// V / max V (ReqDev::fold).  The products differ only where V / max V is
+// subnormal and rounds: below 2^-126, which the largest level scale (2^60)
+// takes to 2^-66.  A minimum importance from there on hides it, and so do alphas
+// none of which is tiny: they are multiples of 2^-24 times the smallest of them
+// but 0, and so is V, and max V is at most their span.
+static bool folds(const ReqHost& r) {
+    if (r.p.min_importance >= 0x1p-66f) return true;
+    float amax = -INFINITY, amin = INFINITY, least = INFINITY;
+    for (float a : r.alpha) {
+        amax = std::max(amax, a);
+        amin = std::min(amin, a);
+        if (a != 0.0f) least = std::min(least, fabsf(a));
+    }
+    return (double)least >= ((double)amax - (double)amin) * 0x1p-100;
+}
+
 // ================================================================== batch plans
 
 // The requests on one volume, consecutive in the batch.
@@ -609,6 +626,7 @@ static dvl_status fill_block(Plan& P, char* h, char* d) {
         const float vm = r.p.vmax_mode == DVL_VMAX_EXACT ? 0.0f : host_vmax(r);
         if (dvl_status st = check_range(r, vm)) return st;
         vmax_h[q] = vm;
+        P.rdev[q].fold = folds(r);
         memcpy(tf_h + r.tf_pos, r.alpha.data(), r.alpha.size() * sizeof(float));
         for (int m = 0; m < r.v->M; ++m) {
             P.rdev[q].s[m] = r.qs[m];

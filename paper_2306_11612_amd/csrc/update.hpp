@@ -93,6 +93,7 @@ struct ReqDev {
     int exp_is_one;
     int clamp_mode;
     int level_shift;          // 1: 2^L, 3: 8^L
+    int fold;                 // V / max V of no cell rounds as a subnormal that shows in f
     int scan_mode;
     int vmax_exact;
     uint32_t* first_cell;

@@ -49,7 +49,7 @@ __device__ __forceinline__ Unit find_unit(const BatchDev& b, int64_t u) {
 
 struct ImpCtx {
     float inv_vmax;
-    bool scalable;   // inv_vmax times the largest level scale (2^60) is finite
+    bool scalable;   // the level scale may go into inv_vmax: ReqDev::fold, and times the largest (2^60) it is finite
     float fmin;
     float p;
     int exp_is_one;
@@ -68,12 +68,13 @@ __device__ __forceinline__ ImpCtx ctx_params(const ReqDev& q) {
     c.exp_is_one = uni(q.exp_is_one);
     c.clamp_mode = uni(q.clamp_mode);
     c.lshift = uni(q.level_shift);
+    c.scalable = uni(q.fold) != 0;
     return c;
 }
 __device__ __forceinline__ void ctx_vmax(ImpCtx& c, float vmax) {
     const float vm = uni(vmax);
     c.inv_vmax = vm > 0.0f ? 1.0f / vm : 0.0f;
-    c.scalable = uni((int)(ldexpf(c.inv_vmax, 60) <= 3.0e38f)) != 0;
+    c.scalable = c.scalable && uni((int)(ldexpf(c.inv_vmax, 60) <= 3.0e38f)) != 0;
 }
 
 // TF entry: clamp(floor(fma(x, s, b)), 0, n_tf - 1); the clamp is one
@@ -652,7 +653,8 @@ struct ModeSum {
 // stored, every cell inside the volume (whole groups of steps): nothing is
 // tested per step but whether its levels are mixed.  In a step without mixed
 // segments a lane's four cells share a level, so the level scale is folded into
-// 1 / max V (a power of two: the product has the same bits).  75 vector and 30
+// 1 / max V (a power of two: the product has the same bits unless V / max V is
+// subnormal and loses some, see ReqDev::fold).  75 vector and 30
 // scalar instructions per step became 62 and 8, and a step's 16 lookups are in
 // flight together: 432 -> 417 us for 501 M cells of 4 fields (vector units now
 // busy 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s).
