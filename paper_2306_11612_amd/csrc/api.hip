@@ -117,9 +117,10 @@ static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 // the call ends, after the device is idle unless the call says it has
 // synchronised.
 constexpr size_t kHostPageBytes = 16384;
-constexpr size_t kHostPagesKept = 8;
+constexpr int kHostPagesKept = 8;
 static std::mutex g_pages_mu;
-static std::vector<void*> g_pages;
+static void* g_pages[kHostPagesKept];
+static int g_n_pages = 0;
 
 struct HostPage {
     void* p = nullptr;
@@ -130,9 +131,8 @@ struct HostPage {
     dvl_status take() {
         {
             std::lock_guard<std::mutex> lk(g_pages_mu);
-            if (!g_pages.empty()) {
-                p = g_pages.back();
-                g_pages.pop_back();
+            if (g_n_pages > 0) {
+                p = g_pages[--g_n_pages];
                 return DVL_OK;
             }
         }
@@ -148,9 +148,8 @@ struct HostPage {
         if (!idle) (void)hipDeviceSynchronize();
         {
             std::lock_guard<std::mutex> lk(g_pages_mu);
-            if (g_pages.size() < kHostPagesKept) {
-                if (g_pages.capacity() == 0) g_pages.reserve(kHostPagesKept);
-                g_pages.push_back(p);
+            if (g_n_pages < kHostPagesKept) {
+                g_pages[g_n_pages++] = p;
                 return;
             }
         }

@@ -22,7 +22,7 @@ static std::mutex mu;
 static std::map<const void*, std::string> names;
 static std::vector<Launch> launches;
 static int n_malloc, n_free, n_host_malloc, n_instantiate, n_fail_malloc;
-static bool fail_new;
+static bool fail_new, fail_attribute;
 static int sync_parties, sync_here;            // hipStreamSynchronize waits for so many threads
 static pthread_cond_t sync_cv = PTHREAD_COND_INITIALIZER;
 static pthread_mutex_t sync_mu = PTHREAD_MUTEX_INITIALIZER;
@@ -37,6 +37,8 @@ void* operator new(size_t n) {
     if (fail_new) throw std::bad_alloc();
     return malloc(n ? n : 1);
 }
+
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return malloc(n ? n : 1); }
 
 static void stand_in(const std::string& name, Dim3 grid, void** args) {
     auto has = [&](const char* s) { return name.find(s) != std::string::npos; };
@@ -74,6 +76,7 @@ int fake_host_mallocs() { return n_host_malloc; }
 int fake_instantiated() { return n_instantiate; }
 void fake_fail_mallocs(int n) { n_fail_malloc = n; }
 void fake_fail_new(int on) { fail_new = on != 0; }
+void fake_fail_attribute(int on) { fail_attribute = on != 0; }
 void fake_sync_parties(int n) { sync_parties = n; sync_here = 0; }
 
 // ------------------------------------------------------------ the runtime
@@ -138,7 +141,10 @@ int hipStreamSynchronize(void*) {
 }
 int hipDeviceSynchronize() { return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
-int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }       // compute units
+int hipDeviceGetAttribute(int* v, int, int) {                               // compute units
+    *v = 256;
+    return fail_attribute ? 1 : 0;
+}
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 5; return 0; }
 int hipFuncGetAttributes(void* a, const void*) { memset(a, 0, 56); return 0; }
 int hipPointerGetAttributes(void*, const void*) { return 1; }

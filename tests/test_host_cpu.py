@@ -60,3 +60,22 @@ def test_value_readers_of_one_volume_share_a_launch(tmp_path):
     for v in (V, small):
         L.dvl_destroy(v)
     ''')
+
+
+def test_failing_build_without_host_memory(tmp_path):
+    """A build whose device allocation fails while the host has no memory left
+    either returns its status: nothing on its way out allocates."""
+    fake_hip.run(tmp_path, '''
+    H.fake_fail_attribute(1)                   # a long message first: its buffer has its size then
+    assert L.dvl_executor_create(C.byref(C.c_void_p())) == D.E_HIP
+    H.fake_fail_attribute(0)
+    v, f = C.c_void_p(), (C.c_void_p * 1)(mem(16))
+    a = [mem(16) for _ in range(4)]
+    for _ in range(12):                        # more than the library keeps pages for
+        H.fake_fail_mallocs(1)
+        H.fake_fail_new(1)
+        st = L.dvl_build_order(1000, *a, 1, 0, C.cast(f, C.c_void_p), None, C.byref(v))
+        H.fake_fail_new(0)
+        assert st == D.E_NOMEM and not v.value, st
+    assert H.fake_host_mallocs() <= 2
+    ''')
