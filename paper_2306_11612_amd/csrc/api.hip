@@ -108,54 +108,57 @@ struct DevBuf {
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// A page of pinned host memory for a call that waits for a few results: a
-// kernel writes them here directly, and the host reads them after it has
-// synchronised the stream (a copy of a few bytes into pageable memory costs
-// 10 to 15 us more).  Pages come from a process-wide list of at most
-// kHostPagesKept free ones (16 KB each; allocating one takes longer than most
-// calls that need it); a page is used by one call at a time and goes back when
-// the call ends, after the device is idle unless the call says it has
-// synchronised.
-constexpr size_t kHostPageBytes = 16384;
-constexpr int kHostPagesKept = 8;
-static std::mutex g_pages_mu;
-static void* g_pages[kHostPagesKept];
-static int g_n_pages = 0;
-
-struct HostPage {
+// Pinned host memory for a call that waits for results: a kernel writes them
+// there directly, and the host reads them after it has synchronised the stream
+// (a copy of a few bytes into pageable memory costs 10 to 15 us more).  Buffers
+// come from a process-wide list of at most kKept free ones (allocating one takes
+// longer than most calls that need it); a buffer is used by one call at a time,
+// whatever its thread, stream and volume, and goes back when the call ends,
+// after the device is idle unless the call says it has synchronised.
+template <size_t kBytes, int kKept>
+struct HostBuffer {
+    inline static std::mutex mu;
+    inline static void* kept[kKept];
+    inline static int n_kept = 0;
     void* p = nullptr;
     bool idle = false;
-    HostPage() = default;
-    HostPage(const HostPage&) = delete;
-    HostPage& operator=(const HostPage&) = delete;
+    HostBuffer() = default;
+    HostBuffer(const HostBuffer&) = delete;
+    HostBuffer& operator=(const HostBuffer&) = delete;
     dvl_status take() {
         {
-            std::lock_guard<std::mutex> lk(g_pages_mu);
-            if (g_n_pages > 0) {
-                p = g_pages[--g_n_pages];
+            std::lock_guard<std::mutex> lk(mu);
+            if (n_kept > 0) {
+                p = kept[--n_kept];
                 return DVL_OK;
             }
         }
-        if (hipHostMalloc(&p, kHostPageBytes, hipHostMallocPortable) != hipSuccess) {
+        if (hipHostMalloc(&p, kBytes, hipHostMallocPortable) != hipSuccess) {
             p = nullptr;
             (void)hipGetLastError();
-            return fail(DVL_E_NOMEM, "pinned host allocation of %zu bytes failed", kHostPageBytes);
+            return fail(DVL_E_NOMEM, "pinned host allocation of %zu bytes failed", kBytes);
         }
         return DVL_OK;
     }
-    ~HostPage() {
+    ~HostBuffer() {
         if (!p) return;
         if (!idle) (void)hipDeviceSynchronize();
         {
-            std::lock_guard<std::mutex> lk(g_pages_mu);
-            if (g_n_pages < kHostPagesKept) {
-                g_pages[g_n_pages++] = p;
+            std::lock_guard<std::mutex> lk(mu);
+            if (n_kept < kKept) {
+                kept[n_kept++] = p;
                 return;
             }
         }
         (void)hipHostFree(p);
     }
 };
+// a few results; the bins that dvl_read_bins returns, up to this size through one
+// kernel (1920 bins of 16 fields: 0.5 MB), larger ones array by array, where the
+// copies' own rate counts
+constexpr size_t kHostPageBytes = 16384, kReadStageBytes = (size_t)1 << 20;
+using HostPage = HostBuffer<kHostPageBytes, 8>;
+using ReadStage = HostBuffer<kReadStageBytes, 4>;
 static_assert((size_t)kRangeParts * sizeof(uint2) <= kHostPageBytes, "the partial ranges fit a page");
 
 // order-preserving uint key (as produced by the range kernel) back to float
@@ -166,10 +169,6 @@ static float unkey(unsigned int u) {
     return f;
 }
 
-// Bins of up to this size are read back through one kernel and a pinned
-// buffer of this size per volume (1920 bins of 16 fields: 0.5 MB); larger
-// ones array by array, where the copies' own rate counts.
-constexpr size_t kReadStageBytes = (size_t)1 << 20;
 constexpr int kRing = 4;                 // descriptor uploads that may be in flight
 
 // The quantisers of every field: the TF entry of a cell depends on its value
@@ -267,8 +266,6 @@ struct dvl_volume {
     dvl::Alloc alloc;        // every device buffer of the volume comes from here
     char* slab = nullptr;    // the arrays above in one hipMalloc, when the caller gave no allocator
     size_t slab_size = 0, slab_used = 0;
-    // pinned staging of dvl_read_bins (kReadStageBytes, made on first use)
-    mutable uint32_t* read_stage = nullptr;
     dvl_status sticky = DVL_OK;
     size_t bytes = 0;
 };
@@ -1669,22 +1666,20 @@ dvl_status dvl_read_bins(const dvl_volume* v, const dvl_bins* b, int32_t W, void
     }
     const uint32_t *fh = first, *lh = last;
     std::vector<uint32_t> f_tmp, l_tmp;
+    ReadStage stage;
     int dev = -1;
     DVL_HIP(hipGetDevice(&dev));
     if (words * 4 <= kReadStageBytes && dev == v->device) {
-        // one kernel writes every array into the volume's pinned staging buffer
-        if (!v->read_stage &&
-            hipHostMalloc((void**)&v->read_stage, kReadStageBytes, hipHostMallocDefault) != hipSuccess) {
-            v->read_stage = nullptr;
-            (void)hipGetLastError();
-            return fail(DVL_E_NOMEM, "pinned host allocation failed");
-        }
-        if (dvl_status st = launch_pack(l, v->read_stage, s)) return st;
+        // one kernel writes every array into pinned memory
+        if (dvl_status st = stage.take()) return st;
+        uint32_t* const staged = (uint32_t*)stage.p;
+        if (dvl_status st = launch_pack(l, staged, s)) return st;
         DVL_HIP(hipStreamSynchronize(s));
+        stage.idle = true;
         int a = 0;
         for (int k = 0; k < 8; ++k) {
             if (!items[k].want) continue;
-            const uint32_t* src = v->read_stage + l.at[a++];
+            const uint32_t* src = staged + l.at[a++];
             if (k == 0) fh = src;
             if (k == 1) lh = src;
             if (items[k].host) memcpy(items[k].host, src, items[k].bytes);
@@ -1988,7 +1983,6 @@ void dvl_destroy(dvl_volume* v) {
     }
     A.put(v->idx_s[0], nullptr);
     if (v->cache_ready) (void)hipEventDestroy(v->cache_ready);
-    if (v->read_stage) (void)hipHostFree(v->read_stage);
     delete v;
 }
 

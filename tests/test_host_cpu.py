@@ -79,3 +79,51 @@ def test_failing_build_without_host_memory(tmp_path):
         assert st == D.E_NOMEM and not v.value, st
     assert H.fake_host_mallocs() <= 2
     ''')
+
+
+def test_bins_of_one_volume_read_by_two_threads(tmp_path):
+    """Two threads read different bins of one volume at the same time (both
+    launches are enqueued before either wait returns): each gets its own.  What
+    is pinned for it does not grow with the volumes."""
+    fake_hip.run(tmp_path, '''
+    import threading
+    W = 64
+    vols = [build(1000, M=1) for _ in range(12)]
+
+    def device_bins(value):
+        b, arrays = D.dvl_bins(), []
+        for name, dt, n in (("first_cell", np.uint32, W), ("last_cell", np.uint32, W), ("mean", np.float32, W), ("vmin", np.float32, W),
+                            ("vmax", np.float32, W), ("y", np.float32, W), ("f_total", np.float64, 1), ("vmax_used", np.float32, 1)):
+            a = np.full(n, value, dt)
+            KEEP.append(a)
+            setattr(b, name, a.ctypes.data)
+        return b
+
+    def read(v, value):
+        out = [np.zeros(W, np.uint32) for _ in range(3)] + [np.zeros(W, np.float32) for _ in range(4)]
+        tot = [np.zeros(1, np.float64), np.zeros(1, np.float32)]
+        b = device_bins(value)
+        ok(L.dvl_read_bins(v, C.byref(b), W, None, *[a.ctypes.data for a in out + tot]))
+        assert (out[0] == 1).all(), out[0]
+        for a in out[1:] + tot:
+            assert (a == value).all(), (value, a)
+
+    fails = []
+    def thread(v, value):
+        try:
+            read(v, value)
+        except AssertionError as e:
+            fails.append(e)
+
+    for rnd in range(3):
+        H.fake_sync_parties(2)
+        ts = [threading.Thread(target=thread, args=(vols[0], x)) for x in (3 + rnd, 40 + rnd)]
+        [t.start() for t in ts]
+        [t.join() for t in ts]
+        H.fake_sync_parties(0)
+        assert not fails, fails
+    H.fake_reset()
+    for i, v in enumerate(vols):
+        read(v, 100 + i)
+    assert H.fake_host_mallocs() == 0
+    ''')
