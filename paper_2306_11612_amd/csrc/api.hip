@@ -656,52 +656,74 @@ struct CacheBuild {
     CacheKey key;
 };
 
-// the requests of group g read their volume's entry cache
-static void use_cache(Plan& P, const VolReqs& g) {
+// requests [k0, k1) of group g read their volume's entry cache
+static void use_cache(Plan& P, const VolReqs& g, int k0, int k1) {
     const dvl_volume* v = P.reqs[g.req0].v;
-    for (int k = 0; k < g.n_req; ++k) {
+    for (int k = k0; k < k1; ++k) {
         ReqDev& d = P.rdev[g.req0 + k];
         d.entries = 1;
         for (int m = 0; m < v->M; ++m) d.v.idx[m] = v->idx_s[m];
     }
 }
 
+// whether some request of group g reads entries (1) or values (0)
+static bool some_read(const Plan& P, const VolReqs& g, int entries) {
+    for (int k = 0; k < g.n_req; ++k)
+        if (P.rdev[g.req0 + k].entries == entries) return true;
+    return false;
+}
+
 // Choose, per request, between reading the field values and reading the
 // volume's TF entry cache; schedule the cache (re)builds this launch needs.
-// The requests on one volume read the cache if they share one key and the
-// cache holds it (or is built for it now): one volume's cache serves one key
-// per launch.
+// The requests on one volume decide in turns of up to kCacheTurn (fewer with
+// tables that exceed kCacheTurnFloats together): a turn reads the cache if its
+// requests share one key and the cache holds it (or is built for it now).  One
+// volume's cache serves one key per launch.  A whole batch deciding at once
+// would let one client with windows of its own send all others to the values.
+constexpr int kCacheTurn = 8, kCacheTurnFloats = 32768;
 static dvl_status decide_cache(Plan& P, std::vector<CacheBuild>& builds) {
     builds.clear();
     for (const VolReqs& g : P.groups) {
         for (int k = 0; k < g.n_req; ++k) P.rdev[g.req0 + k].entries = 0;
         dvl_volume* v = P.reqs[g.req0].v;
         if (v->idx_policy == DVL_ENTRY_CACHE_NEVER) continue;
-        CacheKey key;
-        bool agree = key_of(P.reqs[g.req0], key);
-        for (int k = 1; agree && k < g.n_req; ++k) {
-            CacheKey k2;
-            agree = key_of(P.reqs[g.req0 + k], k2) && k2 == key;
-        }
-        if (!agree) continue;
-        bool use = false;
-        if (v->idx_valid && v->idx_key == key) {
-            use = true;
-        } else if (v->idx_policy == DVL_ENTRY_CACHE_ALWAYS || (v->cand_set && v->cand_key == key)) {
-            if (!v->idx_s[0]) {
-                DevBuf b(v->alloc);
-                if (dvl_status st = b.alloc((size_t)v->n_pad * v->M, "TF entry cache")) return st;
-                uint8_t* base = (uint8_t*)b.release();
-                for (int m = 0; m < v->M; ++m) v->idx_s[m] = base + (size_t)m * v->n_pad;
-                v->bytes += (size_t)v->n_pad * v->M;
+        bool serving = false;
+        CacheKey served;
+        for (int k0 = 0, k1; k0 < g.n_req; k0 = k1) {
+            CacheKey key;
+            bool agree = key_of(P.reqs[g.req0 + k0], key);
+            int floats = P.reqs[g.req0 + k0].total;
+            for (k1 = k0 + 1; k1 < g.n_req && k1 - k0 < kCacheTurn; ++k1) {
+                floats += P.reqs[g.req0 + k1].total;
+                if (floats > kCacheTurnFloats) break;
+                CacheKey k2;
+                agree = agree && key_of(P.reqs[g.req0 + k1], k2) && k2 == key;
             }
-            builds.push_back({v, key});
-            use = true;
-        } else {
-            v->cand_key = key;
-            v->cand_set = true;
+            if (!agree) continue;
+            bool use = false;
+            if (serving) {
+                use = served == key;
+            } else if (v->idx_valid && v->idx_key == key) {
+                use = true;
+            } else if (v->idx_policy == DVL_ENTRY_CACHE_ALWAYS || (v->cand_set && v->cand_key == key)) {
+                if (!v->idx_s[0]) {
+                    DevBuf b(v->alloc);
+                    if (dvl_status st = b.alloc((size_t)v->n_pad * v->M, "TF entry cache")) return st;
+                    uint8_t* base = (uint8_t*)b.release();
+                    for (int m = 0; m < v->M; ++m) v->idx_s[m] = base + (size_t)m * v->n_pad;
+                    v->bytes += (size_t)v->n_pad * v->M;
+                }
+                builds.push_back({v, key});
+                use = true;
+            } else {
+                v->cand_key = key;
+                v->cand_set = true;
+            }
+            if (!use) continue;
+            serving = true;
+            served = key;
+            use_cache(P, g, k0, k1);
         }
-        if (use) use_cache(P, g);
     }
     return DVL_OK;
 }
@@ -771,7 +793,7 @@ static dvl_status run_cache_builds(const std::vector<CacheBuild>& builds, hipStr
 // stream order already follows it).
 static dvl_status cache_wait(const Plan& P, hipStream_t s) {
     for (const VolReqs& g : P.groups) {
-        if (!P.rdev[g.req0].entries) continue;
+        if (!some_read(P, g, 1)) continue;
         dvl_volume* v = P.reqs[g.req0].v;
         if (v->cache_ready_recorded && v->cache_ready_stream != s)
             DVL_HIP(hipStreamWaitEvent(s, v->cache_ready, 0));
@@ -784,7 +806,7 @@ static dvl_status cache_wait(const Plan& P, hipStream_t s) {
 static bool cache_add_readers(const Plan& P, hipStream_t s) {
     bool any = false;
     for (const VolReqs& g : P.groups) {
-        if (!P.rdev[g.req0].entries) continue;
+        if (!some_read(P, g, 1)) continue;
         dvl_volume* v = P.reqs[g.req0].v;
         if (std::find(v->cache_readers.begin(), v->cache_readers.end(), s) == v->cache_readers.end())
             v->cache_readers.push_back(s);
@@ -857,7 +879,7 @@ static bool streams(const Plan& P) {
     bool shared = false;
     for (const VolReqs& g : P.groups) {
         const ReqDev& d = P.rdev[g.req0];
-        bytes += (double)d.v.n * d.v.M * (d.entries ? 1 : elem_bytes_of(P.dtype));
+        bytes += (double)d.v.n * d.v.M * ((some_read(P, g, 1) ? 1 : 0) + (some_read(P, g, 0) ? elem_bytes_of(P.dtype) : 0));
         shared |= g.n_req > 1;
     }
     return bytes > (shared ? 512.0 : 256.0) * 1048576.0;
@@ -1565,7 +1587,7 @@ static void use_existing_cache(Plan& P, hipStream_t s) {
         CacheKey key;
         if (!key_of(P.reqs[g.req0], key) || !(key == v->idx_key)) continue;
         if (std::find(v->cache_readers.begin(), v->cache_readers.end(), s) == v->cache_readers.end()) continue;
-        use_cache(P, g);
+        use_cache(P, g, 0, 1);
     }
 }
 

@@ -105,3 +105,41 @@ def test_captured_shares():
     finally:
         G.close()
         V.close()
+
+
+def test_cached_and_uncached_requests_of_one_volume():
+    """Nine requests, the last with windows of its own: eight read the cached
+    entries, the ninth the values; then the other way round on one volume more."""
+    D = dvl()
+    Vs = [two_level(300_000, 4, torch.float32), two_level(5_000_000, 4, torch.float32)]
+    ex = D.Executor()
+    try:
+        for V in Vs:
+            V.set_entry_cache(D.ENTRY_CACHE_ALWAYS)
+        win = [tuple(np.array(w, np.float32) for w in zip(*[V.field_range(m) for m in range(4)])) for V in Vs]
+        for n_a in (8, 1):
+            reqs = []
+            for V, (lo, hi) in zip(Vs, win):
+                for i in range(9):
+                    up = hi if i < n_a else lo + (hi - lo) / 2
+                    reqs.append(D.Request(V, tfs(70 + i, 4), D.Bins(200 + i, 4), lo=lo, hi=up))
+            ex.update_batch(reqs)
+            got = [r.vol.read_bins(r.bins) for r in reqs]
+            if n_a == 8:
+                assert all(np.array_equal(V.entry_cache_info()[1], hi) for V, (_, hi) in zip(Vs, win))
+            for V in Vs:
+                V.set_entry_cache(D.ENTRY_CACHE_NEVER)
+            for i, r in enumerate(reqs):
+                for m in range(4):
+                    r.vol.set_tf(m, r.alpha[m], float(r.lo[m]), float(r.hi[m]))
+                b = D.Bins(r.bins.n_bins, 4)
+                r.vol.update(b)
+                ref = r.vol.read_bins(b)
+                for key in KEYS:
+                    assert np.asarray(got[i][key]).tobytes() == np.asarray(ref[key]).tobytes(), (n_a, i, key)
+            for V in Vs:
+                V.set_entry_cache(D.ENTRY_CACHE_ALWAYS)
+    finally:
+        ex.close()
+        for V in Vs:
+            V.close()

@@ -127,3 +127,32 @@ def test_bins_of_one_volume_read_by_two_threads(tmp_path):
         read(v, 100 + i)
     assert H.fake_host_mallocs() == 0
     ''')
+
+
+def test_entry_cache_of_mixed_requests(tmp_path):
+    """Requests on one volume decide about its entry cache eight at a time: a
+    batch with one request of other windows builds and reads it for the others."""
+    fake_hip.run(tmp_path, '''
+    ex = executor()
+    sums = "k_tile_sumsILi4ENS_3F32ELi%dE"
+
+    def run(V, *his):
+        H.fake_reset()
+        batch(ex, [request(V, 64, hi=h) for h in his])
+        return len(launched(sums % 1)), len(launched(sums % 0)), len(launched("k_build_index"))
+
+    def cached(V):
+        hi = np.zeros(4, np.float32)
+        return hi[0] if L.dvl_entry_cache_info(V, None, hi.ctypes.data, None) else None
+
+    V = build(1_000_000, entry_cache=D.ENTRY_CACHE_ALWAYS)
+    assert run(V, *[1.0] * 8, 0.5) == (1, 1, 4) and cached(V) == 1.0
+    assert run(V, *[1.0] * 8, 0.5) == (1, 1, 0)              # kept
+    assert run(V, *[1.0] * 8, *[0.5] * 8) == (1, 1, 0) and cached(V) == 1.0
+    assert run(V, 1.0, 0.5) == (0, 1, 0) and cached(V) == 1.0   # no eight agree
+    assert run(V, *[0.5] * 3) == (1, 0, 4) and cached(V) == 0.5
+    # the automatic policy: built when two updates in a row use the same windows
+    W = build(1_000_000)
+    assert run(W, *[1.0] * 8) == (0, 1, 0) and cached(W) is None
+    assert run(W, *[1.0] * 8, 0.5) == (1, 1, 4) and cached(W) == 1.0
+    ''')
