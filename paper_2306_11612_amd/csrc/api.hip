@@ -936,8 +936,13 @@ struct Executor {
     // many requests: tens of KB of tables) are copied from a ring of pinned
     // staging buffers, each released by an event after its copy.
     static constexpr size_t kPokeMaxBytes = (size_t)4 * kPokeWords * 4;
-    char* blk = nullptr;
-    size_t blk_cap = 0;
+    // A buffer of the executor; lent: part of the volume's own allocation.
+    struct Buffer {
+        void* p = nullptr;
+        size_t cap = 0;
+        bool lent = false;
+    };
+    Buffer blk;
     std::vector<char> img;
     struct Staging {
         char* host = nullptr;
@@ -947,7 +952,7 @@ struct Executor {
     };
     Staging ring[kRing];
     int next = 0;
-    std::vector<std::pair<void*, size_t>> ws;   // workspace pool: one per request position
+    std::vector<Buffer> ws;         // workspace pool: one per request position
     // The end of the latest launch is marked by the reader event of its
     // stream (reader_event), recorded after every launch: it serves the
     // entry-cache ordering and this executor alike, one queue packet.
@@ -963,12 +968,12 @@ struct Executor {
 
     ~Executor() {
         (void)hipDeviceSynchronize();
-        alloc.put(blk, nullptr);
+        give_back(blk);
         for (auto& r : ring) {
             if (r.host) (void)hipHostFree(r.host);
             if (r.ev) (void)hipEventDestroy(r.ev);
         }
-        for (auto& w : ws) alloc.put(w.first, nullptr);
+        for (auto& w : ws) give_back(w);
         for (auto* pool : {&ev_pool, &ev_pending})
             for (auto& set : *pool)
                 for (auto e : set) (void)hipEventDestroy(e);
@@ -998,40 +1003,51 @@ struct Executor {
         return DVL_OK;
     }
 
-    // grow workspace i to `need` bytes; if the allocation fails the old
-    // workspace stays, so smaller requests keep working
-    dvl_status ensure_ws(size_t i, size_t need) {
-        if (ws.size() <= i) ws.resize(i + 1, {nullptr, 0});
-        if (ws[i].second >= need) return DVL_OK;
-        DevBuf b(alloc);
-        if (dvl_status st = b.alloc(need, "request workspace")) return st;
-        if (ws[i].first) {
-            if (dvl_status st = wait_idle()) return st;
-            alloc.put(ws[i].first, nullptr);
-            bytes -= ws[i].second;
+    void give_back(Buffer& b) {
+        if (!b.lent && b.p) {
+            alloc.put(b.p, nullptr);
+            bytes -= b.cap;
         }
-        ws[i] = {b.release(), need};
-        bytes += need;
+        b = Buffer();
+    }
+
+    // a larger buffer in place of `b`, whose users are waited for; if the
+    // allocation fails the old one stays, so smaller requests keep working
+    dvl_status grow(Buffer& b, size_t cap, const char* what) {
+        DevBuf d(alloc);
+        if (dvl_status st = d.alloc(cap, what)) return st;
+        if (b.p)
+            if (dvl_status st = wait_idle()) return st;
+        give_back(b);
+        b.p = d.release();
+        b.cap = cap;
+        bytes += cap;
         return DVL_OK;
     }
 
+    // workspace i of at least `need` bytes
+    dvl_status ensure_ws(size_t i, size_t need) {
+        if (ws.size() <= i) ws.resize(i + 1);
+        return ws[i].cap >= need ? DVL_OK : grow(ws[i], need, "request workspace");
+    }
+
     // a descriptor block of at least `need` device bytes (the uploaded image
-    // is a prefix of them); the old block is released once the launches that
-    // read it are done
+    // is a prefix of them)
     dvl_status ensure_block(size_t need) {
-        if (blk_cap >= need) return DVL_OK;
-        const size_t cap = std::max(need * 2, (size_t)65536);
-        DevBuf d(alloc);
-        if (dvl_status st = d.alloc(cap, "batch descriptors")) return st;
-        if (blk) {
-            if (dvl_status st = wait_idle()) return st;
-            alloc.put(blk, nullptr);
-            bytes -= blk_cap;
+        return blk.cap >= need ? DVL_OK : grow(blk, std::max(need * 2, (size_t)65536), "batch descriptors");
+    }
+
+    // memory for the single updates of one volume: part of its slab, or (NULL)
+    // from the executor's allocator
+    dvl_status reserve(char* lent_ws, size_t ws_bytes, char* lent_blk, size_t blk_bytes) {
+        ws.resize(1);
+        if (lent_ws) {
+            ws[0] = {lent_ws, ws_bytes, true};
+            blk = {lent_blk, blk_bytes, true};
+            return DVL_OK;
         }
-        blk = (char*)d.release();
-        blk_cap = cap;
-        bytes += cap;
-        return DVL_OK;
+        if (dvl_status st = grow(ws[0], ws_bytes, "request workspace")) return st;
+        return grow(blk, blk_bytes, "batch descriptors");
     }
 
     // the next pinned staging buffer, its previous copy complete, of at
@@ -1060,13 +1076,13 @@ struct Executor {
     dvl_status upload(Plan& P, hipStream_t s) {
         if (P.block_bytes <= kPokeMaxBytes) {
             img.resize(P.block_bytes);
-            if (dvl_status st = fill_block(P, img.data(), blk)) return st;
-            return poke(blk, img.data(), P.block_bytes, s);
+            if (dvl_status st = fill_block(P, img.data(), (char*)blk.p)) return st;
+            return poke((char*)blk.p, img.data(), P.block_bytes, s);
         }
         Staging* r = nullptr;
         if (dvl_status st = take_staging(P.block_bytes, &r)) return st;
-        if (dvl_status st = fill_block(P, r->host, blk)) return st;
-        DVL_HIP(hipMemcpyAsync(blk, r->host, P.block_bytes, hipMemcpyHostToDevice, s));
+        if (dvl_status st = fill_block(P, r->host, (char*)blk.p)) return st;
+        DVL_HIP(hipMemcpyAsync(blk.p, r->host, P.block_bytes, hipMemcpyHostToDevice, s));
         DVL_HIP(hipEventRecord(r->ev, s));
         r->used = true;
         return DVL_OK;
@@ -1099,7 +1115,7 @@ struct Executor {
         for (size_t q = 0; q < P.reqs.size(); ++q) {
             const ReqHost& r = P.reqs[q];
             if (dvl_status st = ensure_ws(q, request_ws_bytes(r.v, r.p.n_bins))) return st;
-            carve_request(P, q, ws[q].first, fstore_cells(r.v, r.p.n_bins));
+            carve_request(P, q, ws[q].p, fstore_cells(r.v, r.p.n_bins));
         }
         std::vector<CacheBuild> builds;
         if (dvl_status st = decide_cache(P, builds)) return st;
@@ -1117,7 +1133,7 @@ struct Executor {
         if (dvl_status st = upload(P, s)) return st;
         hipEvent_t* ev = nullptr;
         if (dvl_status st = timing_events(&ev)) return st;
-        if (dvl_status st = launch_batch(batch_dev(P, blk, paths), P.dtype, P.max_m, n_cu, s, kDescriptorLayout, ev))
+        if (dvl_status st = launch_batch(batch_dev(P, (char*)blk.p, paths), P.dtype, P.max_m, n_cu, s, kDescriptorLayout, ev))
             return st;
         cache_add_readers(P, s);
         hipEvent_t done = nullptr;
@@ -1241,8 +1257,23 @@ static PlaceStats place_stats(const dvl_volume* v, uint2* range) {
     return st;
 }
 
-// Device memory a build works in before the volume's arrays are filled.
+// What a new volume sets aside for its single updates: the descriptors of any of
+// them, and a workspace for plots of up to 3840 pixels (with f of every cell
+// where a plot of 1920 would store it), so that the first update allocates
+// nothing.  (hipMalloc and hipFree of a workspace cost the first update of a
+// volume 60 to 300 us.)
+constexpr int kReservedBins = 3840, kReservedStoreBins = 1920;
+constexpr size_t kReservedBlock = (size_t)kMaxTfTotal * sizeof(float) + 4096;
+static_assert(sizeof(ReqDev) + 1024 <= 4096, "one request's descriptors and its largest tables");
+static size_t reserved_ws_bytes(const dvl_volume* v) {
+    return workspace_bytes(v->n_tiles, v->M, kReservedBins, fstore_cells(v, kReservedStoreBins));
+}
+
+// Device memory a build works in before the volume's arrays are filled, and what
+// it sets aside in the slab (NULL without one).
 struct BuildScratch {
+    char* ws = nullptr;         // reserved_ws_bytes()
+    char* blk = nullptr;        // kReservedBlock
     char* small = nullptr;      // the extent, then the partial ranges per tile
     char* spare = nullptr;      // the arrays that are filled last, free until then
     size_t spare_bytes = 0;
@@ -1253,8 +1284,8 @@ static size_t build_small_bytes(const dvl_volume* v) {
 
 // The volume's own arrays.  Through the caller's allocator each is an
 // allocation; without one they are parts of one hipMalloc, with the build's
-// small scratch, and the sort may use the space of the arrays that are filled
-// after it.  (hipMalloc and hipFree of more than 4 MB take 50 to 300 us each:
+// small scratch and what is set aside for updates, and the sort may use the
+// space of the arrays that are filled after it.  (hipMalloc and hipFree of more than 4 MB take 50 to 300 us each:
 // loading 1.1 M cells spent 0.9 ms in twenty of them, 0.2 ms in its kernels.)
 static dvl_status alloc_arrays(dvl_volume* v, BuildScratch* scratch) {
     const size_t eb = elem_bytes_of(v->dtype);
@@ -1262,16 +1293,18 @@ static dvl_status alloc_arrays(dvl_volume* v, BuildScratch* scratch) {
     struct Array {
         void** to;
         size_t bytes;
-        const char* what;
-    } arrays[7 + kMaxFields] = {{(void**)&v->keys_s, (size_t)v->n * 8, "keys"},
+        const char* what;     // NULL: only in the slab
+    } arrays[9 + kMaxFields] = {{(void**)&v->keys_s, (size_t)v->n * 8, "keys"},
                                 {(void**)&v->perm, (size_t)v->n * 4, "permutation"},
-                                {(void**)&scratch->small, build_small_bytes(v), "build scratch"},
+                                {(void**)&scratch->small, build_small_bytes(v), nullptr},
                                 {(void**)&v->level_s, (size_t)v->n_pad, "sorted levels"},
                                 {(void**)&v->lcode_s, (size_t)v->n_pad / kStepCells * 4, "level codes"},
                                 {(void**)&v->tile_stat, tile_bytes, "tile statistics"},
-                                {(void**)&v->seg_stat, tile_bytes * v->tile_steps * kSegsPerStep, "segment statistics"}};
+                                {(void**)&v->seg_stat, tile_bytes * v->tile_steps * kSegsPerStep, "segment statistics"},
+                                {(void**)&scratch->ws, reserved_ws_bytes(v), nullptr},
+                                {(void**)&scratch->blk, kReservedBlock, nullptr}};
     constexpr int kFilledLast = 3;     // the first array that nothing reads before it is filled
-    int n_arrays = 7;
+    int n_arrays = 9;
     for (int m = 0; m < v->M; ++m) arrays[n_arrays++] = {&v->fields_s[m], (size_t)v->n_pad * eb, "sorted field"};
     if (!v->alloc.custom) {
         for (int k = 0; k < n_arrays; ++k) v->slab_size += al256(arrays[k].bytes);
@@ -1287,7 +1320,7 @@ static dvl_status alloc_arrays(dvl_volume* v, BuildScratch* scratch) {
             if (k == kFilledLast) scratch->spare = v->slab + v->slab_used;
             v->slab_used += al256(arrays[k].bytes);
             v->bytes += al256(arrays[k].bytes);
-        } else if (arrays[k].to != (void**)&scratch->small) {
+        } else if (arrays[k].what) {
             DevBuf b(v->alloc);
             if (dvl_status st = b.alloc(arrays[k].bytes, arrays[k].what)) return st;
             *arrays[k].to = b.release();
@@ -1445,9 +1478,9 @@ dvl_status dvl_build_order_ex(int64_t n, const int32_t* x, const int32_t* y, con
     }
     DVL_HIP(hipEventCreateWithFlags(&v->cache_ready, hipEventDisableTiming));
 
-    // private executor of dvl_update, with the workspace of one request ready
+    // private executor of dvl_update, with room for its requests
     if (dvl_status st = new_executor(A, &v->ex)) return st;
-    if (dvl_status st = v->ex->ensure_ws(0, request_ws_bytes(v, 1))) return st;
+    if (dvl_status st = v->ex->reserve(scratch.ws, reserved_ws_bytes(v), scratch.blk, kReservedBlock)) return st;
     guard.v = nullptr;
     *out = v;
     return DVL_OK;
@@ -1917,7 +1950,7 @@ dvl_status dvl_zoom(const dvl_volume* v, uint32_t first, uint32_t last, const dv
     }
     DVL_HIP(hipEventCreateWithFlags(&z->cache_ready, hipEventDisableTiming));
     if (dvl_status st = new_executor(A, &z->ex)) return st;
-    if (dvl_status st = z->ex->ensure_ws(0, request_ws_bytes(z, 1))) return st;
+    if (dvl_status st = z->ex->reserve(scratch.ws, reserved_ws_bytes(z), scratch.blk, kReservedBlock)) return st;
     guard.v = nullptr;
     *out = z;
     return DVL_OK;

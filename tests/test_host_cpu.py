@@ -156,3 +156,56 @@ def test_entry_cache_of_mixed_requests(tmp_path):
     assert run(W, *[1.0] * 8) == (0, 1, 0) and cached(W) is None
     assert run(W, *[1.0] * 8, 0.5) == (1, 1, 4) and cached(W) == 1.0
     ''')
+
+
+def test_first_update_allocates_nothing(tmp_path):
+    """A new volume, or a zoom, has room for the descriptors of any single
+    update and for the workspace of plots up to 3840 wide (with stored f where
+    a plot of 1920 stores it), with and without a caller's allocator."""
+    fake_hip.run(tmp_path, '''
+    live, calls = {}, [0]
+    def get(ctx, n, stream):
+        calls[0] += 1
+        a = np.empty(1, np.uint8) if n > 1 << 26 else np.empty(n, np.uint8)
+        live[a.ctypes.data] = a
+        return a.ctypes.data
+    def put(ctx, p, stream):
+        del live[p]
+    cb = (D.ALLOC_FN(get), D.RELEASE_FN(put))
+    own = D.dvl_allocator(cb[0], cb[1], None)
+
+    def first(v, W, n_tf, M):
+        set_tfs(v, M, n_tf)
+        H.fake_reset()
+        before = calls[0]
+        update(v, W, M)
+        return H.fake_mallocs() + H.fake_frees() + calls[0] - before
+
+    H.fake_reset()
+    made = 0
+    for al in (None, C.pointer(own)):
+        for n, M, Ws in ((1000, 1, (1, 3840)), (262144, 4, (1024, 3840)), (1_000_000, 16, (1920,)), (31_000_000, 4, (1920, 3840)),
+                         (60_000_000, 4, (1920,)), (200_000_000, 4, (3840,))):
+            for W in Ws:
+                for n_tf in (256, 16384 // M if M >= 4 else 4096):
+                    v = build(n, M, allocator=al)
+                    assert first(v, W, n_tf, M) == 0, (n, M, W, n_tf)
+                    if W == Ws[0]:
+                        z = zoom(v, 10, n // 2)
+                        assert first(z, W, n_tf, M) == 0, ("zoom", n, M, W, n_tf)
+                        L.dvl_destroy(z)
+                    L.dvl_destroy(v)
+    assert not live
+    # wider plots and more stored f grow the workspace, and all of it is given back
+    for al in (None, C.pointer(own)):
+        H.fake_reset()
+        v = build(300_000, allocator=al)
+        set_tfs(v)
+        for W in (3840, 100_000, 10, 200_000):
+            update(v, W)
+        ex = executor()
+        batch(ex, [request(v, 5000)])
+        L.dvl_executor_destroy(ex)
+        L.dvl_destroy(v)
+        assert H.fake_mallocs() == H.fake_frees() and not live
+    ''')
