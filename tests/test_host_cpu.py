@@ -209,3 +209,15 @@ def test_first_update_allocates_nothing(tmp_path):
         L.dvl_destroy(v)
         assert H.fake_mallocs() == H.fake_frees() and not live
     ''')
+
+
+def test_small_masks_take_one_launch(tmp_path):
+    fake_hip.run(tmp_path, '''
+    r = np.array([0, 5, 9, 9], np.uint64)
+    for n, launches in ((1, 1), (65536, 1), (65537, 1), (4_000_000, 1), (4_000_001, 2)):
+        v = build(n)
+        H.fake_reset()
+        ok(L.dvl_select_mask(v, r.ctypes.data, 2, mem(16), None))
+        assert len(launched()) == launches, (n, launched())
+        L.dvl_destroy(v)
+    ''')
