@@ -18,16 +18,16 @@ namespace dvl {
 // ------------------------------------------------------------------ histograms
 
 // One workgroup per bin (grid-stride over bins): the bin's sorted cells
-// first..last are streamed as aligned vectors of four, four in flight per
-// thread, and counted into an LDS histogram of H buckets; the bucket of a value
-// is its entry under the quantiser of [lo, hi] for H entries (the TF entry
+// first..last are counted into an LDS histogram of H buckets; the bucket of a
+// value is its entry under the quantiser of [lo, hi] for H entries (the TF entry
 // rule), so the counts are exact integers independent of the order of the
-// additions.  Neighbouring cells mostly share a bucket, and the LDS adds equal
-// addresses one after another: C copies of every counter lie in different
-// banks and the lanes take them in turn (the rule is at histograms_typed).
-// 11.8 M fp32 cells, 1920 bins, 64 buckets: 12.5 us, 3.8 TB/s (one load at a
-// time and one copy: 50).
-template <typename S, int C>
+// additions.  QUADS: streamed as aligned vectors of four, four in flight per
+// thread; else a cell per thread.  Neighbouring cells mostly share a bucket, and
+// the LDS adds equal addresses one after another: C copies of every counter lie
+// in different banks and the lanes take them in turn (the rules are at
+// histograms_typed).  11.8 M fp32 cells, 1920 bins, 64 buckets: 12.5 us, 3.8 TB/s
+// (one load at a time and one copy: 50).
+template <typename S, int C, bool QUADS>
 __global__ __launch_bounds__(256) void k_bin_histograms(const typename S::raw* __restrict__ v, int32_t W,
                                                         const uint32_t* __restrict__ first,
                                                         const uint32_t* __restrict__ last, int32_t H,
@@ -40,7 +40,12 @@ __global__ __launch_bounds__(256) void k_bin_histograms(const typename S::raw* _
         for (int32_t k = threadIdx.x; k < H * C; k += blockDim.x) hist[k] = 0u;
         __syncthreads();
         const uint32_t f = first[bin], l = last[bin];
-        if (f <= l) {
+        auto bucket = [&](float x) {
+            return (uint32_t)(int)fminf(fmaxf(fmaf(x, s, b), 0.0f), nmax) * C + copy;
+        };
+        if (!QUADS && f <= l) {
+            for (uint64_t h = (uint64_t)f + threadIdx.x; h <= (uint64_t)l; h += 256) atomicAdd(&hist[bucket(to_f32(S{}, v[h]))], 1u);
+        } else if (f <= l) {
             const uint32_t q1 = l >> 2;
             for (uint64_t q0 = (f >> 2) + threadIdx.x; q0 <= q1; q0 += kAhead * 256) {
                 Quad<S> d[kAhead];
@@ -54,9 +59,7 @@ __global__ __launch_bounds__(256) void k_bin_histograms(const typename S::raw* _
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         if (c + k < f || c + k > l) continue;
-                        float t = fmaf(d[g].get(k), s, b);
-                        t = fminf(fmaxf(t, 0.0f), nmax);
-                        atomicAdd(&hist[(uint32_t)(int)t * C + copy], 1u);
+                        atomicAdd(&hist[bucket(d[g].get(k))], 1u);
                     }
                 }
             }
@@ -72,21 +75,26 @@ __global__ __launch_bounds__(256) void k_bin_histograms(const typename S::raw* _
     }
 }
 
-// Eight copies of the counters pay where a bin holds more cells than it costs to
-// clear and add them (16 H operations), and while their LDS lets eight
-// workgroups run on a compute unit (H <= 512).  11.8 M fp32 cells, eight copies
-// / one: 6138 cells a bin, H = 64 11.4 / 48, H = 512 14.3 / 31.9 us; 3 H cells a
-// bin, H = 64 38 / 50, H = 512 24.4 / 26.3; 0.75 H, H = 256 84 / 44 us.
+// By the cells of a bin on average.  Eight copies of the counters pay where they
+// are many more than it costs to clear and add the copies (16 H operations), and
+// while their LDS lets eight workgroups run on a compute unit (H <= 512): 50 M
+// fp32 cells, eight copies / one, 6.5 H cells a bin, H = 256 58 / 76 us, 3 H, H =
+// 256 102 / 86, 3.3 H, H = 512 89 / 70; for few buckets from 64 cells on (100
+// cells, H = 1 253 / 296, 47 cells 506 / 495).  Vectors of four pay from 256 cells
+// on, whose quarter still fills a wave (vectors / single, 400 cells, H = 512 135 /
+// 154, 200 cells, H = 256 203 / 197, 4 cells 44 / 37).
 template <typename S>
 static void histograms_typed(const void* field, int64_t n, int32_t W, const uint32_t* first, const uint32_t* last,
                              int32_t H, float s, float b, uint32_t* counts, int n_cu, hipStream_t st) {
     const dim3 grid((unsigned)std::max(1, std::min(W, n_cu * 16)));
     const auto* v = (const typename S::raw*)field;
     const size_t lds = (size_t)H * sizeof(uint32_t);
-    if (H <= 512 && 2 * n / W >= 5 * (int64_t)H)
-        hipLaunchKernelGGL((k_bin_histograms<S, 8>), grid, dim3(256), 8 * lds, st, v, W, first, last, H, s, b, counts);
+    if (H <= 512 && n >= W * std::max<int64_t>(64, 4 * H))
+        hipLaunchKernelGGL((k_bin_histograms<S, 8, true>), grid, dim3(256), 8 * lds, st, v, W, first, last, H, s, b, counts);
+    else if (n >= (int64_t)W * 256)
+        hipLaunchKernelGGL((k_bin_histograms<S, 1, true>), grid, dim3(256), lds, st, v, W, first, last, H, s, b, counts);
     else
-        hipLaunchKernelGGL((k_bin_histograms<S, 1>), grid, dim3(256), lds, st, v, W, first, last, H, s, b, counts);
+        hipLaunchKernelGGL((k_bin_histograms<S, 1, false>), grid, dim3(256), lds, st, v, W, first, last, H, s, b, counts);
 }
 
 dvl_status launch_bin_histograms(int dtype, const void* field, int64_t n, int32_t W, const uint32_t* first,

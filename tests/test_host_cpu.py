@@ -221,3 +221,22 @@ def test_small_masks_take_one_launch(tmp_path):
         assert len(launched()) == launches, (n, launched())
         L.dvl_destroy(v)
     ''')
+
+
+def test_histogram_variants(tmp_path):
+    """Counter copies and loads by the cells of a bin."""
+    fake_hip.run(tmp_path, '''
+    def variant(n, W, H_):
+        v = build(n, M=1)
+        H.fake_reset()
+        ok(L.dvl_bin_histograms(v, C.byref(bins(W, 1)), W, 0, H_, C.c_float(0.0), C.c_float(1.0), mem(16), None))
+        (name, _, _), = launched()
+        L.dvl_destroy(v)
+        return name[name.index("F32E") + 4:name.index("EEEvPK")]
+
+    single, quads, copies = "Li1ELb0", "Li1ELb1", "Li8ELb1"
+    for n, W, h, want in ((3_000_000, 1 << 20, 64, single), (47_000, 1000, 1, single), (64_000, 1000, 1, copies), (255_000, 1000, 256, single),
+                          (256_000, 1000, 256, quads), (1_023_999, 1000, 256, quads), (1_024_000, 1000, 256, copies),
+                          (20_000_000, 1000, 513, quads), (11_800_000, 1920, 64, copies)):
+        assert variant(n, W, h) == want, (n, W, h, variant(n, W, h))
+    ''')
