@@ -451,7 +451,7 @@ static dvl_status check_range(const ReqHost& r, float vmax) {
 }
 
 // Whether the importance pass may scale 1 / max V by the level scale instead of
-// V / max V (ReqDev::fold).  The products differ only where V / max V is
+// V / max V (kFold).  The products differ only where V / max V is
 // subnormal and rounds: below 2^-126, which the largest level scale (2^60)
 // takes to 2^-66.  A minimum importance from there on hides it, and so do alphas
 // none of which is tiny: they are multiples of 2^-24 times the smallest of them
@@ -491,6 +491,7 @@ struct Plan {
     int max_w = 1;
     int max_bin_units = 1;
     int any_exact = 0;
+    bool far = false;
     int64_t k1_units = 0;
     int64_t n_steps = 0;
     size_t tf_floats = 0;
@@ -602,6 +603,7 @@ static dvl_status plan_batch(std::vector<ReqHost>&& reqs, Plan& P) {
         P.max_w = std::max(P.max_w, d.W);
         P.max_bin_units = std::max(P.max_bin_units, d.by_tile ? d.v.n_tiles : d.W - 1);
         P.any_exact |= d.vmax_exact;
+        P.far |= far_bins(d.v.n, d.v.n_tiles, d.W);
     }
     if (P.max_m > 8) P.max_m = kMaxFields;
     P.off_reqs = (P.unit0.size() * sizeof(int64_t) + 63) & ~(size_t)63;
@@ -622,7 +624,7 @@ static dvl_status fill_block(Plan& P, char* h, char* d) {
         const float vm = r.p.vmax_mode == DVL_VMAX_EXACT ? 0.0f : host_vmax(r);
         if (dvl_status st = check_range(r, vm)) return st;
         vmax_h[q] = vm;
-        P.rdev[q].fold = folds(r);
+        P.rdev[q].level_shift = r.p.level_scale | (folds(r) ? kFold : 0);
         memcpy(tf_h + r.tf_pos, r.alpha.data(), r.alpha.size() * sizeof(float));
         for (int m = 0; m < r.v->M; ++m) {
             P.rdev[q].s[m] = r.qs[m];
@@ -666,10 +668,10 @@ static void use_cache(Plan& P, const VolReqs& g, int k0, int k1) {
     }
 }
 
-// whether some request of group g reads entries (1) or values (0)
-static bool some_read(const Plan& P, const VolReqs& g, int entries) {
+// whether some request of group g reads cached entries (true) or values (false)
+static bool some_read(const Plan& P, const VolReqs& g, bool cached) {
     for (int k = 0; k < g.n_req; ++k)
-        if (P.rdev[g.req0 + k].entries == entries) return true;
+        if ((P.rdev[g.req0 + k].entries == 1) == cached) return true;
     return false;
 }
 
@@ -793,7 +795,7 @@ static dvl_status run_cache_builds(const std::vector<CacheBuild>& builds, hipStr
 // stream order already follows it).
 static dvl_status cache_wait(const Plan& P, hipStream_t s) {
     for (const VolReqs& g : P.groups) {
-        if (!some_read(P, g, 1)) continue;
+        if (!some_read(P, g, true)) continue;
         dvl_volume* v = P.reqs[g.req0].v;
         if (v->cache_ready_recorded && v->cache_ready_stream != s)
             DVL_HIP(hipStreamWaitEvent(s, v->cache_ready, 0));
@@ -806,7 +808,7 @@ static dvl_status cache_wait(const Plan& P, hipStream_t s) {
 static bool cache_add_readers(const Plan& P, hipStream_t s) {
     bool any = false;
     for (const VolReqs& g : P.groups) {
-        if (!some_read(P, g, 1)) continue;
+        if (!some_read(P, g, true)) continue;
         dvl_volume* v = P.reqs[g.req0].v;
         if (std::find(v->cache_readers.begin(), v->cache_readers.end(), s) == v->cache_readers.end())
             v->cache_readers.push_back(s);
@@ -834,13 +836,13 @@ constexpr double kShareBytes = 64e6;
 static void plan_shares(Plan& P) {
     P.shares.clear();
     for (const VolReqs& g : P.groups) {
-        const ReqDev* r = &P.rdev[g.req0];
-        const bool large = r->v.M > 1 && (double)r->v.n * r->v.M * elem_bytes_of(P.dtype) >= kShareBytes;
+        ReqDev* r = &P.rdev[g.req0];
+        if (r->v.M < 2 || (double)r->v.n * r->v.M * elem_bytes_of(P.dtype) < kShareBytes) continue;
         for (int k = 0, e; k < g.n_req; k = e) {
             for (e = k + 1; e < g.n_req && e - k < kMaxShare && r[e].entries == r[k].entries && r[e].v.split == r[k].v.split;) ++e;
-            const bool share = large && e - k > 1 && !r[k].entries;
-            for (int i = k; i < e; ++i) P.rdev[g.req0 + i].shared = share;
-            if (share) P.shares.push_back({g.req0 + k, e - k, request_units(r[k].v)});
+            if (e - k < 2 || r[k].entries == 1) continue;
+            for (int i = k; i < e; ++i) r[i].entries = kValuesShared;
+            P.shares.push_back({g.req0 + k, e - k, request_units(r[k].v)});
         }
     }
 }
@@ -857,11 +859,11 @@ static int plan_paths(Plan& P) {
     plan_shares(P);
     for (size_t q = 0; q < P.rdev.size(); ++q) {
         ReqDev& d = P.rdev[q];
-        const bool again = d.entries && d.v.M <= 8 && d.exp_is_one;
+        const bool cached = d.entries == 1, again = cached && d.v.M <= 8 && d.exp_is_one;
         d.ws.fstore = again ? nullptr : P.fstore[q];
-        d.bin_path = d.ws.fstore ? 2 : (d.entries ? 1 : 0);
-        paths |= d.entries ? kPathEntries : kPathValues;
-        if (!d.entries && !d.shared) paths |= kPathAlone;
+        d.bin_path = d.ws.fstore ? 2 : (cached ? 1 : 0);
+        paths |= cached ? kPathEntries : kPathValues;
+        if (d.entries == 0) paths |= kPathAlone;
         paths |= d.bin_path == 2 ? kPathBinStoredF : (d.bin_path == 1 ? kPathBinEntries : kPathBinValues);
     }
     return paths;
@@ -879,7 +881,7 @@ static bool streams(const Plan& P) {
     bool shared = false;
     for (const VolReqs& g : P.groups) {
         const ReqDev& d = P.rdev[g.req0];
-        bytes += (double)d.v.n * d.v.M * ((some_read(P, g, 1) ? 1 : 0) + (some_read(P, g, 0) ? elem_bytes_of(P.dtype) : 0));
+        bytes += (double)d.v.n * d.v.M * ((some_read(P, g, true) ? 1 : 0) + (some_read(P, g, false) ? elem_bytes_of(P.dtype) : 0));
         shared |= g.n_req > 1;
     }
     return bytes > (shared ? 512.0 : 256.0) * 1048576.0;
@@ -898,6 +900,7 @@ static BatchLaunch batch_dev(const Plan& P, char* d, int paths) {
     b.n_steps = P.n_steps;
     b.stream = streams(P);
     b.any_exact = P.any_exact;
+    l.far = P.far;
     b.chain = 1;
     b.paths = paths;
     b.max_req_tf = P.max_req_tf;
@@ -1300,12 +1303,13 @@ static dvl_status alloc_arrays(dvl_volume* v, BuildScratch* scratch) {
                                 {(void**)&v->level_s, (size_t)v->n_pad, "sorted levels"},
                                 {(void**)&v->lcode_s, (size_t)v->n_pad / kStepCells * 4, "level codes"},
                                 {(void**)&v->tile_stat, tile_bytes, "tile statistics"},
-                                {(void**)&v->seg_stat, tile_bytes * v->tile_steps * kSegsPerStep, "segment statistics"},
-                                {(void**)&scratch->ws, reserved_ws_bytes(v), nullptr},
-                                {(void**)&scratch->blk, kReservedBlock, nullptr}};
+                                {(void**)&v->seg_stat, tile_bytes * v->tile_steps * kSegsPerStep, "segment statistics"}};
     constexpr int kFilledLast = 3;     // the first array that nothing reads before it is filled
-    int n_arrays = 9;
+    int n_arrays = 7;
     for (int m = 0; m < v->M; ++m) arrays[n_arrays++] = {&v->fields_s[m], (size_t)v->n_pad * eb, "sorted field"};
+    // side by side: kernels read the descriptors and the workspace's first arrays together
+    arrays[n_arrays++] = {(void**)&scratch->blk, kReservedBlock, nullptr};
+    arrays[n_arrays++] = {(void**)&scratch->ws, reserved_ws_bytes(v), nullptr};
     if (!v->alloc.custom) {
         for (int k = 0; k < n_arrays; ++k) v->slab_size += al256(arrays[k].bytes);
         if (hipMalloc((void**)&v->slab, v->slab_size) != hipSuccess) {
@@ -1669,7 +1673,7 @@ dvl_status dvl_update_noalloc(dvl_volume* v, const dvl_params* p, const dvl_bins
         if (st == DVL_E_HIP) v->sticky = st;
         return st;
     }
-    if (P.rdev[0].entries) {
+    if (P.rdev[0].entries == 1) {
         hipEvent_t ev = nullptr;   // exists: s is a reader stream of the volume
         if (dvl_status st = reader_event(s, false, &ev)) return st;
         if (ev) DVL_HIP(hipEventRecord(ev, s));

@@ -131,6 +131,9 @@ constexpr int kCarryWaves = kCarryThreads / kWave;
 // most 1025 runs and the base after them).
 constexpr int kClassifyTiles = kCarryThreads;
 constexpr int kRunBases = kClassifyTiles + 2;
+struct TileSpan {
+    float x0, x1;                   // pixel positions of the tile's ends
+};
 
 // The exclusive scan of request q's R run totals, by the whole workgroup:
 // base[r] = sum of the run totals before r for the runs r_lo .. r_hi + 1 (into
@@ -139,7 +142,7 @@ constexpr int kRunBases = kClassifyTiles + 2;
 // running maximum, and sequential wave and round bases; every base is clamped
 // to the next thread's base, so the bases never decrease.
 template <typename Acc>
-__device__ double carry_scan(const double* run_total, int R, int r_lo, int r_hi, double* base) {
+__device__ __forceinline__ double carry_scan(const double* run_total, int R, int r_lo, int r_hi, double* base) {
     __shared__ double wave_base[kCarryWaves + 1];
     __shared__ Acc wave_acc[kCarryWaves];
     __shared__ Acc round_acc;
@@ -234,8 +237,14 @@ __device__ double carry_scan(const double* run_total, int R, int r_lo, int r_hi,
 // or the next tile when tile t's last cell ends exactly at bin b's left edge
 // (K4 checks it with the tile's tail bin).  These ranges partition the bins.
 // A tile's first inner edge also gets the tile's record: K3b's worklist.
+// FAR: with many bins per tile (far_tiles) the workgroup's waves write them
+// together, a tile after another, a lane per bin.  (One cell plotted 4096 / 2^20
+// wide, a lane each here and in the rescan: 0.52 / 124 ms; now 0.047 / 3.1, 0.26 M
+// cells 2^20 wide 2.4 -> 0.7 ms.)
+template <bool FAR>
 __global__ __launch_bounds__(kCarryThreads) void k_carry_classify(BatchDev bd) {
     __shared__ double base[kRunBases];
+    __shared__ TileSpan span[FAR ? kClassifyTiles : 1];
     const ReqDev& q = bd.reqs[block_y()];
     const VolDev& v = q.v;
     const int T = uni(v.n_tiles), tpr = uni(v.tiles_per_run), R = uni(v.n_runs);
@@ -268,7 +277,7 @@ __global__ __launch_bounds__(kCarryThreads) void k_carry_classify(BatchDev bd) {
         gstore<double>(q.ws.scal, 1, degenerate ? 1.0 : 0.0);
         gstore<double>(q.ws.scal, 2, scale);
     }
-    if (t >= T) return;
+    if (!FAR && t >= T) return;
     const int64_t tile_cells = (int64_t)uni(v.tile_steps) * kStepCells;
     // Sum of the importance of all tiles before tile u (u = T gives F_tot):
     // the run's base plus the tile's prefix inside its run, never above the
@@ -282,6 +291,26 @@ __global__ __launch_bounds__(kCarryThreads) void k_carry_classify(BatchDev bd) {
         return fmin(fmax(lo + prefix, lo), hi);
     };
     const float X0 = (float)(offset(t, lp) * scale), X1 = (float)(offset(t + 1, lp_next) * scale);
+    bool shared_bins = false;
+    if constexpr (FAR) {
+        shared_bins = far_tiles(T, W);
+        if (shared_bins) {
+            // by all waves, a tile after another (as many bins as tiles: no edge records)
+            const int W1 = W - 1;
+            int32_t* const t1 = uni(q.ws.bin_t1);
+            int32_t* const ta = uni(q.ws.bin_ta);
+            span[thread_x()] = TileSpan{X0, X1};
+            __syncthreads();
+            for (int i = thread_x() / kWave; i < t_last + 1 - t0; i += kCarryWaves) {
+                const int u = t0 + i, c0 = bin_of(span[i].x0, W1), c1 = bin_of(span[i].x1, W1), end = u == T - 1 ? W : c1 + 1;
+                for (int b = (u == 0 ? 0 : c0) + lane_id(); b < end; b += kWave) {
+                    if (b >= c0 && (b < c1 || u == T - 1)) gstore<int32_t>(t1, b, u);
+                    if (b > c0 || u == 0) gstore<int32_t>(ta, b, u);
+                }
+            }
+        }
+        if (t >= T) return;
+    }
     gstore<float>(q.ws.x0, t, X0);
     const bool last_tile = t == T - 1;
     if (last_tile) gstore<float>(q.ws.x0, T, X1);
@@ -295,17 +324,19 @@ __global__ __launch_bounds__(kCarryThreads) void k_carry_classify(BatchDev bd) {
         gstore<int32_t>(ta, b, t);
         if (edges) gstore<u32x4>(edge, b, u32x4{(uint32_t)tile, __float_as_uint(X0), __float_as_uint(X1), 0u});
     };
-    for (int b = b0; b < b1; ++b) {
-        gstore<int32_t>(t1, b, t);
-        upto(b + 1, b == b0 ? t : -1);
-    }
-    if (t == 0)
-        for (int b = 0; b <= b0; ++b) upto(b, -1);
-    if (last_tile)
-        for (int b = b1; b <= W1; ++b) {
+    if (!shared_bins) {
+        for (int b = b0; b < b1; ++b) {
             gstore<int32_t>(t1, b, t);
-            if (b > b1) upto(b, -1);
+            upto(b + 1, b == b0 ? t : -1);
         }
+        if (t == 0)
+            for (int b = 0; b <= b0; ++b) upto(b, -1);
+        if (last_tile)
+            for (int b = b1; b <= W1; ++b) {
+                gstore<int32_t>(t1, b, t);
+                if (b > b1) upto(b, -1);
+            }
+    }
     if (b0 == b1) {
         const int64_t tbase = t * tile_cells;
         gstore<uint32_t>(q.ws.rec_first, t, (uint32_t)tbase);
@@ -349,8 +380,10 @@ dvl_status launch_build_index(int64_t n_pad, int dtype, const void* field, float
 
 // ------------------------------------------------------------------ launchers
 
-dvl_status launch_carry_classify(const BatchDev& b, hipStream_t s) {
-    return launch_rows<k_carry_classify>(b, (b.max_tiles + kClassifyTiles - 1) / kClassifyTiles, kCarryThreads, 0, s);
+dvl_status launch_carry_classify(const BatchDev& b, bool far, hipStream_t s) {
+    const int blocks = (b.max_tiles + kClassifyTiles - 1) / kClassifyTiles;
+    return far ? launch_rows<k_carry_classify<true>>(b, blocks, kCarryThreads, 0, s)
+               : launch_rows<k_carry_classify<false>>(b, blocks, kCarryThreads, 0, s);
 }
 
 dvl_status launch_batch(const BatchLaunch& b, int dtype, int max_m, int n_cu, hipStream_t s, uint64_t layout,

@@ -75,6 +75,8 @@ struct VolDev {
     const uint8_t* idx[kMaxFields];   // cached TF entries per field (entries path)
 };
 
+constexpr int kFold = 0x100;
+constexpr int kValuesShared = 2;
 // One request: everything its kernels read, in one place (a kernel's first
 // loads are its chain of cold misses: one descriptor, no pointer to another).
 struct ReqDev {
@@ -83,8 +85,7 @@ struct ReqDev {
     float* vmax_dev;          // max(V) used: host value, or computed (exact mode)
     UpdWorkspace ws;
     int W;
-    int entries;              // the importance pass reads cached entries (1) or values (0)
-    int shared;               // the importance pass serves it in a share (see Share)
+    int entries;              // the importance pass reads cached entries (1), values (0), values in a Share (2)
     int bin_path;             // the projection reads values (0), cached entries (1) or stored f (2)
     int by_tile;              // k_bin: a workgroup per tile (1) or per bin edge (0)
     int tf_total;             // floats in this request's block
@@ -92,8 +93,7 @@ struct ReqDev {
     float fmin;
     int exp_is_one;
     int clamp_mode;
-    int level_shift;          // 1: 2^L, 3: 8^L
-    int fold;                 // V / max V of no cell rounds as a subnormal that shows in f
+    int level_shift;          // 1: 2^L, 3: 8^L; | kFold: V / max V of no cell rounds as a subnormal that shows in f
     int scan_mode;
     int vmax_exact;
     uint32_t* first_cell;
@@ -124,7 +124,6 @@ struct BatchDev {
     int64_t chain;            // consecutive units a workgroup of the importance pass or K0 takes
     int64_t n_steps;          // 256-cell steps of all requests
     int stream;               // read the cells as streams that bypass the caches (see batch_dev)
-    int share;                // requests of a share launched by itself, 0: the rest of the batch
     int any_exact;
     int paths;                // kPath*: which variants of the importance pass and the projection to launch
     int max_req_tf;           // largest request table block (floats)
@@ -133,6 +132,7 @@ struct BatchDev {
     int max_tiles;            // most tiles of a volume
     int max_w;                // most bins of a request
     int max_bin_units;        // most k_bin workgroups of a request
+    int share;                // requests of a share launched by itself, 0: the rest of the batch
 };
 
 // Requests [req0, req0 + n_req) on one volume that read its values in one launch
@@ -144,11 +144,22 @@ struct Share {
     bool operator==(const Share& o) const { return req0 == o.req0 && n_req == o.n_req && units == o.units; }
 };
 
-// What launch_batch is given: the batch as the kernels see it, and its shares.
+// What launch_batch is given: the batch as the kernels see it, its shares, and
+// whether a plot is so wide that single cells or tiles reach many bins.
 struct BatchLaunch {
     BatchDev dev;
     std::vector<Share> shares;
+    bool far;
 };
+
+// Whether a plot is so wide that writing the bins of one tile, or of one cell,
+// is worth the whole wave or workgroup: 32 bins per tile, one per 16 cells.  (Only
+// then the kernels that can do it run: the tests cost the others 0.4 us each.)
+constexpr int kFarTile = 32, kFarCells = 16;
+__host__ __device__ inline bool far_tiles(int64_t n_tiles, int n_bins) { return n_bins >= kFarTile * n_tiles; }
+__host__ __device__ inline bool far_bins(int64_t n, int64_t n_tiles, int n_bins) {
+    return far_tiles(n_tiles, n_bins) || (int64_t)n_bins * kFarCells >= n;
+}
 
 // The descriptor layout a translation unit was compiled with.  The host
 // code that writes the descriptors and every unit whose kernels read them

@@ -49,7 +49,7 @@ __device__ __forceinline__ Unit find_unit(const BatchDev& b, int64_t u) {
 
 struct ImpCtx {
     float inv_vmax;
-    bool scalable;   // the level scale may go into inv_vmax: ReqDev::fold, and times the largest (2^60) it is finite
+    bool scalable;   // the level scale may go into inv_vmax: kFold, and times the largest (2^60) it is finite
     float fmin;
     float p;
     int exp_is_one;
@@ -68,7 +68,7 @@ __device__ __forceinline__ ImpCtx ctx_params(const ReqDev& q) {
     c.exp_is_one = uni(q.exp_is_one);
     c.clamp_mode = uni(q.clamp_mode);
     c.lshift = uni(q.level_shift);
-    c.scalable = uni(q.fold) != 0;
+    c.scalable = (c.lshift & kFold) != 0;
     return c;
 }
 __device__ __forceinline__ void ctx_vmax(ImpCtx& c, float vmax) {
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_vmax_exact(BatchDev b) {
         const Unit un = find_unit(b, u);
         const ReqDev& q = b.reqs[un.req];
         int k = (int)min(u1 - u, (int64_t)un.left);
-        if (uni(q.entries) != IDX || !uni(q.vmax_exact)) {
+        if ((uni(q.entries) == 1) != (IDX == 1) || !uni(q.vmax_exact)) {
             u += k;
             continue;
         }
@@ -654,7 +654,7 @@ struct ModeSum {
 // tested per step but whether its levels are mixed.  In a step without mixed
 // segments a lane's four cells share a level, so the level scale is folded into
 // 1 / max V (a power of two: the product has the same bits unless V / max V is
-// subnormal and loses some, see ReqDev::fold).  75 vector and 30
+// subnormal and loses some, see kFold).  75 vector and 30
 // scalar instructions per step became 62 and 8, and a step's 16 lookups are in
 // flight together: 432 -> 417 us for 501 M cells of 4 fields (vector units now
 // busy 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s).
@@ -868,7 +868,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
             const Unit un = IDX == 0 && shared >= 0 ? Unit{shared, (int)u, (int)(b.k1_units - u)} : find_unit(b, u);
             const ReqDev& q = b.reqs[un.req];
             int k = (int)min(u1 - u, (int64_t)un.left);
-            if (uni(q.entries) != IDX || (IDX == 0 && shared < 0 && uni(q.shared))) {   // another launch's
+            if (uni(q.entries) != (shared >= 0 ? kValuesShared : IDX)) {     // another launch's
                 u += k;
                 continue;
             }
@@ -1078,13 +1078,24 @@ struct TileBins {
     uint32_t *first_cell, *last_cell, *tail_first, *head_last;
 };
 
+__device__ __forceinline__ void bin_start(const TileBins& tb, int b, uint32_t cell) {
+    gstore<uint32_t>(b == tb.O ? tb.tail_first : tb.first_cell + b, 0, cell);
+}
+__device__ __forceinline__ void bin_end(const TileBins& tb, int b, uint32_t cell) {
+    gstore<uint32_t>(b == tb.Bh ? tb.head_last : tb.last_cell + b, 0, cell);
+}
 __device__ __forceinline__ void bin_starts(const TileBins& tb, int from, int to, uint32_t cell) {
-    for (int b = from; b <= to; ++b) gstore<uint32_t>(b == tb.O ? tb.tail_first : tb.first_cell + b, 0, cell);
+    for (int b = from; b <= to; ++b) bin_start(tb, b, cell);
 }
 __device__ __forceinline__ void bin_ends(const TileBins& tb, int from, int before, uint32_t cell) {
-    for (int b = from; b < before; ++b) gstore<uint32_t>(b == tb.Bh ? tb.head_last : tb.last_cell + b, 0, cell);
+    for (int b = from; b < before; ++b) bin_end(tb, b, cell);
 }
 
+// FAR: more bins than kFarBins of one lane's cells are written by the wave
+// (see far_bins).
+constexpr int kFarBins = 64;
+
+template <bool FAR>
 __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0, float X1, float scale_f,
                                             const Stage stage) {
     const int lane = lane_id();
@@ -1192,10 +1203,30 @@ __device__ __forceinline__ void rescan_bins(const ReqDev& q, int64_t t, float X0
         int prev_hi = shfl_i(bhi[3], max(lane - 1, 0)), next_lo = shfl_i(blo[0], min(lane + 1, kWave - 1));
         prev_hi = lane == 0 ? step_prev : prev_hi;
         next_lo = lane == kWave - 1 ? step_next : next_lo;
+        bool far = false;
+        if (FAR && key_end - key0 > kFarBins) {     // such lanes one after another
+            far = bhi[3] - prev_hi > kFarBins;
+            for (uint64_t m = __ballot(far); m; m &= m - 1) {
+                const int l = __builtin_ctzll(m);
+                int from = readlane(prev_hi, l);
+#pragma unroll 1
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t g = (uint32_t)(c0 + 4 * l + k);
+                    if (g > last_valid) break;
+                    const int lo = readlane(k < 2 ? (k == 0 ? blo[0] : blo[1]) : (k == 2 ? blo[2] : blo[3]), l);
+                    const int hi = readlane(k < 2 ? (k == 0 ? bhi[0] : bhi[1]) : (k == 2 ? bhi[2] : bhi[3]), l);
+                    const int next = readlane(k < 2 ? (k == 0 ? blo[1] : blo[2]) : (k == 2 ? blo[3] : next_lo), l);
+                    const int end = g == last_valid ? tb.O : next;
+                    for (int b = from + 1 + lane; b <= hi; b += kWave) bin_start(tb, b, g);
+                    for (int b = lo + lane; b < end; b += kWave) bin_end(tb, b, g);
+                    from = hi;
+                }
+            }
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint32_t g = (uint32_t)((quad << 2) + k);
-            if (g <= last_valid) {
+            if (g <= last_valid && !far) {
                 bin_starts(tb, (k == 0 ? prev_hi : bhi[k - 1]) + 1, bhi[k], g);
                 bin_ends(tb, blo[k], last[k] ? tb.O : (k == 3 ? next_lo : blo[k + 1]), g);
             }
@@ -1222,7 +1253,7 @@ __device__ __forceinline__ int bin_of(float x, int W1) { return max(0, min((int)
 // cached entries (1) or the f the importance pass stored (2).  LDS: the
 // request's tables (as in the importance pass; none for stored f), then the
 // staged prefixes.
-template <int MT, typename S, int IDX>
+template <int MT, typename S, int IDX, bool FAR>
 __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
     extern __shared__ f32x4 bin_lds[];
     const ReqDev& q = bd.reqs[block_y()];
@@ -1264,7 +1295,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BatchDev bd) {
     else
         rescan_stage<MT, D, false>(q, t, vmax, degenerate_d, tf_lds, stage, tables);
     __syncthreads();
-    rescan_bins(q, t, X0, X1, uni((float)scale_d), stage);
+    rescan_bins<FAR>(q, t, X0, X1, uni((float)scale_d), stage);
 }
 
 // ------------------------------------------------------------------ K4
@@ -1522,7 +1553,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_bin_stats(BatchDev bd) {
 // ------------------------------------------------------------------ launcher
 
 // launchers of the kernels that do not depend on the storage type (update.hip)
-dvl_status launch_carry_classify(const BatchDev& b, hipStream_t s);
+dvl_status launch_carry_classify(const BatchDev& b, bool far, hipStream_t s);
 
 // The cached-entry importance kernels address their tables from LDS address
 // 0 (the start of the dynamic LDS array): they must hold no static LDS.
@@ -1605,7 +1636,8 @@ static dvl_status launch_typed(const BatchLaunch& batch, int n_cu, hipStream_t s
     if (b.paths & kPathEntries) {
         if (dvl_status st = check_no_static_lds<k_tile_sums<MT, S, 1>>("k_tile_sums")) return st;
         if (dvl_status st = check_no_static_lds<k_vmax_exact<MT, S, 1>>("k_vmax_exact")) return st;
-        if (dvl_status st = check_no_static_lds<k_bin<MT, S, 1>>("k_bin")) return st;
+        if (dvl_status st = check_no_static_lds<k_bin<MT, S, 1, false>>("k_bin")) return st;
+        if (dvl_status st = check_no_static_lds<k_bin<MT, S, 1, true>>("k_bin")) return st;
     }
     auto mark = [&](int i) -> dvl_status {
         if (ev && ev[i]) DVL_HIP(hipEventRecord(ev[i], s));
@@ -1647,17 +1679,22 @@ static dvl_status launch_typed(const BatchLaunch& batch, int n_cu, hipStream_t s
         if (dvl_status st = launch_sums<k_tile_sums<MT, S, 1>>(b, lds1i, n_cu, s)) return st;
     }
     if (dvl_status st = mark(2)) return st;
-    if (dvl_status st = launch_carry_classify(b, s)) return st;
+    if (dvl_status st = launch_carry_classify(b, batch.far, s)) return st;
     if (dvl_status st = mark(3)) return st;
     const size_t stage = (size_t)b.max_tile_steps * kStageBytesPerStep;
     const size_t tables = ((size_t)b.max_req_tf * sizeof(float) + 15) & ~(size_t)15;
     const size_t tables_i = (size_t)b.max_fields * kIdxTable * sizeof(float);
-    if (b.paths & kPathBinValues)
-        if (dvl_status st = launch_rows<k_bin<MT, S, 0>>(b, b.max_bin_units, kBinThreads, stage + tables, s)) return st;
-    if (b.paths & kPathBinEntries)
-        if (dvl_status st = launch_rows<k_bin<MT, S, 1>>(b, b.max_bin_units, kBinThreads, stage + tables_i, s)) return st;
-    if (b.paths & kPathBinStoredF)
-        if (dvl_status st = launch_rows<k_bin<MT, S, 2>>(b, b.max_bin_units, kBinThreads, stage, s)) return st;
+    auto rescan = [&](auto far) -> dvl_status {
+        constexpr bool FAR = decltype(far)::value;
+        if (b.paths & kPathBinValues)
+            if (dvl_status st = launch_rows<k_bin<MT, S, 0, FAR>>(b, b.max_bin_units, kBinThreads, stage + tables, s)) return st;
+        if (b.paths & kPathBinEntries)
+            if (dvl_status st = launch_rows<k_bin<MT, S, 1, FAR>>(b, b.max_bin_units, kBinThreads, stage + tables_i, s)) return st;
+        if (b.paths & kPathBinStoredF)
+            if (dvl_status st = launch_rows<k_bin<MT, S, 2, FAR>>(b, b.max_bin_units, kBinThreads, stage, s)) return st;
+        return DVL_OK;
+    };
+    if (dvl_status st = batch.far ? rescan(std::true_type{}) : rescan(std::false_type{})) return st;
     if (dvl_status st = mark(4)) return st;
     if (dvl_status st = launch_rows<k_bin_stats<MT, S>>(b, (b.max_w + kUpdWaves - 1) / kUpdWaves, kUpdThreads, 0, s)) return st;
     return mark(5);
