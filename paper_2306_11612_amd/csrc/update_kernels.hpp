@@ -1390,7 +1390,8 @@ __device__ __forceinline__ FieldStat bin_range_stats(const VolDev& j, int M, boo
         need[k] = act && e < 32 && !(e < 16 ? wf : wl) && c[k] + 3 >= first && c[k] <= last;
         if (need[k]) qd[k].load(field, c[k] >> 2);
     }
-    for (int i0 = 0; i0 == 0 || i0 < ns || i0 < nt; i0 += KS * L) {
+    int i0 = 0;
+    for (; i0 == 0 || i0 < ns; i0 += KS * L) {
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
             const int i = i0 + li + k * L;
@@ -1415,6 +1416,16 @@ __device__ __forceinline__ FieldStat bin_range_stats(const VolDev& j, int M, boo
             if (act && i < ns) add(ss[k].sum, ss[k].mn, ss[k].mx);
             if (act && i < nt) add(ts[k].sum, ts[k].mn, ts[k].mx);
         }
+    }
+    // the tiles of a long range: twice as many in flight
+    for (; i0 < nt; i0 += 2 * KS * L) {
+        FieldStat t2[2 * KS];
+#pragma unroll
+        for (int k = 0; k < 2 * KS; ++k)
+            if (act && i0 + li + k * L < nt) t2[k] = stat(tile_stat, (int64_t)(ta + i0 + li + k * L) * M);
+#pragma unroll
+        for (int k = 0; k < 2 * KS; ++k)
+            if (act && i0 + li + k * L < nt) add(t2[k].sum, t2[k].mn, t2[k].mx);
     }
     uint32_t w[4];
     {
