@@ -451,7 +451,7 @@ static dvl_status check_range(const ReqHost& r, float vmax) {
 }
 
 // Whether the importance pass may scale 1 / max V by the level scale instead of
-// V / max V (kFold).  The products differ only where V / max V is
+// V / max V (kNoFold: it may not).  The products differ only where V / max V is
 // subnormal and rounds: below 2^-126, which the largest level scale (2^60)
 // takes to 2^-66.  A minimum importance from there on hides it, and so do alphas
 // none of which is tiny: they are multiples of 2^-24 times the smallest of them
@@ -624,7 +624,7 @@ static dvl_status fill_block(Plan& P, char* h, char* d) {
         const float vm = r.p.vmax_mode == DVL_VMAX_EXACT ? 0.0f : host_vmax(r);
         if (dvl_status st = check_range(r, vm)) return st;
         vmax_h[q] = vm;
-        P.rdev[q].level_shift = r.p.level_scale | (folds(r) ? kFold : 0);
+        P.rdev[q].level_shift = r.p.level_scale | (folds(r) ? 0 : kNoFold);
         memcpy(tf_h + r.tf_pos, r.alpha.data(), r.alpha.size() * sizeof(float));
         for (int m = 0; m < r.v->M; ++m) {
             P.rdev[q].s[m] = r.qs[m];

@@ -75,7 +75,7 @@ struct VolDev {
     const uint8_t* idx[kMaxFields];   // cached TF entries per field (entries path)
 };
 
-constexpr int kFold = 0x100;
+constexpr int kNoFold = 0x100;
 constexpr int kValuesShared = 2;
 // One request: everything its kernels read, in one place (a kernel's first
 // loads are its chain of cold misses: one descriptor, no pointer to another).
@@ -93,7 +93,7 @@ struct ReqDev {
     float fmin;
     int exp_is_one;
     int clamp_mode;
-    int level_shift;          // 1: 2^L, 3: 8^L; | kFold: V / max V of no cell rounds as a subnormal that shows in f
+    int level_shift;          // 1: 2^L, 3: 8^L; | kNoFold: V / max V may round as a subnormal that shows in f
     int scan_mode;
     int vmax_exact;
     uint32_t* first_cell;

@@ -49,7 +49,7 @@ __device__ __forceinline__ Unit find_unit(const BatchDev& b, int64_t u) {
 
 struct ImpCtx {
     float inv_vmax;
-    bool scalable;   // the level scale may go into inv_vmax: kFold, and times the largest (2^60) it is finite
+    bool scalable;   // inv_vmax times the largest level scale (2^60) is finite
     float fmin;
     float p;
     int exp_is_one;
@@ -68,13 +68,12 @@ __device__ __forceinline__ ImpCtx ctx_params(const ReqDev& q) {
     c.exp_is_one = uni(q.exp_is_one);
     c.clamp_mode = uni(q.clamp_mode);
     c.lshift = uni(q.level_shift);
-    c.scalable = (c.lshift & kFold) != 0;
     return c;
 }
 __device__ __forceinline__ void ctx_vmax(ImpCtx& c, float vmax) {
     const float vm = uni(vmax);
     c.inv_vmax = vm > 0.0f ? 1.0f / vm : 0.0f;
-    c.scalable = c.scalable && uni((int)(ldexpf(c.inv_vmax, 60) <= 3.0e38f)) != 0;
+    c.scalable = uni((int)(ldexpf(c.inv_vmax, 60) <= 3.0e38f)) != 0;
 }
 
 // TF entry: clamp(floor(fma(x, s, b)), 0, n_tf - 1); the clamp is one
@@ -654,7 +653,7 @@ struct ModeSum {
 // tested per step but whether its levels are mixed.  In a step without mixed
 // segments a lane's four cells share a level, so the level scale is folded into
 // 1 / max V (a power of two: the product has the same bits unless V / max V is
-// subnormal and loses some, see kFold).  75 vector and 30
+// subnormal and loses some: requests where that can show run kRunP1, see kNoFold).  75 vector and 30
 // scalar instructions per step became 62 and 8, and a step's 16 lookups are in
 // flight together: 432 -> 417 us for 501 M cells of 4 fields (vector units now
 // busy 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s).
@@ -886,6 +885,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
             using D = typename std::conditional<IDX != 0, StepIdx<MT>, StepData<MT, S>>::type;
             // P = 1 with the importance clamp: no pow
             const bool p1 = uni((int)(q.exp_is_one && q.clamp_mode == 0)) != 0;
+            const bool fold = uni(q.level_shift) < kNoFold;
             const bool stored = uni(q.ws.fstore) != nullptr;
             k = max(1, min(min(k, kMaxChain), kMaxStreamSteps / (tpr * tile_steps)));
             if (!split) {
@@ -893,7 +893,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
                 const int64_t c_begin = (int64_t)r0 * tpr * tile_cells;
                 const int64_t c_end = min(n, (int64_t)r1 * tpr * tile_cells);
                 const int nsteps = r1 > r0 ? (int)((c_end - c_begin + kStepCells - 1) / kStepCells) : 0;
-                const bool plain = p1 && uni(q.scan_mode) == DVL_SCAN_FP64 && !stored &&
+                const bool plain = p1 && fold && uni(q.scan_mode) == DVL_SCAN_FP64 && !stored &&
                                    c_begin + (int64_t)nsteps * kStepCells <= n && nsteps % tile_steps == 0;
                 if (plain && b.stream)
                     tile_sums_run<MT, D, kRunStream>(q, r0, r0 * tpr, c_begin, nsteps, 0, nullptr, tf_lds, tables);
@@ -914,7 +914,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_tile_sums(BatchDev b) {
                 const int64_t here = n - c_begin;       // cells left in the volume
                 const int nsteps = whole > 0 ? k * part : (int)max((int64_t)0, min((int64_t)part, (here + kStepCells - 1) / kStepCells));
                 if (nsteps == 0 && lane_id() == 0) part_sums[wv] = 0.0;
-                if (whole > 0 && p1 && !stored)
+                if (whole > 0 && p1 && fold && !stored)
                     tile_sums_run<MT, D, kRunSplit>(q, t0, t0, c_begin, nsteps, part, part_sums + wv, tf_lds, tables);
                 else
                     tile_sums_run<MT, D, kRunSplitAny>(q, t0, t0, c_begin, nsteps, part, part_sums + wv, tf_lds, tables);
