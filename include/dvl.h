@@ -282,8 +282,10 @@ size_t dvl_update_noalloc_max_bytes(void);
  * A request is one update of one volume with its own TFs, windows,
  * parameters and outputs; it does not touch the volume's own TF state.
  * Requests on the same volume read its cells at about the same time in the
- * importance pass (neighbouring workgroups take the same cells for each of
- * them), so that most of these reads come from the caches.  Every request's
+ * importance pass, up to 8 that read the values of a large volume side by side,
+ * so that most of these reads come from the caches.  Requests on one volume
+ * decide in turns of 8 whether they read its TF entry cache (a turn whose
+ * requests use one set of windows and table sizes does).  Every request's
  * results are bitwise equal
  * to those of a dvl_update with the same TFs and parameters, whatever else is
  * in the batch.  All requests of a batch must share the volumes' storage

@@ -502,8 +502,12 @@ struct Plan {
 
 // Volumes of at most this many one-tile runs have each tile shared by a
 // workgroup's four waves in the importance pass: a wave per tile would leave
-// half the chip's wave slots or more idle (1264 tiles with P = 2: 52 us against
-// 35; 2880 tiles: 17.7 against 23.5, three cold rounds of short units).
+// half the chip's wave slots or more idle.  Whole updates, W = 1920, fp32, a wave
+// per tile / four: P = 2 (4 fields, entries) 1264 tiles 90 / 71 us, 2040 93 / 89,
+// 2880 108 / 104; entries of 4 fields 1000 tiles 50 / 48, 1400 53 / 54, 2040 57 / 62,
+// 2880 61 / 65; values of 8 fields 1000 67 / 72, 1400 77 / 84, 2040 100 / 109, 2100
+// 120 / 111, 2880 134 / 141.  The line is where it pays with an exponent; without
+// one a wave per tile is up to 14 % ahead from some 1200 tiles on.
 constexpr int kSplitTiles = 2048;
 
 static VolDev vol_dev(const dvl_volume* v) {
@@ -851,9 +855,10 @@ static void plan_shares(Plan& P) {
 // variants that have work.  A request whose bins number a quarter of its tiles
 // or more rescans most of the volume; it stores f in the importance pass (4
 // bytes per cell written and read again) unless reading the cached entries
-// again (M bytes) costs no more and f is cheap to compute again (no pow):
-// stored, 20 M cells of 4 fields with three such requests of four spent 480
-// of 820 MB of the importance pass on f.
+// again (M bytes) costs no more and f is cheap to compute again (no pow).  Whole
+// updates from entries, stored / again, 1, 4 and 8 fields: 60 M cells, W = 3670, 88 /
+// 59, 154 / 103, 209 / 164 us; 20 M, W = 9764 (every tile), 73 / 58, 89 / 87, 120 / 123; 8
+// M, W = 3906, 49 / 44, 62 / 61, 81 / 85.
 static int plan_paths(Plan& P) {
     int paths = 0;
     plan_shares(P);
@@ -1608,9 +1613,6 @@ static dvl_status scratch_address(int dev, char** out) {
     *out = g_scratch_dev[dev];
     return DVL_OK;
 }
-
-// Upload of a host image into device memory through kernel arguments (the
-// runtime copies them at launch): no staging buffer, no memcpy node.
 
 // A request reads the volume's entry cache here only when the cache already
 // holds its key (it is never built here) and this stream is already one of the

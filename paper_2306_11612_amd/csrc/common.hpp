@@ -328,10 +328,6 @@ constexpr int kSegsPerStep = 4;
 
 // ---------------------------------------------------------------- host side
 
-struct Status {
-    dvl_status code = DVL_OK;
-};
-
 void set_error(const char* fmt, ...);
 dvl_status hip_fail(hipError_t e, const char* what);
 

@@ -561,8 +561,8 @@ __global__ __launch_bounds__(kUpdThreads) void k_vmax_exact(BatchDev b) {
         k = max(1, min(k, kUpdWaves * kMaxStreamSteps / unit_steps));
         const int64_t n_steps = (uni(q.v.n) + kStepCells - 1) / kStepCells;
         const int64_t s0 = (int64_t)un.local * unit_steps, s1 = min(n_steps, s0 + (int64_t)k * unit_steps);
-        const int64_t part = (s1 - s0 + kUpdWaves - 1) / kUpdWaves;
-        const int64_t w0 = s0 + wv * part, w1 = min(s1, w0 + part);
+        const int64_t steps = (s1 - s0 + kUpdWaves - 1) / kUpdWaves;     // of each wave
+        const int64_t w0 = s0 + wv * steps, w1 = min(s1, w0 + steps);
         vmax = fmaxf(vmax, b.stream ? vmax_run<MT, D, true>(q, w0 * kStepCells, (int)(w1 - w0), tf_lds, tables)
                                     : vmax_run<MT, D, false>(q, w0 * kStepCells, (int)(w1 - w0), tf_lds, tables));
         u += k;
@@ -656,7 +656,8 @@ struct ModeSum {
 // subnormal and loses some: requests where that can show run kRunP1, see kNoFold).  75 vector and 30
 // scalar instructions per step became 62 and 8, and a step's 16 lookups are in
 // flight together: 432 -> 417 us for 501 M cells of 4 fields (vector units now
-// busy 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s).
+// busy 52 % of the time, LDS 26 %, no bank conflicts; 5 TB/s; 346 us at 6.0 TB/s
+// since the cells are read as non-temporal streams).
 // kRunSplitAny: fp64 sums; kRunP1, kRunPow: anything.
 // kRunStream, kRunP1Stream: kRunPlain and kRunP1 over a volume too large for the
 // caches (BatchDev::stream).
@@ -1064,10 +1065,11 @@ __device__ __forceinline__ void rescan_stage(const ReqDev& q, int t, float vmax,
 // the first bin `next_lo` of the cell after it, which bins start with it,
 // (prev_hi, bhi], and which end with it, [blo, next_lo): no walk from bin to
 // bin.  (One wave walking the open bin through the steps, three wave
-// reductions per bin, took 36 us for the 64 tiles of a 64^3 grid plotted 1024
-// wide, 60 us for 50 M cells from values and 34 us for the 1900 tiles of
-// 501 M cells at W = 1920; this takes 16, 45 and 33 us, most of it the loads
-// before.)  Bins inside the tile are written as outputs; the tile's first bin
+// reductions per bin, made the kernel take 36 us for the 64 tiles of a 64^3 grid
+// plotted 1024 wide, 60 us for 50 M cells from values and 34 us for the 1900
+// tiles of 501 M cells at W = 1920; settled like this 16, 45 and 33 us, most of it
+// the loads before, which now leave 8.4, 29 and 16 us: see k_bin.)  Bins inside the
+// tile are written as outputs; the tile's first bin
 // (Bh) and last bin (O) go to its head and tail records,
 // merged across tiles by K4.
 struct TileBins {
