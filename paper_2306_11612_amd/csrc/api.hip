@@ -1293,8 +1293,9 @@ static size_t build_small_bytes(const dvl_volume* v) {
 // The volume's own arrays.  Through the caller's allocator each is an
 // allocation; without one they are parts of one hipMalloc, with the build's
 // small scratch and what is set aside for updates, and the sort may use the
-// space of the arrays that are filled after it.  (hipMalloc and hipFree of more than 4 MB take 50 to 300 us each:
-// loading 1.1 M cells spent 0.9 ms in twenty of them, 0.2 ms in its kernels.)
+// space of the arrays that are filled after it.  (hipMalloc and hipFree of more
+// than 4 MB take 50 to 300 us each: loading 1.1 M cells spent 0.9 ms in twenty of
+// them, 0.2 ms in its kernels.)
 static dvl_status alloc_arrays(dvl_volume* v, BuildScratch* scratch) {
     const size_t eb = elem_bytes_of(v->dtype);
     const size_t tile_bytes = (size_t)v->M * v->n_tiles * sizeof(FieldStat);
@@ -2046,7 +2047,6 @@ void dvl_destroy(dvl_volume* v) {
     if (v->cache_ready) (void)hipEventDestroy(v->cache_ready);
     delete v;
 }
-
 
 // ------------------------------------------------------------------ executors and batches
 
